@@ -3,14 +3,13 @@
 // destination cache.
 //
 // Two kernels.  (1) Per head, the evicted slots are grouped by merge target into a CSR list: an LDS
-// histogram of match[], a block scan for the row starts, and the (target, position) keys put in
-// order in LDS (by counting inside each group when all groups are short, else by a bitonic network),
-// so every group lists its members in ascending slot order (deterministic summation order, no float
-// atomics).  With few evictable slots per head this kernel is not launched: the second one finds each
+// histogram of match[], a block scan for the row starts, and each group's members put in order by
+// counting, so every group lists its members in ascending slot order (deterministic summation order,
+// no float atomics).  With few evictable slots per head this kernel is not launched: the second one finds each
 // group's members in the match list itself.  (2) One lane group (LPS lanes, 16 bytes of a row each) per retained
-// position gathers its group: the merge weights w_i = p_i s_hat_i are formed in f64 relative to
-// the group's largest ln s_hat, one member per lane, and broadcast; K and V rows are accumulated in
-// f32 and scaled once at the end.  Positions without members are copied bit for bit.
+// position: the merge weights w_i = p_i s_hat_i are formed in f64 relative to the group's largest
+// ln s_hat, one member per lane; the K and V rows of a position are then accumulated in f32 by the whole
+// wavefront and scaled once at the end.  Positions without members are copied bit for bit.
 #include "kk_common.hpp"
 
 namespace kk {
@@ -24,23 +23,38 @@ namespace {
 
 constexpr int kGroupThreads = 1024;
 constexpr int kMaxBudget = 4096;
-constexpr int kRankSortMax = 256;      // longest group that is ordered by counting instead of the sorting network
-constexpr int kMaxEvict = 32768;          // sort keys are (target << 15) | position
+constexpr int kMaxGroupShares = 8;        // workgroups that share one head's targets in the grouping kernel
+typedef __attribute__((ext_vector_type(2))) uint16_t u16x2_t;
+constexpr int kRankMax = 256;             // longest group that is ordered by counting
+constexpr int kMaxEvict = 32768;          // positions in the evict list fit 16 bits
 constexpr double kEllGuard = 1.0e-3;
 
-// Groups the evicted slots of one head by merge target.  Keys (target << 15 | position in the evict
-// list) are put in ascending order in LDS, so each group's members come out in ascending slot order;
-// CSR starts come from a histogram and a block scan.
+// Groups the evicted slots of one head by merge target into a CSR list whose members are in ascending order.
+// A histogram of the targets and a block scan give every group its range; the entries (their positions in the
+// evict list, 16 bits) are dropped into their group's range of an LDS array in arrival order; then every entry
+// takes the place given by the number of smaller positions in its group.  That last step runs over the grouped
+// array, so that neighbouring lanes belong to one group: their reads are broadcasts and their trip counts agree.
+// A group longer than kRankMax would make that quadratic: one wavefront scans the head's match list in order
+// for it instead.  With few heads up to kMaxGroupShares workgroups share a head, each taking a range of the
+// targets: every one of them reads the whole match list, so none waits for another.
+// What bounds it: the latency of one workgroup's passes over the match list (three, of a list that stays in the L2).
+// Measured (MI355X): 8 heads x 29491 entries, clustered keys, all matched: 275 us with a sorting network of one workgroup
+// per head, 103 with counting, 35 with eight workgroups per head; 1024 heads x 7372: 186 -> 90 us; 24 heads x about 3500 (D
+// 64): 40 -> 12 us.
 __global__ __launch_bounds__(kGroupThreads) void merge_group_kernel(
     const int32_t* __restrict__ match, const int32_t* __restrict__ evict_idx, const int32_t* __restrict__ n_evict,
     const int32_t* __restrict__ votes, int32_t* __restrict__ start, int32_t* __restrict__ members,
-    int64_t* __restrict__ dropped_votes, int capacity, int budget, int max_evict, int key_words) {
-  extern __shared__ unsigned int s_key[];          // key_words words: pow2ceil(max_evict) sort keys, twice if that fits
-  __shared__ int s_cnt[kMaxBudget + 1];
+    int64_t* __restrict__ dropped_votes, int capacity, int budget, int max_evict, int shares) {
+  extern __shared__ __align__(16) uint16_t s_place[];   // [max_evict] positions in the evict list, grouped by target
+  __shared__ int s_cnt[kMaxBudget + 1];            // members per target; after the scan the next free place, then the end
   __shared__ int s_wave[kGroupThreads / 64];
+  __shared__ int s_long[kMaxEvict / kRankMax];     // targets of the long groups
   __shared__ long long s_drop;
-  __shared__ int s_nm, s_longest;
-  const int unit = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  __shared__ int s_n_long, s_below;
+  const int unit = blockIdx.x / shares, share = blockIdx.x % shares;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  // this workgroup's targets: [t_lo, t_hi)
+  const int t_lo = (int)((long)budget * share / shares), t_hi = (int)((long)budget * (share + 1) / shares);
   const int n_ev = n_evict[unit];
   const int32_t* mt = match + (size_t)unit * max_evict;
   const int32_t* ev = evict_idx + (size_t)unit * max_evict;
@@ -48,63 +62,62 @@ __global__ __launch_bounds__(kGroupThreads) void merge_group_kernel(
   int32_t* mem = members + (size_t)unit * capacity;
 
   KM_TS(0);
-  for (int r = tid; r <= budget; r += kGroupThreads) s_cnt[r] = 0;
+  for (int r = t_lo + tid; r < t_hi; r += kGroupThreads) s_cnt[r] = 0;
   if (tid == 0) {
     s_drop = 0;
-    s_nm = 0;
-    s_longest = 0;
+    s_n_long = s_below = 0;
   }
   __syncthreads();
-  // histogram of targets; matched slots append their key to the (unordered) sort buffer, unmatched
-  // slots give up their votes.  Loads of eight slots are issued together (two dependent round trips per batch).
-  long long drop = 0;
+  // histogram of targets, and the number of entries whose targets lie below this workgroup's; unmatched slots (of
+  // every shares-th batch here) give up their votes.  Loads of eight slots are issued together.
   constexpr int kBatch = 8;
+  long long drop = 0;
+  int below = 0, turn = 0;
   for (int j0 = tid; j0 < n_ev; j0 += kBatch * kGroupThreads) {
-    int t[kBatch], e[kBatch];
+    const bool votes_here = dropped_votes != nullptr && turn == share;   // uniform over the workgroup
+    turn = turn + 1 == shares ? 0 : turn + 1;
+    int t[kBatch], pv[kBatch];
 #pragma unroll
-    for (int u = 0; u < kBatch; ++u) {
-      const int j = min(j0 + u * kGroupThreads, n_ev - 1);
-      t[u] = mt[j];
-      e[u] = ev[j];
+    for (int u = 0; u < kBatch; ++u) t[u] = mt[min(j0 + u * kGroupThreads, n_ev - 1)];
+    if (votes_here) {
+      int e[kBatch];
+#pragma unroll
+      for (int u = 0; u < kBatch; ++u) e[u] = ev[min(j0 + u * kGroupThreads, n_ev - 1)];
+#pragma unroll
+      for (int u = 0; u < kBatch; ++u) pv[u] = votes[(size_t)unit * capacity + e[u]];
     }
-    int pv[kBatch];
-#pragma unroll
-    for (int u = 0; u < kBatch; ++u) pv[u] = votes[(size_t)unit * capacity + e[u]];
 #pragma unroll
     for (int u = 0; u < kBatch; ++u) {
-      const int j = j0 + u * kGroupThreads;
-      if (j < n_ev) {
-        if (t[u] >= 0) {
-          atomicAdd(&s_cnt[t[u]], 1);
-          s_key[atomicAdd(&s_nm, 1)] = ((unsigned int)t[u] << 15) | (unsigned int)j;
-        } else {
-          drop += pv[u];
-        }
+      if (j0 + u * kGroupThreads < n_ev) {
+        if (t[u] >= t_lo && t[u] < t_hi) atomicAdd(&s_cnt[t[u]], 1);
+        else if (t[u] >= 0 && t[u] < t_lo) ++below;
+        else if (t[u] < 0 && votes_here) drop += pv[u];
       }
     }
   }
   // one LDS add per wavefront: adds to one word are served a lane at a time
 #pragma unroll
-  for (int off = 32; off > 0; off >>= 1) drop += __shfl_xor(drop, off);
-  if (lane == 0 && drop != 0) atomicAdd((unsigned long long*)&s_drop, (unsigned long long)drop);
+  for (int off = 32; off > 0; off >>= 1) {
+    drop += __shfl_xor(drop, off);
+    below += __shfl_xor(below, off);
+  }
+  if (lane == 0) {
+    if (drop != 0) atomicAdd((unsigned long long*)&s_drop, (unsigned long long)drop);
+    if (below != 0) atomicAdd(&s_below, below);
+  }
   __syncthreads();
   KM_TS(1);
-  const int n_matched = s_nm;
-  int n2 = 1;
-  while (n2 < n_matched) n2 <<= 1;
-  for (int i = n_matched + tid; i < n2; i += kGroupThreads) s_key[i] = 0xFFFFFFFFu;   // padding sorts to the end
 
-  // exclusive scan of s_cnt[0..budget): thread t owns a contiguous run of positions
-  const int per = (budget + kGroupThreads - 1) / kGroupThreads;
-  const int r0 = min(budget, tid * per), r1 = min(budget, r0 + per);
-  int mine = 0, longest = 0;
+  // exclusive scan of s_cnt[t_lo .. t_hi): thread t owns a contiguous run of positions.  Places in s_place count
+  // from this workgroup's first member, places in the CSR list from the head's (s_below more).
+  const int per = (t_hi - t_lo + kGroupThreads - 1) / kGroupThreads;
+  const int r0 = min(t_hi, t_lo + tid * per), r1 = min(t_hi, r0 + per);
+  int mine = 0;
   for (int r = r0; r < r1; ++r) {
-    mine += s_cnt[r];
-    longest = max(longest, s_cnt[r]);
+    const int cnt = s_cnt[r];
+    mine += cnt;
+    if (cnt > kRankMax) s_long[atomicAdd(&s_n_long, 1)] = r;
   }
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) longest = max(longest, __shfl_xor(longest, off));
-  if (lane == 0 && longest > 0) atomicMax(&s_longest, longest);
   int incl = mine;
 #pragma unroll
   for (int off = 1; off < 64; off <<= 1) {
@@ -113,110 +126,93 @@ __global__ __launch_bounds__(kGroupThreads) void merge_group_kernel(
   }
   if (lane == 63) s_wave[wave] = incl;
   __syncthreads();
-  int before = 0;
-  for (int w = 0; w < wave; ++w) before += s_wave[w];
+  int before = 0, n_matched = 0;
+#pragma unroll
+  for (int w = 0; w < kGroupThreads / 64; ++w) {
+    const int v = s_wave[w];
+    if (w < wave) before += v;
+    n_matched += v;
+  }
+  const int base = s_below;
+  mem += base;
   int run = before + incl - mine;
   for (int r = r0; r < r1; ++r) {
     const int cnt = s_cnt[r];
-    st[r] = run;
+    st[r] = base + run;
     s_cnt[r] = run;                                  // from here on: where the group's next member goes
     run += cnt;
   }
-  if (tid == kGroupThreads - 1) st[budget] = run;
-  if (tid == 0 && dropped_votes != nullptr && s_drop != 0) dropped_votes[unit] += s_drop;
+  if (tid == 0 && t_hi == budget) st[budget] = base + n_matched;
+  if (tid == 0 && s_drop != 0) atomicAdd((unsigned long long*)&dropped_votes[unit], (unsigned long long)s_drop);
   KM_TS(2);
   if (n_matched == 0) return;                       // uniform over the block
+  __syncthreads();                                  // cursors complete
 
-  if (s_longest <= kRankSortMax && 2 * n2 <= key_words) {   // uniform over the block
-    // Short groups (the rule): every key is dropped into its group's range in arrival order, then takes the
-    // place given by the number of smaller keys in its group.  Three barriers; the sorting network below needs
-    // 91 stages for 8192 keys and takes five times as long.
-    __syncthreads();                                // cursors complete
-    unsigned int* s_place = s_key + n2;             // the keys again, grouped; the launch reserves both halves
-    for (int u0 = 0; u0 * kGroupThreads < n_matched; u0 += 8) {   // eight keys per thread at a time
-      unsigned int mykey[8];
+  for (int j0 = tid; j0 < n_ev; j0 += kBatch * kGroupThreads) {
+    int t[kBatch];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const int i = tid + (u0 + u) * kGroupThreads;
-        mykey[u] = i < n_matched ? s_key[i] : 0u;
-      }
+    for (int u = 0; u < kBatch; ++u) t[u] = mt[min(j0 + u * kGroupThreads, n_ev - 1)];
 #pragma unroll
-      for (int u = 0; u < 8; ++u)
-        if (tid + (u0 + u) * kGroupThreads < n_matched) s_place[atomicAdd(&s_cnt[mykey[u] >> 15], 1)] = mykey[u];
+    for (int u = 0; u < kBatch; ++u) {
+      const int j = j0 + u * kGroupThreads;
+      if (j < n_ev && t[u] >= t_lo && t[u] < t_hi) s_place[atomicAdd(&s_cnt[t[u]], 1)] = (uint16_t)j;
     }
-    __syncthreads();                                // s_cnt[r] is now the end of group r
-    for (int u0 = 0; u0 * kGroupThreads < n_matched; u0 += 8) {
-      unsigned int key[8];
-      int slot[8], g0[8], g1[8];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const int i = min(tid + (u0 + u) * kGroupThreads, n_matched - 1);
-        key[u] = s_key[i];
-        slot[u] = ev[key[u] & 0x7FFFu];
-        const int r = (int)(key[u] >> 15);
-        g0[u] = r > 0 ? s_cnt[r - 1] : 0;
-        g1[u] = s_cnt[r];
-      }
-#pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        int rank = 0;
-        for (int m = g0[u]; m < g1[u]; m += 4) {    // four members per round trip
-          unsigned int o[4];
-#pragma unroll
-          for (int q = 0; q < 4; ++q) o[q] = s_place[min(m + q, g1[u] - 1)];
-#pragma unroll
-          for (int q = 0; q < 4; ++q) rank += (m + q < g1[u]) && o[q] < key[u];
-        }
-        if (tid + (u0 + u) * kGroupThreads < n_matched) mem[g0[u] + rank] = slot[u];
-      }
-    }
-    KM_TS(3);
-    KM_TS(4);
-    return;
   }
-
-  // bitonic sort, ascending.  Thread i + 1024 m handles pair i of every stage; for strides j <= 64 both
-  // elements of all pairs of a wavefront lie in that wavefront's own 128-element blocks, so those stages
-  // need only a wavefront-level fence instead of a workgroup barrier.
-  auto stage = [&](int j, int k) {
-    // up to kMaxEvict / 2 / 1024 = 16 pairs per thread, four at a time so that the LDS reads overlap
-    for (int i0 = tid; i0 < (n2 >> 1); i0 += 4 * kGroupThreads) {
-      int lo[4], hi[4];
-      unsigned int x[4], y[4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int i = min(i0 + u * kGroupThreads, (n2 >> 1) - 1);
-        lo[u] = ((i & ~(j - 1)) << 1) | (i & (j - 1));
-        hi[u] = lo[u] | j;
-        x[u] = s_key[lo[u]];
-        y[u] = s_key[hi[u]];
-      }
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const bool act = i0 + u * kGroupThreads < (n2 >> 1);
-        const bool up = (lo[u] & k) == 0;
-        if (act && (x[u] > y[u]) == up) {
-          s_key[lo[u]] = y[u];
-          s_key[hi[u]] = x[u];
-        }
-      }
-    }
-  };
-  for (int k = 2; k <= n2; k <<= 1) {
-    int j = k >> 1;
-    for (; j > 64; j >>= 1) {
-      stage(j, k);
-      __syncthreads();
-    }
-    for (; j > 0; j >>= 1) {
-      stage(j, k);
-      __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-    }
-    __syncthreads();
-  }
+  __syncthreads();                                  // s_cnt[r] is now the end of group r
   KM_TS(3);
-  for (int i = tid; i < n_matched; i += kGroupThreads) mem[i] = ev[s_key[i] & 0x7FFFu];
+
+  for (int i0 = tid; i0 < n_matched; i0 += kBatch * kGroupThreads) {
+    int j[kBatch], t[kBatch], slot[kBatch];
+#pragma unroll
+    for (int u = 0; u < kBatch; ++u) j[u] = s_place[min(i0 + u * kGroupThreads, n_matched - 1)];
+#pragma unroll
+    for (int u = 0; u < kBatch; ++u) {
+      t[u] = mt[j[u]];
+      slot[u] = ev[j[u]];
+    }
+#pragma unroll
+    for (int u = 0; u < kBatch; ++u) {
+      const int g0 = t[u] > t_lo ? s_cnt[t[u] - 1] : 0, g1 = s_cnt[t[u]];
+      if (i0 + u * kGroupThreads >= n_matched || g1 - g0 > kRankMax) continue;
+      // eight members per LDS read, two per instruction: min(max(j - o, 0), 1) counts the smaller ones.  The first
+      // and the last eight may hold neighbours' members, which are replaced by the largest value.
+      u16x2_t rank2 = {0, 0};
+      const u16x2_t one = {1, 1}, jj = {(uint16_t)j[u], (uint16_t)j[u]};
+      for (int m = g0 & ~7; m < g1; m += 8) {
+        const uint4 x = *reinterpret_cast<const uint4*>(s_place + m);
+        uint32_t o[4] = {x.x, x.y, x.z, x.w};
+        if (m < g0 || m + 8 > g1) {
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            if (m + 2 * q < g0 || m + 2 * q >= g1) o[q] |= 0xFFFFu;
+            if (m + 2 * q + 1 < g0 || m + 2 * q + 1 >= g1) o[q] |= 0xFFFF0000u;
+          }
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          rank2 += __builtin_elementwise_min(__builtin_elementwise_sub_sat(jj, __builtin_bit_cast(u16x2_t, o[q])), one);
+      }
+      mem[g0 + rank2[0] + rank2[1]] = slot[u];
+    }
+  }
+  const int n_long = s_n_long;
+  for (int l = wave; l < n_long; l += kGroupThreads / 64) {   // uniform over the wavefront
+    const int r = s_long[l];
+    int at = r > t_lo ? s_cnt[r - 1] : 0;
+    for (int j0 = 0; j0 < n_ev; j0 += kBatch * 64) {
+      int t[kBatch];
+#pragma unroll
+      for (int u = 0; u < kBatch; ++u) t[u] = mt[min(j0 + u * 64 + lane, n_ev - 1)];
+#pragma unroll
+      for (int u = 0; u < kBatch; ++u) {
+        const int j = j0 + u * 64 + lane;
+        const bool hit = j < n_ev && t[u] == r;
+        const unsigned long long m = __ballot(hit);
+        if (hit) mem[at + __popcll(m & ((1ull << lane) - 1ull))] = ev[j];
+        at += __popcll(m);
+      }
+    }
+  }
   KM_TS(4);
 }
 
@@ -241,18 +237,42 @@ struct MergeParams {
   const int32_t* evict_idx;
   int64_t* dropped_votes;
   int scap, dcap, budget, max_evict;
+  int positions_per_wave;      // merge_apply_kernel without DIRECT
   int write_len;               // 0: the caller's grouping kernel has set dst.len (prefill pass)
   double ln_alpha;
 };
 
 constexpr int kDirectMaxEvict = 256;   // up to this many evictable slots per head no CSR list is built
 
+// The f64 library routines as calls: inlined, their polynomial coefficients kept some forty registers busy all
+// through the kernels, and with 135 registers instead of 95 the apply kernel took 1450 us instead of 1024 on the batch-128
+// first event.
+__device__ __attribute__((noinline)) double log_f64(double x) { return log(x); }
+__device__ __attribute__((noinline)) double exp_f64(double x) { return exp(x); }
+__device__ __attribute__((noinline)) double log_1m_exp_f64(double t) { return log(-expm1(t)); }
+
+// ln(1 - alpha^n), the bias correction of Eq. 8.  It depends on the count alone and exactly 0 is left of it once
+// n ln alpha <= -40 (alpha^n is then below half an ulp of 1); the f64 library routines behind it are hundreds of
+// instructions.  So a wavefront evaluates it only where one of its lanes needs a value that is neither 0 nor the
+// lane's last one (after a prefill all slots of a head have the same count).
+struct CountTerm {
+  int n = 0;
+  double value = 0.0;
+  __device__ __forceinline__ double of(int m, double ln_alpha) {
+    const double t = (double)m * ln_alpha;         // (-inf with alpha == 0)
+    const bool zero = m <= 0 || !(t > -40.0);
+    if (__any(!zero && m != n)) {
+      value = zero ? 0.0 : log_1m_exp_f64(t);
+      n = m;
+    }
+    return zero ? 0.0 : value;
+  }
+};
+
 // ln s_hat_i = ln S_i - ln(1 - alpha^n_i); -inf when never observed
-__device__ __forceinline__ double log_s_hat(float log_s, int n, double ln_alpha) {
-  if (n <= 0) return -INFINITY;
-  double e = (double)log_s;
-  if (ln_alpha > -INFINITY) e -= log(-expm1((double)n * ln_alpha));
-  return e;
+__device__ __forceinline__ double log_s_hat(float log_s, int n, double ln_alpha, CountTerm& term) {
+  const double t = term.of(n, ln_alpha);
+  return n <= 0 ? -INFINITY : (double)log_s - t;
 }
 
 template <int LPS>
@@ -268,117 +288,207 @@ __device__ __forceinline__ double group_sum_f64(double x) {
   return x;
 }
 
-// One retained slot c (row kc / vc, votes p_c, ln S ls_c, observation count n_c) absorbs the nm evicted slots
-// listed in mem, in list order: the multi-way merge of App. A.3 / A.4 with weights p * s_hat formed in f64
-// relative to the group's largest ln s_hat, rows accumulated in f32 and scaled once.  Called by all LPS lanes
-// of the position's lane group (lane `sub` holds 16 bytes of each row; gbase = the group's first lane in the
-// wavefront).  Shared by the compacting and the in-place kernels, so both produce the same bits.
-struct MergedRow {
-  uint4 k, v;
-  int32_t votes;
-  float log_s;
-  int32_t n_r;       // observation count of the merged slot
-};
+// Each lane group of a wavefront (LPS lanes, 64 / LPS groups) brings one retained slot c, the nm evicted slots
+// list[off .. off + nm) that it absorbs (nm = 0: nothing to do for this group) and the destination slot: the multi-way
+// merge of App. A.3 / A.4 over the entries (c, list[off], ..., list[off + nm - 1]) with weights p * s_hat formed in
+// f64 relative to the largest ln s_hat, rows accumulated in f32 and scaled once.  Called by whole wavefronts.
+// The scalars of positions with up to LPS entries (most of them) are worked out side by side, one entry per lane, so
+// that the f64 routines run once for all groups; a longer list has its scalars spread over the whole wavefront.
+// The rows are summed one position after the other by the whole wavefront, entry e by lane group e mod
+// (64 / LPS), and the groups' partial sums meet in a fixed tree: a position's bits depend on its list alone and not
+// on the kernel or on its place in the wavefront.
+// Why: the members per target vary widely (mean 9, largest 147 on the clustered keys of the long-context
+// workload).  With one lane group per position a wavefront took as long as its largest group, one dependent round
+// trip for every LPS scalars and every few rows.
+// What bounds it: HBM for the members' rows, and the f64 arithmetic.  Measured against one lane group per position
+// (MI355X): 1024 heads x 820 positions, 7372 evicted rows each, 4.6 GB moved: 1637 -> 1020 us (4.5 TB/s; a plain copy
+// reaches 5.1); 8 heads x 3277, 29491 rows: 163 -> 65 us; 24 heads x 501 of D 64: 64 -> 25 us; the in-place event of 128
+// heads: 14.6 -> 13.7 us.
 template <typename T, int D>
-__device__ __forceinline__ MergedRow merge_position(const MergeParams& p, size_t sbase, int t_head, int c, const uint4& kc,
-                                                    const uint4& vc, int p_c, float ls_c, int n_c, const int32_t* mem,
-                                                    int nm, int sub, int gbase) {
-  constexpr int EPL = 16 / (int)sizeof(T), LPS = D / EPL;
-  const uint4* sk = reinterpret_cast<const uint4*>(p.sk);
-  const uint4* sv = reinterpret_cast<const uint4*>(p.sv);
-  const double E_c = log_s_hat(ls_c, n_c, p.ln_alpha);
+__device__ __forceinline__ void merge_positions(const MergeParams& p, int unit, int t_head, int c, const int32_t* list,
+                                                int off, int nm, int dst) {
+  constexpr int EPL = 16 / (int)sizeof(T), LPS = D / EPL, GPW = 64 / LPS;
+  constexpr int kRowBatch = 2;                      // entries per lane group and round trip
+  const size_t sbase = (size_t)unit * p.scap, dbase = (size_t)unit * p.dcap;
+  const uint4* sk = reinterpret_cast<const uint4*>(p.sk) + sbase * LPS;
+  const uint4* sv = reinterpret_cast<const uint4*>(p.sv) + sbase * LPS;
+  const int lane = threadIdx.x & 63, sub = lane % LPS, grp = lane / LPS;
+  const int ne = nm > 0 ? nm + 1 : 0;               // entries of this group's position
 
-  // pass 1 over the scalars: largest ln s_hat and total votes of the group
-  double mx = E_c;
-  long long P = p_c;
-  for (int i0 = 0; i0 < nm; i0 += LPS) {
-    const int i = i0 + sub;
-    double E = -INFINITY;
-    int pv = 0;
-    if (i < nm) {
-      const int s = mem[i];
-      pv = p.svotes[sbase + s];
-      E = log_s_hat(p.slog_s[sbase + s], t_head - p.sborn[sbase + s], p.ln_alpha);
+  struct Entry {
+    int s, pv, n;
+    double E;
+  };
+  CountTerm term;
+  auto entry = [&](int slot_c, int first, int i, int n_entries) {   // scalars of entry i (beyond the list: slot c, no weight)
+    Entry x{slot_c, 0, 0, -INFINITY};
+    float ls = 0.f;
+    if (i < n_entries) {
+      if (i > 0) x.s = list[first + i - 1];
+      x.pv = p.svotes[sbase + x.s];
+      ls = p.slog_s[sbase + x.s];
+      x.n = t_head - p.sborn[sbase + x.s];
     }
-    mx = fmax(mx, group_max_f64<LPS>(E));
-    P += (long long)group_sum_f64<LPS>((double)pv);
-  }
-  const bool none_seen = !(mx > -INFINITY);
-
-  // pass 2: weights, weighted sums of rows
-  float ak[EPL], av[EPL];
-  auto fma_row = [&](const uint4& x, float w, float* a) {
-    if constexpr (sizeof(T) == 2) {
-      const uint32_t u[4] = {x.x, x.y, x.z, x.w};
+    x.E = log_s_hat(ls, x.n, p.ln_alpha, term);
+    return x;
+  };
+  auto weight = [](const Entry& x, double mx) {
+    if (!(mx > -INFINITY)) return (double)x.pv;     // nothing observed: vote weights
+    return x.E > -INFINITY ? (double)x.pv * exp_f64(x.E - mx) : 0.0;
+  };
+  auto weighted_e = [](double w, const Entry& x, double mx) { return (w > 0.0 && mx > -INFINITY) ? w * x.E : 0.0; };
+  // the merged slot's scalars and the factors of its rows, from the sums over its entries
+  struct Scales {
+    float fk, fv, log_s;
+    int votes, n_r;
+  };
+  auto scales = [&](double mx, double P, double W, double WE, int n_c) {
+    Scales o;
+    o.votes = (int)(long long)P;
+    o.log_s = -INFINITY;
+    o.n_r = 0;
+    double kscale = 1.0 / W;                        // nothing observed: W = P, the vote-weighted mean stays unobserved
+    o.fv = (float)kscale;
+    if (mx > -INFINITY) {
+      const double L = mx + log_f64(W / P);             // ln(sum p s_hat / sum p)
+      const double ell_bar = WE / W;                // sum w ln s_hat / W
+      if (!(fabs(ell_bar) < kEllGuard)) kscale = (L / ell_bar) / W;
+      o.n_r = n_c > 1 ? n_c : 1;
+      o.log_s = (float)(L + term.of(o.n_r, p.ln_alpha));
+    }
+    o.fk = (float)kscale;
+    return o;
+  };
+  auto fma_row = [](const uint4& x, float w, float* a) {
+    const uint32_t u[4] = {x.x, x.y, x.z, x.w};
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
+    for (int q = 0; q < 4; ++q) {
+      if constexpr (sizeof(T) == 2) {
         a[2 * q] = fmaf(w, bf16_lo(u[q]), a[2 * q]);
         a[2 * q + 1] = fmaf(w, bf16_hi(u[q]), a[2 * q + 1]);
+      } else {
+        a[q] = fmaf(w, __builtin_bit_cast(float, u[q]), a[q]);
       }
-    } else {
-      const uint32_t u[4] = {x.x, x.y, x.z, x.w};
-#pragma unroll
-      for (int q = 0; q < 4; ++q) a[q] = fmaf(w, __builtin_bit_cast(float, u[q]), a[q]);
     }
   };
+  float acc[2 * EPL];                               // this lane's channels of the K sum, then of the V sum
+  // adds the rows of entries 0 .. cnt - 1 whose slots and weights lanes first, first + 1, ... hold
+  auto add_rows = [&](int s, float wf, int first, int cnt) {
+    for (int q0 = 0; q0 < cnt; q0 += kRowBatch * GPW) {
+      uint4 kr[kRowBatch], vr[kRowBatch];
+      float wq[kRowBatch];
 #pragma unroll
-  for (int e = 0; e < EPL; ++e) ak[e] = av[e] = 0.f;
-  const double w_c = none_seen ? (double)p_c : (E_c > -INFINITY ? (double)p_c * exp(E_c - mx) : 0.0);
-  double W = w_c, WE = (w_c > 0.0 && !none_seen) ? w_c * E_c : 0.0;
-  fma_row(kc, (float)w_c, ak);
-  fma_row(vc, (float)w_c, av);
-  for (int i0 = 0; i0 < nm; i0 += LPS) {
-    const int i = i0 + sub;
-    double w = 0.0, E = 0.0;
-    int s = c;
-    if (i < nm) {
-      s = mem[i];
-      const int pv = p.svotes[sbase + s];
-      E = log_s_hat(p.slog_s[sbase + s], t_head - p.sborn[sbase + s], p.ln_alpha);
-      w = none_seen ? (double)pv : (E > -INFINITY ? (double)pv * exp(E - mx) : 0.0);
+      for (int u = 0; u < kRowBatch; ++u) {
+        const int at = first + min(q0 + u * GPW + grp, cnt - 1);     // (surplus: the last entry again, not added)
+        const uint32_t row = (uint32_t)__shfl(s, at) * LPS + sub;
+        wq[u] = __shfl(wf, at);
+        kr[u] = sk[row];
+        vr[u] = sv[row];
+      }
+#pragma unroll
+      for (int u = 0; u < kRowBatch; ++u)
+        if (q0 + u * GPW + grp < cnt) {
+          fma_row(kr[u], wq[u], acc);
+          fma_row(vr[u], wq[u], acc + EPL);
+        }
     }
-    W += group_sum_f64<LPS>(w);
-    WE += group_sum_f64<LPS>((w > 0.0 && !none_seen) ? w * E : 0.0);
-    const float wf = (float)w;
-    const int cnt = min(LPS, nm - i0);
-    for (int q = 0; q < cnt; ++q) {
-      const int sq = __shfl(s, gbase + q);
-      const float wq = __shfl(wf, gbase + q);
-      fma_row(sk[(sbase + sq) * LPS + sub], wq, ak);
-      fma_row(sv[(sbase + sq) * LPS + sub], wq, av);
-    }
-  }
+  };
 
-  double kscale, L = -INFINITY;
-  int n_r = 0;
-  float out_log_s = -INFINITY;
-  if (none_seen) {
-    kscale = 1.0 / W;                            // W = P: vote-weighted mean, stays unobserved
-  } else {
-    L = mx + log(W / (double)P);                 // ln(sum p s_hat / sum p)
-    const double ell_bar = WE / W;               // sum w ln s_hat / W
-    kscale = (fabs(ell_bar) < kEllGuard) ? 1.0 / W : (L / ell_bar) / W;
-    n_r = n_c > 1 ? n_c : 1;
-    double ls = L;
-    if (p.ln_alpha > -INFINITY) ls += log(-expm1((double)n_r * p.ln_alpha));
-    out_log_s = (float)ls;
+  auto store_scalars = [&](int to, const Scales& sc) {
+    p.dvotes[dbase + to] = sc.votes;
+    p.dlog_s[dbase + to] = sc.log_s;
+    p.dborn[dbase + to] = t_head - sc.n_r;
+  };
+  auto clear = [&]() {
+#pragma unroll
+    for (int e = 0; e < 2 * EPL; ++e) acc[e] = 0.f;
+  };
+  auto sum2 = [](uint32_t a, uint32_t b) { return __builtin_bit_cast(float, a) + __builtin_bit_cast(float, b); };
+  auto store_rows = [&](int g, float fk, float fv) {            // the sums of group g's position, scaled
+    // The lane groups' sums meet, and are dealt out on the way: an exchange of half-wavefronts between value e and
+    // value e + half of the list adds both pairs with one addition and leaves half as many values in each lane.
+    // Lanes 0 - 31 end up with K, lanes 32 - 63 with V.
+    if constexpr (LPS == 8) {
+#pragma unroll
+      for (int e = 0; e < 2 * EPL; ++e) acc[e] += dpp_f32<0x128>(acc[e]);     // row_ror:8: the other group of this row
+    }
+    constexpr int kLeft = LPS >= 32 ? EPL : EPL / 2;            // values per lane at the end
+#pragma unroll
+    for (int e = 0; e < EPL; ++e) {
+      const auto r = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(uint32_t, acc[e]),
+                                                      __builtin_bit_cast(uint32_t, acc[e + EPL]), false, false);
+      acc[e] = sum2(r[0], r[1]);
+    }
+    if constexpr (LPS < 32) {
+#pragma unroll
+      for (int e = 0; e < EPL / 2; ++e) {
+        const auto r = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(uint32_t, acc[e]),
+                                                        __builtin_bit_cast(uint32_t, acc[e + EPL / 2]), false, false);
+        acc[e] = sum2(r[0], r[1]);
+      }
+    }
+    const float f = lane < 32 ? fk : fv;
+    const size_t row = (dbase + __builtin_amdgcn_readlane(dst, g * LPS)) * D;
+    const int ch = sub * EPL + (LPS < 32 ? ((lane >> 4) & 1) * kLeft : 0);   // this lane's first channel
+    T* out = reinterpret_cast<T*>(lane < 32 ? p.dk : p.dv) + row + ch;
+    if (LPS > 8 || (lane & 8) == 0) {
+      if constexpr (sizeof(T) == 2) {
+        static_assert(sizeof(T) != 2 || kLeft == 4, "one 8-byte store");
+        *reinterpret_cast<uint2*>(out) = make_uint2(pack_bf16x2(acc[0] * f, acc[1] * f), pack_bf16x2(acc[2] * f, acc[3] * f));
+      } else {
+#pragma unroll
+        for (int e = 0; e < kLeft; ++e) out[e] = acc[e] * f;
+      }
+    }
+  };
+
+  // ---- short lists: scalars side by side, then the rows position by position
+  if (__any(ne > 0 && ne <= LPS)) {
+    const Entry x = entry(c, off, sub, ne <= LPS ? ne : 0);
+    const double mx = group_max_f64<LPS>(x.E);
+    const double w = weight(x, mx);
+    const float wf = (float)w;
+    const Scales sc = scales(mx, group_sum_f64<LPS>((double)x.pv), group_sum_f64<LPS>(w),
+                             group_sum_f64<LPS>(weighted_e(w, x, mx)), __shfl(x.n, grp * LPS));
+    if (ne > 0 && ne <= LPS && sub == 0) store_scalars(dst, sc);
+#pragma unroll 1
+    for (int g = 0; g < GPW; ++g) {
+      const int n = __builtin_amdgcn_readlane(ne, g * LPS);     // uniform: entries of group g's position
+      if (n == 0 || n > LPS) continue;
+      clear();
+      add_rows(x.s, wf, g * LPS, n);
+      store_rows(g, __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, sc.fk), g * LPS)),
+                 __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, sc.fv), g * LPS)));
+    }
   }
-  const float fk = (float)kscale, fv = (float)(1.0 / W);
-  uint4 ok, ov;
-  if constexpr (sizeof(T) == 2) {
-    ok.x = pack_bf16x2(ak[0] * fk, ak[1] * fk); ok.y = pack_bf16x2(ak[2] * fk, ak[3] * fk);
-    ok.z = pack_bf16x2(ak[4] * fk, ak[5] * fk); ok.w = pack_bf16x2(ak[6] * fk, ak[7] * fk);
-    ov.x = pack_bf16x2(av[0] * fv, av[1] * fv); ov.y = pack_bf16x2(av[2] * fv, av[3] * fv);
-    ov.z = pack_bf16x2(av[4] * fv, av[5] * fv); ov.w = pack_bf16x2(av[6] * fv, av[7] * fv);
-  } else {
-    ok.x = __builtin_bit_cast(uint32_t, ak[0] * fk); ok.y = __builtin_bit_cast(uint32_t, ak[1] * fk);
-    ok.z = __builtin_bit_cast(uint32_t, ak[2] * fk); ok.w = __builtin_bit_cast(uint32_t, ak[3] * fk);
-    ov.x = __builtin_bit_cast(uint32_t, av[0] * fv); ov.y = __builtin_bit_cast(uint32_t, av[1] * fv);
-    ov.z = __builtin_bit_cast(uint32_t, av[2] * fv); ov.w = __builtin_bit_cast(uint32_t, av[3] * fv);
+  // ---- long lists, one after the other
+  if (!__any(ne > LPS)) return;
+#pragma unroll 1
+  for (int g = 0; g < GPW; ++g) {
+    const int n = __builtin_amdgcn_readlane(ne, g * LPS);
+    if (n <= LPS) continue;
+    const int c_g = __builtin_amdgcn_readlane(c, g * LPS), off_g = __builtin_amdgcn_readlane(off, g * LPS);
+    Entry x = entry(c_g, off_g, lane, n);
+    const int n_c = __builtin_amdgcn_readfirstlane(x.n);
+    double mx = group_max_f64<64>(x.E), P = group_sum_f64<64>((double)x.pv);
+    for (int i0 = 64; i0 < n; i0 += 64) {
+      const Entry y = entry(c_g, off_g, i0 + lane, n);
+      mx = fmax(mx, group_max_f64<64>(y.E));
+      P += group_sum_f64<64>((double)y.pv);
+    }
+    double W = 0.0, WE = 0.0;
+    clear();
+    for (int i0 = 0; i0 < n; i0 += 64) {
+      if (i0 > 0) x = entry(c_g, off_g, i0 + lane, n);
+      const double w = weight(x, mx);
+      W += group_sum_f64<64>(w);
+      WE += group_sum_f64<64>(weighted_e(w, x, mx));
+      add_rows(x.s, (float)w, 0, min(64, n - i0));
+    }
+    const Scales sc = scales(mx, P, W, WE, n_c);
+    if (lane == 0) store_scalars(__builtin_amdgcn_readlane(dst, g * LPS), sc);
+    store_rows(g, sc.fk, sc.fv);
   }
-  MergedRow out;
-  out.k = ok; out.v = ov; out.votes = (int32_t)P; out.log_s = out_log_s; out.n_r = n_r;
-  return out;
 }
 
 // DIRECT (few evictable slots per head, the steady state): no CSR list has been built; the workgroup reads
@@ -392,10 +502,12 @@ __global__ __launch_bounds__(256) void merge_apply_kernel(MergeParams p) {
   __shared__ int s_mem[DIRECT ? GPB : 1][DIRECT ? kDirectMaxEvict : 1];
   __shared__ long long s_drop;
   const int unit = blockIdx.y;
-  const int r = blockIdx.x * GPB + threadIdx.x / LPS;
   const int sub = threadIdx.x % LPS;
   const int lane = threadIdx.x & 63;
   const int gbase = lane - sub;                 // first lane of this group within the wavefront
+  // positions per wavefront: one for each lane group, or fewer (the other groups then only help with the rows)
+  const int ppw = DIRECT ? 64 / LPS : p.positions_per_wave;
+  const int r = lane / LPS < ppw ? ((int)blockIdx.x * 4 + (int)(threadIdx.x >> 6)) * ppw + lane / LPS : p.budget;
   const int t_head = p.st_obs[unit];            // the head's step counter: unchanged by a merge
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     p.dt_obs[unit] = t_head;
@@ -410,7 +522,7 @@ __global__ __launch_bounds__(256) void merge_apply_kernel(MergeParams p) {
   // The slot number of this position is requested first, and with DIRECT the retained row and its scalars are
   // requested before the head's lists are waited for: requests complete in the order of issue, so the
   // lists' round trip and the row's overlap instead of following each other.
-  const int c = r < p.budget ? p.keep_idx[(size_t)unit * p.budget + r] : -1;
+  const int c = r < p.budget ? p.keep_idx[(size_t)unit * p.budget + r] : -1;   // (-1: nothing to write)
   int n_ev = 0;
   uint4 kc = make_uint4(0, 0, 0, 0), vc = make_uint4(0, 0, 0, 0);
   int p_c = 0, n_c = 0;
@@ -449,12 +561,13 @@ __global__ __launch_bounds__(256) void merge_apply_kernel(MergeParams p) {
       if (threadIdx.x == 0 && s_drop != 0) p.dropped_votes[unit] += s_drop;   // no other workgroup touches it
     }
   }
-  if (r >= p.budget) return;
   // (without DIRECT: two dependent round trips per row, (slot number, member range), then (rows, scalars))
   int m0 = 0, m1 = 0;
   if constexpr (!DIRECT) {
-    m0 = p.start[(size_t)unit * (p.budget + 1) + r];
-    m1 = p.start[(size_t)unit * (p.budget + 1) + r + 1];
+    if (r < p.budget) {
+      m0 = p.start[(size_t)unit * (p.budget + 1) + r];
+      m1 = p.start[(size_t)unit * (p.budget + 1) + r + 1];
+    }
   } else {
     // this group's members: positions of the evict list whose target is r, LPS candidates at a time
     int* mine = s_mem[threadIdx.x / LPS];
@@ -469,32 +582,23 @@ __global__ __launch_bounds__(256) void merge_apply_kernel(MergeParams p) {
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
   }
-  if (c < 0) return;
   uint4* dk = reinterpret_cast<uint4*>(p.dk);
   uint4* dv = reinterpret_cast<uint4*>(p.dv);
-  const int nm = m1 - m0;                        // evicted members of this group
-  if constexpr (!DIRECT) request_row();
-
-  if (nm == 0) {                                  // nothing merged here: copy
-    dk[(dbase + r) * LPS + sub] = kc;
-    dv[(dbase + r) * LPS + sub] = vc;
+  const int nm = c >= 0 ? m1 - m0 : 0;           // evicted members of this group
+  const size_t at = dbase + r;
+  if (c >= 0 && nm == 0) {                       // nothing merged here: copy
+    if constexpr (!DIRECT) request_row();
+    dk[at * LPS + sub] = kc;
+    dv[at * LPS + sub] = vc;
     if (sub == 0) {
-      p.dvotes[dbase + r] = p_c;
-      p.dlog_s[dbase + r] = ls_c;
-      p.dborn[dbase + r] = t_head - n_c;
+      p.dvotes[at] = p_c;
+      p.dlog_s[at] = ls_c;
+      p.dborn[at] = t_head - n_c;
     }
-    return;
   }
-
-  const int32_t* mem = DIRECT ? s_mem[threadIdx.x / LPS] : p.members + sbase + m0;
-  const MergedRow mr = merge_position<T, D>(p, sbase, t_head, c, kc, vc, p_c, ls_c, n_c, mem, nm, sub, gbase);
-  dk[(dbase + r) * LPS + sub] = mr.k;
-  dv[(dbase + r) * LPS + sub] = mr.v;
-  if (sub == 0) {
-    p.dvotes[dbase + r] = mr.votes;
-    p.dlog_s[dbase + r] = mr.log_s;
-    p.dborn[dbase + r] = t_head - mr.n_r;
-  }
+  if (!__any(nm > 0)) return;                    // uniform over the wavefront
+  const int32_t* list = DIRECT ? &s_mem[0][0] : p.members + sbase;
+  merge_positions<T, D>(p, unit, t_head, max(c, 0), list, DIRECT ? (int)(threadIdx.x / LPS) * kDirectMaxEvict : m0, nm, r);
 }
 
 // ---------------------------------------------------------------------------------------------------
@@ -682,7 +786,7 @@ __global__ __launch_bounds__(kInplaceThreads) void merge_inplace_kernel(MergePar
   __shared__ int s_wcnt[kWaves];
   __shared__ long long s_drop;
   const int unit = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int sub = tid % LPS, grp = tid / LPS, gbase = lane - sub;
+  const int sub = tid % LPS, grp = tid / LPS;
   const int t_head = p.st_obs[unit];
   const int n_ev = min(p.n_evict[unit], kDirectMaxEvict);
   if (n_ev <= 0) return;                              // uniform over the workgroup
@@ -746,27 +850,15 @@ __global__ __launch_bounds__(kInplaceThreads) void merge_inplace_kernel(MergePar
   const uint4* sv = reinterpret_cast<const uint4*>(p.sv);
   uint4* dk = reinterpret_cast<uint4*>(p.dk);
   uint4* dv = reinterpret_cast<uint4*>(p.dv);
-  for (int t0 = 0; t0 < nt; t0 += GPB) {              // uniform trip count: a group without a target repeats the first one and writes nothing
-    const bool active = t0 + grp < nt;
-    const int ti = active ? t0 + grp : 0;
+  for (int t0 = 0; t0 < nt; t0 += GPB) {              // uniform trip count: a group without a target has nothing to merge
+    // (the targets are dealt to the wavefronts in turn: a wavefront sums its positions' rows one after the other)
+    const int t = t0 + (grp % (64 / LPS)) * kWaves + wave;
+    const bool active = t < nt;
+    const int ti = active ? t : 0;
     const int r = s_tgt[ti];
     const int c = p.keep_idx[(size_t)unit * p.budget + r];
-    const size_t at = sbase + max(c, 0);
-    const uint4 kc = sk[at * LPS + sub], vc = sv[at * LPS + sub];
-    const int p_c = p.svotes[at];
-    const float ls_c = p.slog_s[at];
-    const int n_c = t_head - p.sborn[at];
-    const MergedRow mr = merge_position<T, D>(p, sbase, t_head, c, kc, vc, p_c, ls_c, n_c, s_members + s_start[ti], s_cnt[ti],
-                                              sub, gbase);
-    if (active && c >= 0) {
-      dk[at * LPS + sub] = mr.k;
-      dv[at * LPS + sub] = mr.v;
-      if (sub == 0) {
-        p.dvotes[at] = mr.votes;
-        p.dlog_s[at] = mr.log_s;
-        p.dborn[at] = t_head - mr.n_r;
-      }
-    }
+    const int nm = active && c >= 0 ? s_cnt[ti] : 0;
+    merge_positions<T, D>(p, unit, t_head, max(c, 0), s_members, s_start[ti], nm, max(c, 0));
   }
 
   // ---- move the retained tokens of the append region into the evicted slots below `budget`.  Every read of an
@@ -812,6 +904,18 @@ __global__ __launch_bounds__(kInplaceThreads) void merge_inplace_kernel(MergePar
 }
 
 }  // namespace
+
+// Positions that a wavefront of merge_apply_kernel takes (lps lanes each).  Side by side they share the f64 scalars;
+// but a wavefront sums their rows one position after the other, so with few positions on the chip it takes fewer, until
+// there are kApplyWaves wavefronts (four for each SIMD): 24 heads x 501 positions
+// of D 64 take 38 us with eight positions per wavefront and 25 with four; more wavefronts than that lose (64 heads x
+// 820 positions, mostly copies: 16.7 us at 4096, 20.4 at 16384, 27.6 at 65536).
+constexpr int kApplyWaves = 4096;
+static int positions_per_wave(unsigned units, int positions, int lps) {
+  int ppw = 64 / lps;
+  while (ppw > 1 && (long)units * positions / ppw < kApplyWaves) ppw /= 2;
+  return ppw;
+}
 
 PrefillMergePlan plan_prefill_merge(const keepkv_layout* L, int capacity) {
   PrefillMergePlan pl;
@@ -860,19 +964,18 @@ extern "C" keepkv_status keepkv_merge(const keepkv_layout* layout, const keepkv_
   int32_t* start = reinterpret_cast<int32_t*>(reinterpret_cast<char*>(workspace) + pl.start_off);
   int32_t* members = reinterpret_cast<int32_t*>(reinterpret_cast<char*>(workspace) + pl.member_off);
 
-  size_t key_bytes = 4;
-  while (key_bytes < (size_t)max_evict * 4) key_bytes <<= 1;
-  if (key_bytes <= kMaxEvict * 4 / 2) key_bytes *= 2;   // room for the grouped copy of the keys (counting path)
-  if (key_bytes > 32 * 1024) {
-    static const hipError_t attr = hipFuncSetAttribute((const void*)merge_group_kernel,
-                                                       hipFuncAttributeMaxDynamicSharedMemorySize, kMaxEvict * 4);
-    if (attr != hipSuccess) return KEEPKV_ERR_DEVICE;
-  }
+  const size_t place_bytes = ((size_t)max_evict * sizeof(uint16_t) + 15) / 16 * 16;   // (read 16 bytes at a time)
+  static const hipError_t attr = hipFuncSetAttribute((const void*)merge_group_kernel,
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, kMaxEvict * (int)sizeof(uint16_t));
+  if (attr != hipSuccess) return KEEPKV_ERR_DEVICE;
   const bool direct = max_evict <= kDirectMaxEvict;   // the steady state: the apply kernel finds its members itself
-  if (!direct)
-    merge_group_kernel<<<units, kGroupThreads, key_bytes, st>>>(match, evict_idx, n_evict, src->votes, start, members,
-                                                                dropped_votes, src->capacity, budget, max_evict,
-                                                                (int)(key_bytes / 4));
+  if (!direct) {
+    int shares = (int)(256 / units);
+    shares = shares < 1 ? 1 : (shares > kMaxGroupShares ? kMaxGroupShares : shares);
+    if (shares > budget) shares = budget;
+    merge_group_kernel<<<units * shares, kGroupThreads, place_bytes, st>>>(
+        match, evict_idx, n_evict, src->votes, start, members, dropped_votes, src->capacity, budget, max_evict, shares);
+  }
   MergeParams p;
   p.sk = src->k; p.sv = src->v; p.svotes = src->votes; p.slog_s = src->log_s; p.sborn = src->born; p.st_obs = src->t_obs; p.slen = src->len;
   p.dk = dst->k; p.dv = dst->v; p.dvotes = dst->votes; p.dlog_s = dst->log_s; p.dborn = dst->born; p.dt_obs = dst->t_obs; p.dlen = dst->len;
@@ -882,8 +985,8 @@ extern "C" keepkv_status keepkv_merge(const keepkv_layout* layout, const keepkv_
   p.write_len = 1;
   p.ln_alpha = alpha > 0.f ? log((double)alpha) : -INFINITY;
   const int esz = layout->dtype == KEEPKV_BF16 ? 2 : 4;
-  const int lps = layout->head_dim * esz / 16, gpb = 256 / lps;
-  const dim3 grid((budget + gpb - 1) / gpb, units);
+  p.positions_per_wave = direct ? 64 / (layout->head_dim * esz / 16) : positions_per_wave(units, budget, layout->head_dim * esz / 16);
+  const dim3 grid((budget + 4 * p.positions_per_wave - 1) / (4 * p.positions_per_wave), units);
   if (layout->dtype == KEEPKV_BF16) {
     if (layout->head_dim == 128) {
       if (direct) merge_apply_kernel<uint16_t, 128, true><<<grid, 256, 0, st>>>(p);
@@ -991,8 +1094,8 @@ extern "C" keepkv_status keepkv_prefill_merge(const keepkv_layout* layout, const
   p.write_len = 0;
   p.ln_alpha = alpha > 0.f ? log((double)alpha) : -INFINITY;
   const int esz = layout->dtype == KEEPKV_BF16 ? 2 : 4;
-  const int lps = layout->head_dim * esz / 16, gpb = 256 / lps;
-  const dim3 grid((cap + gpb - 1) / gpb, units);
+  p.positions_per_wave = positions_per_wave(units, cap, layout->head_dim * esz / 16);
+  const dim3 grid((cap + 4 * p.positions_per_wave - 1) / (4 * p.positions_per_wave), units);
   if (layout->dtype == KEEPKV_BF16) {
     if (layout->head_dim == 128) merge_apply_kernel<uint16_t, 128, false><<<grid, 256, 0, st>>>(p);
     else merge_apply_kernel<uint16_t, 64, false><<<grid, 256, 0, st>>>(p);
