@@ -117,7 +117,7 @@ SelectPlan plan_select(const keepkv_layout* L, int capacity);
 
 struct MatchPlan {
   size_t rnorm_off;   // float [B*Hkv, budget]      1/|k_c| of the retained keys
-  size_t flag_off;    // int32 [1 + B*Hkv*(capacity-budget)]  counter + flagged row list
+  size_t flag_off;    // int32 [2][B*Hkv*(capacity-budget)]  queued rows, their candidate columns
   size_t panel_off;   // bf16 [B*Hkv, padded budget, D]  retained keys gathered for the first event's kernel
   size_t partial_off; // per-share results of the f64 kernel when it splits queued rows
   size_t small_partial_off; // per-share results of the steady-state kernel when workgroups share a row block
@@ -127,7 +127,7 @@ MatchPlan plan_match(const keepkv_layout* L, int capacity, int budget);
 
 struct PrefillMatchPlan {
   size_t rnorm_off;   // float [B*Hkv, capacity]      1/|k_i| of every live slot
-  size_t flag_off;    // int32 [1 + B*Hkv*capacity]   queue of rows for the f64 kernel
+  size_t flag_off;    // int32 [2][B*Hkv*capacity]   queue of rows for the f64 kernel, their candidate columns
   size_t partial_off; // per-share results of the f64 kernel
   size_t bytes;
 };

@@ -112,6 +112,8 @@ struct MatchParams {
   int32_t* flag_count;   // [1] rows queued for the f64 kernel; zero between calls (the f64 kernel clears it)
   int32_t* exact_done;   // [1] queued rows that the f64 kernel has finished; zero between calls
   int32_t* flag_rows;    // [units * max_evict]: unit * max_evict + j
+  uint32_t* flag_cols;   // [units * max_evict]: the queued row's candidate columns, bit o for the columns 32 b + o
+                         // (first event and prefill pass; the steady-state kernel's rows are re-checked against all columns)
   int capacity, budget, max_evict, rn_pitch;
   float threshold, delta;
   int per_unit, n_units;   // first event's kernel: workgroups per head, heads
@@ -154,21 +156,32 @@ __device__ __forceinline__ void decide_row(const MatchParams& p, int unit, int j
 }
 
 // f32 decision of one row from its best value y1 (column c1) and an upper bound y2 of every other column's
-// value, both still lacking the factor 1/|k_e|; rows that the f32 arithmetic cannot decide are queued.
-__device__ __forceinline__ void decide_row_f32(const MatchParams& p, int unit, int j, float y1, int c1, float y2,
-                                               float ss) {
+// value, both still lacking the factor 1/|k_e|.  Returns whether the f32 arithmetic cannot decide the row, which the
+// caller then queues.
+__device__ __forceinline__ bool decide_row_f32(const MatchParams& p, size_t o, float y1, int c1, float y2, float ss, int n_cols) {
   const float rn_e = 1.0f / sqrtf(ss);
   const float cos1 = y1 * rn_e;
   bool fragile = !(y1 > 0.f) || !(ss > 0.f) || !(rn_e < INFINITY) || !((y1 - y2) * rn_e > p.delta) ||
-                 !(fabsf(cos1 - p.threshold) > p.delta) || c1 >= p.budget;
+                 !(fabsf(cos1 - p.threshold) > p.delta) || c1 >= n_cols;
   if (surely_below(p, (y1 <= 0.f) ? 0.f : cos1, ss, rn_e)) fragile = false;
-  const size_t o = (size_t)unit * p.max_evict + j;
   p.match[o] = (cos1 > p.threshold) ? c1 : -1;
   if (p.sim_out != nullptr) p.sim_out[o] = cos1;
-  if (fragile) {
-    const int at = atomicAdd(p.flag_count, 1);
-    p.flag_rows[at] = (int)o;
-  }
+  return fragile;
+}
+
+// The columns that can hold a row's true best value, as a mask over the column number modulo 32: those whose column
+// class has an f32 best within the margin of the row's best (the rule by which a row without a close runner-up is
+// decided, a little wider for the rounding of `lim`).  cls: this lane's 16 classes, columns 8 (i / 4) + 4 half + i % 4
+// of every block; the lanes l and l ^ 32 hold the two halves.  A row of a few hundred columns has two or three candidate
+// classes as a rule, so the f64 kernel has a tenth of its columns or less to look at.  NaN: all columns.
+__device__ __forceinline__ uint32_t candidate_columns(const MatchParams& p, const int (&cls)[16], float y1, float ss, int half) {
+  const float lim = y1 - 1.01f * p.delta * sqrtf(ss);
+  uint32_t m = 0;
+#pragma unroll
+  for (int i = 0; i < 16; ++i)
+    m |= (!(__builtin_bit_cast(float, cls[i]) < lim) ? 1u : 0u) << (8 * (i / 4) + (i % 4));
+  m <<= 4 * half;
+  return m | (uint32_t)__shfl_xor((int)m, 32);
 }
 
 // The first event's kernel.  The product is taken transposed, retained keys as the A operand and the
@@ -427,9 +440,20 @@ __global__ __launch_bounds__(kMWaves* kWave, 2) void match_mfma_kernel(MatchPara
     y2[t] = __builtin_bit_cast(float, imax(imax(rest, orest), imin(s1, o1)));
   }
   const int j = rb * kRowsPerBlock + wave * kRowsPerWave + lane;   // lane = 32 half + l32 finishes row l32 of tile `half`
+  const size_t o = (size_t)unit * p.max_evict + j;
+  bool fragile = false;
   if (j < n_ev)
-    decide_row_f32(p, unit, j, half ? y1[1] : y1[0], half ? c1[1] : c1[0], half ? y2[1] : y2[0],
-                   half ? ss_row[1] : ss_row[0]);
+    fragile = decide_row_f32(p, o, half ? y1[1] : y1[0], half ? c1[1] : c1[0], half ? y2[1] : y2[0],
+                             half ? ss_row[1] : ss_row[0], n_keep);
+  if (__any(fragile)) {                      // uniform over the wavefront
+    const uint32_t m0 = candidate_columns(p, cls[0], y1[0], ss_row[0], half);
+    const uint32_t m1 = candidate_columns(p, cls[1], y1[1], ss_row[1], half);
+    if (fragile) {
+      const int at = atomicAdd(p.flag_count, 1);
+      p.flag_rows[at] = (int)o;
+      p.flag_cols[at] = half ? m1 : m0;
+    }
+  }
   { const int pass = (rb - first_rb) / p.per_unit; if (pass < 4) KX_TS(4 + pass); }
   if (!more) break;
   rb = rb_next;
@@ -1029,22 +1053,28 @@ __global__ __launch_bounds__(kPfWaves* kWave) void prefill_near_kernel(MatchPara
     bcol = (s1 > o1) ? col : ((o1 > s1) ? ocol : min(col, ocol));
     second = __builtin_bit_cast(float, imax(imax(rest, orest), imin(s1, o1)));
   }
-  if (half != 0 || row >= n) return;
+  const bool mine = half == 0 && row < n;
   const size_t o = (size_t)unit * p.max_evict + row;
-  if (row == 0) {                                        // no earlier key
+  bool fragile = false;
+  const float ss_row = 1.0f / (rn_row * rn_row);         // (rn_row = 0: a zero key, or |k|^2 beyond f32)
+  if (mine && row == 0) {                                // no earlier key
     p.match[o] = -1;
     if (p.sim_out != nullptr) p.sim_out[o] = -INFINITY;
-    return;
+  } else if (mine) {
+    const float cos1 = best * rn_row;
+    fragile = !(best > 0.f) || !(rn_row > 0.f) || !(rn_row < INFINITY) || !((best - second) * rn_row > p.delta) ||
+              !(fabsf(cos1 - p.threshold) > p.delta);
+    if (surely_below(p, (best <= 0.f) ? 0.f : cos1, rn_row, rn_row)) fragile = false;
+    p.match[o] = (cos1 > p.threshold) ? bcol : -1;
+    if (p.sim_out != nullptr) p.sim_out[o] = cos1;
   }
-  const float cos1 = best * rn_row;
-  bool fragile = !(best > 0.f) || !(rn_row > 0.f) || !(rn_row < INFINITY) || !((best - second) * rn_row > p.delta) ||
-                 !(fabsf(cos1 - p.threshold) > p.delta);
-  if (surely_below(p, (best <= 0.f) ? 0.f : cos1, rn_row, rn_row)) fragile = false;
-  p.match[o] = (cos1 > p.threshold) ? bcol : -1;
-  if (p.sim_out != nullptr) p.sim_out[o] = cos1;
-  if (fragile) {
-    const int at = atomicAdd(p.flag_count, 1);
-    p.flag_rows[at] = (int)o;
+  if (__any(fragile)) {                                  // uniform over the wavefront
+    const uint32_t m = candidate_columns(p, cls, best, ss_row, half);
+    if (fragile) {
+      const int at = atomicAdd(p.flag_count, 1);
+      p.flag_rows[at] = (int)o;
+      p.flag_cols[at] = m;
+    }
   }
 }
 
@@ -1064,17 +1094,149 @@ __global__ void flag_all_causal_kernel(const int32_t* __restrict__ len, int32_t*
   }
 }
 
-// The f64 kernel for bf16 caches.  Products of bf16 values are exact in f64 and so are their sums over the head
+// The f64 kernels for bf16 caches.  Products of bf16 values are exact in f64 and so are their sums over the head
 // dimension (for any ordinary exponent spread), whatever the order, so a key's channels may be split over lanes:
 // four lanes share a key, each holding a quarter of the channels of the evicted row in registers (as f64) and
-// loading the same quarter of the key, 64 keys per workgroup at a time and kExactBatch such rounds in flight.
+// loading the same quarter of the key.
+template <int D>
+struct ExactQuarter {
+  static constexpr int CPL = D / 32, EPL = CPL * 8;          // 16-byte chunks / channels per lane
+  double ed[EPL];
+  double rn_e;
+  __device__ __forceinline__ void load(const unsigned char* row, int sub) {
+    uint4 ev[CPL];
+#pragma unroll
+    for (int q = 0; q < CPL; ++q) ev[q] = *reinterpret_cast<const uint4*>(row + (sub * CPL + q) * 16);
+    double ss_e = 0.0;
+#pragma unroll
+    for (int q = 0; q < CPL; ++q) {
+      const uint32_t wv[4] = {ev[q].x, ev[q].y, ev[q].z, ev[q].w};
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        ed[q * 8 + 2 * i] = (double)bf16_lo(wv[i]);
+        ed[q * 8 + 2 * i + 1] = (double)bf16_hi(wv[i]);
+        ss_e = fma(ed[q * 8 + 2 * i], ed[q * 8 + 2 * i], ss_e);
+        ss_e = fma(ed[q * 8 + 2 * i + 1], ed[q * 8 + 2 * i + 1], ss_e);
+      }
+    }
+    ss_e += __shfl_xor(ss_e, 1);
+    ss_e += __shfl_xor(ss_e, 2);
+    rn_e = 1.0 / sqrt(ss_e);
+  }
+  // the cosine with the key whose quarter is in x (the same value in the four lanes); -inf for a zero-norm key
+  __device__ __forceinline__ double cosine(const uint4 (&x)[CPL]) const {
+    double dot = 0.0, ss_c = 0.0;
+#pragma unroll
+    for (int q = 0; q < CPL; ++q) {
+      const uint32_t wv[4] = {x[q].x, x[q].y, x[q].z, x[q].w};
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const double lo = (double)bf16_lo(wv[i]), hi = (double)bf16_hi(wv[i]);
+        dot = fma(ed[q * 8 + 2 * i], lo, dot);
+        ss_c = fma(lo, lo, ss_c);
+        dot = fma(ed[q * 8 + 2 * i + 1], hi, dot);
+        ss_c = fma(hi, hi, ss_c);
+      }
+    }
+    dot += __shfl_xor(dot, 1);
+    ss_c += __shfl_xor(ss_c, 1);
+    dot += __shfl_xor(dot, 2);
+    ss_c += __shfl_xor(ss_c, 2);
+    const double u = (dot * rn_e) * (1.0 / sqrt(ss_c));
+    return fabs(u) <= 1.79e308 ? u : -INFINITY;               // zero-norm keys (nan / inf) match nothing
+  }
+};
+// best value and lowest column of the 16 quads of a wavefront (the four lanes of a quad hold the same pair)
+__device__ __forceinline__ void best_of_quads(double& best, int& best_c) {
+#pragma unroll
+  for (int off = 4; off < 64; off <<= 1) {
+    const double ob = __shfl_xor(best, off);
+    const int oc = __shfl_xor(best_c, off);
+    if (ob > best || (ob == best && oc < best_c)) {
+      best = ob;
+      best_c = oc;
+    }
+  }
+}
+
+// First event and prefill pass: every queued row comes with the mask of its candidate columns (candidate_columns above),
+// and one wavefront re-evaluates them, 16 at a time and kRecheckBatch such rounds in flight.  The first event reads the
+// retained keys from the gathered panel; the prefill pass (causal) the slots before the row.
+// What bounds it: a chain of four dependent round trips per row (queue, evicted slot, its row, keys).  Evaluating every
+// column of a row with a whole workgroup took (MI355X) 218 us for the long-context first event and 450 us for the
+// batch-128 one; the candidates alone take 21 and 32 us.
+constexpr int kRecheckBatch = 4;
+template <int D>
+__global__ __launch_bounds__(256) void match_recheck_kernel(MatchParams p) {
+  constexpr int ROWB = D * 2, CHUNKS = ROWB / 16, CPL = ExactQuarter<D>::CPL;
+  __shared__ int s_done;
+  __shared__ unsigned char s_off[4][32];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, quad = lane >> 2, sub = lane & 3;
+  const int n_flag = *p.flag_count;
+  if (tid == 0) s_done = 0;
+  __syncthreads();
+  int finished = 0;                          // rows whose result this wavefront has written
+  for (int f = blockIdx.x * 4 + wave; f < n_flag; f += gridDim.x * 4) {
+    const int o = p.flag_rows[f];
+    const uint32_t cols = p.flag_cols[f];
+    const int unit = o / p.max_evict, j = o % p.max_evict;
+    const unsigned char* kunit = reinterpret_cast<const unsigned char*>(p.k) + (size_t)unit * p.capacity * ROWB;
+    const int e = p.causal ? j : p.evict_idx[(size_t)unit * p.max_evict + j];
+    const int n_cols = p.causal ? j : p.budget;
+    // the k-th candidate is column 32 (k / n_off) + s_off[k mod n_off]: ascending in k
+    const int n_off = __popc(cols);
+    if (lane < 32 && ((cols >> lane) & 1u)) s_off[wave][__popc(cols & ((1u << lane) - 1u))] = (unsigned char)lane;
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    const int n_cand = n_off * ((n_cols + 31) / 32);
+    const unsigned char* keys = p.causal ? kunit : p.panel + (size_t)unit * p.rn_pitch * ROWB;
+    ExactQuarter<D> row;
+    row.load(kunit + (size_t)e * ROWB, sub);
+    double best = -INFINITY;
+    int best_c = 0x7FFFFFFF;
+    for (int k0 = 0; k0 < n_cand; k0 += 16 * kRecheckBatch) {
+      int col[kRecheckBatch];
+      uint4 x[kRecheckBatch][CPL];
+#pragma unroll
+      for (int b = 0; b < kRecheckBatch; ++b) {
+        const int k = k0 + b * 16 + quad;
+        const int blk = k / n_off;
+        const int c = 32 * blk + s_off[wave][k - blk * n_off];
+        col[b] = (k < n_cand && c < n_cols) ? c : -1;
+        const int at = max(col[b], 0);                             // (n_cand > 0: column 0 exists)
+        const unsigned char* rp = keys + (size_t)at * ROWB;
+        const int swz = p.causal ? 0 : (at & (CHUNKS - 1));        // panel: chunk ch of key c at position ch ^ (c mod CHUNKS)
+#pragma unroll
+        for (int q = 0; q < CPL; ++q) x[b][q] = *reinterpret_cast<const uint4*>(rp + (((sub * CPL + q) ^ swz) * 16));
+      }
+#pragma unroll
+      for (int b = 0; b < kRecheckBatch; ++b) {
+        const double u = row.cosine(x[b]);
+        if (col[b] >= 0 && (u > best || (u == best && col[b] < best_c))) {
+          best = u;
+          best_c = col[b];
+        }
+      }
+    }
+    best_of_quads(best, best_c);
+    if (lane == 0) {
+      p.match[o] = (best > (double)p.threshold) ? best_c : -1;
+      if (p.sim_out != nullptr) p.sim_out[o] = (float)best;
+    }
+    ++finished;
+  }
+  if (lane == 0 && finished > 0) atomicAdd(&s_done, finished);
+  __syncthreads();
+  exact_exit(p, n_flag, s_done);
+}
+
+// Steady state: few queued rows, each against all retained keys.
 // One workgroup per queued row, or per share of a row's columns when the queue is short (joined by a ticket, as
-// in the generic kernel below).  The first event reads the retained keys from the gathered panel (no slot
-// list to wait for); otherwise the slot numbers of a whole batch are requested first, then their rows.
+// in the generic kernel above).  The slot numbers of a whole batch are requested first, then their rows.
 constexpr int kExactBatch = 4;
 template <int D>
 __global__ __launch_bounds__(256) void match_exact_bf16_kernel(MatchParams p) {
-  constexpr int ROWB = D * 2, CHUNKS = ROWB / 16, CPL = CHUNKS / 4, EPL = CPL * 8;   // chunks / channels per lane
+  constexpr int ROWB = D * 2, CPL = ExactQuarter<D>::CPL;
   __shared__ double s_best[4];
   __shared__ int s_bestc[4];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -1092,97 +1254,38 @@ __global__ __launch_bounds__(256) void match_exact_bf16_kernel(MatchParams p) {
     const int o = p.flag_rows[f];
     const int unit = o / p.max_evict, j = o % p.max_evict;
     const unsigned char* kunit = kall + (size_t)unit * p.capacity * ROWB;
-    const int32_t* keep = p.causal ? nullptr : p.keep_idx + (size_t)unit * p.budget;
-    const unsigned char* panel = (p.panel != nullptr && !p.causal) ? p.panel + (size_t)unit * p.rn_pitch * ROWB : nullptr;
-    const int n_cols = p.causal ? j : p.budget;
-    const int share = (n_cols + parts - 1) / parts;
-    const int c_lo = part * share, c_hi = imin(n_cols, c_lo + share);
+    const int32_t* keep = p.keep_idx + (size_t)unit * p.budget;
+    const int share = (p.budget + parts - 1) / parts;
+    const int c_lo = part * share, c_hi = imin(p.budget, c_lo + share);
     // this lane's quarter of the evicted row (its slot number is one more round trip; the keys below do not wait for it)
-    const int e = p.causal ? j : p.evict_idx[(size_t)unit * p.max_evict + j];
-    uint4 ev[CPL];
-#pragma unroll
-    for (int q = 0; q < CPL; ++q) ev[q] = *reinterpret_cast<const uint4*>(kunit + (size_t)e * ROWB + (sub * CPL + q) * 16);
-    double ed[EPL];
-    double ss_e = 0.0;
-#pragma unroll
-    for (int q = 0; q < CPL; ++q) {
-      const uint32_t wv[4] = {ev[q].x, ev[q].y, ev[q].z, ev[q].w};
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        ed[q * 8 + 2 * i] = (double)bf16_lo(wv[i]);
-        ed[q * 8 + 2 * i + 1] = (double)bf16_hi(wv[i]);
-        ss_e = fma(ed[q * 8 + 2 * i], ed[q * 8 + 2 * i], ss_e);
-        ss_e = fma(ed[q * 8 + 2 * i + 1], ed[q * 8 + 2 * i + 1], ss_e);
-      }
-    }
-    ss_e += __shfl_xor(ss_e, 1);
-    ss_e += __shfl_xor(ss_e, 2);
-    const double rn_e = 1.0 / sqrt(ss_e);
+    ExactQuarter<D> row_e;
+    row_e.load(kunit + (size_t)p.evict_idx[(size_t)unit * p.max_evict + j] * ROWB, sub);
     double best = -INFINITY;
     int best_c = 0x7FFFFFFF;
     for (int c0 = c_lo; c0 < c_hi; c0 += 64 * kExactBatch) {
       int slot[kExactBatch];
       uint4 row[kExactBatch][CPL];
-      if (panel == nullptr) {
-#pragma unroll
-        for (int b = 0; b < kExactBatch; ++b) {
-          const int c = c0 + b * 64 + quad;
-          slot[b] = (c < c_hi) ? (p.causal ? c : keep[c]) : -1;
-        }
-      }
 #pragma unroll
       for (int b = 0; b < kExactBatch; ++b) {
         const int c = c0 + b * 64 + quad;
-        if (panel != nullptr) {                  // key c of the list, its chunk ch stored at position ch ^ (c mod CHUNKS)
-          slot[b] = c < c_hi ? c : -1;
-          const unsigned char* rp = panel + (size_t)imin(c, n_cols - 1) * ROWB;
-#pragma unroll
-          for (int q = 0; q < CPL; ++q)
-            row[b][q] = *reinterpret_cast<const uint4*>(rp + (((sub * CPL + q) ^ (imin(c, n_cols - 1) & (CHUNKS - 1))) * 16));
-        } else {
-          const unsigned char* rp = kunit + (size_t)imax(slot[b], 0) * ROWB + sub * CPL * 16;
-#pragma unroll
-          for (int q = 0; q < CPL; ++q) row[b][q] = *reinterpret_cast<const uint4*>(rp + q * 16);
-        }
+        slot[b] = (c < c_hi) ? keep[c] : -1;
       }
 #pragma unroll
       for (int b = 0; b < kExactBatch; ++b) {
-        double dot = 0.0, ss_c = 0.0;
+        const unsigned char* rp = kunit + (size_t)imax(slot[b], 0) * ROWB + sub * CPL * 16;
 #pragma unroll
-        for (int q = 0; q < CPL; ++q) {
-          const uint32_t wv[4] = {row[b][q].x, row[b][q].y, row[b][q].z, row[b][q].w};
+        for (int q = 0; q < CPL; ++q) row[b][q] = *reinterpret_cast<const uint4*>(rp + q * 16);
+      }
 #pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            const double lo = (double)bf16_lo(wv[i]), hi = (double)bf16_hi(wv[i]);
-            dot = fma(ed[q * 8 + 2 * i], lo, dot);
-            ss_c = fma(lo, lo, ss_c);
-            dot = fma(ed[q * 8 + 2 * i + 1], hi, dot);
-            ss_c = fma(hi, hi, ss_c);
-          }
-        }
-        dot += __shfl_xor(dot, 1);
-        ss_c += __shfl_xor(ss_c, 1);
-        dot += __shfl_xor(dot, 2);
-        ss_c += __shfl_xor(ss_c, 2);
-        const double rn_c = 1.0 / sqrt(ss_c);
-        double u = (dot * rn_e) * rn_c;
-        if (!(fabs(u) <= 1.79e308)) u = -INFINITY;   // zero-norm keys (nan / inf) match nothing
-        const int c = c0 + b * 64 + quad;
+      for (int b = 0; b < kExactBatch; ++b) {
+        const double u = row_e.cosine(row[b]);
         if (slot[b] >= 0 && u > best) {              // ascending c per lane and strict: the first maximiser stays
           best = u;
-          best_c = c;
+          best_c = c0 + b * 64 + quad;
         }
       }
     }
-#pragma unroll
-    for (int off = 4; off < 64; off <<= 1) {         // (the four lanes of a quad hold the same pair)
-      const double ob = __shfl_xor(best, off);
-      const int oc = __shfl_xor(best_c, off);
-      if (ob > best || (ob == best && oc < best_c)) {
-        best = ob;
-        best_c = oc;
-      }
-    }
+    best_of_quads(best, best_c);
     __syncthreads();                                 // the previous row's shared values are no longer read
     if (lane == 0) {
       s_best[wave] = best;
@@ -1288,7 +1391,7 @@ MatchPlan plan_match(const keepkv_layout* L, int capacity, int budget) {
   const size_t units = (size_t)L->batch * L->n_kv_heads;
   pl.rnorm_off = kWorkspaceHead;
   pl.flag_off = kWorkspaceHead + align_up(units * rn_pitch_of(budget) * sizeof(float), 256);
-  pl.panel_off = pl.flag_off + align_up((1 + units * (size_t)(capacity - budget)) * sizeof(int32_t) + 256, 256);
+  pl.panel_off = pl.flag_off + align_up(2 * units * (size_t)(capacity - budget) * sizeof(int32_t), 256);
   // the panel is used by bf16 caches with more evictable slots than the column-split kernel takes
   const bool panel = L->dtype == KEEPKV_BF16 && capacity - budget > kSmallMaxEvict;
   pl.partial_off = pl.panel_off + (panel ? align_up(units * rn_pitch_of(budget) * (size_t)L->head_dim * 2, 256) : 0);
@@ -1302,7 +1405,7 @@ PrefillMatchPlan plan_prefill_match(const keepkv_layout* L, int capacity) {
   const size_t units = (size_t)L->batch * L->n_kv_heads;
   pl.rnorm_off = kWorkspaceHead;
   pl.flag_off = pl.rnorm_off + align_up(units * capacity * sizeof(float), 256);
-  pl.partial_off = pl.flag_off + align_up((1 + units * (size_t)capacity) * sizeof(int32_t) + 256, 256);
+  pl.partial_off = pl.flag_off + align_up(2 * units * (size_t)capacity * sizeof(int32_t), 256);
   pl.bytes = pl.partial_off + (size_t)kExactResident * 16;
   return pl;
 }
@@ -1331,6 +1434,7 @@ extern "C" keepkv_status keepkv_prefill_match(const keepkv_layout* layout, const
   p.flag_count = reinterpret_cast<int32_t*>(reinterpret_cast<char*>(workspace) + kMatchCountersOff);
   p.exact_done = p.flag_count + 1;
   p.flag_rows = reinterpret_cast<int32_t*>(reinterpret_cast<char*>(workspace) + pl.flag_off);
+  p.flag_cols = reinterpret_cast<uint32_t*>(p.flag_rows + units * cap);
   p.exact_partial = reinterpret_cast<ExactPartial*>(reinterpret_cast<char*>(workspace) + pl.partial_off);
   p.exact_ticket = reinterpret_cast<int32_t*>(workspace);
   p.match = near; p.sim_out = sim_out;
@@ -1349,12 +1453,12 @@ extern "C" keepkv_status keepkv_prefill_match(const keepkv_layout* layout, const
       slot_rnorm_kernel<uint16_t, 128><<<ngrid, 256, 0, st>>>((const uint16_t*)cache->k, cache->len,
                                                             const_cast<float*>(p.rnorm), cap);
       prefill_near_kernel<128><<<pgrid, kPfWaves * kWave, 0, st>>>(p);
-      match_exact_bf16_kernel<128><<<exact_blocks, 256, 0, st>>>(p);
+      match_recheck_kernel<128><<<exact_blocks, 256, 0, st>>>(p);
     } else {
       slot_rnorm_kernel<uint16_t, 64><<<ngrid, 256, 0, st>>>((const uint16_t*)cache->k, cache->len,
                                                            const_cast<float*>(p.rnorm), cap);
       prefill_near_kernel<64><<<pgrid, kPfWaves * kWave, 0, st>>>(p);
-      match_exact_bf16_kernel<64><<<exact_blocks, 256, 0, st>>>(p);
+      match_recheck_kernel<64><<<exact_blocks, 256, 0, st>>>(p);
     }
   } else {
     int bx = (cap + 255) / 256;
@@ -1394,6 +1498,7 @@ extern "C" keepkv_status keepkv_match(const keepkv_layout* layout, const keepkv_
   p.flag_count = reinterpret_cast<int32_t*>(reinterpret_cast<char*>(workspace) + kMatchCountersOff);
   p.exact_done = p.flag_count + 1;
   p.flag_rows = reinterpret_cast<int32_t*>(reinterpret_cast<char*>(workspace) + pl.flag_off);
+  p.flag_cols = reinterpret_cast<uint32_t*>(p.flag_rows + units * max_evict);
   p.panel = reinterpret_cast<const unsigned char*>(workspace) + pl.panel_off;
   p.exact_partial = reinterpret_cast<ExactPartial*>(reinterpret_cast<char*>(workspace) + pl.partial_off);
   p.exact_ticket = reinterpret_cast<int32_t*>(workspace);
@@ -1418,11 +1523,13 @@ extern "C" keepkv_status keepkv_match(const keepkv_layout* layout, const keepkv_
     if (layout->head_dim == 128) {
       rc = launch_bf16<128>(p, cache->k, (unsigned)units, st);
       if (rc != KEEPKV_OK) return rc;
-      match_exact_bf16_kernel<128><<<exact_blocks, 256, 0, st>>>(p);
+      if (max_evict <= kSmallMaxEvict) match_exact_bf16_kernel<128><<<exact_blocks, 256, 0, st>>>(p);
+      else match_recheck_kernel<128><<<exact_blocks, 256, 0, st>>>(p);
     } else {
       rc = launch_bf16<64>(p, cache->k, (unsigned)units, st);
       if (rc != KEEPKV_OK) return rc;
-      match_exact_bf16_kernel<64><<<exact_blocks, 256, 0, st>>>(p);
+      if (max_evict <= kSmallMaxEvict) match_exact_bf16_kernel<64><<<exact_blocks, 256, 0, st>>>(p);
+      else match_recheck_kernel<64><<<exact_blocks, 256, 0, st>>>(p);
     }
   } else {
     int bx = (max_evict + 255) / 256;

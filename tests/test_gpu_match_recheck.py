@@ -1,0 +1,72 @@
+"""The f64 re-check of undecided rows looks only at the column classes that can hold the best value (columns of equal
+number modulo 32).  Rows whose two best columns are equal, or one bf16 step apart, and lie in the same class, in the
+same block, in the two halves of a lane pair, in the first and the last column; all-zero rows and keys; rows whose
+best value is negative: targets and similarities equal the oracle's."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import keepkv_oracle as O
+from paper_2504_09936_amd import workloads as W
+from tests import gpu_util as U
+
+pytestmark = pytest.mark.gpu
+
+
+def _nudge(row, g):
+    """`row` with one element moved by one bf16 step."""
+    out = row.copy()
+    i = int(g.integers(0, len(row)))
+    out[i] = W.from_bf16_bits((W.to_bf16_bits(row[i:i + 1]) + np.uint16(1)))[0]
+    return out
+
+
+@pytest.mark.parametrize("head_dim", [64, 128])
+@pytest.mark.parametrize("budget,n_ev", [(40, 300), (128, 513), (129, 1100), (820, 600)])
+@pytest.mark.parametrize("threshold", [-2.0, 0.8])
+def test_ties_and_near_ties(head_dim, budget, n_ev, threshold):
+    kk = U.kk()
+    g = np.random.default_rng(budget + n_ev + head_dim)
+    cap = budget + n_ev
+    w = W.CONFIGS["llama3_8b"].scaled(batch=1, n_q_heads=8, n_kv_heads=2, head_dim=head_dim, context=cap)
+    K = W.round_bf16(g.standard_normal((1, 2, cap, head_dim)))
+    gaps = [1, 3, 4, 8, 31, 32, 33, 36, 64, 96, 128, budget - 1]
+    for h in range(2):
+        at = budget
+        for gap in gaps:
+            for c in (0, 5, int(g.integers(0, budget))):
+                if c + gap >= budget or at + 4 > cap:
+                    continue
+                near = h == 1
+                K[0, h, c + gap] = _nudge(K[0, h, c], g) if near else K[0, h, c]
+                K[0, h, at] = K[0, h, c]                       # evicted rows: copies, scaled copies
+                K[0, h, at + 1] = K[0, h, c] * 2
+                K[0, h, at + 2] = _nudge(K[0, h, c], g)
+                K[0, h, at + 3] = -K[0, h, c]
+                at += 4
+    K[0, 0, budget // 2] = 0                                   # a zero retained key, a zero evicted row
+    K[0, 0, cap - 1] = 0
+    K[0, 1, cap - 3:] = -np.abs(K[0, 1, cap - 3:])             # rows against which everything scores low
+    lay, c = U.new_cache(w, capacity=cap, K=K, V=K)
+    ws = U.workspace(lay, cap, budget)
+    keep = torch.arange(budget, dtype=torch.int32, device="cuda").repeat(1, 2, 1).contiguous()
+    evict = torch.arange(budget, cap, dtype=torch.int32, device="cuda").repeat(1, 2, 1).contiguous()
+    n_evict = torch.full((1, 2), n_ev, dtype=torch.int32, device="cuda")
+    T = U.f32(threshold)
+    for want_sim in (True, False):
+        match = torch.full((1, 2, n_ev), -9, dtype=torch.int32, device="cuda")
+        sim = torch.zeros(1, 2, n_ev, device="cuda") if want_sim else None
+        kk.match(lay, c, budget, keep, evict, n_evict, T, match, sim, ws)
+        torch.cuda.synchronize()
+        for h in range(2):
+            tgt, s = O.match(K[0, h].astype(np.float64), np.arange(budget), np.arange(budget, cap), T, exact_any_order=True)
+            np.testing.assert_array_equal(match[0, h].cpu().numpy(), tgt)
+            if want_sim:                                       # f32 sums of at most 128 exact products, two f32 norms
+                np.testing.assert_allclose(sim[0, h].cpu().numpy(), s, rtol=0, atol=2e-5)
+    # the causal search of the prefill pass on the same keys
+    near = torch.full((1, 2, cap), -9, dtype=torch.int32, device="cuda")
+    kk.prefill_match(lay, c, T, near, None, ws)
+    torch.cuda.synchronize()
+    for h in range(2):
+        ref, _ = O.prefill_nearest_earlier(K[0, h].astype(np.float64), cap, T, exact_any_order=True)
+        np.testing.assert_array_equal(near[0, h].cpu().numpy(), ref)
