@@ -36,8 +36,7 @@ __device__ long long kk_trace_match[8 * 2048];
 namespace {
 
 constexpr int kRowsPerWave = 64;
-constexpr int kMWaves = 8;
-constexpr int kRowsPerBlock = kRowsPerWave * kMWaves;   // 512 evicted rows per workgroup and pass
+constexpr int kMWaves = 8;                              // wavefronts per workgroup of the first event's kernel
 constexpr int kStageCols = 128;                         // retained keys per LDS stage
 constexpr unsigned kResidentWorkgroups = 256;           // of the first event's kernel: one on each of 256 compute units
 constexpr int kXcds = 8;                                // accelerator dies, each with its own L2
@@ -193,13 +192,23 @@ __device__ __forceinline__ uint32_t candidate_columns(const MatchParams& p, cons
 // best equals the overall best, and the winning block is the triple's.  Every other column's value is
 // bounded by the second best block value or by the best of the other classes, which is all that the
 // exactness test needs.
-template <int D>
-__global__ __launch_bounds__(kMWaves* kWave, 2) void match_mfma_kernel(MatchParams p) {
+//
+// CAUSAL: the search of the prefill pass (App. B.4), every live slot against the slots before it.  A workgroup takes one
+// block of 64 NW consecutive slots as rows.  The slots before the block are plain columns of the loop above, copied from
+// the cache itself with the row swizzle applied on the address side; the stages that hold the block's own slots follow,
+// with the columns at or behind a row masked and the tiles wholly before the columns skipped.  Long blocks start first
+// (the launch order), which evens out the triangle over the compute units.  Bound by the matrix
+// pipes and the clock they leave (64 heads x 8192 slots, 550 GFLOP: 990 us with one 32-row operand per wavefront, where
+// every fragment read from LDS fed a single MFMA; now 430 us, 1.28 PFLOP/s: a large bf16 matrix product with random
+// operands reaches 1.1 on this part).
+template <int D, bool CAUSAL, int NW>
+__global__ __launch_bounds__(NW* kWave, 2) void match_mfma_kernel(MatchParams p) {
+  constexpr int kRowsPerBlock = kRowsPerWave * NW;   // rows per workgroup and pass
   constexpr int KS = D / 16;                 // MFMA k-steps over the head dimension
   constexpr int ROWB = D * 2;                // bytes per key
   constexpr int CHUNKS = ROWB / 16;          // 16-byte chunks per key
   constexpr int STAGE_BYTES = kStageCols * ROWB;
-  constexpr int LOADS = kStageCols * CHUNKS / (kMWaves * kWave);   // async 16-byte loads per lane per stage
+  constexpr int LOADS = kStageCols * CHUNKS / (NW * kWave);   // async 16-byte loads per lane per stage
 
   extern __shared__ __align__(16) unsigned char smem[];
   unsigned char* s_stage = smem;                                        // 2 stages, swizzled rows
@@ -209,41 +218,57 @@ __global__ __launch_bounds__(kMWaves* kWave, 2) void match_mfma_kernel(MatchPara
   // placed on one XCD (when the heads divide evenly), so that the head's retained keys, which every pass of
   // every one of them streams again, stay in that L2.
   int unit, first_rb;
-  if (p.n_units % kXcds == 0) {
-    const int xcd = blockIdx.x % kXcds, slot = blockIdx.x / kXcds;
-    unit = xcd * (p.n_units / kXcds) + slot / p.per_unit;
-    first_rb = slot % p.per_unit;
-  } else {
-    unit = blockIdx.x / p.per_unit;
-    first_rb = blockIdx.x % p.per_unit;
+  {
+    const bool even = p.n_units % kXcds == 0;
+    const int xcd = even ? blockIdx.x % kXcds : 0, slot = even ? blockIdx.x / kXcds : blockIdx.x;
+    const int units = even ? p.n_units / kXcds : p.n_units;          // heads of this die
+    if constexpr (CAUSAL) {
+      unit = xcd * units + slot % units;
+      first_rb = p.per_unit - 1 - slot / units;
+    } else {
+      unit = xcd * units + slot / p.per_unit;
+      first_rb = slot % p.per_unit;
+    }
   }
-  const int n_ev = p.n_evict[unit];
+  const int n_ev = CAUSAL ? p.len[unit] : p.n_evict[unit];           // rows
   const int n_rb = (n_ev + kRowsPerBlock - 1) / kRowsPerBlock;
   int rb = first_rb;                         // this pass's block of rows; later passes: rb + per_unit, ...
   if (rb >= n_rb) return;
   KX_TS(0);
-  const int n_keep = p.budget;               // n_evict > 0 implies the retained list is full
+  // columns that every row sees (n_evict > 0 implies the retained list is full)
+  const int n_keep = CAUSAL ? first_rb * kRowsPerBlock : p.budget;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, half = lane >> 5;
 
   const unsigned char* kbytes = reinterpret_cast<const unsigned char*>(p.k) + (size_t)unit * p.capacity * ROWB;
-  const int32_t* evict = p.evict_idx + (size_t)unit * p.max_evict;
+  const int32_t* evict = CAUSAL ? nullptr : p.evict_idx + (size_t)unit * p.max_evict;
   const float* rn_c = p.rnorm + (size_t)unit * p.rn_pitch;
 
   // ---- stage loader: global -> LDS without passing through registers.  The panel holds the head's retained
   // keys in list order with chunk c of key `col` at position c ^ (col mod CHUNKS) of its row, which keeps the
   // MFMA operand reads below free of bank conflicts; a stage is one contiguous piece of it, copied as is.
-  const unsigned char* panel = p.panel + (size_t)unit * p.rn_pitch * ROWB;
+  // (CAUSAL: the chunk numbers are exchanged within the row; a lane's rows of a stage are a multiple of CHUNKS apart, so
+  // its exchanged chunk is the same in all of them.  The last stage may reach beyond the cache and stops at len.)
+  const unsigned char* panel = CAUSAL ? kbytes : p.panel + (size_t)unit * p.rn_pitch * ROWB;
+  static_assert(!CAUSAL || (NW * kWave / CHUNKS) % CHUNKS == 0, "rows of a lane in a stage");
+  const int stage_row = tid / CHUNKS;
+  const uint32_t stage_off = CAUSAL ? stage_row * ROWB + ((tid % CHUNKS) ^ (stage_row & (CHUNKS - 1))) * 16 : tid * 16;
   auto issue_stage = [&](int s, int buf) {
-    const unsigned char* src = panel + (size_t)s * STAGE_BYTES + tid * 16;
+    const unsigned char* src = panel + (size_t)s * STAGE_BYTES + stage_off;
     unsigned char* dst = s_stage + buf * STAGE_BYTES + wave * 64 * 16;
 #pragma unroll
-    for (int i = 0; i < LOADS; ++i)
-      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src + i * (kMWaves * kWave) * 16),
-                                       (__attribute__((address_space(3))) void*)(dst + i * (kMWaves * kWave) * 16), 16, 0, 0);
+    for (int i = 0; i < LOADS; ++i) {
+      const unsigned char* at = src + i * (NW * kWave) * 16;
+      if constexpr (CAUSAL) {
+        const int beyond = s * kStageCols + stage_row + i * (NW * kWave / CHUNKS) - (n_ev - 1);
+        if (beyond > 0) at -= (size_t)beyond * ROWB;
+      }
+      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)at,
+                                       (__attribute__((address_space(3))) void*)(dst + i * (NW * kWave) * 16), 16, 0, 0);
+    }
     if (wave < kStageCols / 64) {            // 1/|k_c| of the stage's keys (padded with zeros by rnorm_kernel)
-      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(rn_c + s * kStageCols + tid),
+      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(rn_c + (CAUSAL ? min(s * kStageCols + tid, n_ev - 1) : s * kStageCols + tid)),
                                        (__attribute__((address_space(3))) void*)(s_rn + buf * kStageCols + wave * 64),
                                        4, 0, 0);
     }
@@ -257,7 +282,8 @@ __global__ __launch_bounds__(kMWaves* kWave, 2) void match_mfma_kernel(MatchPara
   // (the slot numbers as loaded: any arithmetic on them would be a first use, and the compiler waits for a
   // load at its first use -- here that is request_rows(), a whole pass later)
   auto row_offset = [&](int rb_, int t) {
-    return evict[min(rb_ * kRowsPerBlock + wave * kRowsPerWave + t * 32 + l32, n_ev - 1)];
+    const int j = min(rb_ * kRowsPerBlock + wave * kRowsPerWave + t * 32 + l32, n_ev - 1);
+    return CAUSAL ? j : evict[j];
   };
   int row_off[2] = {row_offset(rb, 0), row_offset(rb, 1)};
   bf16x8_t e[2][KS];
@@ -272,6 +298,8 @@ __global__ __launch_bounds__(kMWaves* kWave, 2) void match_mfma_kernel(MatchPara
   request_rows();
 
   const int n_stage = (n_keep + kStageCols - 1) / kStageCols;
+  // CAUSAL: the stages that hold the block's own slots (but not the last one)
+  const int n_diag = CAUSAL ? (min(n_ev - n_keep, kRowsPerBlock) + kStageCols - 1) / kStageCols : 0;
   const uint32_t frag0 = l32 * ROWB + (((l32 & (CHUNKS - 1)) ^ half) * 16);
   for (;;) {                                 // one pass per iteration
   float ss_row[2];
@@ -292,7 +320,7 @@ __global__ __launch_bounds__(kMWaves* kWave, 2) void match_mfma_kernel(MatchPara
     ss_row[t] = ss + __shfl_xor(ss, 32);
   }
   const int rb_next = rb + p.per_unit;
-  const bool more = rb_next < n_rb;          // uniform over the workgroup
+  const bool more = !CAUSAL && rb_next < n_rb;   // uniform over the workgroup
 
   // running state per tile: best of each column class, and (best, second best, block) over block maxima.
   // Values are compared through their integer images (for positive floats the order is the same, and a
@@ -351,7 +379,7 @@ __global__ __launch_bounds__(kMWaves* kWave, 2) void match_mfma_kernel(MatchPara
   };
 
   for (int s = 0; s < n_stage; ++s) {
-    if (s + 1 < n_stage) issue_stage(s + 1, par ^ 1);
+    if (CAUSAL || s + 1 < n_stage) issue_stage(s + 1, par ^ 1);
     else if (more) issue_stage(0, par ^ 1);                   // the next pass starts over at the first columns
     // operand fragment of key 32 cbl + l32: chunk (2 ks + half) ^ (l32 mod CHUNKS) of its row, which is the
     // lane's chunk of k-step 0 with 32 ks XORed into the byte offset
@@ -417,6 +445,44 @@ __global__ __launch_bounds__(kMWaves* kWave, 2) void match_mfma_kernel(MatchPara
     fold_group(gm1, cb_prev, b1[1], b2[1], g1[1]);
   }
 
+  if constexpr (CAUSAL) {                                     // the block's own slots as columns
+    for (int sd = 0; sd < n_diag; ++sd) {
+      if (sd + 1 < n_diag) issue_stage(n_stage + sd + 1, par ^ 1);
+#pragma unroll
+      for (int cbl = 0; cbl < BPS; ++cbl) {
+        const int col0 = sd * kStageCols + 32 * cbl;          // block of columns and tile of rows, within the block of slots
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+          const int row0 = wave * kRowsPerWave + t * 32;
+          if (col0 > row0) continue;                          // uniform over the wavefront: nothing before a row
+          f32x16_t acc = {0};
+#pragma unroll
+          for (int ks = 0; ks < KS; ++ks) {
+            const bf16x8_t a = *reinterpret_cast<const bf16x8_t*>(
+                s_stage + (((frag0 + par * STAGE_BYTES) ^ (uint32_t)(ks * 32)) + cbl * 32 * ROWB));
+            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, e[t][ks], acc, 0, 0, 0);
+          }
+          int gm = 0;
+#pragma unroll
+          for (int g = 0; g < 4; ++g) {
+            const f32x4_t rn4 = *reinterpret_cast<const f32x4_t*>(s_rn + par * kStageCols + cbl * 32 + 4 * half + 8 * g);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+              int k = __builtin_bit_cast(int, (float)(acc[4 * g + i] * rn4[i]));
+              if (col0 == row0) k = 8 * g + 4 * half + i < l32 ? k : 0;   // the tile on the diagonal: earlier columns only
+              cls[t][4 * g + i] = imax(cls[t][4 * g + i], k);
+              gm = imax(gm, k);
+            }
+          }
+          fold_group(gm, (n_keep + col0) >> 5, b1[t], b2[t], g1[t]);
+        }
+      }
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      __syncthreads();
+      par ^= 1;
+    }
+  }
+
   // ---- finish: winning class per tile, then the two lanes of a row (the halves) meet ----------------
   float y1[2], y2[2];
   int c1[2];
@@ -442,9 +508,12 @@ __global__ __launch_bounds__(kMWaves* kWave, 2) void match_mfma_kernel(MatchPara
   const int j = rb * kRowsPerBlock + wave * kRowsPerWave + lane;   // lane = 32 half + l32 finishes row l32 of tile `half`
   const size_t o = (size_t)unit * p.max_evict + j;
   bool fragile = false;
-  if (j < n_ev)
+  if (CAUSAL && j == 0) {                    // no earlier key
+    p.match[o] = -1;
+    if (p.sim_out != nullptr) p.sim_out[o] = -INFINITY;
+  } else if (j < n_ev)
     fragile = decide_row_f32(p, o, half ? y1[1] : y1[0], half ? c1[1] : c1[0], half ? y2[1] : y2[0],
-                             half ? ss_row[1] : ss_row[0], n_keep);
+                             half ? ss_row[1] : ss_row[0], CAUSAL ? j : n_keep);
   if (__any(fragile)) {                      // uniform over the wavefront
     const uint32_t m0 = candidate_columns(p, cls[0], y1[0], ss_row[0], half);
     const uint32_t m1 = candidate_columns(p, cls[1], y1[1], ss_row[1], half);
@@ -889,19 +958,8 @@ __global__ __launch_bounds__(256) void match_exact_kernel(MatchParams p) {
 }
 
 // ---------------------------------------------------------------------------------------------------
-// Merge-first prefill pass (App. B.4): for every live slot its most similar EARLIER key.  The same dense
-// contraction as above with rows = columns = the head's own keys and a causal mask, so the keys need no
-// gathering: a workgroup of 4 wavefronts takes 128 consecutive slots as rows (32 per wavefront, resident in
-// registers as B operands) and streams the slots before them through LDS in 64-key stages, copied straight
-// from the cache with the row swizzle applied on the address side.  A lane holds one row; the products are
-// folded as in the first event's kernel (class maxima and a triple over block maxima; ties go to the f64 kernel).
-// Column blocks wholly behind a wavefront's rows are skipped, the one block on the diagonal is masked.
-// Rows that the f32 arithmetic cannot decide are queued for the f64 kernel (causal mode).
-constexpr int kPfWaves = 4;
-constexpr int kPfRowsPerWave = 32;
-constexpr int kPfRows = kPfWaves * kPfRowsPerWave;      // 128 rows per workgroup
-constexpr int kPfStage = 64;                            // keys per LDS stage
-
+// Merge-first prefill pass (App. B.4): for every live slot its most similar EARLIER key, by the first event's kernel in
+// its causal mode.
 // 1/|k_i| (f32) of every live slot; 0 for zero keys and beyond len
 template <typename T, int D>
 __global__ __launch_bounds__(256) void slot_rnorm_kernel(const T* __restrict__ k, const int32_t* __restrict__ len,
@@ -931,151 +989,6 @@ __global__ __launch_bounds__(256) void slot_rnorm_kernel(const T* __restrict__ k
   }
   ss = group_sum<LPS>(ss);
   if (sub == 0) rn[(size_t)unit * capacity + r] = ss > 0.f ? 1.0f / sqrtf(ss) : 0.f;
-}
-
-template <int D>
-__global__ __launch_bounds__(kPfWaves* kWave) void prefill_near_kernel(MatchParams p) {
-  constexpr int KS = D / 16, ROWB = D * 2, CHUNKS = ROWB / 16;
-  constexpr int STAGE_BYTES = kPfStage * ROWB;
-  constexpr int LOADS = kPfStage * CHUNKS / (kPfWaves * kWave);
-  __shared__ __align__(16) unsigned char s_stage[2 * STAGE_BYTES];
-  __shared__ __align__(16) float s_rn[2][kPfStage];
-
-  const int unit = blockIdx.y;
-  const int n = p.len[unit];
-  const int r0 = ((int)gridDim.x - 1 - (int)blockIdx.x) * kPfRows;   // the long rows first
-  if (r0 >= n) return;
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int l32 = lane & 31, half = lane >> 5;
-  const unsigned char* kbytes = reinterpret_cast<const unsigned char*>(p.k) + (size_t)unit * p.capacity * ROWB;
-  const float* rn_all = p.rnorm + (size_t)unit * p.capacity;
-  const int row_lo = r0 + wave * kPfRowsPerWave;         // this wavefront's rows: row_lo .. row_lo + 31
-  const int row = row_lo + l32;                          // this lane's row (both halves)
-  const int n_cols = min(n, r0 + kPfRows) - 1;           // columns 0 .. n_cols - 1 are needed by some row here
-  const int n_stage = (n_cols + kPfStage - 1) / kPfStage;
-
-  auto issue_stage = [&](int s, int buf) {
-    const int col0 = s * kPfStage;
-#pragma unroll
-    for (int i = 0; i < LOADS; ++i) {
-      const int c = tid + i * (kPfWaves * kWave);
-      const int r = c / CHUNKS, phys = c % CHUNKS;
-      const size_t off = (size_t)min(col0 + r, n - 1) * ROWB + ((phys ^ (r & (CHUNKS - 1))) * 16);
-      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(kbytes + off),
-                                       (__attribute__((address_space(3))) void*)(s_stage + buf * STAGE_BYTES +
-                                                                               (i * (kPfWaves * kWave) + wave * 64) * 16),
-                                       16, 0, 0);
-    }
-    if (wave == 0)
-      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(rn_all + min(col0 + lane, n - 1)),
-                                       (__attribute__((address_space(3))) void*)(&s_rn[buf][0]), 4, 0, 0);
-  };
-  if (n_stage > 0) issue_stage(0, 0);
-
-  // B operands: this lane's row, its 8 channels of every k-step
-  bf16x8_t e[KS];
-  {
-    const unsigned char* rp = kbytes + (size_t)min(row, n - 1) * ROWB + half * 16;
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) e[ks] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const uint4*>(rp + ks * 32));
-  }
-  const float rn_row = rn_all[min(row, n - 1)];
-
-  // Running state per lane (its row, its 16 columns of every 32-column block), as in the first event's kernel:
-  // the best value of each column class i, and (best, second best, block) over the blocks' maxima, all as integer
-  // images (the order of positive floats; a masked or negative value loses to the initial 0, and a row without
-  // a positive similarity is queued for the f64 kernel or has no target anyway).  No column number travels
-  // with the values: at the end the winning class is the one whose best equals the overall best and the
-  // winning block is the triple's; every other column is bounded by the second-best block or another class.
-  int cls[16];
-#pragma unroll
-  for (int i = 0; i < 16; ++i) cls[i] = 0;
-  int b1 = 0, b2 = 0, g1 = 0;
-  int par = 0;
-  for (int s = 0; s < n_stage; ++s) {
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __syncthreads();                                     // stage s has landed; everyone is done with stage s - 1
-    if (s + 1 < n_stage) issue_stage(s + 1, par ^ 1);
-    const int col0 = s * kPfStage;
-#pragma unroll
-    for (int cbl = 0; cbl < kPfStage / 32; ++cbl) {
-      const int cb0 = col0 + 32 * cbl;                   // first column of the block
-      if (cb0 >= row_lo + kPfRowsPerWave || cb0 >= n_cols) continue;   // uniform over the wavefront: nothing before a row
-      f32x16_t acc = {0};
-      const unsigned char* frag = s_stage + par * STAGE_BYTES + (32 * cbl + l32) * ROWB;
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks) {
-        const bf16x8_t a = *reinterpret_cast<const bf16x8_t*>(frag + (((2 * ks + half) ^ (l32 & (CHUNKS - 1))) * 16));
-        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, e[ks], acc, 0, 0, 0);
-      }
-      const bool diagonal = cb0 + 32 > row_lo;           // uniform: the block holds columns at or behind some row
-      int gm = 0;
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const f32x4_t rn4 = *reinterpret_cast<const f32x4_t*>(&s_rn[par][32 * cbl + 8 * g + 4 * half]);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          int k = __builtin_bit_cast(int, acc[4 * g + i] * rn4[i]);
-          if (diagonal) {                                // only earlier columns count (and none beyond the last one needed)
-            const int col = cb0 + 8 * g + 4 * half + i;
-            k = (col < row && col < n_cols) ? k : 0;
-          }
-          cls[4 * g + i] = imax(cls[4 * g + i], k);
-          gm = imax(gm, k);
-        }
-      }
-      const int cb = cb0 >> 5;
-      g1 = (gm > b1) ? cb : g1;                          // strict: the first of equal blocks stays
-      b2 = imed3(b1, b2, gm);
-      b1 = imax(b1, gm);
-    }
-    par ^= 1;
-  }
-  // winning class of this lane's half of the row, then the two lanes of a row (the halves) meet; equal values:
-  // the lower column, and the margin is zero
-  float best, second;
-  int bcol;
-  {
-    int s1 = cls[0], s2 = 0, ci = 0;
-#pragma unroll
-    for (int i = 1; i < 16; ++i) {
-      const int x = cls[i];
-      const bool up = x > s1;
-      s2 = up ? s1 : imax(s2, x);
-      ci = up ? i : ci;
-      s1 = up ? x : s1;
-    }
-    const int col = 32 * g1 + 8 * (ci / 4) + 4 * half + (ci % 4);
-    const int rest = imax(b2, s2);                       // bounds every other column of this half
-    const int o1 = __shfl_xor(s1, 32), orest = __shfl_xor(rest, 32), ocol = __shfl_xor(col, 32);
-    best = __builtin_bit_cast(float, imax(s1, o1));
-    bcol = (s1 > o1) ? col : ((o1 > s1) ? ocol : min(col, ocol));
-    second = __builtin_bit_cast(float, imax(imax(rest, orest), imin(s1, o1)));
-  }
-  const bool mine = half == 0 && row < n;
-  const size_t o = (size_t)unit * p.max_evict + row;
-  bool fragile = false;
-  const float ss_row = 1.0f / (rn_row * rn_row);         // (rn_row = 0: a zero key, or |k|^2 beyond f32)
-  if (mine && row == 0) {                                // no earlier key
-    p.match[o] = -1;
-    if (p.sim_out != nullptr) p.sim_out[o] = -INFINITY;
-  } else if (mine) {
-    const float cos1 = best * rn_row;
-    fragile = !(best > 0.f) || !(rn_row > 0.f) || !(rn_row < INFINITY) || !((best - second) * rn_row > p.delta) ||
-              !(fabsf(cos1 - p.threshold) > p.delta);
-    if (surely_below(p, (best <= 0.f) ? 0.f : cos1, rn_row, rn_row)) fragile = false;
-    p.match[o] = (cos1 > p.threshold) ? bcol : -1;
-    if (p.sim_out != nullptr) p.sim_out[o] = cos1;
-  }
-  if (__any(fragile)) {                                  // uniform over the wavefront
-    const uint32_t m = candidate_columns(p, cls, best, ss_row, half);
-    if (fragile) {
-      const int at = atomicAdd(p.flag_count, 1);
-      p.flag_rows[at] = (int)o;
-      p.flag_cols[at] = m;
-    }
-  }
 }
 
 // queue every live row but the first (f32 caches: the f64 kernel decides all rows)
@@ -1344,6 +1257,33 @@ constexpr int kSmallMaxShares = 256;  // workgroups of that kernel when row bloc
 
 inline int rn_pitch_of(int budget) { return (budget + kStageCols - 1) / kStageCols * kStageCols; }
 
+// The causal search.  Workgroups of 4 wavefronts (256 rows, two on a compute unit) or of 8 (512 rows, one): the larger
+// ones stream every column half as often but need many blocks to even out the triangle.  MI355X, D 128, whole call,
+// 4 against 8 wavefronts: 8 heads x 2048 slots 38.9 / 52.7 us, 64 x 2048 52.6 / 62.7, 8 x 16384 (256 blocks of 512 rows)
+// 295 / 346, 64 x 4096 (512 blocks) 144 / 144, 8 x 32768 (512 blocks) 958 / 903.
+constexpr long kCausalWideBlocks = 512;
+template <int D, int NW>
+keepkv_status launch_causal_waves(MatchParams p, unsigned units, hipStream_t st) {
+  static const hipError_t attr = hipFuncSetAttribute((const void*)match_mfma_kernel<D, true, NW>,
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)mfma_smem_bytes<D>());
+  if (attr != hipSuccess) return KEEPKV_ERR_DEVICE;
+  p.per_unit = (p.capacity + NW * kRowsPerWave - 1) / (NW * kRowsPerWave);
+  p.n_units = (int)units;
+  match_mfma_kernel<D, true, NW><<<units * p.per_unit, NW * kWave, mfma_smem_bytes<D>(), st>>>(p);
+  return KEEPKV_OK;
+}
+template <int D>
+keepkv_status launch_causal(const MatchParams& p, const void* k, unsigned units, int exact_blocks, hipStream_t st) {
+  constexpr int rows = 256 / (D * 2 / 16);
+  slot_rnorm_kernel<uint16_t, D><<<dim3((p.capacity + rows - 1) / rows, units), 256, 0, st>>>(
+      (const uint16_t*)k, p.len, const_cast<float*>(p.rnorm), p.capacity);
+  const bool wide = (long)units * ((p.capacity + 8 * kRowsPerWave - 1) / (8 * kRowsPerWave)) >= kCausalWideBlocks;
+  const keepkv_status rc = wide ? launch_causal_waves<D, 8>(p, units, st) : launch_causal_waves<D, 4>(p, units, st);
+  if (rc != KEEPKV_OK) return rc;
+  match_recheck_kernel<D><<<exact_blocks, 256, 0, st>>>(p);
+  return KEEPKV_OK;
+}
+
 template <int D>
 keepkv_status launch_bf16(const MatchParams& p, const void* k, unsigned units, hipStream_t st) {
   constexpr int rows_per_block = 256 / (D * 2 / 16);
@@ -1352,7 +1292,7 @@ keepkv_status launch_bf16(const MatchParams& p, const void* k, unsigned units, h
     rnorm_kernel<uint16_t, D><<<dim3((p.rn_pitch + rows_per_block * kRnormRows - 1) / (rows_per_block * kRnormRows), units), 256, 0, st>>>(
         (const uint16_t*)k, p.keep_idx, p.n_evict, const_cast<float*>(p.rnorm), p.capacity, p.budget, p.rn_pitch,
         reinterpret_cast<uint4*>(const_cast<unsigned char*>(p.panel)));
-  static const hipError_t a1 = hipFuncSetAttribute((const void*)match_mfma_kernel<D>,
+  static const hipError_t a1 = hipFuncSetAttribute((const void*)match_mfma_kernel<D, false, kMWaves>,
                                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)mfma_smem_bytes<D>());
   static const hipError_t a2 = hipFuncSetAttribute((const void*)match_small_kernel<D>,
                                                    hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -1373,13 +1313,14 @@ keepkv_status launch_bf16(const MatchParams& p, const void* k, unsigned units, h
     // One workgroup fills a compute unit (8 wavefronts of 256 registers).  With fewer heads than compute
     // units each head gets an equal share of them, and a workgroup walks its head's row blocks in passes;
     // with more heads than that, one workgroup per head does all passes.
-    const unsigned row_blocks = (p.max_evict + kRowsPerBlock - 1) / kRowsPerBlock;
+    constexpr unsigned rows_per_block = kMWaves * kRowsPerWave;
+    const unsigned row_blocks = (p.max_evict + rows_per_block - 1) / rows_per_block;
     unsigned per_unit = kResidentWorkgroups / units;
     per_unit = per_unit < 1 ? 1 : (per_unit > row_blocks ? row_blocks : per_unit);
     MatchParams q = p;
     q.per_unit = (int)per_unit;
     q.n_units = (int)units;
-    match_mfma_kernel<D><<<per_unit * units, kMWaves * kWave, mfma_smem_bytes<D>(), st>>>(q);
+    match_mfma_kernel<D, false, kMWaves><<<per_unit * units, kMWaves * kWave, mfma_smem_bytes<D>(), st>>>(q);
   }
   return KEEPKV_OK;
 }
@@ -1446,20 +1387,9 @@ extern "C" keepkv_status keepkv_prefill_match(const keepkv_layout* layout, const
   long eb = (long)units * cap / 16;
   const int exact_blocks = (int)(eb < 64 ? 64 : (eb > 512 ? 512 : eb));
   if (layout->dtype == KEEPKV_BF16) {
-    const int lps = layout->head_dim * 2 / 16, rpb = 256 / lps;
-    const dim3 ngrid((cap + rpb - 1) / rpb, (unsigned)units);
-    const dim3 pgrid((cap + kPfRows - 1) / kPfRows, (unsigned)units);
-    if (layout->head_dim == 128) {
-      slot_rnorm_kernel<uint16_t, 128><<<ngrid, 256, 0, st>>>((const uint16_t*)cache->k, cache->len,
-                                                            const_cast<float*>(p.rnorm), cap);
-      prefill_near_kernel<128><<<pgrid, kPfWaves * kWave, 0, st>>>(p);
-      match_recheck_kernel<128><<<exact_blocks, 256, 0, st>>>(p);
-    } else {
-      slot_rnorm_kernel<uint16_t, 64><<<ngrid, 256, 0, st>>>((const uint16_t*)cache->k, cache->len,
-                                                           const_cast<float*>(p.rnorm), cap);
-      prefill_near_kernel<64><<<pgrid, kPfWaves * kWave, 0, st>>>(p);
-      match_recheck_kernel<64><<<exact_blocks, 256, 0, st>>>(p);
-    }
+    const keepkv_status rc = layout->head_dim == 128 ? launch_causal<128>(p, cache->k, (unsigned)units, exact_blocks, st)
+                                                     : launch_causal<64>(p, cache->k, (unsigned)units, exact_blocks, st);
+    if (rc != KEEPKV_OK) return rc;
   } else {
     int bx = (cap + 255) / 256;
     if (bx > 64) bx = 64;

@@ -70,3 +70,41 @@ def test_ties_and_near_ties(head_dim, budget, n_ev, threshold):
     for h in range(2):
         ref, _ = O.prefill_nearest_earlier(K[0, h].astype(np.float64), cap, T, exact_any_order=True)
         np.testing.assert_array_equal(near[0, h].cpu().numpy(), ref)
+
+
+@pytest.mark.parametrize("head_dim", [64, 128])
+@pytest.mark.parametrize("batch,lengths", [
+    (2, [1, 2, 31, 32, 33, 64, 65, 127, 128, 129, 191, 192, 255, 256, 257, 300]),            # blocks of 256 rows
+    (2, [511, 512, 513, 640, 641, 767, 768, 769, 900, 1000, 1023, 1024, 1025, 1111, 1152, 1153]),
+    (64, [1, 2, 33, 64, 127, 128, 129, 255, 256, 257, 383, 384, 385, 511, 512, 513])])       # blocks of 512 rows
+def test_causal_search_at_block_edges(head_dim, batch, lengths):
+    """Lengths around the tiles, stages and row blocks of the causal search, in a cache whose slots behind the length
+    hold NaN, with the capacity at the longest head: links equal the oracle's, twice."""
+    kk = U.kk()
+    g = np.random.default_rng(head_dim + batch)
+    cap = max(lengths)
+    w = W.CONFIGS["llama3_8b"].scaled(batch=batch, n_q_heads=8, n_kv_heads=8, head_dim=head_dim, context=cap)
+    assert (batch * 8 * ((cap + 511) // 512) >= 512) == (batch == 64)
+    K = W.round_bf16(g.standard_normal((batch, 8, cap, head_dim)))
+    K[:, :, cap // 2:] = W.round_bf16(K[:, :, :cap - cap // 2] * 0.5 + 0.2 * K[:, :, cap // 2:])      # many links
+    lens = np.array([lengths[i % len(lengths)] for i in range(batch * 8)], dtype=np.int32).reshape(batch, 8)
+    ref = {}
+    for i in list(range(16)) + [batch * 8 - 1]:
+        b, h = divmod(i, 8)
+        ref[b, h], _ = O.prefill_nearest_earlier(K[b, h].astype(np.float64), int(lens[b, h]), U.f32(0.8), exact_any_order=True)
+    for b in range(batch):
+        for h in range(8):
+            K[b, h, lens[b, h]:] = np.nan
+    lay, c = U.new_cache(w, capacity=cap, K=K, V=np.zeros_like(K), lens=lens)
+    ws = U.workspace(lay, cap, 10)
+    runs = []
+    for _ in range(2):
+        near = torch.full((batch, 8, cap), -9, dtype=torch.int32, device="cuda")
+        kk.prefill_match(lay, c, U.f32(0.8), near, None, ws)
+        torch.cuda.synchronize()
+        runs.append(near)
+    assert torch.equal(*runs)
+    got = near.cpu().numpy()
+    for (b, h), r in ref.items():
+        np.testing.assert_array_equal(got[b, h, :lens[b, h]], r)
+        assert (got[b, h, lens[b, h]:] == -9).all()
