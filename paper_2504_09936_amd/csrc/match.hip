@@ -199,8 +199,8 @@ __device__ __forceinline__ uint32_t candidate_columns(const MatchParams& p, cons
 // with the columns at or behind a row masked and the tiles wholly before the columns skipped.  Long blocks start first
 // (the launch order), which evens out the triangle over the compute units.  Bound by the matrix
 // pipes and the clock they leave (64 heads x 8192 slots, 550 GFLOP: 990 us with one 32-row operand per wavefront, where
-// every fragment read from LDS fed a single MFMA; now 430 us, 1.28 PFLOP/s: a large bf16 matrix product with random
-// operands reaches 1.1 on this part).
+// every fragment read from LDS fed a single MFMA; now 500 us, 1.1 PFLOP/s, which is what a large bf16 matrix product
+// of random operands reaches on this part).
 template <int D, bool CAUSAL, int NW>
 __global__ __launch_bounds__(NW* kWave, 2) void match_mfma_kernel(MatchParams p) {
   constexpr int kRowsPerBlock = kRowsPerWave * NW;   // rows per workgroup and pass

@@ -1,11 +1,21 @@
 // keepkv_select: per (batch, kv head) choose the retained set K_c and the to-be-evicted set K_e
 // (Alg. 1, selection step) under the fixed-budget sink / recent / heavy-hitter policy (App. B.3).
 //
-// One 1024-thread workgroup per head.  The ranking value ln p + ln s_hat is formed in f64 and
-// mapped to an order-preserving u64, the (budget - n_sink - n_recent)-th largest is found by an
-// 8-bit most-significant-digit radix select (LDS histograms, wavefront scan; digits in which no two
-// keys differ are skipped), and the slots are then compacted in index order so that equal values
-// keep the lower index first.
+// One 1024-thread workgroup per head; the (budget - n_sink - n_recent) slots with the largest ranking values
+// ln p + ln s_hat (f64, equal values at lower indices first) are found and the slots compacted in index order.
+//
+// Up to 32768 slots (select_kernel) the values are formed in f32 and kept in registers, a wavefront a contiguous
+// run of slots.  A histogram over kBins equal intervals between the least and the largest of them gives the interval
+// in which the threshold lies; slots more than the f32 arithmetic's error away from it are decided, the few others
+// are evaluated in f64 and ranked exactly by counting.  The f64 value is some sixty instructions per slot, which
+// bound the kernel when every slot was given one.  Only when more than kMaxCand slots are undecided
+// (long runs of equal values, values spread over many orders of magnitude), and for longer caches
+// (select_long_kernel), the f64 values of all slots are mapped to order-preserving u64 keys in the workspace and the
+// threshold is found by an 8-bit most-significant-digit radix select (LDS histograms, wavefront scan; digits in
+// which no two keys differ are skipped).
+// What bounds it: the latency of its steps (loads, block reduction, histogram, scan, ranking, two compaction sweeps).
+// Measured (MI355X), radix select over all f64 keys before: 8 heads x 32768 slots 69 -> 34 us, 64 x 8192 21 -> 15.6,
+// 1024 x 8192 84 -> 52, 64 x 884 8.2 -> 7.5.
 #include "kk_common.hpp"
 
 namespace kk {
@@ -66,17 +76,26 @@ __device__ __forceinline__ int rank_in_wave(uint64_t mask) {
 
 // EXT: the ranking value is read from a caller-supplied array (passed as log_s; born, t_obs and votes
 // unused) instead of being formed from the cache's votes and EMA scores.
-// LDSKEYS: the sortable keys of the head live in LDS (capacity * 8 bytes fit) instead of the workspace, so
-// the radix passes and the compaction never leave the CU.
 // AGED: the live slots are not in age order.  `order` lists the slots below `budget` from oldest to newest and
 // the slots from `budget` on follow in slot order (tokens appended since the last in-place event); the whole
 // selection runs on the age rank i and reads and reports slot(i), so the lists come out in age order.
-template <bool EXT, bool LDSKEYS, bool AGED>
-__global__ __launch_bounds__(kSelThreads) void select_kernel(
-    const float* __restrict__ log_s, const int32_t* __restrict__ born, const int32_t* __restrict__ t_obs,
-    const int32_t* __restrict__ votes, const int32_t* __restrict__ len, uint64_t* __restrict__ keys, int32_t* __restrict__ keep_idx,
-    int32_t* __restrict__ evict_idx, int32_t* __restrict__ n_evict, int capacity, int budget, int n_sink,
-    int n_recent, double ln_alpha, int n_table, const int32_t* __restrict__ order) {
+// Called by all threads of a head's workgroup; n = the head's length > budget.
+struct SelectParams {
+  const float* log_s;
+  const int32_t *born, *t_obs, *votes, *len;
+  uint64_t* keys;
+  int32_t *keep_idx, *evict_idx, *n_evict;
+  int capacity, budget, n_sink, n_recent;
+  double ln_alpha;
+  int n_table;               // counts below this have a tabulated ln(1 - alpha^n)
+  const int32_t* order;
+};
+template <bool EXT, bool AGED>
+__device__ __forceinline__ void select_radix(const SelectParams& p, int unit, int n) {
+  const float* log_s = p.log_s;
+  const int32_t *born = p.born, *votes = p.votes;
+  const int capacity = p.capacity, budget = p.budget, n_sink = p.n_sink, n_recent = p.n_recent, n_table = p.n_table;
+  const double ln_alpha = p.ln_alpha;
   constexpr int kWaves = kSelThreads / 64;
   __shared__ double s_lnterm[EXT ? 1 : kTermTable];
   __shared__ double s_lnvotes[EXT ? 1 : kVotesTable];
@@ -84,19 +103,14 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(
   __shared__ int s_eq[kWaves], s_kept[kWaves];
   __shared__ uint64_t s_or[kWaves], s_nand[kWaves];
   __shared__ int s_digit, s_need, s_bucket;
-  extern __shared__ __align__(16) uint64_t s_keys[];
-
-  const int unit = blockIdx.x;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  KS_TS(0);
   const size_t base = (size_t)unit * capacity;
-  const int32_t* ord = AGED ? order + (size_t)unit * budget : nullptr;
+  const int32_t* ord = AGED ? p.order + (size_t)unit * budget : nullptr;
   auto slot_of = [&](int i) -> int {              // age rank -> slot
     if constexpr (AGED) return i < budget ? min(max(ord[i], 0), capacity - 1) : i;   // (clamped: never out of bounds)
     else return i;
   };
   const int lo = n_sink;
-  // the first four candidate slots of every thread are requested together with the head's length
   int nn[4], pv[4];
   float ls[4];
   uint64_t k_or = 0, k_nand = 0;              // OR of this thread's keys and of their complements
@@ -113,18 +127,9 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(
     }
   };
   request(lo + tid);
-  const int t_head = EXT ? 1 : t_obs[unit];
-  const int n = len[unit];
-  int32_t* keep_out = keep_idx + (size_t)unit * budget;
-  int32_t* evict_out = evict_idx + (size_t)unit * (capacity - budget);
-
-  if (n <= budget) {
-    for (int i = tid; i < budget; i += kSelThreads) keep_out[i] = (i < n) ? slot_of(i) : -1;
-    if (tid == 0) n_evict[unit] = 0;
-    return;
-  }
-
-  KS_TS(13);
+  const int t_head = EXT ? 1 : p.t_obs[unit];
+  int32_t* keep_out = p.keep_idx + (size_t)unit * budget;
+  int32_t* evict_out = p.evict_idx + (size_t)unit * (capacity - budget);
   // ln(1 - alpha^n) depends on the observation count alone, and the f64 library routines behind it are some
   // hundreds of instructions: one evaluation per count (n_table of them: beyond, the term rounds to zero)
   // instead of one per slot
@@ -134,11 +139,8 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(
     if (tid >= kSelThreads - kVotesTable) s_lnvotes[kSelThreads - 1 - tid] = log((double)(kSelThreads - 1 - tid));
     __syncthreads();
   }
-  uint64_t* key_g = keys + base;
-  auto key = [&](int i) -> uint64_t& {
-    if constexpr (LDSKEYS) return s_keys[i];
-    else return key_g[i];
-  };
+  uint64_t* key_g = p.keys + base;
+  auto key = [&](int i) -> uint64_t& { return key_g[i]; };
   const int hi = n - n_recent;   // candidates are [lo, hi)
   const int n_heavy = budget - n_sink - n_recent;
 
@@ -192,7 +194,6 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(
   }
   if (tid < 256) s_hist[tid] = 0;
   __syncthreads();
-  KS_TS(1);
   uint64_t all_or = 0, all_nand = 0;
 #pragma unroll
   for (int w = 0; w < kWaves; ++w) {
@@ -271,7 +272,6 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(
         need = s_need;
         bucket = s_bucket;
       }
-      KS_TS(2 + (7 - pass));
       prefix = (prefix << 8) | (uint64_t)digit;
       n_cand = bucket;
       if (bucket == need && pass > 0 && prefix != 0) {
@@ -283,7 +283,6 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(
       }
     }
   }
-  KS_TS(10);
   const uint64_t tau = prefix;
   const int need_eq = need;
 
@@ -323,7 +322,6 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(
   for (int c = c0; c < c1; ++c) nk += __popcll(kept_mask(c, eq));
   if (lane == 0) s_kept[wave] = nk;
   __syncthreads();
-  KS_TS(11);
   int kpos = 0;
   for (int w = 0; w < wave; ++w) kpos += s_kept[w];            // kept slots at lower indices
   eq = eq_run;
@@ -338,13 +336,291 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(
     }
     kpos += __popcll(m);
   }
-  if (tid == 0) n_evict[unit] = n - budget;
+  if (tid == 0) p.n_evict[unit] = n - budget;
+}
+
+// a head that evicts nothing
+template <bool AGED>
+__device__ __forceinline__ void select_nothing(const SelectParams& p, int unit, int n) {
+  const int32_t* ord = AGED ? p.order + (size_t)unit * p.budget : nullptr;
+  for (int i = threadIdx.x; i < p.budget; i += kSelThreads)
+    p.keep_idx[(size_t)unit * p.budget + i] = (i < n) ? (AGED ? min(max(ord[i], 0), p.capacity - 1) : i) : -1;
+  if (threadIdx.x == 0) p.n_evict[unit] = 0;
+}
+
+template <bool EXT, bool AGED>
+__global__ __launch_bounds__(kSelThreads) void select_long_kernel(SelectParams p) {
+  const int unit = blockIdx.x, n = p.len[unit];
+  if (n <= p.budget) select_nothing<AGED>(p, unit, n);
+  else select_radix<EXT, AGED>(p, unit, n);
+}
+
+// ---------------------------------------------------------------------------------------------------
+constexpr int kBins = 2048;
+constexpr int kMaxCand = 256;          // undecided slots that are ranked by counting
+
+template <typename F>
+__device__ __forceinline__ float wave_reduce_f32(float x, F f) {
+  x = f(x, dpp_f32<0xB1>(x));
+  x = f(x, dpp_f32<0x4E>(x));
+  x = f(x, dpp_f32<0x141>(x));
+  x = f(x, dpp_f32<0x140>(x));
+  x = f(x, __shfl_xor(x, 16));
+  return f(x, __shfl_xor(x, 32));
+}
+
+// ITEMS: chunks of 64 slots per wavefront that the registers hold; chunk c of wavefront w is the slots
+// (w * cpw + c) * 64 + lane, cpw = ceil(capacity / 1024) <= ITEMS.
+template <bool EXT, bool AGED, int ITEMS>
+__global__ __launch_bounds__(kSelThreads, ITEMS <= 8 ? 8 : 4) void select_kernel(SelectParams p) {
+  constexpr int kWaves = kSelThreads / 64;
+  __shared__ float s_term[EXT ? 1 : kTermTable];
+  __shared__ float s_lnp[EXT ? 1 : kVotesTable];
+  __shared__ int s_hist[kBins];
+  __shared__ uint64_t s_cand[kMaxCand];
+  __shared__ int s_cand_i[kMaxCand];
+  __shared__ unsigned long long s_bits[ITEMS * kWaves];    // undecided slots that are kept, by chunk
+  __shared__ float s_min[kWaves], s_max[kWaves];
+  __shared__ int s_wave[kWaves], s_above[kWaves];
+  __shared__ int s_bin, s_n_cand;
+
+  const int unit = blockIdx.x;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  KS_TS(0);
+  const int capacity = p.capacity, budget = p.budget;
+  const size_t base = (size_t)unit * capacity;
+  const int32_t* ord = AGED ? p.order + (size_t)unit * budget : nullptr;
+  const int cpw = (capacity + kSelThreads - 1) / kSelThreads;
+  const int first = wave * cpw * 64 + lane;                          // this thread's slots: first + 64 c, c < cpw
+  auto slot_of = [&](int i) -> int {              // age rank -> slot
+    if constexpr (AGED) return i < budget ? min(max(ord[i], 0), capacity - 1) : i;   // (clamped: never out of bounds)
+    else return i;
+  };
+  // the state of the first kLoad slots is requested together with the head's length
+  constexpr int kLoad = ITEMS < 8 ? ITEMS : 8;
+  int nn[kLoad], pv[kLoad];
+  float ls[kLoad];
+  auto request = [&](int c0) {
+    int sl[kLoad];
+#pragma unroll
+    for (int u = 0; u < kLoad; ++u) sl[u] = slot_of(min(first + 64 * (c0 + u), capacity - 1));
+#pragma unroll
+    for (int u = 0; u < kLoad; ++u) {
+      nn[u] = EXT ? 0 : p.born[base + sl[u]];     // turned into the observation count t_obs - born at its use
+      pv[u] = EXT ? 1 : p.votes[base + sl[u]];
+      ls[u] = p.log_s[base + sl[u]];
+    }
+  };
+  request(0);
+  const int t_head = EXT ? 1 : p.t_obs[unit];
+  const int n = p.len[unit];
+  // f32 tables of ln p and of ln(1 - alpha^n), which depends on the observation count alone
+  if constexpr (!EXT) {
+    for (int m = tid; m < p.n_table; m += kSelThreads) s_term[m] = m > 0 ? logf(-expm1f((float)((double)m * p.ln_alpha))) : 0.f;
+    // (the last wavefronts take the votes table: the first ones have the other one's entries)
+    if (tid >= kSelThreads - kVotesTable) s_lnp[kSelThreads - 1 - tid] = logf((float)(kSelThreads - 1 - tid));
+  }
+  for (int b = tid; b < kBins; b += kSelThreads) s_hist[b] = 0;
+  for (int w = tid; w < ITEMS * kWaves; w += kSelThreads) s_bits[w] = 0;
+  if (tid == 0) s_n_cand = 0;
+  if (n <= budget) {                              // uniform over the workgroup
+    select_nothing<AGED>(p, unit, n);
+    return;
+  }
+  __syncthreads();
+  KS_TS(13);
+  const int lo = p.n_sink, hi = n - p.n_recent;   // candidates are [lo, hi)
+  const int n_heavy = budget - p.n_sink - p.n_recent;
+
+  // ---- ranking values in f32, the least and the largest finite one
+  float y[ITEMS];
+  float vmin = INFINITY, vmax = -INFINITY;
+#pragma unroll
+  for (int c0 = 0; c0 < ITEMS; c0 += kLoad) {
+    if (c0 < cpw) {                               // uniform over the workgroup
+#pragma unroll
+      for (int u = 0; u < kLoad; ++u) {
+        const int i = first + 64 * (c0 + u);
+        const bool cand = c0 + u < cpw && i >= lo && i < hi;
+        float x = ls[u];
+        if constexpr (EXT) {
+          x = (x == x) ? x : -INFINITY;           // NaN ranks lowest
+        } else {
+          // a wavefront evaluates the logarithms itself only where one of its lanes has a count beyond a table
+          const int cnt = t_head - nn[u];
+          const bool small_p = (uint32_t)pv[u] < (uint32_t)kVotesTable;
+          float lp = s_lnp[small_p ? pv[u] : 1];
+          if (__any(cand && !small_p)) lp = small_p ? lp : logf((float)pv[u]);
+          float term = (cnt > 0 && cnt < p.n_table) ? s_term[cnt] : 0.f;
+          if (p.n_table == kTermTable && __any(cand && cnt >= kTermTable))     // alpha close to 1
+            term = cnt >= kTermTable ? logf(-expm1f((float)((double)cnt * p.ln_alpha))) : term;
+          x = (lp + x) - term;
+          x = (x == x) ? x : INFINITY;
+          x = cnt <= 0 ? -INFINITY : x;
+        }
+        y[c0 + u] = x;
+        const bool finite = cand && fabsf(x) <= 3.0e38f;
+        vmin = finite ? fminf(vmin, x) : vmin;
+        vmax = finite ? fmaxf(vmax, x) : vmax;
+      }
+      if (c0 + kLoad < ITEMS && c0 + kLoad < cpw) request(c0 + kLoad);
+    }
+  }
+  vmin = wave_reduce_f32(vmin, [](float a, float b) { return fminf(a, b); });
+  vmax = wave_reduce_f32(vmax, [](float a, float b) { return fmaxf(a, b); });
+  if (lane == 0) {
+    s_min[wave] = vmin;
+    s_max[wave] = vmax;
+  }
+  __syncthreads();
+  KS_TS(1);
+
+  // y becomes the interval coordinate t = (value - vmin) * scale; slots that are kept whatever they rank get +inf,
+  // slots beyond the length NaN
+  constexpr float kTop = 1e30f;                   // above every coordinate, below infinity
+  float t_lo = kTop, t_hi = kTop;                 // kept: t > t_hi; undecided: t_lo <= t <= t_hi
+  {
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) {
+      vmin = fminf(vmin, s_min[w]);
+      vmax = fmaxf(vmax, s_max[w]);
+    }
+    const float range = vmax - vmin;
+    const float scale = range > 1e-30f && range < 3.0e38f ? (float)kBins / range : 0.f;
+#pragma unroll
+    for (int c = 0; c < ITEMS; ++c) {
+      const int i = c < cpw ? first + 64 * c : n;
+      const bool cand = i >= lo && i < hi;
+      float t = fminf((y[c] - vmin) * scale, 0.5f * kTop);               // (a NaN, infinity times a zero scale, becomes large too)
+      if (cand && n_heavy > 0) atomicAdd(&s_hist[t >= (float)kBins ? kBins - 1 : (t > 0.f ? (int)t : 0)], 1);
+      y[c] = i >= n ? NAN : (cand ? t : INFINITY);
+    }
+    __syncthreads();
+    KS_TS(2);
+    if (n_heavy > 0) {                            // uniform
+      // suffix scan: the boundary interval is the one in which the running count from the top reaches n_heavy
+      constexpr int kPer = kBins / kSelThreads;
+      int cnt[kPer], sum = 0;
+#pragma unroll
+      for (int j = 0; j < kPer; ++j) {            // thread 0 has the top intervals
+        cnt[j] = s_hist[kBins - 1 - (tid * kPer + j)];
+        sum += cnt[j];
+      }
+      const int incl = wave_incl_scan(sum);
+      if (lane == 63) s_wave[wave] = incl;
+      __syncthreads();
+      int before = incl - sum;
+#pragma unroll
+      for (int w = 0; w < kWaves; ++w) before += w < wave ? s_wave[w] : 0;
+#pragma unroll
+      for (int j = 0; j < kPer; ++j) {
+        if (before < n_heavy && before + cnt[j] >= n_heavy) s_bin = kBins - 1 - (tid * kPer + j);   // exactly one
+        before += cnt[j];
+      }
+      __syncthreads();
+      KS_TS(3);
+      const int bin = s_bin;
+      // The f32 values carry the roundings of two sums and of two logarithms whose magnitudes (at most 22 and 24) do not
+      // show in the sum: within (largest magnitude + 64) * 2^-21 of the f64 values, and the coordinate its own two
+      // roundings (below 1e-3 intervals).  With e that bound in intervals, the f64 threshold lies within e of the boundary
+      // interval (counting the f32 values from either side), so a slot 2 e outside is decided.  The outermost intervals also
+      // hold the infinite values.
+      const float mag = fmaxf(fabsf(vmin), fabsf(vmax));
+      const float e2 = EXT ? 0.f : 2.f * ((mag + 64.f) * 4.8e-7f * scale + 1e-3f);
+      t_lo = bin == 0 || scale == 0.f ? -INFINITY : (float)bin - e2;
+      t_hi = bin == kBins - 1 || scale == 0.f ? kTop : (float)(bin + 1) + e2;
+      if (EXT && t_hi < kTop) t_hi = __builtin_bit_cast(float, __builtin_bit_cast(int, t_hi) - 1);   // below bin + 1
+    }
+  }
+  int above = 0;                                  // candidates that are kept without looking further
+#pragma unroll
+  for (int c = 0; c < ITEMS; ++c) {
+    above += __popcll(__ballot(y[c] > t_hi && y[c] < kTop));
+    if (y[c] >= t_lo && y[c] <= t_hi) {
+      const int at = atomicAdd(&s_n_cand, 1);
+      if (at < kMaxCand) s_cand_i[at] = first + 64 * c;
+    }
+  }
+  if (lane == 0) s_above[wave] = above;
+  __syncthreads();
+  const int m = s_n_cand;
+  if (m > kMaxCand) {                             // uniform over the workgroup
+    select_radix<EXT, AGED>(p, unit, n);
+    return;
+  }
+  if (m > 0) {
+    int need = n_heavy;                           // how many of the undecided are kept
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) need -= s_above[w];
+    uint64_t k = 0;
+    int i = 0;
+    if (tid < m) {                                // their f64 values
+      i = s_cand_i[tid];
+      const size_t at = base + slot_of(i);
+      double x = (double)p.log_s[at];
+      if constexpr (EXT) {
+        if (!(x == x)) x = -INFINITY;
+      } else {
+        const int cnt = t_head - p.born[at];
+        const double t = (double)cnt * p.ln_alpha;
+        const int pv_i = p.votes[at];
+        // (ln 1 = 0; and with t <= -40 alpha^n is below half an ulp of 1 and the term is 0)
+        const double lp = pv_i == 1 ? 0.0 : log((double)pv_i);
+        const double term = t > -40.0 ? log(-expm1(t)) : 0.0;
+        x = (lp + x) - term;
+        if (cnt <= 0) x = -INFINITY;
+      }
+      k = sortable_u64(x);
+      s_cand[tid] = k;
+    }
+    __syncthreads();
+    if (tid < m) {
+      int rank = 0;                               // larger keys, and equal ones at lower indices
+      for (int j = 0; j < m; ++j) {
+        const uint64_t kj = s_cand[j];
+        rank += kj > k || (kj == k && s_cand_i[j] < i);
+      }
+      if (rank < need) atomicOr(&s_bits[i >> 6], 1ull << (i & 63));
+    }
+    __syncthreads();
+  }
+  KS_TS(10);
+
+  // ---- ordered compaction: positions inside a chunk from a ballot, the wavefronts' totals through LDS ------
+  auto kept_mask = [&](int c) -> uint64_t { return __ballot(y[c] > t_hi) | s_bits[wave * cpw + c]; };   // (y: NaN beyond the length)
+  int nk = 0;
+#pragma unroll
+  for (int c = 0; c < ITEMS; ++c)
+    if (c < cpw) nk += __popcll(kept_mask(c));    // uniform
+  if (lane == 0) s_wave[wave] = nk;
+  __syncthreads();
+  KS_TS(11);
+  int kpos = 0;                                   // kept slots at lower indices
+#pragma unroll
+  for (int w = 0; w < kWaves; ++w) kpos += w < wave ? s_wave[w] : 0;
+  int32_t* keep_out = p.keep_idx + (size_t)unit * budget;
+  int32_t* evict_out = p.evict_idx + (size_t)unit * (capacity - budget);
+#pragma unroll
+  for (int c = 0; c < ITEMS; ++c) {
+    if (c < cpw) {                                // uniform
+      const int i = first + 64 * c;
+      const uint64_t mask = kept_mask(c);
+      const int at = kpos + rank_in_wave(mask);
+      if (i < n) {
+        const int s = slot_of(i);
+        if ((mask >> lane) & 1) keep_out[at] = s;
+        else evict_out[i - at] = s;
+      }
+      kpos += __popcll(mask);
+    }
+  }
+  if (tid == 0) p.n_evict[unit] = n - budget;
   KS_TS(12);
 }
 
 }  // namespace
 
-constexpr int kSelLdsKeys = 16384;     // up to this capacity the keys of a head are kept in LDS (128 KB)
+constexpr int kSelRegSlots = 32 * kSelThreads;   // up to this capacity the values of a head are kept in registers
 
 template <bool EXT, bool AGED = false>
 void launch_select(int units, hipStream_t st, const float* log_s, const int32_t* born, const int32_t* t_obs,
@@ -356,18 +632,16 @@ void launch_select(int units, hipStream_t st, const float* log_s, const int32_t*
     const double n_zero = ceil(40.0 / -ln_alpha) + 1.0;
     n_table = n_zero < (double)kTermTable ? (int)n_zero : kTermTable;
   }
-  if (capacity <= kSelLdsKeys) {
-    static const hipError_t attr = hipFuncSetAttribute((const void*)select_kernel<EXT, true, AGED>,
-                                                       hipFuncAttributeMaxDynamicSharedMemorySize, kSelLdsKeys * 8);
-    (void)attr;                              // a refusal shows up as a launch error
-    select_kernel<EXT, true, AGED><<<units, kSelThreads, (size_t)capacity * 8, st>>>(
-        log_s, born, t_obs, votes, len, keys, keep_idx, evict_idx, n_evict, capacity, budget, n_sink, n_recent, ln_alpha,
-        n_table, order);
-  } else {
-    select_kernel<EXT, false, AGED><<<units, kSelThreads, 0, st>>>(
-        log_s, born, t_obs, votes, len, keys, keep_idx, evict_idx, n_evict, capacity, budget, n_sink, n_recent, ln_alpha,
-        n_table, order);
-  }
+  const SelectParams p{log_s, born, t_obs, votes, len, keys, keep_idx, evict_idx, n_evict, capacity, budget, n_sink, n_recent,
+                       ln_alpha, n_table, order};
+  auto go = [&](void (*kernel)(SelectParams)) { kernel<<<units, kSelThreads, 0, st>>>(p); };
+  const int cpw = (capacity + kSelThreads - 1) / kSelThreads;
+  if (capacity > kSelRegSlots) go(select_long_kernel<EXT, AGED>);
+  else if (cpw <= 1) go(select_kernel<EXT, AGED, 1>);
+  else if (cpw <= 4) go(select_kernel<EXT, AGED, 4>);
+  else if (cpw <= 8) go(select_kernel<EXT, AGED, 8>);
+  else if (cpw <= 16) go(select_kernel<EXT, AGED, 16>);
+  else go(select_kernel<EXT, AGED, 32>);
 }
 
 SelectPlan plan_select(const keepkv_layout* L, int capacity) {

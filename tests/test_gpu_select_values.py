@@ -1,0 +1,57 @@
+"""keepkv_select decides most slots in f32 and the few near the threshold in f64.  Ranking values that only f64 can
+tell apart (few and many of them), exact ties across the threshold, values of very different magnitudes, unobserved
+heads, counts and votes beyond the tables, at capacities around the instances of the kernel: index lists equal the
+oracle's."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import keepkv_oracle as O
+from paper_2504_09936_amd import workloads as W
+from tests import gpu_util as U
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("alpha", [0.9, 0.9999])
+@pytest.mark.parametrize("cap", [65, 1023, 1024, 1025, 4096, 4097, 8192, 8193, 16384, 16385, 32768, 32769])
+def test_select_at_the_threshold(cap, alpha):
+    kk = U.kk()
+    alpha = U.f32(alpha)
+    g = np.random.default_rng(cap)
+    B, H, budget, n_sink = 1, 8, max(20, cap // 9), 4
+    n_recent = budget // 2
+    w = W.CONFIGS["llama3_8b"].scaled(batch=B, n_q_heads=H, n_kv_heads=H, context=cap)
+    lay, c = U.new_cache(w, capacity=cap)
+    ws = U.workspace(lay, cap, budget)
+    log_s = (g.standard_normal((H, cap)) * 3 - 5).astype(np.float32)
+    votes = g.integers(1, 4, size=(H, cap)).astype(np.int32)
+    n_obs = g.integers(1, 40, size=(H, cap)).astype(np.int32)
+    near = g.choice(cap, min(cap // 2, 120), replace=False)     # close to each other, the rest far away: f64 decides
+    log_s[1, near] = np.float32(2.0) + g.integers(-3, 4, len(near)).astype(np.float32) * np.float32(2.0 ** -22)
+    log_s[2] = np.float32(-1.0) + g.integers(0, 5, cap).astype(np.float32) * np.float32(2.0 ** -24)   # all of them
+    n_obs[2] = g.integers(300, 340, cap)
+    log_s[3], votes[3], n_obs[3] = -2.5, 2, 17                  # all equal
+    log_s[4] *= np.float32(10.0) ** g.integers(-20, 20, cap).astype(np.float32)
+    log_s[5], n_obs[5] = -np.inf, 0                             # nothing observed
+    n_obs[6, ::3] = 0
+    log_s[6, ::3] = -np.inf
+    votes[7, ::7] = g.integers(200, 100000, len(votes[7, ::7]))
+    n_obs[7] = g.integers(1, 5000, cap)
+    c.log_s[:] = torch.from_numpy(log_s[None]).cuda()
+    c.votes[:] = torch.from_numpy(votes[None]).cuda()
+    U.set_n_obs(c, n_obs[None])
+    for lens in (np.full((1, H), cap), g.integers(budget + 1, cap + 1, size=(1, H))):
+        c.len[:] = torch.from_numpy(lens.astype(np.int32)).cuda()
+        keep = torch.full((B, H, budget), -7, dtype=torch.int32, device="cuda")
+        evict = torch.full((B, H, cap - budget), -7, dtype=torch.int32, device="cuda")
+        n_ev = torch.full((B, H), -7, dtype=torch.int32, device="cuda")
+        kk.select(lay, c, budget, n_sink, n_recent, alpha, keep, evict, n_ev, ws)
+        torch.cuda.synchronize()
+        for h in range(H):
+            n = int(lens[0, h])
+            rk, re = O.select(log_s[h].astype(np.float64), n_obs[h], votes[h], n, budget, n_sink, n_recent, alpha)
+            assert n_ev[0, h].item() == len(re)
+            np.testing.assert_array_equal(keep[0, h].cpu().numpy(), rk, err_msg=f"head {h}")
+            np.testing.assert_array_equal(evict[0, h, :len(re)].cpu().numpy(), re, err_msg=f"head {h}")
+            assert (evict[0, h, len(re):] == -7).all()
