@@ -12,6 +12,7 @@
 // shuffles and LDS; splits are combined by the last workgroup of each head to finish (a ticket
 // counter in the workspace head), so no second kernel is launched.
 #include <math.h>
+#include <string.h>
 
 #include <mutex>
 
@@ -1142,7 +1143,7 @@ keepkv_status static_scratch(void** out, hipStream_t st) {
 
 }  // namespace
 
-DecodePlan plan_decode(const keepkv_layout* L, int capacity, int force_per, int force_waves) {
+static DecodePlan make_plan(const keepkv_layout* L, int capacity, int force_per, int force_waves) {
   // Slots per split, and for the matrix-core kernel its workgroup size, from a small cost model fitted to
   // measurements on MI355X (batch 1..128, 850..32768 slots per head).  Workgroups of 4 wavefronts fit two to
   // a compute unit (512 resident), those of 8 wavefronts one (128 KB of tile buffers at D = 128: 256
@@ -1204,6 +1205,27 @@ DecodePlan plan_decode(const keepkv_layout* L, int capacity, int force_per, int 
   pl.partial_off = kWorkspaceHead;
   pl.bytes = kWorkspaceHead + align_up((size_t)L->batch * L->n_q_heads * ns * (L->head_dim + 2) * sizeof(float), 256);
   return pl;
+}
+
+
+// The cost model walks up to 2048 candidate plans (2 us for 884 slots, 27 us for 32768), and a program asks for the same
+// few plans again and again (one per layer shape and step): each thread keeps its last ones.  A plan is a pure function
+// of the fields compared here.
+DecodePlan plan_decode(const keepkv_layout* L, int capacity, int force_per, int force_waves) {
+  struct Entry {
+    int32_t key[8];
+    DecodePlan plan;
+  };
+  static thread_local Entry kept[8] = {};          // (a zero batch is no valid key)
+  const int32_t key[8] = {L->batch, L->n_q_heads, L->n_kv_heads, L->head_dim, L->dtype, capacity, force_per, force_waves};
+  uint32_t h = 0;
+  for (int32_t k : key) h = h * 31u + (uint32_t)k;
+  Entry& e = kept[(h ^ (h >> 15)) & 7u];
+  if (memcmp(e.key, key, sizeof key) != 0) {
+    e.plan = make_plan(L, capacity, force_per, force_waves);
+    memcpy(e.key, key, sizeof key);
+  }
+  return e.plan;
 }
 
 }  // namespace kk
