@@ -25,7 +25,8 @@ namespace kk {
 // Phase timestamps for kernel tuning; compiled in only with -DKEEPKV_TRACE (never in the product build).
 #ifdef KEEPKV_TRACE
 __device__ long long kk_trace[8 * 8192];
-#define KK_TS(i) do { if (threadIdx.x == 0 && blockIdx.x < 8192) kk_trace[blockIdx.x * 8 + (i)] = wall_clock64(); } while (0)
+#define KK_TS(i) do { const int b_ = blockIdx.y * gridDim.x + blockIdx.x; if (threadIdx.x == 0 && b_ < 8192) \
+  kk_trace[b_ * 8 + (i)] = wall_clock64(); } while (0)
 #else
 #define KK_TS(i) do { } while (0)
 #endif
@@ -64,6 +65,8 @@ constexpr int kWavesPerBlock = 4;   // the vector-ALU kernel
 // D = 128: two workgroups or one per compute unit); plan_decode picks.
 
 
+constexpr float kLowest = -3.402823466e38f;   // lower end of the running maxima: finite, so that maxima can be subtracted
+
 __device__ __forceinline__ void st_agent(float* p, float v) {
   __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
@@ -71,17 +74,37 @@ __device__ __forceinline__ float ld_agent(const float* p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// Two floats that live side by side, as one device-scope access.
+__device__ __forceinline__ void st_agent2(float* p, float a, float b) {
+  const uint64_t v = (uint64_t)__builtin_bit_cast(uint32_t, a) | (uint64_t)__builtin_bit_cast(uint32_t, b) << 32;
+  __hip_atomic_store(reinterpret_cast<uint64_t*>(p), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void ld_agent2(const float* p, float& a, float& b) {
+  const uint64_t v = __hip_atomic_load(reinterpret_cast<const uint64_t*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  a = __builtin_bit_cast(float, (uint32_t)v);
+  b = __builtin_bit_cast(float, (uint32_t)(v >> 32));
+}
+
 // Everything after the workgroup's kParts partial softmax states (m, l, acc[D] per head) have been
 // deposited in LDS and a barrier has passed: reduce them; a single split finishes the head, otherwise the
 // partial result goes to the workspace and the last workgroup of the head to arrive combines the splits,
 // resets the ticket and (step mode) publishes the new len.
-template <typename T, int D, int G, int kParts, bool STEP, int WAVES>
+// acc of a part: [D][G] (kInner) or [G][D]; parts are acc_stride / ml_stride floats apart.  A split's partial result in
+// the workspace: acc in the same order, then (m, l) per head.
+// An empty part or split has l = 0 and any m; maxima are held at or above the lowest finite value, so that they can be
+// subtracted without a test for -inf.
+template <typename T, int D, int G, int kParts, bool STEP, int WAVES, bool kInner>
 __device__ __forceinline__ void combine_and_finish(const DecodeParams& p, const float* s_m, const float* s_l,
-                                                   const float* s_acc, int* s_last_p, int unit, int split, bool grow,
-                                                   int len, int t_old) {
+                                                   const float* s_acc, int ml_stride, int acc_stride, int* s_last_p,
+                                                   int unit, int split, bool grow, int len, int t_old) {
   constexpr bool kBf16 = sizeof(T) == 2;
+  constexpr int kThreads = WAVES * kWave;
+  constexpr int kSplitFloats = G * (D + 2);
   int& s_last = *s_last_p;
-  auto finish = [&](size_t row, int d, float M, float L, float A) {
+  auto head_of = [](int idx) { return kInner ? idx % G : idx / D; };
+  auto finish = [&](int idx, float M, float L, float A) {
+    const int g = head_of(idx), d = kInner ? idx / G : idx % D;
+    const size_t row = (size_t)unit * G + g;   // == b * Hq + h * G + g
     const float o = (L > 0.f) ? A / L : 0.f;
     if constexpr (kBf16)
       reinterpret_cast<uint16_t*>(p.out)[row * D + d] = (uint16_t)f32_to_bf16_bits(o);
@@ -90,30 +113,26 @@ __device__ __forceinline__ void combine_and_finish(const DecodeParams& p, const 
     if (d == 0 && p.lse_out != nullptr) p.lse_out[row] = (L > 0.f) ? (M + fast_log2(L)) * kLn2 : -INFINITY;
   };
 
-  for (int idx = threadIdx.x; idx < G * D; idx += WAVES * kWave) {
-    const int g = idx / D, d = idx % D;
-    float M = s_m[g];
+  float* const partials = p.partial + (size_t)unit * p.nsplit * kSplitFloats;   // this head's splits
+  for (int idx = threadIdx.x; idx < G * D; idx += kThreads) {
+    const int g = head_of(idx);
+    float M = kLowest;
 #pragma unroll
-    for (int w = 1; w < kParts; ++w) M = fmaxf(M, s_m[w * G + g]);
+    for (int w = 0; w < kParts; ++w) M = fmaxf(M, s_m[w * ml_stride + g]);
     float L = 0.f, A = 0.f;
 #pragma unroll
     for (int w = 0; w < kParts; ++w) {
-      const float mw = s_m[w * G + g];
-      const float c = (mw == -INFINITY) ? 0.f : fast_exp2(mw - M);
-      L = fmaf(s_l[w * G + g], c, L);
-      A = fmaf(s_acc[(w * G + g) * D + d], c, A);
+      const float c = fast_exp2(s_m[w * ml_stride + g] - M);
+      L = fmaf(s_l[w * ml_stride + g], c, L);
+      A = fmaf(s_acc[w * acc_stride + idx], c, A);
     }
-    const size_t row = (size_t)unit * G + g;   // == b * Hq + h * G + g
     if (p.nsplit == 1) {
-      finish(row, d, M, L, A);
+      finish(idx, M, L, A);
     } else {
       // device-coherent (write-through) stores: the combining workgroup may run on another XCD
-      float* dst = p.partial + (row * p.nsplit + split) * (D + 2);
-      st_agent(dst + 2 + d, A);
-      if (d == 0) {
-        st_agent(dst, M);
-        st_agent(dst + 1, L);
-      }
+      float* dst = partials + (size_t)split * kSplitFloats;
+      st_agent(dst + idx, A);
+      if ((kInner ? idx / G : idx % D) == 0) st_agent2(dst + G * D + 2 * g, M, L);
     }
   }
 
@@ -139,46 +158,43 @@ __device__ __forceinline__ void combine_and_finish(const DecodeParams& p, const 
   __syncthreads();
   KK_TS(4);
   if (!s_last) return;
-  // CH splits of EB output elements are fetched per round trip of device-scope loads: 8 splits of two
+  // CH splits of EB output elements are fetched per round trip of device-scope loads: 4 or 8 splits of two
   // elements when that covers all splits (the common case; surplus loads would only cost), else 16 of one
-  constexpr int kThreads = WAVES * kWave;
   constexpr int kPerThread = (G * D + kThreads - 1) / kThreads;   // output elements per thread
   auto combine = [&](auto ch_tag, auto eb_tag) {
     constexpr int CH = decltype(ch_tag)::value, EB = decltype(eb_tag)::value;
     for (int e0 = 0; e0 < kPerThread; e0 += EB) {
       int idx[EB];
-      const float* src[EB];
       float M[EB], L[EB], A[EB];
 #pragma unroll
       for (int j = 0; j < EB; ++j) {
         idx[j] = min((int)threadIdx.x + (e0 + j) * kThreads, G * D - 1);   // surplus threads repeat the last element
-        src[j] = p.partial + ((size_t)unit * G + idx[j] / D) * p.nsplit * (D + 2);
-        M[j] = -INFINITY;
+        M[j] = kLowest;
         L[j] = 0.f;
         A[j] = 0.f;
       }
       for (int s0 = 0; s0 < p.nsplit; s0 += CH) {
         float ms[EB][CH], ls[EB][CH], as[EB][CH];
 #pragma unroll
-        for (int j = 0; j < EB; ++j)
+        for (int i = 0; i < CH; ++i) {
+          const float* src = partials + (size_t)min(s0 + i, p.nsplit - 1) * kSplitFloats;
 #pragma unroll
-          for (int i = 0; i < CH; ++i) {
-            const int s = min(s0 + i, p.nsplit - 1);
-            ms[j][i] = ld_agent(src[j] + s * (D + 2));
-            ls[j][i] = ld_agent(src[j] + s * (D + 2) + 1);
-            as[j][i] = ld_agent(src[j] + s * (D + 2) + 2 + idx[j] % D);
+          for (int j = 0; j < EB; ++j) {
+            ld_agent2(src + G * D + 2 * head_of(idx[j]), ms[j][i], ls[j][i]);
+            as[j][i] = ld_agent(src + idx[j]);
           }
+        }
 #pragma unroll
         for (int j = 0; j < EB; ++j) {
           float mc = M[j];
 #pragma unroll
           for (int i = 0; i < CH; ++i) mc = fmaxf(mc, ms[j][i]);
-          const float c0 = (M[j] == -INFINITY) ? 0.f : fast_exp2(M[j] - mc);
+          const float c0 = fast_exp2(M[j] - mc);
           L[j] *= c0;
           A[j] *= c0;
 #pragma unroll
           for (int i = 0; i < CH; ++i) {
-            const float c = (s0 + i < p.nsplit && ms[j][i] != -INFINITY) ? fast_exp2(ms[j][i] - mc) : 0.f;
+            const float c = s0 + i < p.nsplit ? fast_exp2(ms[j][i] - mc) : 0.f;
             L[j] = fmaf(ls[j][i], c, L[j]);
             A[j] = fmaf(as[j][i], c, A[j]);
           }
@@ -187,11 +203,12 @@ __device__ __forceinline__ void combine_and_finish(const DecodeParams& p, const 
       }
 #pragma unroll
       for (int j = 0; j < EB; ++j)
-        if ((int)threadIdx.x + (e0 + j) * kThreads < G * D)
-          finish((size_t)unit * G + idx[j] / D, idx[j] % D, M[j], L[j], A[j]);
+        if ((int)threadIdx.x + (e0 + j) * kThreads < G * D) finish(idx[j], M[j], L[j], A[j]);
     }
   };
-  if (p.nsplit <= 8) combine(std::integral_constant<int, 8>{}, std::integral_constant<int, (kPerThread >= 2 ? 2 : 1)>{});
+  constexpr int kTwo = kPerThread >= 2 ? 2 : 1;
+  if (p.nsplit <= 4) combine(std::integral_constant<int, 4>{}, std::integral_constant<int, kTwo>{});
+  else if (p.nsplit <= 8) combine(std::integral_constant<int, 8>{}, std::integral_constant<int, kTwo>{});
   else combine(std::integral_constant<int, 16>{}, std::integral_constant<int, 1>{});
   KK_TS(5);
   if (threadIdx.x == 0) {
@@ -202,6 +219,7 @@ __device__ __forceinline__ void combine_and_finish(const DecodeParams& p, const 
   }
 }
 
+// ---------------------------------------------------------------------------------------------------
 // LPS lanes share one slot's row, each holding VPL 16-byte vectors of it (vector v of lane `sub` is
 // row vector v * LPS + sub, so the LPS lanes of a group read LPS * 16 contiguous bytes per load).
 // kUnroll slots per lane group are in flight per iteration.
@@ -221,8 +239,7 @@ __global__ __launch_bounds__(kWavesPerBlock* kWave) void decode_attn_kernel(Deco
   __shared__ int s_last;
   __shared__ uint4 s_new[2 * RV];             // step mode: the appended token's K row, then its V row
 
-  const int unit = blockIdx.x / p.nsplit;    // b * Hkv + h
-  const int split = blockIdx.x % p.nsplit;
+  const int unit = blockIdx.y, split = blockIdx.x;   // unit = b * Hkv + h
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int grp = lane / LPS, sub = lane % LPS;
   KK_TS(0);
@@ -480,7 +497,8 @@ __global__ __launch_bounds__(kWavesPerBlock* kWave) void decode_attn_kernel(Deco
   __syncthreads();
   KK_TS(2);
 
-  combine_and_finish<T, D, G, kParts, STEP, kWavesPerBlock>(p, s_m, s_l, s_acc, &s_last, unit, split, grow, len, t_old);
+  combine_and_finish<T, D, G, kParts, STEP, kWavesPerBlock, false>(p, s_m, s_l, s_acc, G, G * D, &s_last, unit, split,
+                                                                  grow, len, t_old);
 }
 
 // ---------------------------------------------------------------------------------------------------
@@ -512,20 +530,6 @@ constexpr int mfma_stage_bytes(int D, int G) { return (G * D * 2 + 1023) / 1024 
 // already awaited, while later copies (to other addresses) are still under way.  The wait for the read itself
 // is part of the statement.
 typedef __attribute__((ext_vector_type(4))) int i32x4_t;
-__device__ __forceinline__ i32x4_t lds_read_b128_awaited(const void* lds_ptr) {
-  i32x4_t r;
-  const uint32_t a = (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void*)lds_ptr;
-  asm volatile("ds_read_b128 %0, %1\n\ts_waitcnt lgkmcnt(0)" : "=v"(r) : "v"(a) : "memory");
-  return r;
-}
-__device__ __forceinline__ int lds_read_b32_awaited(const void* lds_ptr) {
-  int r;
-  const uint32_t a = (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void*)lds_ptr;
-  asm volatile("ds_read_b32 %0, %1\n\ts_waitcnt lgkmcnt(0)" : "=v"(r) : "v"(a) : "memory");
-  return r;
-}
-
-typedef __attribute__((ext_vector_type(4))) short v4i16_t;
 
 template <int G>
 __device__ __forceinline__ float head_sum(float x) {   // sum over the G heads held by G consecutive lanes
@@ -539,6 +543,45 @@ __device__ __forceinline__ uint32_t pack_hi16(float lo_elem, float hi_elem) {   
   return (__builtin_bit_cast(uint32_t, lo_elem) >> 16) | (__builtin_bit_cast(uint32_t, hi_elem) & 0xFFFF0000u);
 }
 
+// a <- {a of the lower half, b of the lower half}, b <- {a of the upper half, b of the upper half} (lanes 0 .. 31 / 32 .. 63)
+__device__ __forceinline__ void swap_halves(float& a, float& b) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(uint32_t, a), __builtin_bit_cast(uint32_t, b), false, false);
+  const uint32_t ra = r[0], rb = r[1];           // (a bit cast of a vector element itself reads element 0)
+  a = __builtin_bit_cast(float, ra);
+  b = __builtin_bit_cast(float, rb);
+}
+// the same for the rows of 16 lanes of each half: a <- {a row 0, b row 0, a row 2, b row 2}, b <- {a row 1, b row 1, a 3, b 3}
+__device__ __forceinline__ void swap_rows(float& a, float& b) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(uint32_t, a), __builtin_bit_cast(uint32_t, b), false, false);
+  const uint32_t ra = r[0], rb = r[1];           // (a bit cast of a vector element itself reads element 0)
+  a = __builtin_bit_cast(float, ra);
+  b = __builtin_bit_cast(float, rb);
+}
+// maximum / sum over the lanes that hold the same head: equal l16 mod G in all four rows of 16 lanes
+template <int G, typename F>
+__device__ __forceinline__ float over_head_lanes(float x, F op) {
+  if constexpr (G <= 1) x = op(x, dpp_f32<0x121>(x));   // row_ror:1
+  if constexpr (G <= 2) x = op(x, dpp_f32<0x122>(x));   // row_ror:2
+  if constexpr (G <= 4) x = op(x, dpp_f32<0x124>(x));   // row_ror:4
+  x = op(x, dpp_f32<0x128>(x));                         // row_ror:8
+  float y = x;
+  swap_rows(x, y);
+  x = y = op(x, y);
+  swap_halves(x, y);
+  return op(x, y);
+}
+
+// The vector ALU's share.  A SIMD has two of these wavefronts and issues one 64-lane instruction in four cycles, so what a
+// tile costs beyond its loads is its instruction count: with every lane working out all 8 slots of its column (16 / G
+// lanes then do the same work) a tile took 430 instructions, 0.8 us alone and 1.6 us beside a second wavefront, most of
+// it after the last row had arrived.  The 16 / G lanes (c mod G equal) of a head therefore share the column's slots: lane
+// r = c / G takes NV of the 8 and leaves the others' places in its row of P empty, so that row r G + g of the second
+// product is head g's sum over lane r's slots and the rows of a head are added once at the end (permlane swaps).
+// Addresses: a tile's base is uniform (scalar registers), a lane adds a 32-bit offset that K and V share.
+// Measured before / after, graph replays, one step (D 128): 64 heads x 852 slots (G 4) 10.6 / 9.8 us, 8 heads 7.9 / 7.0,
+// 128 heads x 828 16.6 / 15.5, 1024 heads x 852 (G 8) 81.9 / 80.8.  Of the 9.8 us the rows need 5 (28.6 MB), the reduction
+// over the wavefronts 0.5, publishing a split's result and taking the ticket 0.9, the combination 1.1, launch and drain 2.
+//
 // ONE: a split is at most one tile per wavefront (128 or 256 slots), so there is no tile loop, no prefetch and no
 // rescaling of the accumulators (the common steady-state shape).
 template <int D, int G, bool STEP, bool ONE, int kMfmaWaves>
@@ -548,12 +591,13 @@ __global__ __launch_bounds__(kMfmaWaves* kWave, 2) void decode_mfma_kernel(Decod
   constexpr int TILE_BYTES = kMTile * ROWB;
   constexpr int LOADS = TILE_BYTES / (kWave * 16);
   constexpr int kParts = kMfmaWaves;
-  extern __shared__ __align__(16) unsigned char smem_raw[];     // [wave][K tile | V tile]; later the deposit
+  constexpr int NV = G >= 2 ? G / 2 : 1;         // slots of a tile whose weights one lane works out
+  extern __shared__ __align__(256) unsigned char smem_tiles[];   // [wave][two tile buffers]; later each wave's deposit
   __shared__ int s_last;
   __shared__ __align__(16) unsigned char s_new[2 * ROWB];       // step mode: the appended token's K row, V row
 
-  const int unit = blockIdx.x / p.nsplit, split = blockIdx.x % p.nsplit;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int unit = blockIdx.y, split = blockIdx.x;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int l16 = lane & 15, q = lane >> 4;
   KK_TS(0);
   const int len_old = p.len[unit];
@@ -573,35 +617,45 @@ __global__ __launch_bounds__(kMfmaWaves* kWave, 2) void decode_mfma_kernel(Decod
   const unsigned char* vbytes = reinterpret_cast<const unsigned char*>(p.v) + ubase * ROWB;
   // ONE: [K tile | V tile] of the wavefront's single tile.  Otherwise the K rows travel straight into registers
   // (below) and the two buffers hold the V rows of the current and of the next tile.
-  unsigned char* const Tb = smem_raw + wave * (2 * TILE_BYTES);
+  unsigned char* const Tb = smem_tiles + wave * (2 * TILE_BYTES);
   unsigned char* const Kb = Tb;
   unsigned char* Vb = ONE ? Tb + TILE_BYTES : Tb;
+  // This lane's head and its NV slots of every tile, rows row0 .. row0 + NV - 1: the places pos0 .. of the 8 slots
+  // 16 st + 4 q + i that its column of the score product holds.  row_mine: the slot whose votes and EMA state it loads
+  // (one of the NV; lanes 0 .. 3 of its quad hold all of them) and, if `writer`, updates.
+  const int g_l = l16 % G, r_l = l16 / G;
+  const int pos0 = (r_l * NV) & 7;
+  const int row0 = 16 * (pos0 >> 2) + 4 * q + (pos0 & 3);
+  const int row_mine = row0 + (g_l & (NV - 1));
+  const bool writer = G == 1 ? r_l < 8 : g_l < NV;
   // ONE: everything this wavefront waits for travels as asynchronous global -> LDS copies, requested in the
   // order query rows, K rows, votes and EMA state, V rows.  Such copies complete in the order of issue, so a
   // wait that leaves the V rows' LOADS copies outstanding guarantees all the others: the score product and
   // the softmax run while the V rows still travel.  (Loads into registers in the same queue would make the
   // compiler wait for everything at their first use.)
   constexpr int Q_PIECES = (G * ROWB + 1023) / 1024;
-  unsigned char* s_q = smem_raw + kMfmaWaves * 2 * TILE_BYTES + wave * mfma_stage_bytes(D, G);
+  unsigned char* s_q = smem_tiles + kMfmaWaves * 2 * TILE_BYTES + wave * mfma_stage_bytes(D, G);
   unsigned char* s_sc = s_q + Q_PIECES * 1024;                  // [votes | ln S][64] 4-byte words
-  if constexpr (ONE) {
+  if constexpr (ONE) {                           // chunk c of head g sits at position c ^ (4 g mod CHUNKS) of its row
     const unsigned char* qbase = reinterpret_cast<const unsigned char*>(p.q) + (size_t)unit * G * ROWB;
 #pragma unroll
     for (int j = 0; j < Q_PIECES; ++j) {
       const int c = min(j * kWave + lane, G * CHUNKS - 1);       // surplus lanes repeat the last chunk
-      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(qbase + c * 16),
+      const uint32_t off = (uint32_t)((c ^ ((4 * (c / CHUNKS)) & (CHUNKS - 1))) * 16);
+      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(qbase + off),
                                        (__attribute__((address_space(3))) void*)(s_q + j * 1024), 16, 0, 0);
     }
   }
 
   // chunk c of row r of a tile sits at position c ^ (r mod CHUNKS); rows at or beyond `bound` are never read
   auto issue_rows = [&](const unsigned char* rows, unsigned char* buf, int tbase) {
+    const unsigned char* tile_rows = rows + (size_t)tbase * ROWB;
+    const int rel = bound - 1 - tbase;
 #pragma unroll
     for (int i = 0; i < LOADS; ++i) {
-      const int c = lane + i * kWave;
-      const int row = c / CHUNKS, phys = c % CHUNKS;
-      const size_t off = (size_t)min(tbase + row, bound - 1) * ROWB + ((phys ^ (row & (CHUNKS - 1))) * 16);
-      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(rows + off),
+      const int row = lane / CHUNKS + i * (kWave / CHUNKS), phys = lane % CHUNKS;
+      const uint32_t off = (uint32_t)(min(row, rel) * ROWB + ((phys ^ (row & (CHUNKS - 1))) * 16));
+      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(tile_rows + off),
                                        (__attribute__((address_space(3))) void*)(buf + i * (kWave * 16)), 16, 0, kStreamOnce);
     }
   };
@@ -611,39 +665,44 @@ __global__ __launch_bounds__(kMfmaWaves* kWave, 2) void decode_mfma_kernel(Decod
   // buffer) in flight during all of the arithmetic on the current one.
   bf16x8_t kn[2][KS], kreg[2][KS];
   auto issue_k = [&](int tbase) {
+    const unsigned char* tile_rows = kbytes + (size_t)tbase * ROWB;
+    const int rel = bound - 1 - tbase;
 #pragma unroll
     for (int st = 0; st < 2; ++st) {
-      const unsigned char* row = kbytes + (size_t)min(tbase + 16 * st + l16, bound - 1) * ROWB + q * 16;
+      const uint32_t off = (uint32_t)(min(16 * st + l16, rel) * ROWB + q * 16);
 #pragma unroll
-      for (int ks = 0; ks < KS; ++ks) kn[st][ks] = __builtin_nontemporal_load(reinterpret_cast<const bf16x8_t*>(row + ks * 64));
+      for (int ks = 0; ks < KS; ++ks)
+        kn[st][ks] = __builtin_nontemporal_load(reinterpret_cast<const bf16x8_t*>(tile_rows + off + ks * 64));
     }
   };
   int base = start + wave * kMTile;
   const int wave_lim = lim;
   constexpr int kTileStep = kMfmaWaves * kMTile;
-  if (base < wave_lim) {
+  const bool has_tile = base < wave_lim;
+  if (has_tile) {
     if constexpr (ONE) issue_rows(kbytes, Kb, base);
     else issue_k(base);
     if constexpr (ONE) {                         // slot base + lane of the tile (lanes beyond the tile repeat a slot)
-      const size_t at = ubase + min(base + lane, bound - 1);
-      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(p.votes + at),
+      const uint32_t at = (uint32_t)min(min(lane, kMTile - 1), bound - 1 - base);
+      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(p.votes + ubase + base + at),
                                        (__attribute__((address_space(3))) void*)s_sc, 4, 0, 0);
       if constexpr (STEP)
-        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(p.log_s + at),
+        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(p.log_s + ubase + base + at),
                                          (__attribute__((address_space(3))) void*)(s_sc + 256), 4, 0, 0);
     }
     issue_rows(vbytes, Vb, base);
   }
   // !ONE: the votes and EMA state of a tile are requested one tile ahead, like its rows (into registers: they
   // are first used behind the loop's full wait)
-  int pv_next = 1;      // votes of slot tbase + lane mod 32; log2 is taken once per slot and handed round by lane shuffles
+  int pv_next = 1;
   float ls_next = -INFINITY;
   auto request_scalars = [&](int tbase) {
-    pv_next = p.votes[ubase + min(tbase + (lane & 31), bound - 1)];
-    if constexpr (STEP) ls_next = p.log_s[ubase + min(tbase + 16 * (l16 >> 2) + 4 * q + (l16 & 3), bound - 1)];
+    const uint32_t at = (uint32_t)min(row_mine, bound - 1 - tbase);
+    pv_next = (p.votes + ubase + tbase)[at];
+    if constexpr (STEP) ls_next = (p.log_s + ubase + tbase)[at];
   };
   if constexpr (!ONE) {
-    if (base < wave_lim) request_scalars(base);
+    if (has_tile) request_scalars(base);
   }
 
   // B operand of the score product: column l16 is head l16 mod G, this lane's 8 channels of every k-step
@@ -651,10 +710,10 @@ __global__ __launch_bounds__(kMfmaWaves* kWave, 2) void decode_mfma_kernel(Decod
   auto read_q = [&]() {                          // ONE: from this wavefront's LDS copy, once it has landed
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks)
-      qb[ks] = *reinterpret_cast<const bf16x8_t*>(s_q + (l16 % G) * ROWB + ks * 64 + q * 16);
+      qb[ks] = *reinterpret_cast<const bf16x8_t*>(s_q + g_l * ROWB + (((4 * ks + q) ^ ((4 * g_l) & (CHUNKS - 1))) * 16));
   };
   if constexpr (!ONE) {
-    const unsigned char* qrow = reinterpret_cast<const unsigned char*>(p.q) + ((size_t)unit * G + (l16 % G)) * ROWB;
+    const unsigned char* qrow = reinterpret_cast<const unsigned char*>(p.q) + ((size_t)unit * G + g_l) * ROWB;
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) qb[ks] = *reinterpret_cast<const bf16x8_t*>(qrow + ks * 64 + q * 16);
   }
@@ -663,10 +722,10 @@ __global__ __launch_bounds__(kMfmaWaves* kWave, 2) void decode_mfma_kernel(Decod
   // single-tile variant uses for queries and scalars) and written out by the whole workgroup once all tiles
   // are done, when it fits: many small stores spread over the streaming phase slow the row stream down more
   // than their bytes account for, one burst per workgroup less so.
-  unsigned char* const s_stage = smem_raw + kMfmaWaves * 2 * TILE_BYTES;
+  unsigned char* const s_stage = smem_tiles + kMfmaWaves * 2 * TILE_BYTES;
   const bool staged = !ONE && STEP && (size_t)p.per * 4 <= (size_t)kMfmaWaves * mfma_stage_bytes(D, G);
   const float sl2 = p.scale * kLog2e;
-  float m_run = -INFINITY, l_run = 0.f;
+  float m_run = kLowest, l_run = 0.f;
   f32x4_t O[NTILE];
 #pragma unroll
   for (int nt = 0; nt < NTILE; ++nt) O[nt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
@@ -677,8 +736,9 @@ __global__ __launch_bounds__(kMfmaWaves* kWave, 2) void decode_mfma_kernel(Decod
   // `next`: the wavefront's next tile (or -1); its K rows are requested as soon as the score product has
   // consumed the K buffer, its V rows after the second product, so both travel during the arithmetic.
   // `v_in_flight`: the V rows are still outstanding when the call starts (ONE, the wavefront's own tile).
-  auto compute = [&](int tbase, bool extra, int next, const float (&lp)[2][4], float ls_old,
-                     bool v_in_flight) {
+  // lp_lane: log2(votes) of slot row_mine.  x_out: the group-mean logit of slot row_mine (of a `writer` lane), and the
+  // return value whether this lane stores it.
+  auto compute = [&](int tbase, bool extra, int next, float lp_lane, bool v_in_flight, float& x_out) -> bool {
     const int n_live = extra ? 1 : max(0, min(kMTile, live_end - tbase));
     auto clear_masked_v = [&]() {
       if (n_live < kMTile) {                     // uniform: clear the V rows of masked slots (0 * garbage could be NaN)
@@ -704,14 +764,15 @@ __global__ __launch_bounds__(kMfmaWaves* kWave, 2) void decode_mfma_kernel(Decod
         s[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kreg[0][ks], qb[ks], s[0], 0, 0, 0);
         s[1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kreg[1][ks], qb[ks], s[1], 0, 0, 0);
       }
-    } else if (v_in_flight) {
-      // the K tile through reads that the compiler does not order behind the V rows' copies (see above)
+    } else {
+      // the K tile through reads that the compiler does not order behind the V rows' copies (see above).  The buffer is
+      // aligned to its rows, so chunk (4 ks + q) ^ (l16 mod CHUNKS) is that of k-step 0 with 64 ks XORed into the address.
       i32x4_t a0[KS], a1[KS];
       uint32_t ad[KS];
+      const uint32_t ad0 = (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void*)Kb +
+                           (uint32_t)(l16 * ROWB + ((q ^ (l16 & (CHUNKS - 1))) * 16));
 #pragma unroll
-      for (int ks = 0; ks < KS; ++ks)
-        ad[ks] = (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void*)(
-            Kb + l16 * ROWB + (((4 * ks + q) ^ (l16 & (CHUNKS - 1))) * 16));
+      for (int ks = 0; ks < KS; ++ks) ad[ks] = ad0 ^ (uint32_t)(ks * 64);
       if constexpr (KS == 4) {                   // D = 128: rows 16 .. 31 of the tile are 4096 bytes further
         static_assert(KS != 4 || 16 * ROWB == 4096, "offset in the statement below");
         asm volatile(
@@ -738,50 +799,64 @@ __global__ __launch_bounds__(kMfmaWaves* kWave, 2) void decode_mfma_kernel(Decod
         s[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a0[ks]), qb[ks], s[0], 0, 0, 0);
         s[1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a1[ks]), qb[ks], s[1], 0, 0, 0);
       }
-    } else {
+    }
+    // ---- this lane's NV values of the column
+    float sv[NV];
+    if constexpr (NV == 4) {
 #pragma unroll
-      for (int ks = 0; ks < KS; ++ks) {
-        const int off = l16 * ROWB + (((4 * ks + q) ^ (l16 & (CHUNKS - 1))) * 16);
-        const bf16x8_t a0 = *reinterpret_cast<const bf16x8_t*>(Kb + off);
-        const bf16x8_t a1 = *reinterpret_cast<const bf16x8_t*>(Kb + off + 16 * ROWB);
-        s[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a0, qb[ks], s[0], 0, 0, 0);
-        s[1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a1, qb[ks], s[1], 0, 0, 0);
+      for (int v = 0; v < 4; ++v) sv[v] = (r_l & 1) ? s[1][v] : s[0][v];
+    } else if constexpr (NV == 2) {
+#pragma unroll
+      for (int v = 0; v < 2; ++v) {
+        const float t0 = (r_l & 1) ? s[0][2 + v] : s[0][v], t1 = (r_l & 1) ? s[1][2 + v] : s[1][v];
+        sv[v] = (r_l & 2) ? t1 : t0;
       }
+    } else {
+      float t[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) t[j] = (pos0 & 1) ? s[j >> 1][2 * (j & 1) + 1] : s[j >> 1][2 * (j & 1)];
+      const float u0 = (pos0 & 2) ? t[1] : t[0], u1 = (pos0 & 2) ? t[3] : t[2];
+      sv[0] = (pos0 & 4) ? u1 : u0;
     }
     // ---- logits (log2 domain, log2(votes) folded in), group-mean logit for the EMA
-    float z[2][4], xm[2][4];
+    float z[NV], xm[NV], lp[NV];
+    if constexpr (NV == 1) lp[0] = lp_lane;
+    else {                                       // slot row0 + v is loaded by lane v of the quad
+      lp[0] = dpp_f32<0x00>(lp_lane);
+      lp[1] = dpp_f32<0x55>(lp_lane);
+      if constexpr (NV == 4) {
+        lp[2] = dpp_f32<0xAA>(lp_lane);
+        lp[3] = dpp_f32<0xFF>(lp_lane);
+      }
+    }
     float tm = -INFINITY;
 #pragma unroll
-    for (int st = 0; st < 2; ++st)
+    for (int v = 0; v < NV; ++v) {
+      const bool live = row0 + v < n_live && (G > 1 || r_l < 8);
+      z[v] = live ? fmaf(sv[v], sl2, lp[v]) : -INFINITY;
+      tm = fmaxf(tm, z[v]);
+      xm[v] = head_sum<G>(sv[v]);
+    }
+    const float mn = fmaxf(m_run, over_head_lanes<G>(tm, [](float a, float b) { return fmaxf(a, b); }));
+    const float c = fast_exp2(m_run - mn);       // (both finite or the tile holds an infinite logit)
+    float pr[NV], ps = 0.f;
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const bool live = (16 * st + 4 * q + i) < n_live;
-        z[st][i] = live ? fmaf(s[st][i], sl2, lp[st][i]) : -INFINITY;
-        tm = fmaxf(tm, z[st][i]);
-        xm[st][i] = head_sum<G>(s[st][i]) * (p.scale * (1.0f / G));
-      }
-    tm = fmaxf(tm, __shfl_xor(tm, 16));
-    tm = fmaxf(tm, __shfl_xor(tm, 32));
-    const float mn = fmaxf(m_run, tm);
-    const float c = (m_run == -INFINITY) ? 0.f : fast_exp2(m_run - mn);
-    float pr[2][4], ps = 0.f;
-#pragma unroll
-    for (int st = 0; st < 2; ++st)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        pr[st][i] = (mn == -INFINITY) ? 0.f : fast_exp2(z[st][i] - mn);
-        ps += pr[st][i];
-      }
+    for (int v = 0; v < NV; ++v) {
+      pr[v] = fast_exp2(z[v] - mn);
+      ps += pr[v];
+    }
     l_run = fmaf(l_run, c, ps);
     m_run = mn;
-    if (!first) {                                // uniform: rescale the accumulators, row r = head r mod G
+    if (!first && __any(c != 1.f)) {             // uniform: rescale the accumulators, row r = head r mod G
                                                  // (with ONE only the extra tile of the appended token gets here)
+      const float c_other = dpp_f32<0x124>(c);   // G = 8: of the head four further (every lane reads: not inside the choice)
+      const float cq = G < 8 || ((l16 >> 2) & 1) == (q & 1) ? c : c_other;
+      const float ci[4] = {dpp_f32<0x00>(cq), dpp_f32<G == 1 ? 0x00 : 0x55>(cq), dpp_f32<G <= 2 ? 0x00 : 0xAA>(cq),
+                           dpp_f32<G == 1 ? 0x00 : G == 2 ? 0x55 : 0xFF>(cq)};
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const float ci = __shfl(c, (lane & 48) | ((4 * q + i) % G));
+      for (int i = 0; i < 4; ++i)
 #pragma unroll
-        for (int nt = 0; nt < NTILE; ++nt) O[nt][i] *= ci;
-      }
+        for (int nt = 0; nt < NTILE; ++nt) O[nt][i] *= ci[i];
     }
     first = false;
     if (v_in_flight) {                           // before any store is issued: only the V rows are outstanding
@@ -789,35 +864,50 @@ __global__ __launch_bounds__(kMfmaWaves* kWave, 2) void decode_mfma_kernel(Decod
       asm volatile("s_waitcnt vmcnt(0)" : "+v"(l_run) : : "memory");
       clear_masked_v();
     }
-    // ---- O += P V with P = hi + lo in bf16
-    uint4 ah, al;
-    {
-      float lo_[2][4];
+    // ---- O += P V with P = hi + lo in bf16.  The places of the slots that other lanes took hold the smallest normal
+    // number and not zero: against any finite V it vanishes beside the head's largest weight (1), and an infinity in V
+    // stays one, where zero would make it a NaN.
+    constexpr uint32_t kNone = 0x00800080u;
+    uint32_t ah[4], al[4];
+    if constexpr (NV == 1) {
+      const uint32_t hb = __builtin_bit_cast(uint32_t, pr[0]) & 0xFFFF0000u;
+      const uint32_t lb = __builtin_bit_cast(uint32_t, pr[0] - __builtin_bit_cast(float, hb)) & 0xFFFF0000u;
+      const uint32_t wh = (pos0 & 1) ? hb | (kNone & 0xFFFFu) : hb >> 16 | (kNone & 0xFFFF0000u);
+      const uint32_t wl = (pos0 & 1) ? lb | (kNone & 0xFFFFu) : lb >> 16 | (kNone & 0xFFFF0000u);
 #pragma unroll
-      for (int st = 0; st < 2; ++st)
+      for (int d = 0; d < 4; ++d) {
+        ah[d] = (pos0 >> 1) == d && (G > 1 || r_l < 8) ? wh : kNone;
+        al[d] = (pos0 >> 1) == d && (G > 1 || r_l < 8) ? wl : kNone;
+      }
+    } else {
+      constexpr int NW = NV / 2;
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
-          lo_[st][i] = pr[st][i] - __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, pr[st][i]) & 0xFFFF0000u);
-      ah = make_uint4(pack_hi16(pr[0][0], pr[0][1]), pack_hi16(pr[0][2], pr[0][3]), pack_hi16(pr[1][0], pr[1][1]),
-                      pack_hi16(pr[1][2], pr[1][3]));
-      al = make_uint4(pack_hi16(lo_[0][0], lo_[0][1]), pack_hi16(lo_[0][2], lo_[0][3]), pack_hi16(lo_[1][0], lo_[1][1]),
-                      pack_hi16(lo_[1][2], lo_[1][3]));
+      for (int j = 0; j < NW; ++j) {
+        const float p0 = pr[2 * j], p1 = pr[2 * j + 1];
+        const float l0 = p0 - __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, p0) & 0xFFFF0000u);
+        const float l1 = p1 - __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, p1) & 0xFFFF0000u);
+        const uint32_t wh = pack_hi16(p0, p1), wl = pack_hi16(l0, l1);
+#pragma unroll
+        for (int d = j; d < 4; d += NW) {        // dword d holds the places 2 d, 2 d + 1
+          ah[d] = r_l == d / NW ? wh : kNone;
+          al[d] = r_l == d / NW ? wl : kNone;
+        }
+      }
     }
-    const bf16x8_t a_hi = __builtin_bit_cast(bf16x8_t, ah), a_lo = __builtin_bit_cast(bf16x8_t, al);
+    const bf16x8_t a_hi = __builtin_bit_cast(bf16x8_t, make_uint4(ah[0], ah[1], ah[2], ah[3]));
+    const bf16x8_t a_lo = __builtin_bit_cast(bf16x8_t, make_uint4(al[0], al[1], al[2], al[3]));
     // transpose read: lane s of a 16-lane block supplies the address of row s / 4, columns 4 (s mod 4) .. + 3, and
-    // receives column s of the block's four rows
+    // receives column s of the block's four rows (channel tile nt: chunk 2 nt + c, so 32 nt XORed into the address)
     // The V tile has landed (awaited above or at the top of the loop) while the next tile's K rows may be on
     // their way: the reads go through a statement the compiler does not order behind those copies.
     const int vrow = 4 * q + (l16 >> 2);
     typedef __attribute__((ext_vector_type(2))) uint32_t u32x2_t;
     u32x2_t b0[NTILE], b1[NTILE];
     uint32_t va[NTILE];
+    const uint32_t va0 = (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void*)Vb +
+                         (uint32_t)(vrow * ROWB + ((((l16 & 3) >> 1) ^ (vrow & (CHUNKS - 1))) * 16) + (l16 & 1) * 8);
 #pragma unroll
-    for (int nt = 0; nt < NTILE; ++nt) {
-      const int chunk = 2 * nt + ((l16 & 3) >> 1);
-      va[nt] = (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void*)(
-          Vb + vrow * ROWB + ((chunk ^ (vrow & (CHUNKS - 1))) * 16) + (l16 & 1) * 8);
-    }
+    for (int nt = 0; nt < NTILE; ++nt) va[nt] = va0 ^ (uint32_t)(nt * 32);
     if constexpr (NTILE == 8) {                  // D = 128: rows 16 .. 31 of the tile are 4096 bytes further
       static_assert(NTILE != 8 || 16 * ROWB == 4096, "offset in the statement below");
       asm volatile(
@@ -847,63 +937,42 @@ __global__ __launch_bounds__(kMfmaWaves* kWave, 2) void decode_mfma_kernel(Decod
           : "memory");
     }
 #pragma unroll
-    for (int nt = 0; nt < NTILE; ++nt) {
-      const uint4 bw = make_uint4(b0[nt][0], b0[nt][1], b1[nt][0], b1[nt][1]);
-      const bf16x8_t b = __builtin_bit_cast(bf16x8_t, bw);
-      O[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a_hi, b, O[nt], 0, 0, 0);
-      O[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a_lo, b, O[nt], 0, 0, 0);
-    }
-    // ---- EMA update (Eq. 8) and optional logit output: lane (l16 < 8, q) owns slot 16 (l16 / 4) + 4 q + l16 % 4.
-    // After the second product: the compiler orders the V reads behind every outstanding memory operation,
-    // and stores issued before them would be waited for.
-    {
-      float x = xm[0][0];
+    for (int part = 0; part < 2; ++part)         // (all of one part, then all of the other: no two in a row depend on each other)
 #pragma unroll
-      for (int st = 0; st < 2; ++st)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) x = (l16 == 4 * st + i) ? xm[st][i] : x;
-      const int row_mine = 16 * (l16 >> 2) + 4 * q + (l16 & 3);
-      const bool mine = l16 < 8 && row_mine < n_live;
-      const size_t at = ubase + (extra ? len_old : tbase + row_mine);
-      if (p.logits_out != nullptr && mine) p.logits_out[at] = x;
-      if constexpr (STEP) {
-        const float a = p.ln_alpha + ls_old, b = p.ln_1m_alpha + x;
-        const float hi = fmaxf(a, b), lo = fminf(a, b);
-        // ln(e^hi + e^lo) = hi + ln(1 + e^(lo - hi)) with the hardware exp2 / log2 (absolute error ~1e-7)
-        const float r = (lo == -INFINITY) ? hi : hi + kLn2 * fast_log2(1.f + fast_exp2((lo - hi) * kLog2e));
-        if (mine) {
-          if (staged && !extra) {
-            // (a statement the compiler does not see as an LDS store: it would order one behind the next
-            // tile's outstanding copies into LDS)
-            const uint32_t sa = (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void*)(
-                s_stage + (size_t)(tbase - start + row_mine) * 4);
-            asm volatile("ds_write_b32 %0, %1" : : "v"(sa), "v"(r) : "memory");
-          } else {
-            p.log_s[at] = r;
-          }
-        }
+      for (int nt = 0; nt < NTILE; ++nt) {
+        const uint4 bw = make_uint4(b0[nt][0], b0[nt][1], b1[nt][0], b1[nt][1]);
+        O[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(part ? a_lo : a_hi, __builtin_bit_cast(bf16x8_t, bw), O[nt], 0, 0, 0);
       }
-    }
+    // ---- group-mean logit of the slot that this lane updates
+    float x = xm[0];
+#pragma unroll
+    for (int v = 1; v < NV; ++v) x = (g_l & (NV - 1)) == v ? xm[v] : x;
+    x_out = x * (p.scale * (1.0f / G));
+    return writer && row_mine < n_live;
+  };
+  // ln(alpha S + (1 - alpha) e^x)  (Eq. 8):  ln(e^hi + e^lo) = hi + ln(1 + e^(lo - hi)) with the hardware exp2 / log2
+  // (absolute error ~1e-7)
+  auto ema = [&](float ls_old, float x) {
+    const float a = p.ln_alpha + ls_old, b = p.ln_1m_alpha + x;
+    const float hi = fmaxf(a, b), lo = fminf(a, b);
+    return (lo == -INFINITY) ? hi : hi + kLn2 * fast_log2(1.f + fast_exp2((lo - hi) * kLog2e));
   };
 
+  // ONE: results per slot that are stored at the very end (a store here would be waited for, with its whole round trip
+  // to memory, before this wavefront may deposit its sums)
+  bool own_store = false;
+  float own_x = 0.f, own_ema = 0.f;
   while (base < wave_lim) {                      // a single pass with ONE
-    float lp[2][4];                                // log2(votes) of the slots whose logits this lane holds
-    float ls_old = -INFINITY;
     if constexpr (ONE) {
       // all copies but the youngest LOADS (the V rows) have landed: query rows, K rows, votes and EMA state
       asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LOADS) : "memory");
       read_q();
-#pragma unroll
-      for (int st = 0; st < 2; ++st) {
-        const i32x4_t x = lds_read_b128_awaited(s_sc + (16 * st + 4 * q) * 4);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) lp[st][i] = fast_log2((float)x[i]);
-      }
-      if constexpr (STEP) {
-        const int mine = 16 * (l16 >> 2) + 4 * q + (l16 & 3);
-        ls_old = __builtin_bit_cast(float, lds_read_b32_awaited(s_sc + 256 + mine * 4));
-      }
-      compute(base, false, -1, lp, ls_old, true);
+      uint64_t sc;                               // votes and ln S of slot row_mine
+      const uint32_t sa = (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void*)(s_sc + row_mine * 4);
+      asm volatile("ds_read2_b32 %0, %1 offset1:64\n\ts_waitcnt lgkmcnt(0)" : "=v"(sc) : "v"(sa) : "memory");
+      const float lp_lane = fast_log2((float)(int32_t)(uint32_t)sc);
+      own_store = compute(base, false, -1, lp_lane, true, own_x);
+      if constexpr (STEP) own_ema = ema(__builtin_bit_cast(float, (uint32_t)(sc >> 32)), own_x);
       base = lim;
     } else {
       // the tile's K rows (registers), V rows (LDS) and scalars have landed; the K registers pass through the
@@ -921,16 +990,28 @@ __global__ __launch_bounds__(kMfmaWaves* kWave, 2) void decode_mfma_kernel(Decod
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) kreg[st][ks] = kn[st][ks];
       }
-      {
-        const float lp_lane = fast_log2((float)pv_next);
-#pragma unroll
-        for (int st = 0; st < 2; ++st)
-#pragma unroll
-          for (int i = 0; i < 4; ++i) lp[st][i] = __shfl(lp_lane, 16 * st + 4 * q + i);
-      }
-      ls_old = ls_next;
+      const float lp_lane = fast_log2((float)pv_next);
+      const float ls_old = ls_next;
       const int next = base + kTileStep;
-      compute(base, false, next < wave_lim ? next : -1, lp, ls_old, false);
+      float x;
+      const bool mine = compute(base, false, next < wave_lim ? next : -1, lp_lane, false, x);
+      // After the second product: the compiler orders the V reads behind every outstanding memory operation,
+      // and stores issued before them would be waited for.
+      if (p.logits_out != nullptr && mine) p.logits_out[ubase + base + row_mine] = x;
+      if constexpr (STEP) {
+        const float r = ema(ls_old, x);
+        if (mine) {
+          if (staged) {
+            // (a statement the compiler does not see as an LDS store: it would order one behind the next
+            // tile's outstanding copies into LDS)
+            const uint32_t sa = (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void*)(
+                s_stage + (size_t)(base - start + row_mine) * 4);
+            asm volatile("ds_write_b32 %0, %1" : : "v"(sa), "v"(r) : "memory");
+          } else {
+            p.log_s[ubase + base + row_mine] = r;
+          }
+        }
+      }
       Vb = Tb + (Vb == Tb ? TILE_BYTES : 0);
       base = next;
     }
@@ -938,6 +1019,7 @@ __global__ __launch_bounds__(kMfmaWaves* kWave, 2) void decode_mfma_kernel(Decod
   KK_TS(1);
   const bool grow = STEP && len_old < p.capacity;
   const int len = grow ? len_old + 1 : len_old;
+  float new_x = 0.f;
   if (takes_new) {
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // the copy of the new token has landed
     if constexpr (ONE) read_q();                 // (a wavefront without a tile of its own has not read them yet)
@@ -952,29 +1034,75 @@ __global__ __launch_bounds__(kMfmaWaves* kWave, 2) void decode_mfma_kernel(Decod
           kreg[1][ks] = __builtin_bit_cast(bf16x8_t, z4);
         }
       }
-      if (lane < 2 * CHUNKS) {
+      if (lane < 2 * CHUNKS) {                   // row 0 of the tile (its swizzle is the identity)
         const uint4 x = *reinterpret_cast<const uint4*>(s_new + lane * 16);
-        // row 0 of the tile (its swizzle is the identity) and the cache row of the new slot
         if (ONE || lane >= CHUNKS) *reinterpret_cast<uint4*>((lane < CHUNKS ? Kb : Vb) + (lane % CHUNKS) * 16) = x;
-        unsigned char* dst = reinterpret_cast<unsigned char*>(lane < CHUNKS ? p.k : p.v) + (ubase + len_old) * ROWB;
-        *reinterpret_cast<uint4*>(dst + (lane % CHUNKS) * 16) = x;
-      }
-      if (lane == 0) {
-        p.votes[ubase + len_old] = 1;
-        p.born[ubase + len_old] = t_old;          // first observed in this step
       }
       __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
       __builtin_amdgcn_wave_barrier();
-      const float one[2][4] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};   // one vote: log2 = 0
-      compute(0, true, -1, one, -INFINITY, false);
+      compute(0, true, -1, 0.f, false, new_x);   // one vote: log2 = 0
     }
   }
 
-  // ---- deposit this wavefront's state; the workgroup reduces kParts of them -------------------------
-  float l_tot = l_run + __shfl_xor(l_run, 16);
-  l_tot += __shfl_xor(l_tot, 32);
+  // ---- deposit this wavefront's state in its own tile buffers; the workgroup reduces kParts of them --------------------
+  // Rows of the second product: row 4 q + i is head (4 q + i) mod G, lane share (4 q + i) / G.  The shares are added in
+  // the lane (G <= 2), then over the lane halves and (G <= 4) the rows of 16 lanes; each exchange pairs two channel
+  // tiles, so the lanes end up with different channel tiles and the LDS stores are wide.
+  const float l_tot = over_head_lanes<G>(l_run, [](float a, float b) { return a + b; });
+  constexpr int NH = G < 4 ? G : 4;              // heads per lane
+  float o[NTILE][NH];
+#pragma unroll
+  for (int nt = 0; nt < NTILE; ++nt)
+#pragma unroll
+    for (int h = 0; h < NH; ++h) {
+      if constexpr (G == 1) o[nt][h] = (O[nt][0] + O[nt][1]) + (O[nt][2] + O[nt][3]);
+      else if constexpr (G == 2) o[nt][h] = O[nt][h] + O[nt][h + 2];
+      else o[nt][h] = O[nt][h];
+    }
+#pragma unroll
+  for (int nt = 0; nt < NTILE / 2; ++nt)
+#pragma unroll
+    for (int h = 0; h < NH; ++h) {
+      swap_halves(o[nt][h], o[nt + NTILE / 2][h]);
+      o[nt][h] += o[nt + NTILE / 2][h];
+    }
+  constexpr int NO = G <= 4 ? NTILE / 4 : NTILE / 2;   // channel tiles per lane
+  if constexpr (G <= 4) {
+#pragma unroll
+    for (int nt = 0; nt < NO; ++nt)
+#pragma unroll
+      for (int h = 0; h < NH; ++h) {
+        swap_rows(o[nt][h], o[nt + NO][h]);
+        o[nt][h] += o[nt + NO][h];
+      }
+  }
+  constexpr int kPartStride = 2 * TILE_BYTES / (int)sizeof(float);     // floats between the wavefronts' deposits
+  float* s_acc = reinterpret_cast<float*>(smem_tiles);                 // [kParts] x [D][G]
+  float* s_ml = s_acc + G * D;                                         // [kParts] x ([G] maxima, [G] sums)
+  {
+    float* acc_mine = s_acc + wave * kPartStride;
+    const int nt0 = (NTILE / 2) * (q >> 1) + (G <= 4 ? NO * (q & 1) : 0);
+    const int h0 = G == 8 ? 4 * (q & 1) : 0;
+#pragma unroll
+    for (int nt = 0; nt < NO; ++nt) {
+      float* at = acc_mine + (16 * (nt0 + nt) + l16) * G + h0;
+      if constexpr (NH == 4) *reinterpret_cast<float4*>(at) = make_float4(o[nt][0], o[nt][1], o[nt][2], o[nt][3]);
+      else if constexpr (NH == 2) *reinterpret_cast<float2*>(at) = make_float2(o[nt][0], o[nt][1]);
+      else *at = o[nt][0];
+    }
+    if (q == 0 && l16 < G) {
+      s_ml[wave * kPartStride + l16] = m_run;
+      s_ml[wave * kPartStride + G + l16] = l_tot;
+    }
+  }
   if constexpr (!ONE && STEP) asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the staged EMA state is in LDS
-  __syncthreads();                               // every wavefront is done with its tile buffers
+  __syncthreads();
+  KK_TS(2);
+  if constexpr (ONE) {
+    const size_t at = ubase + start + wave * kMTile + row_mine;
+    if (p.logits_out != nullptr && own_store) p.logits_out[at] = own_x;
+    if (STEP && own_store) p.log_s[at] = own_ema;
+  }
   if constexpr (!ONE && STEP) {
     if (staged) {                                // the split's updated EMA state, slot by slot
       for (int j = threadIdx.x; j < live_end - start; j += kMfmaWaves * kWave) {
@@ -984,24 +1112,20 @@ __global__ __launch_bounds__(kMfmaWaves* kWave, 2) void decode_mfma_kernel(Decod
       }
     }
   }
-  float* s_m = reinterpret_cast<float*>(smem_raw);     // [kParts][G]
-  float* s_l = s_m + kParts * G;                       // [kParts][G]
-  float* s_acc = s_l + kParts * G;                     // [kParts][G][D]
-  if (q == 0 && l16 < G) {
-    s_m[wave * G + l16] = m_run;
-    s_l[wave * G + l16] = l_tot;
-  }
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int head = 4 * q + i;                  // output row; rows >= G repeat heads
-    if (head < G) {
-#pragma unroll
-      for (int nt = 0; nt < NTILE; ++nt) s_acc[(wave * G + head) * D + 16 * nt + l16] = O[nt][i];
+  if (takes_new && grow) {                       // the appended token joins the cache
+    if (lane < 2 * CHUNKS) {
+      unsigned char* dst = reinterpret_cast<unsigned char*>(lane < CHUNKS ? p.k : p.v) + (ubase + len_old) * ROWB;
+      *reinterpret_cast<uint4*>(dst + (lane % CHUNKS) * 16) = *reinterpret_cast<const uint4*>(s_new + lane * 16);
+    }
+    if (lane == 0) {                             // (row 0 of its tile is this lane's)
+      p.votes[ubase + len_old] = 1;
+      p.born[ubase + len_old] = t_old;           // first observed in this step
+      if (p.logits_out != nullptr) p.logits_out[ubase + len_old] = new_x;
+      p.log_s[ubase + len_old] = ema(-INFINITY, new_x);
     }
   }
-  __syncthreads();
-  KK_TS(2);
-  combine_and_finish<T, D, G, kParts, STEP, kMfmaWaves>(p, s_m, s_l, s_acc, &s_last, unit, split, grow, len, t_old);
+  combine_and_finish<T, D, G, kParts, STEP, kMfmaWaves, true>(p, s_ml, s_ml + G, s_acc, kPartStride, kPartStride, &s_last,
+                                                              unit, split, grow, len, t_old);
 }
 
 template <typename T, int D, int G>
@@ -1011,7 +1135,7 @@ keepkv_status launch_decode(const DecodeParams& p, int units, bool step, bool va
   constexpr int RV = D * (int)sizeof(T) / 16;                       // 16-byte vectors per row
   constexpr int LPS = (G >= 8 && RV >= 16) ? RV / (RV >= 32 ? 2 : 1) : (RV >= 32 ? 16 : 8);
   constexpr int U = 4;
-  const dim3 grid(units * p.nsplit), block(kWavesPerBlock * kWave);
+  const dim3 grid(p.nsplit, units), block(kWavesPerBlock * kWave);
   if constexpr (sizeof(T) == 2) {
     if (!valu) {
       auto go = [&](auto waves_tag) -> keepkv_status {
