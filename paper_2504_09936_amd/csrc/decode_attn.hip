@@ -65,6 +65,19 @@ constexpr int kWavesPerBlock = 4;   // the vector-ALU kernel
 // D = 128: two workgroups or one per compute unit); plan_decode picks.
 
 
+// Asynchronous copy of 16 bytes per lane from base + lane_off + off (`bytes` long from base: beyond it reads give zero) to
+// LDS, through a buffer descriptor: the compiler counts these in the order of issue, while behind a global_load_lds it
+// waits for everything before it uses any register load.
+template <int AUX>
+__device__ __forceinline__ void copy_to_lds(const unsigned char* base, size_t bytes, unsigned char* lds, uint32_t lane_off,
+                                            uint32_t off) {
+#ifdef __HIP_DEVICE_COMPILE__                    // (the descriptor's type does not exist in the host pass)
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char*>(base), 0, (int)bytes, 0x00027000),
+      (__attribute__((address_space(3))) void*)lds, 16, lane_off, off, 0, AUX);
+#endif
+}
+
 constexpr float kLowest = -3.402823466e38f;   // lower end of the running maxima: finite, so that maxima can be subtracted
 
 __device__ __forceinline__ void st_agent(float* p, float v) {
@@ -579,12 +592,17 @@ __device__ __forceinline__ float over_head_lanes(float x, F op) {
 // product is head g's sum over lane r's slots and the rows of a head are added once at the end (permlane swaps).
 // Addresses: a tile's base is uniform (scalar registers), a lane adds a 32-bit offset that K and V share.
 // Measured before / after, graph replays, one step (D 128): 64 heads x 852 slots (G 4) 10.6 / 9.8 us, 8 heads 7.9 / 7.0,
-// 128 heads x 828 16.6 / 15.5, 1024 heads x 852 (G 8) 81.9 / 80.8.  Of the 9.8 us the rows need 5 (28.6 MB), the reduction
+// 128 heads x 828 16.6 / 15.7, 1024 heads x 852 (G 8) 81.9 / 80.8.  Of the 9.8 us the rows need 5 (28.6 MB), the reduction
 // over the wavefronts 0.5, publishing a split's result and taking the ticket 0.9, the combination 1.1, launch and drain 2.
 //
-// ONE: a split is at most one tile per wavefront (128 or 256 slots), so there is no tile loop, no prefetch and no
-// rescaling of the accumulators (the common steady-state shape).
-template <int D, int G, bool STEP, bool ONE, int kMfmaWaves>
+// MODE (how many tiles a wavefront has at most, kOneTile / kTwoTiles / kTileLoop):
+// - one tile (a split of 128 or 256 slots): no tile loop, no prefetch and no rescaling of the accumulators (the common
+//   steady-state shape);
+// - two tiles: everything is requested before the first wait.  The loop, which requests the second tile's rows when the
+//   first have landed, took 15.7 us for 128 heads x 828 slots and 16.3 us for 64 x 1683; this way 14.8 and 14.5;
+// - more: a loop that requests the next tile's rows while it works on the current one.
+constexpr int kTileLoop = 0, kOneTile = 1, kTwoTiles = 2;
+template <int D, int G, bool STEP, int MODE, int kMfmaWaves>
 __global__ __launch_bounds__(kMfmaWaves* kWave, 2) void decode_mfma_kernel(DecodeParams p) {
   using T = uint16_t;
   constexpr int ROWB = D * 2, CHUNKS = ROWB / 16, KS = D / 32, NTILE = D / 16;
@@ -592,6 +610,7 @@ __global__ __launch_bounds__(kMfmaWaves* kWave, 2) void decode_mfma_kernel(Decod
   constexpr int LOADS = TILE_BYTES / (kWave * 16);
   constexpr int kParts = kMfmaWaves;
   constexpr int NV = G >= 2 ? G / 2 : 1;         // slots of a tile whose weights one lane works out
+  constexpr bool ONE = MODE == kOneTile, TWO = MODE == kTwoTiles;
   extern __shared__ __align__(256) unsigned char smem_tiles[];   // [wave][two tile buffers]; later each wave's deposit
   __shared__ int s_last;
   __shared__ __align__(16) unsigned char s_new[2 * ROWB];       // step mode: the appended token's K row, V row
@@ -604,11 +623,12 @@ __global__ __launch_bounds__(kMfmaWaves* kWave, 2) void decode_mfma_kernel(Decod
   const int t_old = STEP ? p.t_obs[unit] : 0;   // used at the very end only
   const int start = split * p.per;
   const bool takes_new = STEP && split == p.nsplit - 1 && wave == kMfmaWaves - 1;
-  if (takes_new && lane < 2 * CHUNKS) {        // asynchronous copy of (k_t, v_t) into LDS, awaited after the loop
-    const unsigned char* src = reinterpret_cast<const unsigned char*>(lane < CHUNKS ? p.k_t : p.v_t) +
-                               (size_t)unit * ROWB + (lane % CHUNKS) * 16;
-    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
-                                     (__attribute__((address_space(3))) void*)s_new, 16, 0, 0);
+  if (takes_new) {                             // asynchronous copy of (k_t, v_t) into LDS, awaited after the loop
+    const size_t at = (size_t)unit * ROWB;
+    if (lane < CHUNKS)
+      copy_to_lds<0>(reinterpret_cast<const unsigned char*>(p.k_t) + at, ROWB, s_new, lane * 16, 0);
+    else if (lane < 2 * CHUNKS)
+      copy_to_lds<0>(reinterpret_cast<const unsigned char*>(p.v_t) + at, ROWB, s_new, (lane - CHUNKS) * 16, 0);
   }
   const int bound = p.len_hint > 0 ? min(p.len_hint, p.capacity) : len_old;
   const int lim = min(bound, start + p.per);
@@ -655,16 +675,20 @@ __global__ __launch_bounds__(kMfmaWaves* kWave, 2) void decode_mfma_kernel(Decod
     for (int i = 0; i < LOADS; ++i) {
       const int row = lane / CHUNKS + i * (kWave / CHUNKS), phys = lane % CHUNKS;
       const uint32_t off = (uint32_t)(min(row, rel) * ROWB + ((phys ^ (row & (CHUNKS - 1))) * 16));
-      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(tile_rows + off),
-                                       (__attribute__((address_space(3))) void*)(buf + i * (kWave * 16)), 16, 0, kStreamOnce);
+      if constexpr (TWO)
+        copy_to_lds<kStreamOnce>(rows, (size_t)bound * ROWB, buf + i * (kWave * 16), off, tbase * ROWB);
+      else
+        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(tile_rows + off),
+                                         (__attribute__((address_space(3))) void*)(buf + i * (kWave * 16)), 16, 0, kStreamOnce);
     }
   };
   // !ONE: the K rows of a tile are loaded in the layout of the score product's A operand (lane (l16, q): rows
   // l16 and 16 + l16 of the tile, chunk 4 ks + q of the row for k-step ks), one tile ahead, so a tile's K rows
   // pass through no LDS at all and a wavefront has a whole tile (K in registers, V on its way to the other LDS
   // buffer) in flight during all of the arithmetic on the current one.
+  // (TWO: the second tile's K rows in kreg.)
   bf16x8_t kn[2][KS], kreg[2][KS];
-  auto issue_k = [&](int tbase) {
+  auto issue_k = [&](int tbase, bf16x8_t (&to)[2][KS]) {
     const unsigned char* tile_rows = kbytes + (size_t)tbase * ROWB;
     const int rel = bound - 1 - tbase;
 #pragma unroll
@@ -672,37 +696,40 @@ __global__ __launch_bounds__(kMfmaWaves* kWave, 2) void decode_mfma_kernel(Decod
       const uint32_t off = (uint32_t)(min(16 * st + l16, rel) * ROWB + q * 16);
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks)
-        kn[st][ks] = __builtin_nontemporal_load(reinterpret_cast<const bf16x8_t*>(tile_rows + off + ks * 64));
+        to[st][ks] = __builtin_nontemporal_load(reinterpret_cast<const bf16x8_t*>(tile_rows + off + ks * 64));
     }
   };
   int base = start + wave * kMTile;
   const int wave_lim = lim;
   constexpr int kTileStep = kMfmaWaves * kMTile;
   const bool has_tile = base < wave_lim;
-  if (has_tile) {
-    if constexpr (ONE) issue_rows(kbytes, Kb, base);
-    else issue_k(base);
-    if constexpr (ONE) {                         // slot base + lane of the tile (lanes beyond the tile repeat a slot)
+  if constexpr (ONE) {
+    if (has_tile) {
+      issue_rows(kbytes, Kb, base);
+      // slot base + lane of the tile (lanes beyond the tile repeat a slot)
       const uint32_t at = (uint32_t)min(min(lane, kMTile - 1), bound - 1 - base);
       __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(p.votes + ubase + base + at),
                                        (__attribute__((address_space(3))) void*)s_sc, 4, 0, 0);
       if constexpr (STEP)
         __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(p.log_s + ubase + base + at),
                                          (__attribute__((address_space(3))) void*)(s_sc + 256), 4, 0, 0);
+      issue_rows(vbytes, Vb, base);
     }
-    issue_rows(vbytes, Vb, base);
   }
-  // !ONE: the votes and EMA state of a tile are requested one tile ahead, like its rows (into registers: they
-  // are first used behind the loop's full wait)
+  // Otherwise the votes and EMA state of a tile are requested with its rows, into registers.
   int pv_next = 1;
   float ls_next = -INFINITY;
-  auto request_scalars = [&](int tbase) {
+  auto request_scalars = [&](int tbase, int& pv, float& ls) {
     const uint32_t at = (uint32_t)min(row_mine, bound - 1 - tbase);
-    pv_next = (p.votes + ubase + tbase)[at];
-    if constexpr (STEP) ls_next = (p.log_s + ubase + tbase)[at];
+    pv = (p.votes + ubase + tbase)[at];
+    if constexpr (STEP) ls = (p.log_s + ubase + tbase)[at];
   };
-  if constexpr (!ONE) {
-    if (has_tile) request_scalars(base);
+  if constexpr (MODE == kTileLoop) {
+    if (has_tile) {
+      issue_k(base, kn);
+      issue_rows(vbytes, Vb, base);
+      request_scalars(base, pv_next, ls_next);
+    }
   }
 
   // B operand of the score product: column l16 is head l16 mod G, this lane's 8 channels of every k-step
@@ -735,10 +762,12 @@ __global__ __launch_bounds__(kMfmaWaves* kWave, 2) void decode_mfma_kernel(Decod
   // One tile.  `extra`: the appended token alone (row 0 of the tile, copied from s_new).
   // `next`: the wavefront's next tile (or -1); its K rows are requested as soon as the score product has
   // consumed the K buffer, its V rows after the second product, so both travel during the arithmetic.
-  // `v_in_flight`: the V rows are still outstanding when the call starts (ONE, the wavefront's own tile).
-  // lp_lane: log2(votes) of slot row_mine.  x_out: the group-mean logit of slot row_mine (of a `writer` lane), and the
+  // v_wait: the V rows have landed when at most that many requests are outstanding; negative: they have landed.
+  // k_rows: the K operand (unless ONE).  lp_lane: log2(votes) of slot row_mine.  x_out: the group-mean logit of slot row_mine (of a `writer` lane), and the
   // return value whether this lane stores it.
-  auto compute = [&](int tbase, bool extra, int next, float lp_lane, bool v_in_flight, float& x_out) -> bool {
+  auto compute = [&](int tbase, bool extra, int next, const bf16x8_t (&k_rows)[2][KS], float lp_lane, auto v_wait,
+                     float& x_out) -> bool {
+    constexpr int kVWait = decltype(v_wait)::value;
     const int n_live = extra ? 1 : max(0, min(kMTile, live_end - tbase));
     auto clear_masked_v = [&]() {
       if (n_live < kMTile) {                     // uniform: clear the V rows of masked slots (0 * garbage could be NaN)
@@ -748,12 +777,12 @@ __global__ __launch_bounds__(kMfmaWaves* kWave, 2) void decode_mfma_kernel(Decod
         __builtin_amdgcn_wave_barrier();
       }
     };
-    if (!v_in_flight) clear_masked_v();
-    if (!ONE && next >= 0) {
+    if constexpr (kVWait < 0) clear_masked_v();
+    if (MODE == kTileLoop && next >= 0) {
       // the next tile: K rows and scalars into registers, V rows into the other buffer (after the clearing
       // stores above: the compiler orders LDS stores behind outstanding copies into LDS)
-      issue_k(next);
-      request_scalars(next);
+      issue_k(next, kn);
+      request_scalars(next, pv_next, ls_next);
       issue_rows(vbytes, Tb + (Vb == Tb ? TILE_BYTES : 0), next);
     }
     // ---- S^T = K Q^T
@@ -761,8 +790,8 @@ __global__ __launch_bounds__(kMfmaWaves* kWave, 2) void decode_mfma_kernel(Decod
     if constexpr (!ONE) {
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks) {
-        s[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kreg[0][ks], qb[ks], s[0], 0, 0, 0);
-        s[1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kreg[1][ks], qb[ks], s[1], 0, 0, 0);
+        s[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(k_rows[0][ks], qb[ks], s[0], 0, 0, 0);
+        s[1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(k_rows[1][ks], qb[ks], s[1], 0, 0, 0);
       }
     } else {
       // the K tile through reads that the compiler does not order behind the V rows' copies (see above).  The buffer is
@@ -859,9 +888,9 @@ __global__ __launch_bounds__(kMfmaWaves* kWave, 2) void decode_mfma_kernel(Decod
         for (int nt = 0; nt < NTILE; ++nt) O[nt][i] *= ci[i];
     }
     first = false;
-    if (v_in_flight) {                           // before any store is issued: only the V rows are outstanding
+    if constexpr (kVWait >= 0) {                 // before any store is issued
       // (tied to the softmax sum, so that the wait is not scheduled ahead of the arithmetic it is meant to hide)
-      asm volatile("s_waitcnt vmcnt(0)" : "+v"(l_run) : : "memory");
+      asm volatile("s_waitcnt vmcnt(%1)" : "+v"(l_run) : "n"(kVWait) : "memory");
       clear_masked_v();
     }
     // ---- O += P V with P = hi + lo in bf16.  The places of the slots that other lanes took hold the smallest normal
@@ -962,7 +991,57 @@ __global__ __launch_bounds__(kMfmaWaves* kWave, 2) void decode_mfma_kernel(Decod
   // to memory, before this wavefront may deposit its sums)
   bool own_store = false;
   float own_x = 0.f, own_ema = 0.f;
-  while (base < wave_lim) {                      // a single pass with ONE
+  constexpr std::integral_constant<int, -1> kLanded{};
+  constexpr std::integral_constant<int, 0> kAwaitAll{};
+  auto publish = [&](int tbase, bool mine, float x, float ls_old) {   // the results per slot of one tile of several
+    if (p.logits_out != nullptr && mine) p.logits_out[ubase + tbase + row_mine] = x;
+    if constexpr (STEP) {
+      const float r = ema(ls_old, x);
+      if (mine) {
+        if (staged) {
+          // (a statement the compiler does not see as an LDS store: it would order one behind the next
+          // tile's outstanding copies into LDS)
+          const uint32_t sa = (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void*)(
+              s_stage + (size_t)(tbase - start + row_mine) * 4);
+          asm volatile("ds_write_b32 %0, %1" : : "v"(sa), "v"(r) : "memory");
+        } else {
+          p.log_s[ubase + tbase + row_mine] = r;
+        }
+      }
+    }
+  };
+  if constexpr (TWO) {
+    // Requests complete in the order of issue: with the second tile's outstanding the first one has landed.  (The
+    // scheduling barriers keep the two tiles' requests apart and ahead of the arithmetic.)
+    constexpr std::integral_constant<int, 2 * KS + LOADS + (STEP ? 2 : 1)> kAwaitFirst{};
+    const int second = base + kTileStep;
+    if (second < wave_lim) {
+      int pv2;
+      float ls2 = -INFINITY, x, x2;
+      issue_k(base, kn);
+      request_scalars(base, pv_next, ls_next);
+      issue_rows(vbytes, Tb, base);
+      __builtin_amdgcn_sched_barrier(0);
+      issue_k(second, kreg);
+      request_scalars(second, pv2, ls2);
+      issue_rows(vbytes, Tb + TILE_BYTES, second);
+      __builtin_amdgcn_sched_barrier(0);
+      const bool mine = compute(base, false, -1, kn, fast_log2((float)pv_next), kAwaitFirst, x);
+      Vb = Tb + TILE_BYTES;
+      const bool mine2 = compute(second, false, -1, kreg, fast_log2((float)pv2), kAwaitAll, x2);
+      publish(base, mine, x, ls_next);
+      publish(second, mine2, x2, ls2);
+    } else if (has_tile) {
+      float x;
+      issue_k(base, kn);
+      request_scalars(base, pv_next, ls_next);
+      issue_rows(vbytes, Tb, base);
+      const bool mine = compute(base, false, -1, kn, fast_log2((float)pv_next), kAwaitAll, x);
+      publish(base, mine, x, ls_next);
+    }
+    base = lim;
+  }
+  while (!TWO && base < wave_lim) {              // a single pass with ONE
     if constexpr (ONE) {
       // all copies but the youngest LOADS (the V rows) have landed: query rows, K rows, votes and EMA state
       asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LOADS) : "memory");
@@ -971,7 +1050,7 @@ __global__ __launch_bounds__(kMfmaWaves* kWave, 2) void decode_mfma_kernel(Decod
       const uint32_t sa = (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void*)(s_sc + row_mine * 4);
       asm volatile("ds_read2_b32 %0, %1 offset1:64\n\ts_waitcnt lgkmcnt(0)" : "=v"(sc) : "v"(sa) : "memory");
       const float lp_lane = fast_log2((float)(int32_t)(uint32_t)sc);
-      own_store = compute(base, false, -1, lp_lane, true, own_x);
+      own_store = compute(base, false, -1, kreg, lp_lane, kAwaitAll, own_x);
       if constexpr (STEP) own_ema = ema(__builtin_bit_cast(float, (uint32_t)(sc >> 32)), own_x);
       base = lim;
     } else {
@@ -994,24 +1073,10 @@ __global__ __launch_bounds__(kMfmaWaves* kWave, 2) void decode_mfma_kernel(Decod
       const float ls_old = ls_next;
       const int next = base + kTileStep;
       float x;
-      const bool mine = compute(base, false, next < wave_lim ? next : -1, lp_lane, false, x);
+      const bool mine = compute(base, false, next < wave_lim ? next : -1, kreg, lp_lane, kLanded, x);
       // After the second product: the compiler orders the V reads behind every outstanding memory operation,
       // and stores issued before them would be waited for.
-      if (p.logits_out != nullptr && mine) p.logits_out[ubase + base + row_mine] = x;
-      if constexpr (STEP) {
-        const float r = ema(ls_old, x);
-        if (mine) {
-          if (staged) {
-            // (a statement the compiler does not see as an LDS store: it would order one behind the next
-            // tile's outstanding copies into LDS)
-            const uint32_t sa = (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void*)(
-                s_stage + (size_t)(base - start + row_mine) * 4);
-            asm volatile("ds_write_b32 %0, %1" : : "v"(sa), "v"(r) : "memory");
-          } else {
-            p.log_s[ubase + base + row_mine] = r;
-          }
-        }
-      }
+      publish(base, mine, x, ls_old);
       Vb = Tb + (Vb == Tb ? TILE_BYTES : 0);
       base = next;
     }
@@ -1040,7 +1105,7 @@ __global__ __launch_bounds__(kMfmaWaves* kWave, 2) void decode_mfma_kernel(Decod
       }
       __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
       __builtin_amdgcn_wave_barrier();
-      compute(0, true, -1, 0.f, false, new_x);   // one vote: log2 = 0
+      compute(0, true, -1, kreg, 0.f, kLanded, new_x);   // one vote: log2 = 0
     }
   }
 
@@ -1144,21 +1209,27 @@ keepkv_status launch_decode(const DecodeParams& p, int units, bool step, bool va
         // 64 or 128 KB of tile buffers at D = 128, the per-wavefront staging of queries and scalars, plus the
         // kernel's static LDS: allow it explicitly (once per process and instance)
         static const bool allowed =
-            hipFuncSetAttribute((const void*)decode_mfma_kernel<D, G, true, true, WV>,
+            hipFuncSetAttribute((const void*)decode_mfma_kernel<D, G, true, kOneTile, WV>,
                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)tiles) == hipSuccess &&
-            hipFuncSetAttribute((const void*)decode_mfma_kernel<D, G, true, false, WV>,
+            hipFuncSetAttribute((const void*)decode_mfma_kernel<D, G, true, kTwoTiles, WV>,
                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)tiles) == hipSuccess &&
-            hipFuncSetAttribute((const void*)decode_mfma_kernel<D, G, false, true, WV>,
+            hipFuncSetAttribute((const void*)decode_mfma_kernel<D, G, true, kTileLoop, WV>,
                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)tiles) == hipSuccess &&
-            hipFuncSetAttribute((const void*)decode_mfma_kernel<D, G, false, false, WV>,
+            hipFuncSetAttribute((const void*)decode_mfma_kernel<D, G, false, kOneTile, WV>,
+                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)tiles) == hipSuccess &&
+            hipFuncSetAttribute((const void*)decode_mfma_kernel<D, G, false, kTwoTiles, WV>,
+                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)tiles) == hipSuccess &&
+            hipFuncSetAttribute((const void*)decode_mfma_kernel<D, G, false, kTileLoop, WV>,
                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)tiles) == hipSuccess;
         if (!allowed) return KEEPKV_ERR_DEVICE;
         const dim3 mblock(WV * kWave);
-        const bool one = p.per <= WV * kMTile;
-        if (step && one) decode_mfma_kernel<D, G, true, true, WV><<<grid, mblock, tiles, st>>>(p);
-        else if (step) decode_mfma_kernel<D, G, true, false, WV><<<grid, mblock, tiles, st>>>(p);
-        else if (one) decode_mfma_kernel<D, G, false, true, WV><<<grid, mblock, tiles, st>>>(p);
-        else decode_mfma_kernel<D, G, false, false, WV><<<grid, mblock, tiles, st>>>(p);
+        const int n_tiles = (p.per + WV * kMTile - 1) / (WV * kMTile);      // per wavefront, at most
+        if (step && n_tiles == 1) decode_mfma_kernel<D, G, true, kOneTile, WV><<<grid, mblock, tiles, st>>>(p);
+        else if (step && n_tiles == 2) decode_mfma_kernel<D, G, true, kTwoTiles, WV><<<grid, mblock, tiles, st>>>(p);
+        else if (step) decode_mfma_kernel<D, G, true, kTileLoop, WV><<<grid, mblock, tiles, st>>>(p);
+        else if (n_tiles == 1) decode_mfma_kernel<D, G, false, kOneTile, WV><<<grid, mblock, tiles, st>>>(p);
+        else if (n_tiles == 2) decode_mfma_kernel<D, G, false, kTwoTiles, WV><<<grid, mblock, tiles, st>>>(p);
+        else decode_mfma_kernel<D, G, false, kTileLoop, WV><<<grid, mblock, tiles, st>>>(p);
         return KEEPKV_OK;
       };
       if (p.waves == 8) return go(std::integral_constant<int, 8>{});
