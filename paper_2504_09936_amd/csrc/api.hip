@@ -45,7 +45,7 @@ extern "C" keepkv_status keepkv_decode_plan(const keepkv_layout* layout, int32_t
 extern "C" size_t keepkv_workspace_bytes(const keepkv_layout* layout, int32_t capacity, int32_t budget) {
   using namespace kk;
   if (!layout_ok(layout) || capacity < 1 || capacity > (1 << 20) || budget < 1 || budget > capacity) return 0;
-  size_t need = plan_decode(layout, capacity).bytes;
+  size_t need = decode_workspace_bytes(layout, capacity);
   const size_t s = plan_select(layout, capacity).bytes;
   const size_t m = plan_match(layout, capacity, budget).bytes;
   const size_t g = plan_merge(layout, capacity, budget).bytes;

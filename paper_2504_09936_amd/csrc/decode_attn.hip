@@ -1338,57 +1338,112 @@ keepkv_status static_scratch(void** out, hipStream_t st) {
 
 }  // namespace
 
-static DecodePlan make_plan(const keepkv_layout* L, int capacity, int force_per, int force_waves) {
-  // Slots per split, and for the matrix-core kernel its workgroup size, from a small cost model fitted to
-  // measurements on MI355X (batch 1..128, 850..32768 slots per head).  Workgroups of 4 wavefronts fit two to
-  // a compute unit (512 resident), those of 8 wavefronts one (128 KB of tile buffers at D = 128: 256
-  // resident; 512 at D = 64).  Every round of workgroups costs ~3 us of start-up.  A wavefront streams at no
-  // more than ~6.5 GB/s when all its tiles are requested at once and ~4.4 GB/s when it loops (its rows in
-  // flight over the memory latency); all resident workgroups together reach ~5.1 TB/s when the chip is
-  // full, and a compute unit with two workgroups beside one with a single one sets the pace.  The last
-  // workgroup of a head combines the splits eight or sixteen at a time, ~2.3 / ~3.4 us per round trip of
-  // device-scope loads.  Few long splits starve the chip, many short ones pay for rounds and for the
-  // combine.  On the Llama-3-8B shape (64 heads, ~850 slots) 4 splits of 8 wavefronts are exactly one
-  // workgroup per compute unit: 11.2 us against 11.9 us for 7 splits of 4 wavefronts (448 workgroups on 256
-  // compute units); at 128 heads and more the smaller workgroups win (two rounds instead of four at batch 128).
-  DecodePlan pl;
+// Workgroups of the matrix-core kernel that a compute unit holds: by its LDS (tile buffers, staging, static part), and by
+// the 16 wavefronts that its registers allow.
+static int resident_per_cu(int waves, int head_dim, int group) {
+  const int lds = waves * (2 * kMTile * head_dim * 2 + mfma_stage_bytes(head_dim, group)) + 1024;
+  const int by_lds = 160 * 1024 / lds, by_regs = 16 / waves;
+  const int n = by_lds < by_regs ? by_lds : by_regs;
+  return n > 0 ? n : 1;
+}
+
+// Slots per split and workgroup size of the matrix-core kernel, from a cost model.  A round of n workgroups takes the
+// longer of what one workgroup needs for its rows (a compute unit pulls 34 GB/s, shared by its workgroups; a wavefront
+// 10.2 GB/s with all its tiles requested at once, 7.5 in the tile loop) and of what memory needs for all of them
+// (5.8 TB/s, less when the last workgroups leave compute units empty); further rounds cost 1.7 us each, smaller workgroups
+// 0.5 us, and splits have to be combined, four, eight or sixteen at a time.  At most kMaxSplitWorkgroups workgroups share
+// heads: more of them never paid, and it bounds the workspace.
+// The constants are a fit to 2000 measured (shape, plan) pairs on MI355X: batch 1 .. 128, 116 .. 32768 slots, head dims 64
+// and 128.  Over those 55 shapes the plan chosen is 0.4 % slower than the best one (2.6 % at most); the model before, which
+// rounded a split up to whole workgroup iterations and knew one price for combining, was 3.5 % (36 % at most) off: 8 heads
+// x 32768 slots 43.5 us with 16 splits against 30.1 with 32, 128 heads x 2000 (D 64) 23.8 with one against 16.4 with two, 8
+// heads x 852 7.1 with four against 6.7 with seven.
+constexpr int kMaxSplitWorkgroups = 512;
+constexpr int kMinSplit = 64;
+static void choose_split(const keepkv_layout* L, int capacity, long& per, int& waves) {
   const double units = (double)L->batch * L->n_kv_heads;
-  const double slot_bytes = 2.0 * L->head_dim * (L->dtype == KEEPKV_BF16 ? 2 : 4) + 24.0;
-  const bool valu = L->dtype == KEEPKV_BF16 && force_waves == -1;
-  const bool mfma = L->dtype == KEEPKV_BF16 && !valu;
-  const int rv = L->head_dim * (L->dtype == KEEPKV_BF16 ? 2 : 4) / 16;
-  long per = 128;
-  int waves = kWavesPerBlock;
+  const double slot_bytes = 4.0 * L->head_dim + 24.0;
+  const long max_ns = (capacity + kMinSplit - 1) / kMinSplit;
   double best = 1e300;
-  for (int wv = 4; wv <= (mfma ? 8 : 4); wv += 4) {
-    // a split is a whole number of `unit_slots`; a workgroup consumes `granule` slots per loop iteration
-    const long unit_slots = mfma ? kMTile : 64;
-    const long granule = mfma ? (long)wv * kMTile : (L->dtype == KEEPKV_BF16 ? 128 : (rv >= 32 ? 64 : 128));
-    const double res_max = (mfma && (size_t)wv * 2 * kMTile * L->head_dim * 2 > 72 * 1024) ? 256.0 : 512.0;
-    const long max_ns = (capacity + unit_slots - 1) / unit_slots < 1024 ? (capacity + unit_slots - 1) / unit_slots : 1024;
-    for (long ns = 1; ns <= max_ns; ++ns) {
-      const long cand = ((capacity + ns - 1) / ns + unit_slots - 1) / unit_slots * unit_slots;
+  for (int wv = 4; wv <= 8; wv += 4) {
+    const double res_max = 256.0 * resident_per_cu(wv, L->head_dim, L->n_q_heads / L->n_kv_heads);
+    for (long ns = 1; ns <= max_ns && (ns == 1 || units * (double)ns <= kMaxSplitWorkgroups); ++ns) {
+      long cand = ((capacity + ns - 1) / ns + kMTile - 1) / kMTile * kMTile;
+      if (cand < kMinSplit) cand = kMinSplit;
       const double n_split = (double)((capacity + cand - 1) / cand);
       const double wgs = units * n_split;
-      const double resident = wgs < res_max ? wgs : res_max;
-      const double rounds = (double)(long)((wgs + res_max - 1.0) / res_max);
-      const double wg_rate = (cand <= granule ? 6.5 : 4.4) * wv;                        // GB/s
-      double together = 5100.0 * pow(resident / res_max, 0.15);                         // GB/s, all resident workgroups
-      if (resident > 256.0) together *= (resident / 256.0) / (double)(long)((resident + 255.0) / 256.0);
-      if (together > wg_rate * resident) together = wg_rate * resident;
-      const double streamed = (double)((cand + granule - 1) / granule * granule);       // whole iterations
-      const double t_one = streamed * slot_bytes / (wg_rate * 1e3);                     // us, a workgroup alone
-      const double t_all = units * capacity * slot_bytes / rounds / (together * 1e3);   // us, one round of them
-      const double t_stream = rounds * (3.0 + (t_one > t_all ? t_one : t_all));
-      const double t_trips = n_split <= 8.0 ? 2.3 : 3.4 * (double)(long)((n_split + 15.0) / 16.0);
-      const double t_combine = n_split > 1.0 ? 1.0 + t_trips + 0.02 * n_split : 0.0;
-      if (t_stream + t_combine < best) {
-        best = t_stream + t_combine;
+      const long tiles = cand / kMTile;
+      const double busy = (double)(tiles < wv ? tiles : wv);                           // wavefronts with a tile
+      const double streams = (tiles <= 2 * wv ? 10.2 : 7.5) * busy;                   // GB/s
+      auto round_of = [&](double n) {                                                  // us
+        if (n <= 0.0) return 0.0;
+        const double per_cu = (double)(long)((n + 255.0) / 256.0);
+        const double rate = 33.7 / per_cu < streams ? 33.7 / per_cu : streams;
+        const double alone = (double)cand * slot_bytes / (rate * 1e3);
+        const double together = n * (units * capacity / wgs) * slot_bytes / (5.8e6 * pow(n / (256.0 * per_cu), 0.38));
+        return alone > together ? alone : together;
+      };
+      const double full = (double)(long)(wgs / res_max), rest = wgs - full * res_max;
+      const double rounds = full + (rest > 0.0 ? 1.0 : 0.0);
+      double t = full * round_of(res_max) + round_of(rest) + 1.7 * (rounds - 1.0) + (wv == 4 ? 0.46 : 0.0);
+      if (n_split > 1.0)
+        t += (n_split <= 4.0 ? 1.85 : n_split <= 8.0 ? 2.7 : 4.3 + 1.3 * (double)(long)((n_split - 1.0) / 16.0)) + 0.011 * n_split;
+      if (t < best) {
+        best = t;
         per = cand;
         waves = wv;
       }
     }
   }
+}
+
+// The vector-ALU kernel (4 wavefronts): a wavefront streams at no more than ~6.5 GB/s when all its tiles are requested at
+// once and ~4.4 GB/s when it loops, all resident workgroups (512) together at ~5.1 TB/s when the chip is full; every round
+// costs ~3 us, the combination ~2.3 / ~3.4 us per round trip of device-scope loads.
+static void choose_split_valu(const keepkv_layout* L, int capacity, long& per) {
+  const double units = (double)L->batch * L->n_kv_heads;
+  const bool bf16 = L->dtype == KEEPKV_BF16;
+  const double slot_bytes = 2.0 * L->head_dim * (bf16 ? 2 : 4) + 24.0;
+  const int rv = L->head_dim * (bf16 ? 2 : 4) / 16;
+  const long granule = bf16 ? 128 : (rv >= 32 ? 64 : 128);      // slots per loop iteration of a workgroup
+  const double res_max = 512.0;
+  const long max_ns = (capacity + 63) / 64 < 1024 ? (capacity + 63) / 64 : 1024;
+  double best = 1e300;
+  for (long ns = 1; ns <= max_ns; ++ns) {
+    const long cand = ((capacity + ns - 1) / ns + 63) / 64 * 64;
+    const double n_split = (double)((capacity + cand - 1) / cand);
+    const double wgs = units * n_split;
+    const double resident = wgs < res_max ? wgs : res_max;
+    const double rounds = (double)(long)((wgs + res_max - 1.0) / res_max);
+    const double wg_rate = (cand <= granule ? 6.5 : 4.4) * kWavesPerBlock;            // GB/s
+    double together = 5100.0 * pow(resident / res_max, 0.15);                         // GB/s, all resident workgroups
+    if (resident > 256.0) together *= (resident / 256.0) / (double)(long)((resident + 255.0) / 256.0);
+    if (together > wg_rate * resident) together = wg_rate * resident;
+    const double streamed = (double)((cand + granule - 1) / granule * granule);       // whole iterations
+    const double t_one = streamed * slot_bytes / (wg_rate * 1e3);                     // us, a workgroup alone
+    const double t_all = units * capacity * slot_bytes / rounds / (together * 1e3);   // us, one round of them
+    const double t_stream = rounds * (3.0 + (t_one > t_all ? t_one : t_all));
+    const double t_trips = n_split <= 8.0 ? 2.3 : 3.4 * (double)(long)((n_split + 15.0) / 16.0);
+    const double t_combine = n_split > 1.0 ? 1.0 + t_trips + 0.02 * n_split : 0.0;
+    if (t_stream + t_combine < best) {
+      best = t_stream + t_combine;
+      per = cand;
+    }
+  }
+}
+
+static size_t decode_bytes(const keepkv_layout* L, long nsplit) {
+  return kWorkspaceHead + align_up((size_t)L->batch * L->n_q_heads * nsplit * (L->head_dim + 2) * sizeof(float), 256);
+}
+
+static DecodePlan make_plan(const keepkv_layout* L, int capacity, int force_per, int force_waves) {
+  DecodePlan pl;
+  const bool valu = L->dtype == KEEPKV_BF16 && force_waves == -1;
+  const bool mfma = L->dtype == KEEPKV_BF16 && !valu;
+  long per = 128;
+  int waves = kWavesPerBlock;
+  if (mfma) choose_split(L, capacity, per, waves);
+  else choose_split_valu(L, capacity, per);
   if (mfma && (force_waves == 4 || force_waves == 8)) waves = force_waves;
   pl.waves = waves;
   pl.valu = valu;
@@ -1398,12 +1453,23 @@ static DecodePlan make_plan(const keepkv_layout* L, int capacity, int force_per,
   pl.nsplit = (int)ns;
   pl.per = (int)per;
   pl.partial_off = kWorkspaceHead;
-  pl.bytes = kWorkspaceHead + align_up((size_t)L->batch * L->n_q_heads * ns * (L->head_dim + 2) * sizeof(float), 256);
+  pl.bytes = decode_bytes(L, ns);
   return pl;
 }
 
+// A workspace for caches of up to `capacity` slots: a smaller cache may be split finer than the largest.
+size_t decode_workspace_bytes(const keepkv_layout* L, int capacity) {
+  size_t bytes = plan_decode(L, capacity).bytes;
+  if (L->dtype == KEEPKV_BF16) {
+    const long units = (long)L->batch * L->n_kv_heads;
+    long ns = (capacity + kMinSplit - 1) / kMinSplit;
+    if (ns > kMaxSplitWorkgroups / units) ns = kMaxSplitWorkgroups / units;
+    if (ns > 1 && decode_bytes(L, ns) > bytes) bytes = decode_bytes(L, ns);
+  }
+  return bytes;
+}
 
-// The cost model walks up to 2048 candidate plans (2 us for 884 slots, 27 us for 32768), and a program asks for the same
+// The cost model walks up to 1024 candidate plans, microseconds of host time, and a program asks for the same
 // few plans again and again (one per layer shape and step): each thread keeps its last ones.  A plan is a pure function
 // of the fields compared here.
 DecodePlan plan_decode(const keepkv_layout* L, int capacity, int force_per, int force_waves) {

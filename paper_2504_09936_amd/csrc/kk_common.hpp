@@ -108,6 +108,7 @@ struct DecodePlan {
 };
 // force_per / force_waves: the caller's overrides (keepkv_cache.plan_slots_per_split / plan_wavefronts), 0 = none
 DecodePlan plan_decode(const keepkv_layout* L, int capacity, int force_per = 0, int force_waves = 0);
+size_t decode_workspace_bytes(const keepkv_layout* L, int capacity);   // for automatic plans of any capacity up to this one
 
 struct SelectPlan {
   size_t keys_off;    // uint64 [B*Hkv, capacity]

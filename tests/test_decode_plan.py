@@ -1,0 +1,28 @@
+"""The decode plan (host arithmetic): well-formed for every shape, and covered by the workspace of any larger cache."""
+import pytest
+
+from tests import gpu_util as U
+
+HEAD = 64 * 1024 + 256       # control words at the head of a workspace (keepkv.h)
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("G", [1, 2, 4, 8])
+@pytest.mark.parametrize("units", [1, 8, 40, 256, 1000])
+def test_plan_and_workspace(units, G, D):
+    kk = U.kk()
+    lay = kk.Layout(units, G, 1, D, kk.BF16, 0.1)
+    for cap in (1, 31, 64, 65, 500, 884, 4100, 32768, 1 << 20):
+        ns, per, waves = kk.decode_plan(lay, cap)
+        assert per % 32 == 0 and per >= 64 and waves in (4, 8)
+        assert ns == -(-cap // per) and (ns == 1 or ns * units <= 512)
+    for largest in (100, 900, 5000, 32768):
+        have = kk.workspace_bytes(lay, largest, max(1, largest // 10))
+        for cap in range(1, largest + 1, max(1, largest // 61)):
+            ns = kk.decode_plan(lay, cap)[0]
+            assert ns == 1 or HEAD + units * G * ns * (D + 2) * 4 <= have, (largest, cap)
+
+
+def test_layouts_without_a_kernel_still_get_a_size():
+    kk = U.kk()
+    assert kk.workspace_bytes(kk.Layout(2, 6, 2, 4096, kk.BF16, 0.1), 1000, 100) > HEAD
