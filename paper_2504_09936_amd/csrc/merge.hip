@@ -606,12 +606,16 @@ __global__ __launch_bounds__(256) void merge_apply_kernel(MergeParams p) {
 // threshold, or -1: the links form a forest.  A slot is absorbed by the slot it links to unless that slot is
 // itself absorbed, i.e. slots at odd depth of their tree are absorbed by their parent and slots at even depth
 // stay and receive their children.  Depth parity comes from pointer jumping in LDS (links point to lower
-// slot numbers; ceil(log2 len) rounds); the receiving slots are numbered in ascending order by a block scan,
+// slot numbers; at most ceil(log2 len) rounds, ended when no slot moves any more: two or three where few slots link);
+// the receiving slots are numbered in ascending order by a block scan,
 // the absorbed slots grouped by receiver (histogram, scan, scatter) and put in ascending slot order inside
 // each group by counting, so the merge sums in a fixed order.  Output in the form merge_apply_kernel reads:
 // keep_idx (receivers, -1 behind them), CSR starts and members, all with pitch `capacity`; dst.len = receivers.
 // The two per-slot work arrays live in LDS up to kPrefillLdsSlots slots per head; beyond that (GLOBAL) they are
 // in the workspace and are read and written with device-scope accesses: the same steps, an L2 round trip each.
+// What bounds it: LDS accesses of one workgroup per head.  Neighbouring lanes hold neighbouring slots: with a run of 8 slots
+// per thread every access hit the banks eight times over, and with all 13 rounds 64 heads x 8192 slots took 58 us (now
+// 20 us).
 constexpr int kPrefillLdsSlots = 16384;          // two int arrays of that many words fit in LDS
 constexpr int kPrefillMaxSlots = 32768;
 
@@ -637,8 +641,8 @@ __global__ __launch_bounds__(kGroupThreads) void prefill_group_kernel(
   };
   const int unit = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int n = min(slen[unit], capacity);
-  const int per = (capacity + kGroupThreads - 1) / kGroupThreads;     // slots per thread, a contiguous run (<= kPfItems)
-  const int i0 = tid * per;
+  const int per = (capacity + kGroupThreads - 1) / kGroupThreads;     // slots per thread (<= kPfItems)
+  const int i0 = wave * per * 64 + lane;           // its u-th slot is i0 + 64 u: a wavefront takes a run of 64-slot chunks
   const int32_t* nr = near + (size_t)unit * capacity;
   int* A = GLOBAL ? gwork + (size_t)unit * 2 * per * kGroupThreads : s_pf;
   int* B = A + per * kGroupThreads;
@@ -647,7 +651,7 @@ __global__ __launch_bounds__(kGroupThreads) void prefill_group_kernel(
   int link[kPfItems];
 #pragma unroll
   for (int u = 0; u < kPfItems; ++u) {
-    const int i = i0 + u;
+    const int i = i0 + 64 * u;
     link[u] = -1;
     if (u < per && i < n) {
       const int l = nr[i];
@@ -661,26 +665,30 @@ __global__ __launch_bounds__(kGroupThreads) void prefill_group_kernel(
   int* cur = A;
   int* nxt = B;
   for (int r = 0; r < rounds; ++r) {              // uniform trip count
+    int moved = 0;
 #pragma unroll
     for (int u = 0; u < kPfItems; ++u) {
-      const int i = i0 + u;
+      const int i = i0 + 64 * u;
       if (u < per && i < n) {
         const int x = ld(cur, i);
         const int y = ld(cur, x >> 1);
         st_(nxt, i, (y & ~1) | ((x ^ y) & 1));
+        moved |= (x ^ y) & ~1;
       }
     }
-    sync();
+    if constexpr (GLOBAL) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    const int any = __syncthreads_or(moved);      // (as sync() does)
     int* t = cur; cur = nxt; nxt = t;
+    if (any == 0) break;                          // every slot has its root
   }
-  // absorbed = odd depth; receivers numbered in slot order
+  // absorbed = odd depth; receivers numbered in slot order: positions in a chunk by ballot
   bool absorbed[kPfItems];
-  int n_recv_mine = 0;
+  int recv_wave = 0;
 #pragma unroll
   for (int u = 0; u < kPfItems; ++u) {
-    const int i = i0 + u;
+    const int i = i0 + 64 * u;
     absorbed[u] = (u < per && i < n) ? (ld(cur, i) & 1) != 0 : false;
-    if (u < per && i < n && !absorbed[u]) ++n_recv_mine;
+    recv_wave += __popcll(__ballot(u < per && i < n && !absorbed[u]));
   }
   auto block_exclusive = [&](int mine, int& total) {   // exclusive prefix of `mine` over the threads, and the sum
     int incl = mine;
@@ -701,17 +709,25 @@ __global__ __launch_bounds__(kGroupThreads) void prefill_group_kernel(
     total = all;
     return before + incl - mine;
   };
-  int n_recv = 0;
-  int rpos = block_exclusive(n_recv_mine, n_recv);
+  if (lane == 0) s_wave[wave] = recv_wave;
+  __syncthreads();
+  int n_recv = 0, rbase = 0;
+  for (int w = 0; w < kGroupThreads / 64; ++w) {
+    if (w < wave) rbase += s_wave[w];
+    n_recv += s_wave[w];
+  }
   // nxt: receiver number of every receiving slot; then cur is free
 #pragma unroll
   for (int u = 0; u < kPfItems; ++u) {
-    const int i = i0 + u;
-    if (u < per && i < n && !absorbed[u]) {
+    const int i = i0 + 64 * u;
+    const bool receives = u < per && i < n && !absorbed[u];
+    const uint64_t mask = __ballot(receives);
+    if (receives) {
+      const int rpos = rbase + __popcll(mask & ((1ull << lane) - 1));
       st_(nxt, i, rpos);
       keep_idx[(size_t)unit * capacity + rpos] = i;
-      ++rpos;
     }
+    rbase += __popcll(mask);
   }
   for (int r = n_recv + tid; r < capacity; r += kGroupThreads) keep_idx[(size_t)unit * capacity + r] = -1;
   sync();
@@ -745,7 +761,7 @@ __global__ __launch_bounds__(kGroupThreads) void prefill_group_kernel(
   int* tmp = nxt;                                 // the receiver numbers are in registers now: members in arrival order
 #pragma unroll
   for (int u = 0; u < kPfItems; ++u)
-    if (absorbed[u]) st_(tmp, atomicAdd(&cnt[pos[u]], 1), i0 + u);
+    if (absorbed[u]) st_(tmp, atomicAdd(&cnt[pos[u]], 1), i0 + 64 * u);
   sync();                                // cnt[r] is now the end of group r
   int32_t* mem = members + (size_t)unit * capacity;
 #pragma unroll
@@ -753,8 +769,8 @@ __global__ __launch_bounds__(kGroupThreads) void prefill_group_kernel(
     if (!absorbed[u]) continue;
     const int g0 = pos[u] > 0 ? ld(cnt, pos[u] - 1) : 0, g1 = ld(cnt, pos[u]);
     int rank = 0;
-    for (int m = g0; m < g1; ++m) rank += ld(tmp, m) < i0 + u;
-    mem[g0 + rank] = i0 + u;
+    for (int m = g0; m < g1; ++m) rank += ld(tmp, m) < i0 + 64 * u;
+    mem[g0 + rank] = i0 + 64 * u;
   }
 }
 
