@@ -42,7 +42,24 @@ constexpr unsigned kResidentWorkgroups = 256;           // of the first event's 
 constexpr int kXcds = 8;                                // accelerator dies, each with its own L2
 
 // ---------------------------------------------------------------------------------------------------
-// 1/|k_c| (f32) of every retained key; 0 for padding and for zero keys.  With `panel`, the retained keys are
+// The f32 similarities are good to their margin while both |k|^2 lie in this range: above it sums of squares and
+// products come near the end of the f32 range, below it a product's terms may fall under 2^-126 (at most 128 of them,
+// 2^-119 against |k_e||k_c| >= 2^-80, a relative 2^-39).  A row outside it is evaluated in f64 against every column, a
+// column outside it makes every row that sees it do so (1/|k_c| is NaN then; zero keys match nothing and have 0).
+constexpr float kNormLeast = 0x1p-80f, kNormMost = 0x1p100f;
+__device__ __forceinline__ bool norm_in_range(float ss) { return ss >= kNormLeast && ss <= kNormMost; }   // (NaN: no)
+// 1/|k_c| of a column from |k_c|^2; nonzero: some element of the key is not 0
+__device__ __forceinline__ float column_rnorm(float ss, bool nonzero) {
+  return norm_in_range(ss) ? 1.0f / sqrtf(ss) : (nonzero ? __builtin_nanf("") : 0.f);
+}
+// Whether some element of the row of LPS lanes is not 0; x: this lane's 16 bytes.
+template <typename T, int LPS>
+__device__ __forceinline__ bool row_nonzero(const uint4& x) {
+  const uint32_t magnitudes = sizeof(T) == 2 ? 0x7FFF7FFFu : 0x7FFFFFFFu;
+  return group_sum<LPS>(((x.x | x.y | x.z | x.w) & magnitudes) != 0 ? 1.f : 0.f) > 0.f;
+}
+
+// 1/|k_c| (f32) of every retained key; 0 for padding and for zero keys, NaN where f32 cannot hold the norm.  With `panel`, the retained keys are
 // also copied there in list order, rn_pitch rows per head (padding rows zero), each row with its 16-byte
 // chunk c stored at position c ^ (row mod chunks): the LDS image that the first event's kernel wants, so
 // that its stage loads are straight copies that need no slot index.
@@ -91,7 +108,8 @@ __global__ __launch_bounds__(256) void rnorm_kernel(const T* __restrict__ k, con
     ss = group_sum<LPS>(ss);
     // positions budget .. rn_pitch - 1 are padding: zero, so padded columns score 0; so do zero keys and
     // negative slot numbers
-    if (sub == 0) rnorm[(size_t)unit * rn_pitch + r[i]] = ss > 0.f ? 1.0f / sqrtf(ss) : 0.f;
+    const bool nonzero = norm_in_range(ss) || row_nonzero<T, LPS>(x[i]);   // (whole lane groups)
+    if (sub == 0) rnorm[(size_t)unit * rn_pitch + r[i]] = column_rnorm(ss, nonzero);
   }
 }
 
@@ -160,9 +178,9 @@ __device__ __forceinline__ void decide_row(const MatchParams& p, int unit, int j
 __device__ __forceinline__ bool decide_row_f32(const MatchParams& p, size_t o, float y1, int c1, float y2, float ss, int n_cols) {
   const float rn_e = 1.0f / sqrtf(ss);
   const float cos1 = y1 * rn_e;
-  bool fragile = !(y1 > 0.f) || !(ss > 0.f) || !(rn_e < INFINITY) || !((y1 - y2) * rn_e > p.delta) ||
-                 !(fabsf(cos1 - p.threshold) > p.delta) || c1 >= n_cols;
+  bool fragile = !(y1 > 0.f) || !((y1 - y2) * rn_e > p.delta) || !(fabsf(cos1 - p.threshold) > p.delta) || c1 >= n_cols;
   if (surely_below(p, (y1 <= 0.f) ? 0.f : cos1, ss, rn_e)) fragile = false;
+  if (!norm_in_range(ss)) fragile = true;
   p.match[o] = (cos1 > p.threshold) ? c1 : -1;
   if (p.sim_out != nullptr) p.sim_out[o] = cos1;
   return fragile;
@@ -172,9 +190,10 @@ __device__ __forceinline__ bool decide_row_f32(const MatchParams& p, size_t o, f
 // class has an f32 best within the margin of the row's best (the rule by which a row without a close runner-up is
 // decided, a little wider for the rounding of `lim`).  cls: this lane's 16 classes, columns 8 (i / 4) + 4 half + i % 4
 // of every block; the lanes l and l ^ 32 hold the two halves.  A row of a few hundred columns has two or three candidate
-// classes as a rule, so the f64 kernel has a tenth of its columns or less to look at.  NaN: all columns.
+// classes as a rule, so the f64 kernel has a tenth of its columns or less to look at.  A norm out of range or a NaN: all
+// columns.
 __device__ __forceinline__ uint32_t candidate_columns(const MatchParams& p, const int (&cls)[16], float y1, float ss, int half) {
-  const float lim = y1 - 1.01f * p.delta * sqrtf(ss);
+  const float lim = norm_in_range(ss) ? y1 - 1.01f * p.delta * sqrtf(ss) : -INFINITY;
   uint32_t m = 0;
 #pragma unroll
   for (int i = 0; i < 16; ++i)
@@ -960,7 +979,7 @@ __global__ __launch_bounds__(256) void match_exact_kernel(MatchParams p) {
 // ---------------------------------------------------------------------------------------------------
 // Merge-first prefill pass (App. B.4): for every live slot its most similar EARLIER key, by the first event's kernel in
 // its causal mode.
-// 1/|k_i| (f32) of every live slot; 0 for zero keys and beyond len
+// 1/|k_i| (f32) of every live slot; 0 for zero keys and beyond len, NaN where f32 cannot hold the norm
 template <typename T, int D>
 __global__ __launch_bounds__(256) void slot_rnorm_kernel(const T* __restrict__ k, const int32_t* __restrict__ len,
                                                          float* __restrict__ rn, int capacity) {
@@ -970,8 +989,9 @@ __global__ __launch_bounds__(256) void slot_rnorm_kernel(const T* __restrict__ k
   const int n = len[unit];
   if (r >= capacity) return;
   float ss = 0.f;
+  uint4 x = make_uint4(0, 0, 0, 0);
   if (r < n) {
-    const uint4 x = reinterpret_cast<const uint4*>(k)[((size_t)unit * capacity + r) * LPS + sub];
+    x = reinterpret_cast<const uint4*>(k)[((size_t)unit * capacity + r) * LPS + sub];
     if constexpr (sizeof(T) == 2) {
       const uint32_t w[4] = {x.x, x.y, x.z, x.w};
 #pragma unroll
@@ -988,7 +1008,8 @@ __global__ __launch_bounds__(256) void slot_rnorm_kernel(const T* __restrict__ k
     }
   }
   ss = group_sum<LPS>(ss);
-  if (sub == 0) rn[(size_t)unit * capacity + r] = ss > 0.f ? 1.0f / sqrtf(ss) : 0.f;
+  const bool nonzero = norm_in_range(ss) || row_nonzero<T, LPS>(x);   // (whole lane groups)
+  if (sub == 0) rn[(size_t)unit * capacity + r] = column_rnorm(ss, nonzero);
 }
 
 // queue every live row but the first (f32 caches: the f64 kernel decides all rows)

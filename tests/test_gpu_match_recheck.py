@@ -108,3 +108,48 @@ def test_causal_search_at_block_edges(head_dim, batch, lengths):
     for (b, h), r in ref.items():
         np.testing.assert_array_equal(got[b, h, :lens[b, h]], r)
         assert (got[b, h, lens[b, h]:] == -9).all()
+
+
+@pytest.mark.parametrize("head_dim", [64, 128])
+@pytest.mark.parametrize("budget,n_ev", [(820, 700), (129, 300)])
+@pytest.mark.parametrize("scaled", ["rows", "rows, large", "a column", "a column, large", "the best columns"])
+def test_norms_beyond_f32(head_dim, budget, n_ev, scaled):
+    """Keys whose |k|^2 is below or above the f32 range (elements near 2^-80 or 2^70) beside a dozen near-duplicate
+    columns in different classes: the f32 values decide nothing there, targets are those of an f64 evaluation."""
+    kk = U.kk()
+    g = np.random.default_rng(budget + head_dim + len(scaled))
+    cap = budget + n_ev
+    w = W.CONFIGS["llama3_8b"].scaled(batch=1, n_q_heads=8, n_kv_heads=2, head_dim=head_dim, context=cap)
+    K = W.round_bf16(g.standard_normal((1, 2, cap, head_dim)))
+    for h in range(2):
+        for at, c in enumerate(g.choice(budget, 12, replace=False)):      # one centre, one bf16 step here and there
+            K[0, h, c] = _nudge(K[0, h, 0], g) if at else K[0, h, 0]
+        for j in range(budget, cap, 2):
+            K[0, h, j] = W.round_bf16(K[0, h, 0] + 0.1 * g.standard_normal(head_dim))
+        scale = 2.0 ** 70 if "large" in scaled else 2.0 ** -80
+        if scaled.startswith("rows"):
+            K[0, h, budget:] *= scale
+        elif scaled.startswith("a column"):
+            K[0, h, budget // 3] = K[0, h, 0] * scale
+        else:
+            K[0, h, [5, budget - 1]] = W.round_bf16(K[0, h, 0] * 3.0) * np.array([[2.0 ** -80], [2.0 ** 70]])
+    lay, c = U.new_cache(w, capacity=cap, K=K, V=np.zeros_like(K))
+    np.testing.assert_array_equal(U.to_host(c.k).astype(np.float64), K)   # powers of two: representable as they are
+    ws = U.workspace(lay, cap, budget)
+    keep = torch.arange(budget, dtype=torch.int32, device="cuda").repeat(1, 2, 1).contiguous()
+    evict = torch.arange(budget, cap, dtype=torch.int32, device="cuda").repeat(1, 2, 1).contiguous()
+    n_evict = torch.full((1, 2), n_ev, dtype=torch.int32, device="cuda")
+    T = U.f32(0.3)
+    for want_sim in (True, False):
+        match = torch.full((1, 2, n_ev), -9, dtype=torch.int32, device="cuda")
+        kk.match(lay, c, budget, keep, evict, n_evict, T, match, torch.zeros(1, 2, n_ev, device="cuda") if want_sim else None, ws)
+        torch.cuda.synchronize()
+        for h in range(2):
+            tgt, _ = O.match(K[0, h].astype(np.float64), np.arange(budget), np.arange(budget, cap), T, exact_any_order=True)
+            np.testing.assert_array_equal(match[0, h].cpu().numpy(), tgt)
+    near = torch.full((1, 2, cap), -9, dtype=torch.int32, device="cuda")
+    kk.prefill_match(lay, c, T, near, None, ws)
+    torch.cuda.synchronize()
+    for h in range(2):
+        ref, _ = O.prefill_nearest_earlier(K[0, h].astype(np.float64), cap, T, exact_any_order=True)
+        np.testing.assert_array_equal(near[0, h].cpu().numpy(), ref)
