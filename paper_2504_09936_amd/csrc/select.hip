@@ -9,7 +9,7 @@
 // in which the threshold lies; slots more than the f32 arithmetic's error away from it are decided, the few others
 // are evaluated in f64 and ranked exactly by counting.  The f64 value is some sixty instructions per slot, which
 // bound the kernel when every slot was given one.  Only when more than kMaxCand slots are undecided
-// (long runs of equal values, values spread over many orders of magnitude), and for longer caches
+// (long runs of equal values, values spread over many orders of magnitude) or a value is NaN, and for longer caches
 // (select_long_kernel), the f64 values of all slots are mapped to order-preserving u64 keys in the workspace and the
 // threshold is found by an 8-bit most-significant-digit radix select (LDS histograms, wavefront scan; digits in
 // which no two keys differ are skipped).
@@ -435,6 +435,7 @@ __global__ __launch_bounds__(kSelThreads, ITEMS <= 8 ? 8 : 4) void select_kernel
   // ---- ranking values in f32, the least and the largest finite one
   float y[ITEMS];
   float vmin = INFINITY, vmax = -INFINITY;
+  bool nan = false;                               // a ranking value is NaN: where it ranks depends on its f64 image
 #pragma unroll
   for (int c0 = 0; c0 < ITEMS; c0 += kLoad) {
     if (c0 < cpw) {                               // uniform over the workgroup
@@ -455,8 +456,8 @@ __global__ __launch_bounds__(kSelThreads, ITEMS <= 8 ? 8 : 4) void select_kernel
           if (p.n_table == kTermTable && __any(cand && cnt >= kTermTable))     // alpha close to 1
             term = cnt >= kTermTable ? logf(-expm1f((float)((double)cnt * p.ln_alpha))) : term;
           x = (lp + x) - term;
-          x = (x == x) ? x : INFINITY;
           x = cnt <= 0 ? -INFINITY : x;
+          nan |= cand && !(x == x);
         }
         y[c0 + u] = x;
         const bool finite = cand && fabsf(x) <= 3.0e38f;
@@ -472,6 +473,7 @@ __global__ __launch_bounds__(kSelThreads, ITEMS <= 8 ? 8 : 4) void select_kernel
     s_min[wave] = vmin;
     s_max[wave] = vmax;
   }
+  if (!EXT && __any(nan)) s_n_cand = kMaxCand + 1;   // (any lane: too many undecided slots, so the radix select)
   __syncthreads();
   KS_TS(1);
 

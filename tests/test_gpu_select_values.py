@@ -55,3 +55,39 @@ def test_select_at_the_threshold(cap, alpha):
             np.testing.assert_array_equal(keep[0, h].cpu().numpy(), rk, err_msg=f"head {h}")
             np.testing.assert_array_equal(evict[0, h, :len(re)].cpu().numpy(), re, err_msg=f"head {h}")
             assert (evict[0, h, len(re):] == -7).all()
+
+
+@pytest.mark.parametrize("cap", [100, 1025, 8192, 20000, 32769])
+def test_nan_scores_rank_by_their_sign(cap):
+    """A NaN score ranks by its f64 image, above +inf or below -inf by its sign, whichever kernel decides: with one
+    vote and alpha^n below half an ulp the ranking value is the score itself."""
+    kk = U.kk()
+    g = np.random.default_rng(cap)
+    H, budget, n_sink, n_recent = 4, cap // 4, 3, cap // 9
+    w = W.CONFIGS["llama3_8b"].scaled(batch=1, n_q_heads=H, n_kv_heads=H, context=cap)
+    lay, c = U.new_cache(w, capacity=cap)
+    ws = U.workspace(lay, cap, budget)
+    log_s = (g.standard_normal((H, cap)) * 3).astype(np.float32)
+    n_high = budget - n_sink - n_recent
+    for h, (pos, neg) in enumerate([(5, 0), (0, 5), (n_high // 2, n_high // 2), (n_high + 7, cap // 8)]):
+        at = g.choice(np.arange(n_sink, cap - n_recent), pos + neg + 4, replace=False)
+        log_s[h, at[:pos]] = np.array([0x7FC00000], np.uint32).view(np.float32)
+        log_s[h, at[pos:pos + neg]] = np.array([0xFFC00000], np.uint32).view(np.float32)
+        log_s[h, at[-4:-2]], log_s[h, at[-2:]] = np.inf, -np.inf
+    c.log_s[:] = torch.from_numpy(log_s[None]).cuda()
+    c.votes[:] = 1
+    U.set_n_obs(c, np.full((1, H, cap), 500))
+    c.len[:] = cap
+    keep = torch.full((1, H, budget), -7, dtype=torch.int32, device="cuda")
+    evict = torch.full((1, H, cap - budget), -7, dtype=torch.int32, device="cuda")
+    n_ev = torch.full((1, H), -7, dtype=torch.int32, device="cuda")
+    kk.select(lay, c, budget, n_sink, n_recent, U.f32(0.9), keep, evict, n_ev, ws)
+    torch.cuda.synchronize()
+    bits = log_s.astype(np.float64).view(np.uint64)
+    image = np.where(bits >> np.uint64(63) != 0, ~bits, bits | np.uint64(1 << 63))        # ascending with the value
+    for h in range(H):
+        mid = np.arange(n_sink, cap - n_recent)
+        heavy = mid[np.lexsort((mid, ~image[h, mid]))][:n_high]
+        rk = np.sort(np.concatenate([np.arange(n_sink), heavy, np.arange(cap - n_recent, cap)]))
+        np.testing.assert_array_equal(keep[0, h].cpu().numpy(), rk, err_msg=f"head {h}")
+        np.testing.assert_array_equal(evict[0, h].cpu().numpy(), np.setdiff1d(np.arange(cap), rk))
