@@ -5,17 +5,21 @@
 // ln p + ln s_hat (f64, equal values at lower indices first) are found and the slots compacted in index order.
 //
 // Up to 32768 slots (select_kernel) the values are formed in f32 and kept in registers, a wavefront a contiguous
-// run of slots.  A histogram over kBins equal intervals between the least and the largest of them gives the interval
+// run of slots.  A histogram over kBins equal intervals of their range (a few outliers left out) gives the interval
 // in which the threshold lies; slots more than the f32 arithmetic's error away from it are decided, the few others
 // are evaluated in f64 and ranked exactly by counting.  The f64 value is some sixty instructions per slot, which
-// bound the kernel when every slot was given one.  Only when more than kMaxCand slots are undecided
-// (long runs of equal values, values spread over many orders of magnitude) or a value is NaN, and for longer caches
+// bound the kernel when every slot was given one.  An interval with more than kRankSoon slots (skewed values, values
+// spread over many orders of magnitude) is split again by the values' integer images, at most three times; a long run of
+// equal values is kept in slot order.  Only when more than kMaxCand slots are so close that f32 cannot tell them apart
+// though they differ, or a value is NaN, and for longer caches
 // (select_long_kernel), the f64 values of all slots are mapped to order-preserving u64 keys in the workspace and the
 // threshold is found by an 8-bit most-significant-digit radix select (LDS histograms, wavefront scan; digits in
 // which no two keys differ are skipped).
 // What bounds it: the latency of its steps (loads, block reduction, histogram, scan, ranking, two compaction sweeps).
-// Measured (MI355X), radix select over all f64 keys before: 8 heads x 32768 slots 69 -> 34 us, 64 x 8192 21 -> 15.6,
-// 1024 x 8192 84 -> 52, 64 x 884 8.2 -> 7.5.
+// Measured (MI355X, graph replays), radix select over all f64 keys / now: 8 heads x 32768 slots 66 / 33.5 us, 64 x 8192
+// 20.1 / 13.4, 64 x 884 8.1 / 7.0.  64 x 8192 by a caller's ranks: normal 16.3 / 10.1, exponential with three huge ones
+// 16.2 / 10.1 (27.5 when all of a crowded interval went to the radix select), all equal 12.3 / 9.9 (25.0), log-normal with
+// sigma 5 16.9 / 12.1 (29.5); 64 x 884: exponential 6.9 / 6.0, log-normal with sigma 5 6.4 / 7.8.
 #include "kk_common.hpp"
 
 namespace kk {
@@ -31,6 +35,9 @@ namespace {
 constexpr int kSelThreads = 1024;
 constexpr int kVotesTable = 256;       // ln p is tabulated for vote counts below this
 constexpr int kTermTable = 2048;       // ln(1 - alpha^n) is tabulated for n below this (alpha up to 0.98 in full)
+
+__device__ __attribute__((noinline)) double log_f64(double x) { return log(x); }
+__device__ __attribute__((noinline)) double log_1m_exp_f64(double t) { return log(-expm1(t)); }
 
 __device__ __forceinline__ uint64_t sortable_u64(double x) {
   x = x + 0.0;  // -0.0 -> +0.0
@@ -134,9 +141,9 @@ __device__ __forceinline__ void select_radix(const SelectParams& p, int unit, in
   // hundreds of instructions: one evaluation per count (n_table of them: beyond, the term rounds to zero)
   // instead of one per slot
   if constexpr (!EXT) {
-    for (int m = tid; m < n_table; m += kSelThreads) s_lnterm[m] = m > 0 ? log(-expm1((double)m * ln_alpha)) : 0.0;
+    for (int m = tid; m < n_table; m += kSelThreads) s_lnterm[m] = m > 0 ? log_1m_exp_f64((double)m * ln_alpha) : 0.0;
     // (the last wavefronts take the votes table: the first ones have the other one's entries)
-    if (tid >= kSelThreads - kVotesTable) s_lnvotes[kSelThreads - 1 - tid] = log((double)(kSelThreads - 1 - tid));
+    if (tid >= kSelThreads - kVotesTable) s_lnvotes[kSelThreads - 1 - tid] = log_f64((double)(kSelThreads - 1 - tid));
     __syncthreads();
   }
   uint64_t* key_g = p.keys + base;
@@ -160,11 +167,11 @@ __device__ __forceinline__ void select_radix(const SelectParams& p, int unit, in
         const double t = (double)nn[u] * ln_alpha;
         x[u] = (double)ls[u];
         const bool small_p = pv[u] >= 1 && pv[u] < kVotesTable;
-        if (__any(valid && !small_p)) x[u] = (small_p ? s_lnvotes[pv[u]] : log((double)pv[u])) + x[u];
+        if (__any(valid && !small_p)) x[u] = (small_p ? s_lnvotes[pv[u]] : log_f64((double)pv[u])) + x[u];
         else x[u] = s_lnvotes[small_p ? pv[u] : 1] + x[u];
         const bool need = t > -40.0, listed = nn[u] > 0 && nn[u] < n_table;
         double term = (need && listed) ? s_lnterm[nn[u]] : 0.0;
-        if (__any(valid && need && !listed)) term = (need && !listed) ? log(-expm1(t)) : term;   // alpha close to 1
+        if (__any(valid && need && !listed)) term = (need && !listed) ? log_1m_exp_f64(t) : term;   // alpha close to 1
         x[u] -= term;
       }
 #pragma unroll
@@ -356,9 +363,23 @@ __global__ __launch_bounds__(kSelThreads) void select_long_kernel(SelectParams p
 }
 
 // ---------------------------------------------------------------------------------------------------
-constexpr int kBins = 2048;
-constexpr int kMaxCand = 256;          // undecided slots that are ranked by counting
+constexpr int kBinBits = 11, kBins = 1 << kBinBits;
+constexpr int kMaxCand = 256;          // undecided slots that are ranked by counting, at most
+constexpr int kRankSoon = 128;         // up to this many rather than splitting their interval again
 
+// over the 16 lanes of equal number modulo 4; over the four lanes of a quad
+template <typename F>
+__device__ __forceinline__ float class_reduce(float x, F f) {
+  x = f(x, dpp_f32<0x124>(x));   // row_ror:4
+  x = f(x, dpp_f32<0x128>(x));   // row_ror:8
+  x = f(x, __shfl_xor(x, 16));
+  return f(x, __shfl_xor(x, 32));
+}
+template <typename F>
+__device__ __forceinline__ float quad_reduce(float x, F f) {
+  x = f(x, dpp_f32<0xB1>(x));
+  return f(x, dpp_f32<0x4E>(x));
+}
 template <typename F>
 __device__ __forceinline__ float wave_reduce_f32(float x, F f) {
   x = f(x, dpp_f32<0xB1>(x));
@@ -369,6 +390,21 @@ __device__ __forceinline__ float wave_reduce_f32(float x, F f) {
   return f(x, __shfl_xor(x, 32));
 }
 
+template <typename F>
+__device__ __forceinline__ uint32_t wave_reduce_u32(uint32_t x, F f) {
+  return (uint32_t)__builtin_bit_cast(int, wave_reduce_f32(__builtin_bit_cast(float, x), [&](float a, float b) {
+    return __builtin_bit_cast(float, f(__builtin_bit_cast(uint32_t, a), __builtin_bit_cast(uint32_t, b)));
+  }));
+}
+// order-preserving integer image of an f32 value (both zeros the same), and back
+__device__ __forceinline__ uint32_t sortable_u32(float x) {
+  const uint32_t u = __builtin_bit_cast(uint32_t, x == 0.f ? 0.f : x);
+  return (u >> 31) != 0 ? ~u : u | 0x80000000u;
+}
+__device__ __forceinline__ float from_sortable_u32(uint32_t u) {
+  return __builtin_bit_cast(float, (u >> 31) != 0 ? u & 0x7FFFFFFFu : ~u);
+}
+
 // ITEMS: chunks of 64 slots per wavefront that the registers hold; chunk c of wavefront w is the slots
 // (w * cpw + c) * 64 + lane, cpw = ceil(capacity / 1024) <= ITEMS.
 template <bool EXT, bool AGED, int ITEMS>
@@ -377,12 +413,13 @@ __global__ __launch_bounds__(kSelThreads, ITEMS <= 8 ? 8 : 4) void select_kernel
   __shared__ float s_term[EXT ? 1 : kTermTable];
   __shared__ float s_lnp[EXT ? 1 : kVotesTable];
   __shared__ int s_hist[kBins];
-  __shared__ uint64_t s_cand[kMaxCand];
+  __shared__ double s_cand[kMaxCand];
   __shared__ int s_cand_i[kMaxCand];
   __shared__ unsigned long long s_bits[ITEMS * kWaves];    // undecided slots that are kept, by chunk
-  __shared__ float s_min[kWaves], s_max[kWaves];
+  __shared__ float s_min[kWaves * 4], s_max[kWaves * 4];
+  __shared__ uint32_t s_umin[kWaves], s_umax[kWaves];
   __shared__ int s_wave[kWaves], s_above[kWaves];
-  __shared__ int s_bin, s_n_cand;
+  __shared__ int s_bin, s_count, s_need, s_n_cand, s_n_again, s_nan, s_ref;
 
   const int unit = blockIdx.x;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -422,7 +459,7 @@ __global__ __launch_bounds__(kSelThreads, ITEMS <= 8 ? 8 : 4) void select_kernel
   }
   for (int b = tid; b < kBins; b += kSelThreads) s_hist[b] = 0;
   for (int w = tid; w < ITEMS * kWaves; w += kSelThreads) s_bits[w] = 0;
-  if (tid == 0) s_n_cand = 0;
+  if (tid == 0) s_n_cand = s_n_again = s_nan = 0;
   if (n <= budget) {                              // uniform over the workgroup
     select_nothing<AGED>(p, unit, n);
     return;
@@ -433,7 +470,7 @@ __global__ __launch_bounds__(kSelThreads, ITEMS <= 8 ? 8 : 4) void select_kernel
   const int n_heavy = budget - p.n_sink - p.n_recent;
 
   // ---- ranking values in f32, the least and the largest finite one
-  float y[ITEMS];
+  float y[ITEMS] = {};
   float vmin = INFINITY, vmax = -INFINITY;
   bool nan = false;                               // a ranking value is NaN: where it ranks depends on its f64 image
 #pragma unroll
@@ -467,97 +504,270 @@ __global__ __launch_bounds__(kSelThreads, ITEMS <= 8 ? 8 : 4) void select_kernel
       if (c0 + kLoad < ITEMS && c0 + kLoad < cpw) request(c0 + kLoad);
     }
   }
-  vmin = wave_reduce_f32(vmin, [](float a, float b) { return fminf(a, b); });
-  vmax = wave_reduce_f32(vmax, [](float a, float b) { return fmaxf(a, b); });
-  if (lane == 0) {
-    s_min[wave] = vmin;
-    s_max[wave] = vmax;
+  // by classes of equal slot number modulo 4
+  auto least = [](float a, float b) { return fminf(a, b); };
+  auto largest = [](float a, float b) { return fmaxf(a, b); };
+  vmin = class_reduce(vmin, least);
+  vmax = class_reduce(vmax, largest);
+  if (lane < 4) {
+    s_min[wave * 4 + lane] = vmin;
+    s_max[wave * 4 + lane] = vmax;
   }
-  if (!EXT && __any(nan)) s_n_cand = kMaxCand + 1;   // (any lane: too many undecided slots, so the radix select)
+  if (!EXT && __any(nan)) s_nan = 1;              // (any lane)
   __syncthreads();
   KS_TS(1);
 
-  // y becomes the interval coordinate t = (value - vmin) * scale; slots that are kept whatever they rank get +inf,
-  // slots beyond the length NaN
-  constexpr float kTop = 1e30f;                   // above every coordinate, below infinity
-  float t_lo = kTop, t_hi = kTop;                 // kept: t > t_hi; undecided: t_lo <= t <= t_hi
-  {
-#pragma unroll
-    for (int w = 0; w < kWaves; ++w) {
-      vmin = fminf(vmin, s_min[w]);
-      vmax = fmaxf(vmax, s_max[w]);
-    }
-    const float range = vmax - vmin;
-    const float scale = range > 1e-30f && range < 3.0e38f ? (float)kBins / range : 0.f;
-#pragma unroll
-    for (int c = 0; c < ITEMS; ++c) {
-      const int i = c < cpw ? first + 64 * c : n;
-      const bool cand = i >= lo && i < hi;
-      float t = fminf((y[c] - vmin) * scale, 0.5f * kTop);               // (a NaN, infinity times a zero scale, becomes large too)
-      if (cand && n_heavy > 0) atomicAdd(&s_hist[t >= (float)kBins ? kBins - 1 : (t > 0.f ? (int)t : 0)], 1);
-      y[c] = i >= n ? NAN : (cand ? t : INFINITY);
-    }
-    __syncthreads();
-    KS_TS(2);
-    if (n_heavy > 0) {                            // uniform
-      // suffix scan: the boundary interval is the one in which the running count from the top reaches n_heavy
-      constexpr int kPer = kBins / kSelThreads;
-      int cnt[kPer], sum = 0;
-#pragma unroll
-      for (int j = 0; j < kPer; ++j) {            // thread 0 has the top intervals
-        cnt[j] = s_hist[kBins - 1 - (tid * kPer + j)];
-        sum += cnt[j];
-      }
-      const int incl = wave_incl_scan(sum);
-      if (lane == 63) s_wave[wave] = incl;
-      __syncthreads();
-      int before = incl - sum;
-#pragma unroll
-      for (int w = 0; w < kWaves; ++w) before += w < wave ? s_wave[w] : 0;
-#pragma unroll
-      for (int j = 0; j < kPer; ++j) {
-        if (before < n_heavy && before + cnt[j] >= n_heavy) s_bin = kBins - 1 - (tid * kPer + j);   // exactly one
-        before += cnt[j];
-      }
-      __syncthreads();
-      KS_TS(3);
-      const int bin = s_bin;
-      // The f32 values carry the roundings of two sums and of two logarithms whose magnitudes (at most 22 and 24) do not
-      // show in the sum: within (largest magnitude + 64) * 2^-21 of the f64 values, and the coordinate its own two
-      // roundings (below 1e-3 intervals).  With e that bound in intervals, the f64 threshold lies within e of the boundary
-      // interval (counting the f32 values from either side), so a slot 2 e outside is decided.  The outermost intervals also
-      // hold the infinite values.
-      const float mag = fmaxf(fabsf(vmin), fabsf(vmax));
-      const float e2 = EXT ? 0.f : 2.f * ((mag + 64.f) * 4.8e-7f * scale + 1e-3f);
-      t_lo = bin == 0 || scale == 0.f ? -INFINITY : (float)bin - e2;
-      t_hi = bin == kBins - 1 || scale == 0.f ? kTop : (float)(bin + 1) + e2;
-      if (EXT && t_hi < kTop) t_hi = __builtin_bit_cast(float, __builtin_bit_cast(int, t_hi) - 1);   // below bin + 1
-    }
-  }
-  int above = 0;                                  // candidates that are kept without looking further
+  // What is the same in all lanes goes through a scalar register: the branches below hold barriers and ballots, and are to be
+  // branches of the whole wavefront in the compiler's eyes too (it moved register copies of an outer branch under the lane
+  // mask of an inner one otherwise).
+  auto uniform = [](int x) { return __builtin_amdgcn_readfirstlane(x); };
+  auto uniform_f = [&](float x) { return __builtin_bit_cast(float, uniform(__builtin_bit_cast(int, x))); };
+  // bit c: slot first + 64 c is a candidate / is kept / is undecided
+  uint32_t cand = 0, keep = 0, und = 0;
 #pragma unroll
   for (int c = 0; c < ITEMS; ++c) {
-    above += __popcll(__ballot(y[c] > t_hi && y[c] < kTop));
-    if (y[c] >= t_lo && y[c] <= t_hi) {
-      const int at = atomicAdd(&s_n_cand, 1);
-      if (at < kMaxCand) s_cand_i[at] = first + 64 * c;
+    const int i = c < cpw ? first + 64 * c : n;
+    if (i >= lo && i < hi) cand |= 1u << c;
+    else if (i < n) keep |= 1u << c;
+  }
+  bool radix = !EXT && uniform(s_nan) != 0;       // left to the radix select
+  const uint32_t keep_always = keep;
+  // Adds the slots of `set` to the histogram.  Where many lanes of the wavefront's first chunk share an interval, the lanes
+  // that agree with the first one add their count once in every chunk: adds to one LDS word are served a lane at a time.
+  auto add_to_histogram = [&](uint32_t set, auto bin_of) {
+    bool crowded = false;
+#pragma unroll
+    for (int c = 0; c < ITEMS; ++c) {
+      if (c < cpw) {                              // uniform
+        const bool in = (set >> c) & 1;
+        const int b = bin_of(c);
+        if (c == 0 || crowded) {                  // uniform
+          const uint64_t act = __ballot(in);
+          const int leader = act != 0 ? __ffsll((long long)act) - 1 : 0;
+          const int b0 = __builtin_amdgcn_readlane(b, leader);
+          const uint64_t same = __ballot(in && b == b0);
+          if (c == 0) crowded = __popcll(same) >= 16;
+          if (in && b != b0) atomicAdd(&s_hist[b], 1);
+          if (act != 0 && lane == leader) atomicAdd(&s_hist[b0], __popcll(same));
+        } else if (in) {
+          atomicAdd(&s_hist[b], 1);
+        }
+      }
+    }
+  };
+  // The boundary interval: the one in which the running count from the top reaches `need`; s_bin, its slots (s_count) and how many
+  // of them are needed (s_need).
+  auto find_boundary = [&](int need) {
+    constexpr int kPer = kBins / kSelThreads;
+    int cnt[kPer], sum = 0;
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) {              // thread 0 has the top intervals
+      cnt[j] = s_hist[kBins - 1 - (tid * kPer + j)];
+      s_hist[kBins - 1 - (tid * kPer + j)] = 0;   // for the next histogram
+      sum += cnt[j];
+    }
+    const int incl = wave_incl_scan(sum);
+    if (lane == 63) s_wave[wave] = incl;
+    __syncthreads();
+    int before = incl - sum;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) before += w < wave ? s_wave[w] : 0;
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) {
+      if (before < need && before + cnt[j] >= need) {   // exactly one
+        s_bin = kBins - 1 - (tid * kPer + j);
+        s_count = cnt[j];
+        s_need = need - before;
+      }
+      before += cnt[j];
+    }
+    __syncthreads();
+  };
+  auto list_undecided = [&](int& count) {
+#pragma unroll
+    for (int c = 0; c < ITEMS; ++c)
+      if ((und >> c) & 1) {
+        const int at = atomicAdd(&count, 1);
+        if (at < kMaxCand) s_cand_i[at] = first + 64 * c;
+      }
+  };
+
+  int m = 0;                                      // slots left to rank
+  if (n_heavy > 0 && !radix) {                    // uniform
+    // The histogram's range: from the largest of the four classes' least values to the least of their largest ones.  A few
+    // outliers, which leave some class without one, do not stretch it; a handful of slots lies outside, in the end intervals.
+    static_assert(kWaves * 4 == 64, "one value a lane");
+    vmin = quad_reduce(class_reduce(s_min[lane], least), largest);
+    vmax = quad_reduce(class_reduce(s_max[lane], largest), least);
+    vmin = uniform_f(vmin);
+    vmax = uniform_f(vmax);
+    const float range = vmax - vmin;
+    const float scale = range > 1e-30f && range < 3.0e38f ? (float)kBins / range : 0.f;   // 0: no such range
+    auto coordinate = [&](float x) { return (x - vmin) * scale; };
+    auto interval = [&](float x) {                // (the outermost ones also hold the values outside)
+      const float t = coordinate(x);
+      return t >= (float)kBins ? kBins - 1 : (t > 0.f ? (int)t : 0);
+    };
+    bool fine = scale == 0.f;                     // the equal intervals are too coarse
+    if (!fine) {
+      add_to_histogram(cand, [&](int c) { return interval(y[c]); });
+      __syncthreads();
+      KS_TS(2);
+      find_boundary(n_heavy);
+      KS_TS(3);
+      fine = uniform(s_count) > kRankSoon;
+    }
+    if (!fine) {
+      const int bin = uniform(s_bin);
+      // The f32 values carry the roundings of two sums and of two logarithms whose magnitudes (at most 22 and 24) do not
+      // show in the sum: within (magnitude + 64) * 2^-21 of the f64 values, and the coordinate its own two
+      // roundings (below 1e-3 intervals).  With e that bound in intervals at the magnitude of the range's ends, the f64 threshold
+      // lies within e of the boundary interval (counting the f32 values from either side), so a slot 2 e outside is decided
+      // (one of larger magnitude too: its distance grows with it, the bound 2^21 times slower).
+      const float mag = fmaxf(fabsf(vmin), fabsf(vmax));
+      const float e2 = EXT ? 0.f : 2.f * ((mag + 64.f) * 4.8e-7f * scale + 1e-3f);
+      const float t_lo = bin == 0 ? -INFINITY : (float)bin - e2;
+      float t_hi = bin == kBins - 1 ? INFINITY : (float)(bin + 1) + e2;
+      if (EXT && bin != kBins - 1) t_hi = __builtin_bit_cast(float, __builtin_bit_cast(int, t_hi) - 1);   // below bin + 1
+#pragma unroll
+      for (int c = 0; c < ITEMS; ++c) {
+        const float t = coordinate(y[c]);
+        const uint32_t bit = cand & (1u << c);
+        keep |= t > t_hi ? bit : 0u;
+        und |= t >= t_lo && t <= t_hi ? bit : 0u;
+      }
+      list_undecided(s_n_cand);
+      const int n_above = wave_incl_scan(__popc(keep & cand));
+      if (lane == 63) s_above[wave] = n_above;
+      __syncthreads();
+      m = uniform(s_n_cand);
+      fine = m > kRankSoon;                       // (the f32 error reaches into crowded neighbours)
+    }
+    if (__builtin_expect(fine, 0)) {              // uniform
+      // The boundary interval is split again, into equal intervals of the values' order-preserving integer images between
+      // the least and the largest in it, until few slots or equal values are left: three times at most.
+      int need = n_heavy, left = n;
+      uint32_t u_lo = 0xFFFFFFFFu, u_hi = 0;
+      const int bin0 = uniform(s_bin);
+      if (scale != 0.f) {
+        need = uniform(s_need);
+        left = uniform(s_count);
+      }
+      uint32_t image[ITEMS];
+#pragma unroll
+      for (int c = 0; c < ITEMS; ++c) {
+        image[c] = sortable_u32(y[c]);
+        if (((cand >> c) & 1) && (scale == 0.f || interval(y[c]) == bin0)) {
+          u_lo = min(u_lo, image[c]);
+          u_hi = max(u_hi, image[c]);
+        }
+      }
+      u_lo = wave_reduce_u32(u_lo, [](uint32_t a, uint32_t b) { return a < b ? a : b; });
+      u_hi = wave_reduce_u32(u_hi, [](uint32_t a, uint32_t b) { return a > b ? a : b; });
+      if (lane == 0) {
+        s_umin[wave] = u_lo;
+        s_umax[wave] = u_hi;
+      }
+      __syncthreads();
+#pragma unroll
+      for (int w = 0; w < kWaves; ++w) {
+        u_lo = min(u_lo, s_umin[w]);
+        u_hi = max(u_hi, s_umax[w]);
+      }
+      u_lo = (uint32_t)uniform((int)u_lo);
+      u_hi = (uint32_t)uniform((int)u_hi);
+      while (u_lo != u_hi && left > (EXT ? kRankSoon : kRankSoon / 2)) {   // uniform (not EXT: room for neighbours)
+        const int bits = 32 - __clz((int)(u_hi - u_lo)), shift = bits > kBinBits ? bits - kBinBits : 0;
+        uint32_t in = 0;
+#pragma unroll
+        for (int c = 0; c < ITEMS; ++c) in |= image[c] - u_lo <= u_hi - u_lo ? cand & (1u << c) : 0u;
+        add_to_histogram(in, [&](int c) { return (int)((image[c] - u_lo) >> shift); });
+        __syncthreads();
+        find_boundary(need);
+        need = uniform(s_need);
+        left = uniform(s_count);
+        u_lo += (uint32_t)uniform(s_bin) << shift;
+        u_hi = min(u_hi, u_lo + ((1u << shift) - 1u));
+      }
+      // kept: above the interval; undecided: in it, or within the f32 error of it (as above, with the magnitude there)
+      keep = keep_always;
+      und = 0;
+      const bool run = u_lo == u_hi;
+      bool equal = run;                           // the undecided values are equal in f64 too
+      if constexpr (!EXT) {
+        float y_lo = from_sortable_u32(u_lo), y_hi = from_sortable_u32(u_hi);
+        const bool fin_lo = fabsf(y_lo) < INFINITY, fin_hi = fabsf(y_hi) < INFINITY;
+        const float mag = fmaxf(fin_lo ? fabsf(y_lo) : 0.f, fin_hi ? fabsf(y_hi) : 0.f);
+        const float e2 = 2.02f * 4.8e-7f * (mag + 64.f);
+        equal = run && !fin_lo;
+        u_lo = sortable_u32(fin_lo ? y_lo - e2 : y_lo);
+        u_hi = sortable_u32(fin_hi ? y_hi + e2 : y_hi);
+      }
+#pragma unroll
+      for (int c = 0; c < ITEMS; ++c) {
+        const uint32_t bit = cand & (1u << c);
+        keep |= image[c] > u_hi ? bit : 0u;
+        und |= image[c] >= u_lo && image[c] <= u_hi ? bit : 0u;
+      }
+      const int n_und = wave_incl_scan(__popc(und)), n_above = wave_incl_scan(__popc(keep & cand));
+      if (lane == 63) {
+        s_wave[wave] = n_und;
+        s_above[wave] = n_above;
+      }
+      if (!equal) list_undecided(s_n_again);
+      __syncthreads();
+      m = uniform(s_n_again);
+      if (equal || run || m > kMaxCand) {         // uniform
+        // Equal values, or a run that may be one (the same score, votes and count in all slots): the first ones in slot order.
+        bool same = true;
+        if (!equal) {                             // uniform
+          if (und != 0) s_ref = first + 64 * (__ffs((int)und) - 1);   // any of them
+          __syncthreads();
+          const size_t ref = base + slot_of(s_ref);
+          const int ls_r = __builtin_bit_cast(int, p.log_s[ref]), pv_r = p.votes[ref], born_r = p.born[ref];
+          int differs = 0;
+#pragma unroll 1
+          for (int c0 = 0; c0 < cpw; c0 += 4)     // (four slots a round trip; not listed: the reference again)
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+              const int i = c0 + u < ITEMS && ((und >> (c0 + u)) & 1) ? first + 64 * (c0 + u) : s_ref;
+              const size_t at = base + slot_of(i);
+              differs |= (__builtin_bit_cast(int, p.log_s[at]) ^ ls_r) | (p.votes[at] ^ pv_r) | (p.born[at] ^ born_r);
+            }
+          same = uniform(__syncthreads_or(differs)) == 0;
+        }
+        if (same) {                               // uniform
+          int before = 0, want = n_heavy;
+#pragma unroll
+          for (int w = 0; w < kWaves; ++w) {
+            before += w < wave ? s_wave[w] : 0;
+            want -= s_above[w];
+          }
+#pragma unroll
+          for (int c = 0; c < ITEMS; ++c)
+            if (c < cpw) {                        // uniform
+              const uint64_t mask = __ballot((und >> c) & 1);
+              if (((und >> c) & 1) && before + rank_in_wave(mask) < want) keep |= 1u << c;
+              before += __popcll(mask);
+            }
+          m = 0;
+          __syncthreads();                        // s_wave has been read
+        } else {
+          radix = m > kMaxCand;
+        }
+      }
     }
   }
-  if (lane == 0) s_above[wave] = above;
-  __syncthreads();
-  const int m = s_n_cand;
-  if (m > kMaxCand) {                             // uniform over the workgroup
+  if (__builtin_expect(radix, 0)) {               // uniform
     select_radix<EXT, AGED>(p, unit, n);
     return;
   }
-  if (m > 0) {
-    int need = n_heavy;                           // how many of the undecided are kept
+  if (m > 0) {                                    // uniform: the listed slots' f64 values, ranked by counting
+    int need = n_heavy;                           // how many of them are kept
 #pragma unroll
     for (int w = 0; w < kWaves; ++w) need -= s_above[w];
-    uint64_t k = 0;
-    int i = 0;
-    if (tid < m) {                                // their f64 values
-      i = s_cand_i[tid];
+    if (tid < m) {
+      const int i = s_cand_i[tid];
       const size_t at = base + slot_of(i);
       double x = (double)p.log_s[at];
       if constexpr (EXT) {
@@ -567,29 +777,40 @@ __global__ __launch_bounds__(kSelThreads, ITEMS <= 8 ? 8 : 4) void select_kernel
         const double t = (double)cnt * p.ln_alpha;
         const int pv_i = p.votes[at];
         // (ln 1 = 0; and with t <= -40 alpha^n is below half an ulp of 1 and the term is 0)
-        const double lp = pv_i == 1 ? 0.0 : log((double)pv_i);
-        const double term = t > -40.0 ? log(-expm1(t)) : 0.0;
+        const double lp = pv_i == 1 ? 0.0 : log_f64((double)pv_i);
+        const double term = t > -40.0 ? log_1m_exp_f64(t) : 0.0;
         x = (lp + x) - term;
         if (cnt <= 0) x = -INFINITY;
       }
-      k = sortable_u64(x);
-      s_cand[tid] = k;
+      s_cand[tid] = x;
     }
     __syncthreads();
-    if (tid < m) {
-      int rank = 0;                               // larger keys, and equal ones at lower indices
-      for (int j = 0; j < m; ++j) {
-        const uint64_t kj = s_cand[j];
-        rank += kj > k || (kj == k && s_cand_i[j] < i);
+    if (tid < 4 * m) {                            // four lanes a slot
+      const int at = tid >> 2;
+      const double k = s_cand[at];
+      const int i = s_cand_i[at];
+      int rank = 0;                               // larger values, and equal ones at lower indices
+      for (int j0 = tid & 3; j0 < m; j0 += 16) {  // four of the others a round trip
+        double kj[4];
+        int ij[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          kj[u] = s_cand[min(j0 + 4 * u, m - 1)];
+          ij[u] = s_cand_i[min(j0 + 4 * u, m - 1)];
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) rank += (j0 + 4 * u < m) & ((kj[u] > k) | ((kj[u] == k) & (ij[u] < i)));
       }
-      if (rank < need) atomicOr(&s_bits[i >> 6], 1ull << (i & 63));
+      rank += __builtin_amdgcn_update_dpp(0, rank, 0xB1, 0xF, 0xF, true);   // quad_perm [1,0,3,2]
+      rank += __builtin_amdgcn_update_dpp(0, rank, 0x4E, 0xF, 0xF, true);   // quad_perm [2,3,0,1]
+      if ((tid & 3) == 0 && rank < need) atomicOr(&s_bits[i >> 6], 1ull << (i & 63));
     }
     __syncthreads();
   }
   KS_TS(10);
 
   // ---- ordered compaction: positions inside a chunk from a ballot, the wavefronts' totals through LDS ------
-  auto kept_mask = [&](int c) -> uint64_t { return __ballot(y[c] > t_hi) | s_bits[wave * cpw + c]; };   // (y: NaN beyond the length)
+  auto kept_mask = [&](int c) -> uint64_t { return __ballot((keep >> c) & 1) | s_bits[wave * cpw + c]; };
   int nk = 0;
 #pragma unroll
   for (int c = 0; c < ITEMS; ++c)

@@ -91,3 +91,67 @@ def test_nan_scores_rank_by_their_sign(cap):
         rk = np.sort(np.concatenate([np.arange(n_sink), heavy, np.arange(cap - n_recent, cap)]))
         np.testing.assert_array_equal(keep[0, h].cpu().numpy(), rk, err_msg=f"head {h}")
         np.testing.assert_array_equal(evict[0, h].cpu().numpy(), np.setdiff1d(np.arange(cap), rk))
+
+
+def _distributions(cap, g):
+    """Twelve ranking arrays [12, cap]: outliers beyond and within what the histogram's range leaves out, heavy tails, long runs of
+    equal values across the threshold, mixed with others and filling the head, hundreds of values a few ulps apart, infinities."""
+    x = g.standard_normal((12, cap)).astype(np.float32)
+    far = g.choice(cap, 12, replace=False)
+    x[0, far[:3]] = [3e3, 8e2, 5e2]
+    x[1, far] = -1e4                                            # in all four classes
+    x[2] = np.exp(5 * x[2])
+    # (none so small that ln p + ln S - ln(1 - alpha^n) would absorb it: the oracle adds the three in another order)
+    x[3] *= np.float32(10.0) ** g.integers(-3, 30, cap).astype(np.float32)
+    x[4] = 1.5
+    x[5, g.random(cap) < 0.5] = 0.3
+    x[6] = np.where(g.random(cap) < 0.95, 0.0, g.random(cap))
+    x[7] = np.where(g.random(cap) < 0.9, -np.inf, x[7])
+    x[8] = g.integers(0, 5, cap)
+    x[9] = 2.0 + g.integers(-40, 40, cap).astype(np.float32) * np.float32(2.0 ** -22)
+    x[10, g.random(cap) < 0.6] = np.inf
+    x[11, g.random(cap) < 0.4] = np.float32(0.25) + np.float32(2.0 ** -25)
+    return x
+
+
+@pytest.mark.parametrize("varied", [False, True])
+@pytest.mark.parametrize("cap,budget,n_sink,n_recent", [
+    (300, 60, 2, 10), (884, 820, 4, 652), (1025, 103, 4, 82), (2048, 300, 0, 0), (5003, 501, 4, 397), (8192, 820, 4, 652),
+    (9001, 4090, 4, 6), (20000, 1000, 4, 200), (32768, 3277, 4, 2618)])
+def test_distributions(cap, budget, n_sink, n_recent, varied):
+    """Lists of keepkv_select (votes and counts the same in all slots, or varied) and keepkv_select_by_key on skewed, spread,
+    equal and nearly equal values, full and ragged heads: those of the oracle."""
+    kk = U.kk()
+    alpha = U.f32(0.9)
+    g = np.random.default_rng(cap + varied)
+    x = _distributions(cap, g)
+    H = len(x)
+    w = W.CONFIGS["llama3_8b"].scaled(batch=1, n_q_heads=H, n_kv_heads=H, context=cap)
+    lay, c = U.new_cache(w, capacity=cap)
+    ws = U.workspace(lay, cap, budget)
+    votes = g.integers(1, 4, (H, cap)) if varied else np.full((H, cap), 2)
+    n_obs = g.integers(1, 60, (H, cap)) if varied else np.full((H, cap), 21)
+    c.log_s[:] = torch.from_numpy(x[None]).cuda()
+    c.votes[:] = torch.from_numpy(votes[None].astype(np.int32)).cuda()
+    U.set_n_obs(c, n_obs[None])
+    rank = torch.from_numpy(x[None]).cuda()
+    for lens in (np.full((1, H), cap), g.integers(budget + 1, cap + 1, size=(1, H))):
+        c.len[:] = torch.from_numpy(lens.astype(np.int32)).cuda()
+        for by_key in (False, True):
+            keep = torch.full((1, H, budget), -7, dtype=torch.int32, device="cuda")
+            evict = torch.full((1, H, cap - budget), -7, dtype=torch.int32, device="cuda")
+            n_ev = torch.full((1, H), -7, dtype=torch.int32, device="cuda")
+            if by_key:
+                kk.select_by_key(lay, c, rank, budget, n_sink, n_recent, keep, evict, n_ev, ws)
+            else:
+                kk.select(lay, c, budget, n_sink, n_recent, alpha, keep, evict, n_ev, ws)
+            torch.cuda.synchronize()
+            for h in range(H):
+                n = int(lens[0, h])
+                if by_key:
+                    rk, re = O.select_by_key(x[h], n, budget, n_sink, n_recent)
+                else:
+                    rk, re = O.select(x[h].astype(np.float64), n_obs[h], votes[h], n, budget, n_sink, n_recent, alpha)
+                assert n_ev[0, h].item() == len(re)
+                np.testing.assert_array_equal(keep[0, h].cpu().numpy(), rk, err_msg=f"head {h} by_key {by_key}")
+                np.testing.assert_array_equal(evict[0, h, :len(re)].cpu().numpy(), re, err_msg=f"head {h} by_key {by_key}")
