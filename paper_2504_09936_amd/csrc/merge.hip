@@ -275,17 +275,38 @@ __device__ __forceinline__ double log_s_hat(float log_s, int n, double ln_alpha,
   return n <= 0 ? -INFINITY : (double)log_s - t;
 }
 
-template <int LPS>
-__device__ __forceinline__ double group_max_f64(double x) {
-#pragma unroll
-  for (int off = 1; off < LPS; off <<= 1) x = fmax(x, __shfl_xor(x, off));
+// Over aligned groups of LANES lanes, every lane receives the result; the pairs are those of an exchange with lane ^ 1, ^ 2, ^ 4, ...
+// By register moves between lanes: an exchange through LDS takes a hundred cycles, and a position has 16 to 24 in a row.
+template <int CTRL>
+__device__ __forceinline__ double dpp_f64(double x) {
+  const uint64_t b = __builtin_bit_cast(uint64_t, x);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)b, CTRL, 0xF, 0xF, true);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(b >> 32), CTRL, 0xF, 0xF, true);
+  return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
+}
+template <int LANES, typename F>
+__device__ __forceinline__ double group_reduce_f64(double x, F f) {
+  x = f(x, dpp_f64<0xB1>(x));                             // quad_perm [1,0,3,2]
+  x = f(x, dpp_f64<0x4E>(x));                             // quad_perm [2,3,0,1]
+  if constexpr (LANES >= 8) x = f(x, dpp_f64<0x141>(x));  // row_half_mirror
+  if constexpr (LANES >= 16) x = f(x, dpp_f64<0x140>(x)); // row_mirror
+  auto pair = [&](auto swap) {                            // the two rows, then halves, that an exchange brings together
+    const uint64_t b = __builtin_bit_cast(uint64_t, x);
+    const auto lo = swap((uint32_t)b), hi = swap((uint32_t)(b >> 32));
+    const uint32_t lo0 = lo[0], lo1 = lo[1], hi0 = hi[0], hi1 = hi[1];
+    x = f(__builtin_bit_cast(double, (uint64_t)hi0 << 32 | lo0), __builtin_bit_cast(double, (uint64_t)hi1 << 32 | lo1));
+  };
+  if constexpr (LANES >= 32) pair([](uint32_t v) { return __builtin_amdgcn_permlane16_swap(v, v, false, false); });
+  if constexpr (LANES >= 64) pair([](uint32_t v) { return __builtin_amdgcn_permlane32_swap(v, v, false, false); });
   return x;
 }
-template <int LPS>
+template <int LANES>
+__device__ __forceinline__ double group_max_f64(double x) {
+  return group_reduce_f64<LANES>(x, [](double a, double b) { return fmax(a, b); });
+}
+template <int LANES>
 __device__ __forceinline__ double group_sum_f64(double x) {
-#pragma unroll
-  for (int off = 1; off < LPS; off <<= 1) x += __shfl_xor(x, off);
-  return x;
+  return group_reduce_f64<LANES>(x, [](double a, double b) { return a + b; });
 }
 
 // Each lane group of a wavefront (LPS lanes, 64 / LPS groups) brings one retained slot c, the nm evicted slots
@@ -294,21 +315,25 @@ __device__ __forceinline__ double group_sum_f64(double x) {
 // f64 relative to the largest ln s_hat, rows accumulated in f32 and scaled once.  Called by whole wavefronts.
 // The scalars of positions with up to LPS entries (most of them) are worked out side by side, one entry per lane, so
 // that the f64 routines run once for all groups; a longer list has its scalars spread over the whole wavefront.
-// The rows are summed one position after the other by the whole wavefront, entry e by lane group e mod
-// (64 / LPS), and the groups' partial sums meet in a fixed tree: a position's bits depend on its list alone and not
-// on the kernel or on its place in the wavefront.
+// Up to kOwnRows entries a lane group sums the rows of its position itself, in list order, so that one or two round trips
+// serve all positions of the wavefront.  Longer lists are summed one position after the other by the whole wavefront, entry e by
+// lane group e mod (64 / LPS), and the groups' partial sums meet in a fixed tree.  Either way a position's bits depend on its list
+// alone and not on the kernel or on its place in the wavefront.
 // Why: the members per target vary widely (mean 9, largest 147 on the clustered keys of the long-context
 // workload).  With one lane group per position a wavefront took as long as its largest group, one dependent round
 // trip for every LPS scalars and every few rows.
 // What bounds it: HBM for the members' rows, and the f64 arithmetic.  Measured against one lane group per position
 // (MI355X): 1024 heads x 820 positions, 7372 evicted rows each, 4.6 GB moved: 1637 -> 1020 us (4.5 TB/s; a plain copy
 // reaches 5.1); 8 heads x 3277, 29491 rows: 163 -> 65 us; 24 heads x 501 of D 64: 64 -> 25 us; the in-place event of 128
-// heads: 14.6 -> 13.7 us.
+// heads: 14.6 -> 13.7 us.  Merge-first prefill where every second slot is absorbed by its neighbour (lists of two; D 64, whole
+// call): 56 heads x 4386 slots 58 us with one lane group per position, 82 with whole wavefronts for all lists, 49 now; 88 x 978
+// 31.7, 45.5, 27.5.
 template <typename T, int D>
 __device__ __forceinline__ void merge_positions(const MergeParams& p, int unit, int t_head, int c, const int32_t* list,
                                                 int off, int nm, int dst) {
   constexpr int EPL = 16 / (int)sizeof(T), LPS = D / EPL, GPW = 64 / LPS;
   constexpr int kRowBatch = 2;                      // entries per lane group and round trip
+  constexpr int kOwnRows = LPS == 8 ? 8 : 4;                       // up to this many entries a lane group sums its position by itself
   const size_t sbase = (size_t)unit * p.scap, dbase = (size_t)unit * p.dcap;
   const uint4* sk = reinterpret_cast<const uint4*>(p.sk) + sbase * LPS;
   const uint4* sv = reinterpret_cast<const uint4*>(p.sv) + sbase * LPS;
@@ -451,10 +476,47 @@ __device__ __forceinline__ void merge_positions(const MergeParams& p, int unit, 
     const Scales sc = scales(mx, group_sum_f64<LPS>((double)x.pv), group_sum_f64<LPS>(w),
                              group_sum_f64<LPS>(weighted_e(w, x, mx)), __shfl(x.n, grp * LPS));
     if (ne > 0 && ne <= LPS && sub == 0) store_scalars(dst, sc);
+    const int own = ne <= kOwnRows ? ne : 0;
+    if (__any(own > 0)) {                          // the shortest: every lane group sums its own position, in list order
+      clear();
+#pragma unroll
+      for (int q0 = 0; q0 < kOwnRows; q0 += 4) {   // four rows a round trip
+        if (q0 > 0 && !__any(own > q0)) break;
+        uint4 kr[4], vr[4];
+        float wq[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const uint32_t row = (uint32_t)__shfl(x.s, grp * LPS + q0 + u) * LPS + sub;
+          wq[u] = __shfl(wf, grp * LPS + q0 + u);
+          if (q0 + u < own) {
+            kr[u] = sk[row];
+            vr[u] = sv[row];
+          }
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+          if (q0 + u < own) {
+            fma_row(kr[u], wq[u], acc);
+            fma_row(vr[u], wq[u], acc + EPL);
+          }
+      }
+      if (own > 0) {
+        auto row_of = [](const float* a, float f) {
+          if constexpr (sizeof(T) == 2)
+            return make_uint4(pack_bf16x2(a[0] * f, a[1] * f), pack_bf16x2(a[2] * f, a[3] * f),
+                              pack_bf16x2(a[4] * f, a[5] * f), pack_bf16x2(a[6] * f, a[7] * f));
+          else
+            return make_uint4(__builtin_bit_cast(uint32_t, a[0] * f), __builtin_bit_cast(uint32_t, a[1] * f),
+                              __builtin_bit_cast(uint32_t, a[2] * f), __builtin_bit_cast(uint32_t, a[3] * f));
+        };
+        reinterpret_cast<uint4*>(p.dk)[(dbase + dst) * LPS + sub] = row_of(acc, sc.fk);
+        reinterpret_cast<uint4*>(p.dv)[(dbase + dst) * LPS + sub] = row_of(acc + EPL, sc.fv);
+      }
+    }
 #pragma unroll 1
     for (int g = 0; g < GPW; ++g) {
       const int n = __builtin_amdgcn_readlane(ne, g * LPS);     // uniform: entries of group g's position
-      if (n == 0 || n > LPS) continue;
+      if (n <= kOwnRows || n > LPS) continue;
       clear();
       add_rows(x.s, wf, g * LPS, n);
       store_rows(g, __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, sc.fk), g * LPS)),
@@ -615,9 +677,11 @@ __global__ __launch_bounds__(256) void merge_apply_kernel(MergeParams p) {
 // in the workspace and are read and written with device-scope accesses: the same steps, an L2 round trip each.
 // What bounds it: LDS accesses of one workgroup per head.  Neighbouring lanes hold neighbouring slots: with a run of 8 slots
 // per thread every access hit the banks eight times over, and with all 13 rounds 64 heads x 8192 slots took 58 us (now
-// 20 us).
+// 20 us).  Whether a slot moved is a word of LDS per round (a barrier that also joins a flag over the workgroup cost a quarter more
+// where long chains take all rounds).
 constexpr int kPrefillLdsSlots = 16384;          // two int arrays of that many words fit in LDS
 constexpr int kPrefillMaxSlots = 32768;
+constexpr int kPfRounds = 15;                    // ceil(log2 kPrefillMaxSlots)
 
 template <int kPfItems, bool GLOBAL>
 __global__ __launch_bounds__(kGroupThreads) void prefill_group_kernel(
@@ -626,6 +690,7 @@ __global__ __launch_bounds__(kGroupThreads) void prefill_group_kernel(
     int32_t* __restrict__ gwork) {
   extern __shared__ int s_pf[];                   // [2][n_pad] (unused when GLOBAL)
   __shared__ int s_wave[kGroupThreads / 64];
+  __shared__ int s_moved[kPfRounds];              // by round: some slot moved
   // (device-scope stores of this workgroup are awaited before a barrier that publishes them to its other threads)
   auto sync = [] {
     if constexpr (GLOBAL) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -659,6 +724,7 @@ __global__ __launch_bounds__(kGroupThreads) void prefill_group_kernel(
       st_(A, i, link[u] >= 0 ? ((link[u] << 1) | 1) : (i << 1));
     }
   }
+  if (tid < kPfRounds) s_moved[tid] = 0;
   sync();
   int rounds = 0;
   while ((1 << rounds) < n) ++rounds;
@@ -676,10 +742,10 @@ __global__ __launch_bounds__(kGroupThreads) void prefill_group_kernel(
         moved |= (x ^ y) & ~1;
       }
     }
-    if constexpr (GLOBAL) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    const int any = __syncthreads_or(moved);      // (as sync() does)
+    if (__any(moved != 0) && lane == 0) s_moved[r] = 1;
+    sync();
     int* t = cur; cur = nxt; nxt = t;
-    if (any == 0) break;                          // every slot has its root
+    if (s_moved[r] == 0) break;                   // uniform: every slot has its root
   }
   // absorbed = odd depth; receivers numbered in slot order: positions in a chunk by ballot
   bool absorbed[kPfItems];
@@ -922,14 +988,16 @@ __global__ __launch_bounds__(kInplaceThreads) void merge_inplace_kernel(MergePar
 }  // namespace
 
 // Positions that a wavefront of merge_apply_kernel takes (lps lanes each).  Side by side they share the f64 scalars;
-// but a wavefront sums their rows one position after the other, so with few positions on the chip it takes fewer, until
-// there are kApplyWaves wavefronts (four for each SIMD): 24 heads x 501 positions
+// but a wavefront sums the rows of long lists one position after the other, so with few positions on the chip it takes
+// fewer, until there are kApplyWaves wavefronts (four for each SIMD): 24 heads x 501 positions
 // of D 64 take 38 us with eight positions per wavefront and 25 with four; more wavefronts than that lose (64 heads x
-// 820 positions, mostly copies: 16.7 us at 4096, 20.4 at 16384, 27.6 at 65536).
+// 820 positions, mostly copies: 16.7 us at 4096, 20.4 at 16384, 27.6 at 65536).  Short prefills have short lists and take
+// half as many (whole call, D 64, 4096 / 2048: 56 heads x 217 slots 21.7 / 18.5 us, 16 x 523 20.4 / 19.2; but 16 x 1450
+// 27.1 / 28.2, 8 x 3238 with lists of hundreds 173 / 253).
 constexpr int kApplyWaves = 4096;
-static int positions_per_wave(unsigned units, int positions, int lps) {
+static int positions_per_wave(unsigned units, int positions, int lps, int waves = kApplyWaves) {
   int ppw = 64 / lps;
-  while (ppw > 1 && (long)units * positions / ppw < kApplyWaves) ppw /= 2;
+  while (ppw > 1 && (long)units * positions / ppw < waves) ppw /= 2;
   return ppw;
 }
 
@@ -1110,7 +1178,7 @@ extern "C" keepkv_status keepkv_prefill_merge(const keepkv_layout* layout, const
   p.write_len = 0;
   p.ln_alpha = alpha > 0.f ? log((double)alpha) : -INFINITY;
   const int esz = layout->dtype == KEEPKV_BF16 ? 2 : 4;
-  p.positions_per_wave = positions_per_wave(units, cap, layout->head_dim * esz / 16);
+  p.positions_per_wave = positions_per_wave(units, cap, layout->head_dim * esz / 16, cap <= 1024 ? kApplyWaves / 2 : kApplyWaves);
   const dim3 grid((cap + 4 * p.positions_per_wave - 1) / (4 * p.positions_per_wave), units);
   if (layout->dtype == KEEPKV_BF16) {
     if (layout->head_dim == 128) merge_apply_kernel<uint16_t, 128, false><<<grid, 256, 0, st>>>(p);
