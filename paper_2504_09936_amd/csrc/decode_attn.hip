@@ -1351,22 +1351,26 @@ static int resident_per_cu(int waves, int head_dim, int group) {
 // longer of what one workgroup needs for its rows (a compute unit pulls 34 GB/s, shared by its workgroups; a wavefront
 // 10.2 GB/s with all its tiles requested at once, 7.5 in the tile loop) and of what memory needs for all of them
 // (5.8 TB/s, less when the last workgroups leave compute units empty); further rounds cost 1.7 us each, smaller workgroups
-// 0.5 us, and splits have to be combined, four, eight or sixteen at a time.  At most kMaxSplitWorkgroups workgroups share
+// 0.5 us, and splits have to be combined, four, eight or sixteen at a time and, beyond sixteen, once more for every output
+// element that a thread has.  At most kMaxSplitWorkgroups workgroups share
 // heads: more of them never paid, and it bounds the workspace.
 // The constants are a fit to 2000 measured (shape, plan) pairs on MI355X: batch 1 .. 128, 116 .. 32768 slots, head dims 64
 // and 128.  Over those 55 shapes the plan chosen is 0.4 % slower than the best one (2.6 % at most); the model before, which
 // rounded a split up to whole workgroup iterations and knew one price for combining, was 3.5 % (36 % at most) off: 8 heads
 // x 32768 slots 43.5 us with 16 splits against 30.1 with 32, 128 heads x 2000 (D 64) 23.8 with one against 16.4 with two, 8
-// heads x 852 7.1 with four against 6.7 with seven.
+// heads x 852 7.1 with four against 6.7 with seven.  Over 30 more shapes of one to eight heads and up to 2^20 slots: 0.8 %
+// slower than the best plan (8.6 % at most; 3.6 % and 20 % with one price for combining: one head of 8 query heads x 3405 slots
+// 12.0 us with 27 splits against 9.9 with 16, x 50000 32.3 with 112 against 29.4 with 63).
 constexpr int kMaxSplitWorkgroups = 512;
 constexpr int kMinSplit = 64;
 static void choose_split(const keepkv_layout* L, int capacity, long& per, int& waves) {
   const double units = (double)L->batch * L->n_kv_heads;
+  const int group = L->n_q_heads / L->n_kv_heads;
   const double slot_bytes = 4.0 * L->head_dim + 24.0;
   const long max_ns = (capacity + kMinSplit - 1) / kMinSplit;
   double best = 1e300;
   for (int wv = 4; wv <= 8; wv += 4) {
-    const double res_max = 256.0 * resident_per_cu(wv, L->head_dim, L->n_q_heads / L->n_kv_heads);
+    const double res_max = 256.0 * resident_per_cu(wv, L->head_dim, group);
     for (long ns = 1; ns <= max_ns && (ns == 1 || units * (double)ns <= kMaxSplitWorkgroups); ++ns) {
       long cand = ((capacity + ns - 1) / ns + kMTile - 1) / kMTile * kMTile;
       if (cand < kMinSplit) cand = kMinSplit;
@@ -1385,9 +1389,10 @@ static void choose_split(const keepkv_layout* L, int capacity, long& per, int& w
       };
       const double full = (double)(long)(wgs / res_max), rest = wgs - full * res_max;
       const double rounds = full + (rest > 0.0 ? 1.0 : 0.0);
+      const double elements = (double)((group * L->head_dim + wv * kWave - 1) / (wv * kWave));   // per thread
       double t = full * round_of(res_max) + round_of(rest) + 1.7 * (rounds - 1.0) + (wv == 4 ? 0.46 : 0.0);
       if (n_split > 1.0)
-        t += (n_split <= 4.0 ? 1.85 : n_split <= 8.0 ? 2.7 : 4.3 + 1.3 * (double)(long)((n_split - 1.0) / 16.0)) + 0.011 * n_split;
+        t += (n_split <= 4.0 ? 1.85 : n_split <= 8.0 ? 2.7 : 4.3 + 1.3 * elements * (double)(long)((n_split - 1.0) / 16.0)) + 0.011 * n_split;
       if (t < best) {
         best = t;
         per = cand;

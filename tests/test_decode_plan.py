@@ -23,6 +23,14 @@ def test_plan_and_workspace(units, G, D):
             assert ns == 1 or HEAD + units * G * ns * (D + 2) * 4 <= have, (largest, cap)
 
 
+def test_combining_is_priced_per_output_element():
+    """One long head: eight query heads give a thread two output elements to combine, so it is split less than one."""
+    kk = U.kk()
+    for cap in (50000, 100000):
+        few, many = (kk.decode_plan(kk.Layout(1, g, 1, 128, kk.BF16, 0.1), cap)[0] for g in (8, 1))
+        assert 16 < few < many
+
+
 def test_layouts_without_a_kernel_still_get_a_size():
     kk = U.kk()
     assert kk.workspace_bytes(kk.Layout(2, 6, 2, 4096, kk.BF16, 0.1), 1000, 100) > HEAD
