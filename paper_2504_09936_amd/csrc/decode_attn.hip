@@ -1404,7 +1404,9 @@ static void choose_split(const keepkv_layout* L, int capacity, long& per, int& w
 
 // The vector-ALU kernel (4 wavefronts): a wavefront streams at no more than ~6.5 GB/s when all its tiles are requested at
 // once and ~4.4 GB/s when it loops, all resident workgroups (512) together at ~5.1 TB/s when the chip is full; every round
-// costs ~3 us, the combination ~2.3 / ~3.4 us per round trip of device-scope loads.
+// costs ~3 us, the combination ~2.3 / ~3.4 us per round trip of device-scope loads.  kMaxSplitWorkgroupsValu only bounds the
+// workspace: the model's own choices stay below it (at most 1539 workgroups share heads, 513 heads of three splits).
+constexpr int kMaxSplitWorkgroupsValu = 2048;
 static void choose_split_valu(const keepkv_layout* L, int capacity, long& per) {
   const double units = (double)L->batch * L->n_kv_heads;
   const bool bf16 = L->dtype == KEEPKV_BF16;
@@ -1414,7 +1416,7 @@ static void choose_split_valu(const keepkv_layout* L, int capacity, long& per) {
   const double res_max = 512.0;
   const long max_ns = (capacity + 63) / 64 < 1024 ? (capacity + 63) / 64 : 1024;
   double best = 1e300;
-  for (long ns = 1; ns <= max_ns; ++ns) {
+  for (long ns = 1; ns <= max_ns && (ns == 1 || units * (double)ns <= kMaxSplitWorkgroupsValu); ++ns) {
     const long cand = ((capacity + ns - 1) / ns + 63) / 64 * 64;
     const double n_split = (double)((capacity + cand - 1) / cand);
     const double wgs = units * n_split;
@@ -1465,12 +1467,11 @@ static DecodePlan make_plan(const keepkv_layout* L, int capacity, int force_per,
 // A workspace for caches of up to `capacity` slots: a smaller cache may be split finer than the largest.
 size_t decode_workspace_bytes(const keepkv_layout* L, int capacity) {
   size_t bytes = plan_decode(L, capacity).bytes;
-  if (L->dtype == KEEPKV_BF16) {
-    const long units = (long)L->batch * L->n_kv_heads;
-    long ns = (capacity + kMinSplit - 1) / kMinSplit;
-    if (ns > kMaxSplitWorkgroups / units) ns = kMaxSplitWorkgroups / units;
-    if (ns > 1 && decode_bytes(L, ns) > bytes) bytes = decode_bytes(L, ns);
-  }
+  const long units = (long)L->batch * L->n_kv_heads;
+  const long most = (L->dtype == KEEPKV_BF16 ? kMaxSplitWorkgroups : kMaxSplitWorkgroupsValu) / units;
+  long ns = (capacity + kMinSplit - 1) / kMinSplit;
+  if (ns > most) ns = most;
+  if (ns > 1 && decode_bytes(L, ns) > bytes) bytes = decode_bytes(L, ns);
   return bytes;
 }
 

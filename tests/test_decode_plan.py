@@ -6,17 +6,19 @@ from tests import gpu_util as U
 HEAD = 64 * 1024 + 256       # control words at the head of a workspace (keepkv.h)
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
 @pytest.mark.parametrize("D", [64, 128])
 @pytest.mark.parametrize("G", [1, 2, 4, 8])
-@pytest.mark.parametrize("units", [1, 8, 40, 256, 1000])
-def test_plan_and_workspace(units, G, D):
+@pytest.mark.parametrize("units", [1, 8, 40, 64, 256, 513, 1000])
+def test_plan_and_workspace(units, G, D, dtype):
     kk = U.kk()
-    lay = kk.Layout(units, G, 1, D, kk.BF16, 0.1)
+    bf16 = dtype == "bf16"
+    lay = kk.Layout(units, G, 1, D, kk.BF16 if bf16 else kk.F32, 0.1)
     for cap in (1, 31, 64, 65, 500, 884, 4100, 32768, 1 << 20):
         ns, per, waves = kk.decode_plan(lay, cap)
-        assert per % 32 == 0 and per >= 64 and waves in (4, 8)
-        assert ns == -(-cap // per) and (ns == 1 or ns * units <= 512)
-    for largest in (100, 900, 5000, 32768):
+        assert per % (32 if bf16 else 64) == 0 and per >= 64 and waves in ((4, 8) if bf16 else (4,))
+        assert ns == -(-cap // per) and (ns == 1 or ns * units <= (512 if bf16 else 2048))
+    for largest in (100, 600, 900, 5000, 16384, 32768):
         have = kk.workspace_bytes(lay, largest, max(1, largest // 10))
         for cap in range(1, largest + 1, max(1, largest // 61)):
             ns = kk.decode_plan(lay, cap)[0]
