@@ -160,9 +160,9 @@ __device__ __forceinline__ void decide_row(const MatchParams& p, int unit, int j
   const float rn_e = 1.0f / sqrtf(ss);
   const float y1 = __builtin_bit_cast(float, v1), y2 = (v2 > 0) ? __builtin_bit_cast(float, v2) : 0.f;
   const float cos1 = y1 * rn_e;
-  bool fragile = !(v1 > 0) || !(ss > 0.f) || !(rn_e < INFINITY) || (y1 - y2) * rn_e <= p.delta ||
-                 fabsf(cos1 - p.threshold) <= p.delta || c1 >= p.budget;
+  bool fragile = !(v1 > 0) || !((y1 - y2) * rn_e > p.delta) || !(fabsf(cos1 - p.threshold) > p.delta) || c1 >= p.budget;
   if (surely_below(p, (v1 > 0) ? cos1 : 0.f, ss, rn_e)) fragile = false;
+  if (!norm_in_range(ss)) fragile = true;
   const size_t o = (size_t)unit * p.max_evict + j;
   p.match[o] = (cos1 > p.threshold) ? c1 : -1;
   if (p.sim_out != nullptr) p.sim_out[o] = cos1;
@@ -672,8 +672,14 @@ __global__ __launch_bounds__(kSmallWaves* kWave, 2) void match_small_kernel(Matc
             }
           }
           ssq += __shfl_xor(ssq, 32);
-          const bool real = cb * 32 + l32 < n_keep && slot_ok[i] && ssq > 0.f;
-          if (half == 0) s_rn[wave * 32 + l32] = real ? 1.0f / sqrtf(ssq) : 0.f;
+          uint32_t bits = 0;
+          if (__any(!norm_in_range(ssq))) {   // (rare: a zero key, or a norm that f32 cannot hold)
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) bits |= akey[i][ks].x | akey[i][ks].y | akey[i][ks].z | akey[i][ks].w;
+            bits |= (uint32_t)__shfl_xor((int)bits, 32);
+          }
+          const bool real = cb * 32 + l32 < n_keep && slot_ok[i];
+          if (half == 0) s_rn[wave * 32 + l32] = real ? column_rnorm(ssq, (bits & 0x7FFF7FFFu) != 0) : 0.f;
           __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
           __builtin_amdgcn_wave_barrier();
           __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");

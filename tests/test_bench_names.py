@@ -1,0 +1,30 @@
+"""bench.py names the decode kernel instance that a launch plan runs, and reports recorded HBM traffic for that one only."""
+import os
+import re
+
+import pytest
+
+import bench
+from paper_2504_09936_amd import workloads as W
+from tests import gpu_util as U
+
+PROFILES = os.path.join(bench.ROOT, "profiles")
+
+
+def test_decode_kernel_name():
+    assert bench.decode_kernel_name(128, 4, True, 224, 8) == "decode_mfma_kernel<128,4,true,1,8>"
+    assert bench.decode_kernel_name(128, 4, True, 256, 8) == "decode_mfma_kernel<128,4,true,1,8>"
+    assert bench.decode_kernel_name(128, 8, False, 288, 8) == "decode_mfma_kernel<128,8,false,2,8>"
+    assert bench.decode_kernel_name(64, 1, True, 256, 4) == "decode_mfma_kernel<64,1,true,2,4>"
+    assert bench.decode_kernel_name(128, 8, True, 896, 4) == "decode_mfma_kernel<128,8,true,0,4>"
+
+
+@pytest.mark.parametrize("name", ["llama3_8b", "llama3_70b"])
+def test_recorded_traffic_is_that_of_the_planned_instance(name):
+    w = W.CONFIGS[name]
+    _, per, waves = U.kk().decode_plan(U.layout_of(w), w.budget + w.period)
+    kernel = bench.decode_kernel_name(w.head_dim, w.group, True, per, waves)
+    assert bench.traffic_from_profile(name, kernel) is not None
+    text = open(os.path.join(PROFILES, f"decode_hbm_traffic_{name}.md")).read()
+    assert re.search(r"kernel=(\S+)", text).group(1) == kernel
+    assert bench.traffic_from_profile(name, kernel.replace("true", "false")) is None

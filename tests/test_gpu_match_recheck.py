@@ -111,11 +111,12 @@ def test_causal_search_at_block_edges(head_dim, batch, lengths):
 
 
 @pytest.mark.parametrize("head_dim", [64, 128])
-@pytest.mark.parametrize("budget,n_ev", [(820, 700), (129, 300)])
-@pytest.mark.parametrize("scaled", ["rows", "rows, large", "a column", "a column, large", "the best columns"])
+@pytest.mark.parametrize("budget,n_ev", [(820, 700), (129, 300), (820, 130), (100, 50)])     # first events, steady states
+@pytest.mark.parametrize("scaled", ["rows", "rows, large", "a column", "a column, large", "the best columns", "not finite"])
 def test_norms_beyond_f32(head_dim, budget, n_ev, scaled):
     """Keys whose |k|^2 is below or above the f32 range (elements near 2^-80 or 2^70) beside a dozen near-duplicate
-    columns in different classes: the f32 values decide nothing there, targets are those of an f64 evaluation."""
+    columns in different classes: the f32 values decide nothing there, targets are those of an f64 evaluation.  So they are
+    beside keys that hold an infinity or a NaN."""
     kk = U.kk()
     g = np.random.default_rng(budget + head_dim + len(scaled))
     cap = budget + n_ev
@@ -131,6 +132,9 @@ def test_norms_beyond_f32(head_dim, budget, n_ev, scaled):
             K[0, h, budget:] *= scale
         elif scaled.startswith("a column"):
             K[0, h, budget // 3] = K[0, h, 0] * scale
+        elif scaled == "not finite":                                       # match nothing, and hide no other column
+            K[0, h, budget // 4, 1], K[0, h, budget // 2, 0], K[0, h, cap - 1, 2] = np.inf, np.nan, np.inf
+            K[0, h, budget // 4 + 1, 1], K[0, h, cap - 2, 2] = -np.inf, np.nan
         else:
             K[0, h, [5, budget - 1]] = W.round_bf16(K[0, h, 0] * 3.0) * np.array([[2.0 ** -80], [2.0 ** 70]])
     lay, c = U.new_cache(w, capacity=cap, K=K, V=np.zeros_like(K))
