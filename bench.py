@@ -34,6 +34,13 @@ N_REPLAY = 5               # timed replays of the K-step graph; the median is re
 MFMA_BF16_PEAK_TFLOPS = 2500.0
 
 
+def decode_kernel_name(head_dim: int, group: int, step: bool, slots_per_split: int, wavefronts: int) -> str:
+    """The matrix-core decode kernel's instance for a launch plan: its fourth template argument is 1 or 2 where a wavefront
+    has at most that many tiles of 32 slots, 0 for the tile loop."""
+    tiles = -(-slots_per_split // (wavefronts * 32))
+    return f"decode_mfma_kernel<{head_dim},{group},{'true' if step else 'false'},{tiles if tiles <= 2 else 0},{wavefronts}>"
+
+
 def traffic_from_profile(workload: str, kernel: str):
     """HBM bytes per launch of the decode kernel as recorded in profiles/decode_hbm_traffic_<workload>.md
     (rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE in KiB per dispatch, each scaled by what the same counter reads
@@ -257,12 +264,14 @@ def main():
             j1 = min(w.window, j0 + win_chunk)
             kk.score_window(lay, big, q_win[:, :, j0:j1].contiguous() if (j0, j1) != (0, w.window) else q_win,
                             j1 - j0, alpha, -1)
-        if layer < 2 and N <= 32768:
+        if layer < 3 and N <= 32768:
             # the merge-first prefill pass (App. B.4), timed on the same prefill cache; its output is not used
             # further: the timed decode loop continues from the usual (evict-first) event below
             if layer == 0:
                 mf_near = torch.zeros(B, H, N, dtype=torch.int32, device=dev)
                 mf_dst = kk.Cache(lay, N)
+                kk.prefill_match(lay, big, T, mf_near, None, ws)       # (untimed: the first calls load the kernels)
+                kk.prefill_merge(lay, big, mf_dst, mf_near, alpha, ws)
             p = [ev() for _ in range(3)]
             p[0].record()
             kk.prefill_match(lay, big, T, mf_near, None, ws)
@@ -273,7 +282,7 @@ def main():
             merge_first["match"].append(p[0].elapsed_time(p[1]) * 1e3)
             merge_first["merge"].append(p[1].elapsed_time(p[2]) * 1e3)
             merge_first["receivers"] = float(mf_dst.len.float().mean().item())
-            if layer == 1:
+            if layer == min(2, R - 1):
                 del mf_near, mf_dst
         e[0].record()
         kk.select(lay, big, Bud, w.n_sink, w.n_recent, alpha, keep, evict_big, n_ev, ws)
@@ -623,8 +632,7 @@ def main():
     if bf16 and args.decode_wavefronts == -1:
         kernel_instance = "decode_attn_kernel (vector ALU, bf16)"
     elif bf16:
-        kernel_instance = (f"decode_mfma_kernel<{D},{Hq // H},{'false' if args.unfused else 'true'},"
-                           f"{'true' if per_ <= wv_ * 32 else 'false'},{wv_}>")
+        kernel_instance = decode_kernel_name(D, Hq // H, not args.unfused, per_, wv_)
     else:
         kernel_instance = "decode_attn_kernel"
     traffic = traffic_from_profile(w.name, kernel_instance)

@@ -201,13 +201,16 @@ def test_every_d128_instance_attention_only(base, waves, per):
 
 
 def test_full_size_plans_are_among_the_forced_instances():
-    """Host arithmetic only: the (wavefronts, single tile / loop) pair every benchmark configuration plans to
+    """Host arithmetic only: the (wavefronts, one tile / two tiles / loop) pair every benchmark configuration plans to
     is one of the pairs the forced tests above run at head dim 128, for both group sizes."""
     kk = U.kk()
-    forced = {(wv, per <= wv * 32) for wv, per in FORCED}
-    assert forced == {(4, True), (4, False), (8, True), (8, False)}
+
+    def instance(per, waves):
+        return waves, min(3, -(-per // (waves * 32)))          # tiles of a wavefront: the kernel's three forms
+    forced = {instance(per, wv) for wv, per in FORCED}
+    assert forced == {(wv, tiles) for wv in (4, 8) for tiles in (1, 2, 3)}
     for name in FULL:
         w = W.CONFIGS[name]
         nsplit, per, waves = kk.decode_plan(U.layout_of(w), w.budget + w.period)
-        assert (waves, per <= waves * 32) in forced, (name, nsplit, per, waves)
+        assert instance(per, waves) in forced, (name, nsplit, per, waves)
         assert w.head_dim == 128 and w.group in (4, 8)
