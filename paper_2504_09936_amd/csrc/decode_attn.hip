@@ -25,7 +25,7 @@ namespace kk {
 // Phase timestamps for kernel tuning; compiled in only with -DKEEPKV_TRACE (never in the product build).
 #ifdef KEEPKV_TRACE
 __device__ long long kk_trace[8 * 8192];
-#define KK_TS(i) do { const int b_ = blockIdx.y * gridDim.x + blockIdx.x; if (threadIdx.x == 0 && b_ < 8192) \
+#define KK_TS(i) do { const int b_ = (blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x; if (threadIdx.x == 0 && b_ < 8192) \
   kk_trace[b_ * 8 + (i)] = wall_clock64(); } while (0)
 #else
 #define KK_TS(i) do { } while (0)
@@ -48,8 +48,11 @@ struct DecodeParams {
   void* out;
   float* logits_out;
   float* lse_out;
-  float* partial;     // [B*Hq, nsplit, D + 2]
+  float* partial;     // [B*Hkv, nsplit, split_stride]
   int32_t* ticket;    // [B*Hkv] zero between launches
+  uint64_t* arrivals; // [B*Hkv] zero between launches: where the head's workgroups run (null: not recorded, any XCD)
+  int32_t* ticket_xcd;   // [B*Hkv] zero between launches, like `ticket` but counted in the L2 of the head's XCD
+  int split_stride;   // floats between the partial results of two splits
   int n_kv_heads;
   int capacity;
   int nsplit;
@@ -61,6 +64,16 @@ struct DecodeParams {
 };
 
 constexpr int kWavesPerBlock = 4;   // the vector-ALU kernel
+
+// Control words of heads whose workgroups may share an XCD: at most kMaxXcdUnits heads, behind their tickets.
+constexpr int kMaxXcdUnits = 2048;
+constexpr size_t kXcdTicketsOff = 16 * 1024, kArrivalsOff = 32 * 1024;
+static_assert(kMaxXcdUnits * sizeof(int32_t) <= kXcdTicketsOff && kXcdTicketsOff + kMaxXcdUnits * sizeof(int32_t) <= kArrivalsOff &&
+              kArrivalsOff + kMaxXcdUnits * sizeof(uint64_t) <= kMatchCountersOff, "control words");
+constexpr size_t kLine = 128;       // bytes of a cache line
+inline int xcd_split_stride(const keepkv_layout* L) {           // floats of a split's partial result, whole lines
+  return (int)align_up((size_t)L->n_q_heads / L->n_kv_heads * (L->head_dim + 2), kLine / sizeof(float));
+}
 // The matrix-core kernel comes with 4 and with 8 wavefronts per workgroup (64 / 128 KB of tile buffers at
 // D = 128: two workgroups or one per compute unit); plan_decode picks.
 
@@ -87,6 +100,16 @@ __device__ __forceinline__ float ld_agent(const float* p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// loads of what another workgroup of this XCD wrote (see all_on_this_xcd): they miss L1, L2 serves them
+__device__ __forceinline__ float ld_xcd(const float* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+__device__ __forceinline__ void ld_xcd2(const float* p, float& a, float& b) {
+  const uint64_t v = __hip_atomic_load(reinterpret_cast<const uint64_t*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  a = __builtin_bit_cast(float, (uint32_t)v);
+  b = __builtin_bit_cast(float, (uint32_t)(v >> 32));
+}
+
 // Two floats that live side by side, as one device-scope access.
 __device__ __forceinline__ void st_agent2(float* p, float a, float b) {
   const uint64_t v = (uint64_t)__builtin_bit_cast(uint32_t, a) | (uint64_t)__builtin_bit_cast(uint32_t, b) << 32;
@@ -98,21 +121,83 @@ __device__ __forceinline__ void ld_agent2(const float* p, float& a, float& b) {
   b = __builtin_bit_cast(float, (uint32_t)(v >> 32));
 }
 
+// a <- {a of the lower half, b of the lower half}, b <- {a of the upper half, b of the upper half} (lanes 0 .. 31 / 32 .. 63)
+__device__ __forceinline__ void swap_halves(float& a, float& b) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(uint32_t, a), __builtin_bit_cast(uint32_t, b), false, false);
+  const uint32_t ra = r[0], rb = r[1];           // (a bit cast of a vector element itself reads element 0)
+  a = __builtin_bit_cast(float, ra);
+  b = __builtin_bit_cast(float, rb);
+}
+// the same for the rows of 16 lanes of each half: a <- {a row 0, b row 0, a row 2, b row 2}, b <- {a row 1, b row 1, a 3, b 3}
+__device__ __forceinline__ void swap_rows(float& a, float& b) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(uint32_t, a), __builtin_bit_cast(uint32_t, b), false, false);
+  const uint32_t ra = r[0], rb = r[1];           // (a bit cast of a vector element itself reads element 0)
+  a = __builtin_bit_cast(float, ra);
+  b = __builtin_bit_cast(float, rb);
+}
+// maximum / sum over the lanes that hold the same head: equal l16 mod G in all four rows of 16 lanes
+template <int G, typename F>
+__device__ __forceinline__ float over_head_lanes(float x, F op) {
+  if constexpr (G <= 1) x = op(x, dpp_f32<0x121>(x));   // row_ror:1
+  if constexpr (G <= 2) x = op(x, dpp_f32<0x122>(x));   // row_ror:2
+  if constexpr (G <= 4) x = op(x, dpp_f32<0x124>(x));   // row_ror:4
+  x = op(x, dpp_f32<0x128>(x));                         // row_ror:8
+  float y = x;
+  swap_rows(x, y);
+  x = y = op(x, y);
+  swap_halves(x, y);
+  return op(x, y);
+}
+
+// ---- heads whose workgroups all run on one XCD ----------------------------------------------------------------
+// Partial results and a ticket that travel at device scope go to memory and back three times (store, ticket, load), about
+// 2.5 us of a 10 us step; through the L2 that the workgroups of one XCD share it is a third of that.  Workgroups are dealt to the
+// eight XCDs in turn, so the grid puts the splits of a head eight workgroup ids apart; but that order is a habit of
+// the hardware and nothing documented, so a workgroup only relies on what it can read: its own XCD's number.  It adds it to the head's
+// `arrivals` when it starts (byte x: workgroups on XCD x; device scope, nothing waits for it) and looks at the word before it publishes its
+// result, some microseconds later.  If by then all splits have arrived, all on its own XCD, it publishes within that XCD; every
+// other workgroup of the head sees the same word and does the same, because a workgroup that finds the word incomplete
+// marks it (kArriveMark, compare-and-swap on the incomplete word), and a marked word stays marked, so that those who look later
+// use device scope too.
+// Measured through memory / within the XCD (graph replays, a step; the weights below counted in): 64 heads x 852 slots in four
+// splits 9.9 / 9.6 us, 8 heads in seven 6.6 / 6.2, 128 heads x 828 in two 14.7 / 14.6.
+constexpr uint64_t kArriveMark = 1ull << 63;
+constexpr int kMaxLocalSplits = 127;            // a byte of `arrivals`, less the mark
+__device__ __forceinline__ int xcd_id() { return __builtin_amdgcn_s_getreg(20 | (3 << 11)); }   // XCC_ID[3:0]
+__device__ __forceinline__ uint64_t ld_arrivals(const DecodeParams& p, int unit) {
+  return __hip_atomic_load(&p.arrivals[unit], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// v: the word as last read.  One thread per workgroup.
+__device__ __forceinline__ bool all_on_this_xcd(const DecodeParams& p, int unit, uint64_t v) {
+  const uint64_t here = (uint64_t)p.nsplit << (8 * xcd_id());
+  while (v != here && !(v & kArriveMark)) {
+    int sum = 0;
+    for (int x = 0; x < 64; x += 8) sum += (int)(v >> x) & 255;
+    if (sum >= p.nsplit) break;                  // complete, on several XCDs
+    // still incomplete: mark it (at most nsplit attempts fail, one for each arrival)
+    if (__hip_atomic_compare_exchange_strong(&p.arrivals[unit], &v, v | kArriveMark, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                             __HIP_MEMORY_SCOPE_AGENT))
+      break;
+  }
+  return v == here;
+}
+
 // Everything after the workgroup's kParts partial softmax states (m, l, acc[D] per head) have been
 // deposited in LDS and a barrier has passed: reduce them; a single split finishes the head, otherwise the
 // partial result goes to the workspace and the last workgroup of the head to arrive combines the splits,
 // resets the ticket and (step mode) publishes the new len.
 // acc of a part: [D][G] (kInner) or [G][D]; parts are acc_stride / ml_stride floats apart.  A split's partial result in
 // the workspace: acc in the same order, then (m, l) per head.
+// one_xcd (uniform): every workgroup of the head runs on this XCD and knows it (see all_on_this_xcd).
 // An empty part or split has l = 0 and any m; maxima are held at or above the lowest finite value, so that they can be
 // subtracted without a test for -inf.
-template <typename T, int D, int G, int kParts, bool STEP, int WAVES, bool kInner>
+template <typename T, int D, int G, int kParts, bool STEP, int WAVES, bool kInner, bool kSolo, bool kMayShareXcd>
 __device__ __forceinline__ void combine_and_finish(const DecodeParams& p, const float* s_m, const float* s_l,
                                                    const float* s_acc, int ml_stride, int acc_stride, int* s_last_p,
-                                                   int unit, int split, bool grow, int len, int t_old) {
+                                                   int unit, int split, bool grow, int len, int t_old, bool one_xcd_) {
+  const bool one_xcd = kMayShareXcd && one_xcd_;
   constexpr bool kBf16 = sizeof(T) == 2;
   constexpr int kThreads = WAVES * kWave;
-  constexpr int kSplitFloats = G * (D + 2);
   int& s_last = *s_last_p;
   auto head_of = [](int idx) { return kInner ? idx % G : idx / D; };
   auto finish = [&](int idx, float M, float L, float A) {
@@ -126,30 +211,64 @@ __device__ __forceinline__ void combine_and_finish(const DecodeParams& p, const 
     if (d == 0 && p.lse_out != nullptr) p.lse_out[row] = (L > 0.f) ? (M + fast_log2(L)) * kLn2 : -INFINITY;
   };
 
-  float* const partials = p.partial + (size_t)unit * p.nsplit * kSplitFloats;   // this head's splits
+  float* const partials = p.partial + (size_t)unit * p.nsplit * p.split_stride;   // this head's splits
+  // kInner: a lane's head is lane mod G for all of its elements, and what the parts weigh in that head is the same for
+  // every channel, so lane i works out the weight of part i / G and the lanes of a head hand them around through a table of the wavefront's
+  // own in LDS: one exponential per lane instead of one per part and element.  weigh(): n parts; m, l: those of part
+  // lane / G (lowest and 0 beyond n); leaves the head's M and L and the n weights.
+  const int lane = threadIdx.x & 63;
+  float* const s_c = const_cast<float*>(s_acc) + (threadIdx.x >> 6) * acc_stride + G * D + 16;   // [G][n], behind this wavefront's deposit
+  auto weigh = [&](float m, float l, auto n_tag, float& M, float& L, float (&c)[decltype(n_tag)::value]) {
+    constexpr int n = decltype(n_tag)::value;
+    static_assert(n % 4 == 0 && n * G <= kWave, "one weight per lane");
+    M = over_head_lanes<G>(m, [](float a, float b) { return fmaxf(a, b); });
+    const float mine = lane < n * G ? fast_exp2(m - M) : 0.f;
+    L = over_head_lanes<G>(l * mine, [](float a, float b) { return a + b; });
+    if (lane < n * G) s_c[(lane % G) * n + lane / G] = mine;
+#pragma unroll
+    for (int i = 0; i < n; i += 4) {
+      const float4 t = *reinterpret_cast<const float4*>(s_c + (lane % G) * n + i);
+      c[i] = t.x; c[i + 1] = t.y; c[i + 2] = t.z; c[i + 3] = t.w;
+    }
+  };
+  float M_mine = kLowest, L_mine = 0.f, c_mine[kInner ? kParts : 1];
+  if constexpr (kInner) {
+    const bool held = lane < kParts * G;
+    const int at = (held ? lane / G : 0) * ml_stride + lane % G;
+    weigh(held ? s_m[at] : kLowest, held ? s_l[at] : 0.f, std::integral_constant<int, kParts>{}, M_mine, L_mine, c_mine);
+  }
   for (int idx = threadIdx.x; idx < G * D; idx += kThreads) {
     const int g = head_of(idx);
-    float M = kLowest;
+    float M = M_mine, L = L_mine, A = 0.f;
+    if constexpr (kInner) {
 #pragma unroll
-    for (int w = 0; w < kParts; ++w) M = fmaxf(M, s_m[w * ml_stride + g]);
-    float L = 0.f, A = 0.f;
+      for (int w = 0; w < kParts; ++w) A = fmaf(s_acc[w * acc_stride + idx], c_mine[w], A);
+    } else {
 #pragma unroll
-    for (int w = 0; w < kParts; ++w) {
-      const float c = fast_exp2(s_m[w * ml_stride + g] - M);
-      L = fmaf(s_l[w * ml_stride + g], c, L);
-      A = fmaf(s_acc[w * acc_stride + idx], c, A);
+      for (int w = 0; w < kParts; ++w) M = fmaxf(M, s_m[w * ml_stride + g]);
+#pragma unroll
+      for (int w = 0; w < kParts; ++w) {
+        const float c = fast_exp2(s_m[w * ml_stride + g] - M);
+        L = fmaf(s_l[w * ml_stride + g], c, L);
+        A = fmaf(s_acc[w * acc_stride + idx], c, A);
+      }
     }
-    if (p.nsplit == 1) {
+    if (kSolo || p.nsplit == 1) {
       finish(idx, M, L, A);
     } else {
-      // device-coherent (write-through) stores: the combining workgroup may run on another XCD
-      float* dst = partials + (size_t)split * kSplitFloats;
-      st_agent(dst + idx, A);
-      if ((kInner ? idx / G : idx % D) == 0) st_agent2(dst + G * D + 2 * g, M, L);
+      float* dst = partials + (size_t)split * p.split_stride;
+      const bool has_ml = (kInner ? idx / G : idx % D) == 0;
+      if (one_xcd) {
+        dst[idx] = A;
+        if (has_ml) *reinterpret_cast<float2*>(dst + G * D + 2 * g) = make_float2(M, L);
+      } else {                                   // device-coherent (write-through): the combining workgroup may run on another XCD
+        st_agent(dst + idx, A);
+        if (has_ml) st_agent2(dst + G * D + 2 * g, M, L);
+      }
     }
   }
 
-  if (p.nsplit == 1) {
+  if (kSolo || p.nsplit == 1) {
     if (STEP && threadIdx.x == 0) p.t_obs[unit] = t_old + 1;   // one more observation of every slot of the head
     if (STEP && threadIdx.x == 0 && grow) p.len[unit] = len;   // every wavefront read len before the barrier above
     if (STEP && threadIdx.x == 0 && !grow && p.overflow != nullptr) *p.overflow = 1;
@@ -158,24 +277,31 @@ __device__ __forceinline__ void combine_and_finish(const DecodeParams& p, const 
 
   KK_TS(3);
   // ---- the last workgroup of this head to arrive combines the splits ------------------------------
-  // The partial results were stored write-through at device scope, so it is enough that every
+  // The partial results were stored write-through at device scope (or, one_xcd, into the L2 that all of the head's
+  // workgroups share, where the ticket is counted too), so it is enough that every
   // wavefront's stores have completed before the ticket is taken: each wavefront waits on its own
   // memory counter (stores count there on this part), then the barrier orders all of them before
   // thread 0's ticket.  A workgroup-scope release fence emits no such wait here (the workgroup shares
   // one L2, so the compiler needs none for that scope), and a device-scope release fence would write
-  // back the whole L2 per workgroup.  The combining workgroup reads the partials with device-scope loads.
+  // back the whole L2 per workgroup.  The combining workgroup reads the partials with device-scope loads; one_xcd: with loads
+  // that find nothing in its L1, because a split's result has cache lines of its own (split_stride) that nobody reads but the
+  // combining workgroup, once a launch.
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
-  if (threadIdx.x == 0)
-    s_last = (__hip_atomic_fetch_add(&p.ticket[unit], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == p.nsplit - 1);
+  if (threadIdx.x == 0) {
+    const int before = one_xcd ? __hip_atomic_fetch_add(&p.ticket_xcd[unit], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)
+                               : __hip_atomic_fetch_add(&p.ticket[unit], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    s_last = before == p.nsplit - 1;
+  }
   __syncthreads();
   KK_TS(4);
   if (!s_last) return;
   // CH splits of EB output elements are fetched per round trip of device-scope loads: 4 or 8 splits of two
   // elements when that covers all splits (the common case; surplus loads would only cost), else 16 of one
   constexpr int kPerThread = (G * D + kThreads - 1) / kThreads;   // output elements per thread
-  auto combine = [&](auto ch_tag, auto eb_tag) {
+  auto combine = [&](auto ch_tag, auto eb_tag, auto xcd_tag) {
     constexpr int CH = decltype(ch_tag)::value, EB = decltype(eb_tag)::value;
+    constexpr bool kXcd = decltype(xcd_tag)::value;
     for (int e0 = 0; e0 < kPerThread; e0 += EB) {
       int idx[EB];
       float M[EB], L[EB], A[EB];
@@ -190,11 +316,17 @@ __device__ __forceinline__ void combine_and_finish(const DecodeParams& p, const 
         float ms[EB][CH], ls[EB][CH], as[EB][CH];
 #pragma unroll
         for (int i = 0; i < CH; ++i) {
-          const float* src = partials + (size_t)min(s0 + i, p.nsplit - 1) * kSplitFloats;
+          const float* src = partials + (size_t)min(s0 + i, p.nsplit - 1) * p.split_stride;
 #pragma unroll
           for (int j = 0; j < EB; ++j) {
-            ld_agent2(src + G * D + 2 * head_of(idx[j]), ms[j][i], ls[j][i]);
-            as[j][i] = ld_agent(src + idx[j]);
+            const float* ml = src + G * D + 2 * head_of(idx[j]);
+            if constexpr (kXcd) {
+              ld_xcd2(ml, ms[j][i], ls[j][i]);
+              as[j][i] = ld_xcd(src + idx[j]);
+            } else {
+              ld_agent2(ml, ms[j][i], ls[j][i]);
+              as[j][i] = ld_agent(src + idx[j]);
+            }
           }
         }
 #pragma unroll
@@ -219,13 +351,57 @@ __device__ __forceinline__ void combine_and_finish(const DecodeParams& p, const 
         if ((int)threadIdx.x + (e0 + j) * kThreads < G * D) finish(idx[j], M[j], L[j], A[j]);
     }
   };
+  // kInner and no more than CH splits: the weights once per lane (see weigh), CH values of every element per round trip
+  auto combine_few = [&](auto ch_tag, auto xcd_tag) {
+    constexpr int CH = decltype(ch_tag)::value;
+    constexpr bool kXcd = decltype(xcd_tag)::value;
+    const int mine = lane / G;
+    const float* ml = partials + (size_t)min(mine, p.nsplit - 1) * p.split_stride + G * D + 2 * (lane % G);
+    float m, l, as[kPerThread][CH];
+    if constexpr (kXcd) ld_xcd2(ml, m, l);
+    else ld_agent2(ml, m, l);
+#pragma unroll
+    for (int i = 0; i < CH; ++i) {
+      const float* src = partials + (size_t)min(i, p.nsplit - 1) * p.split_stride;
+#pragma unroll
+      for (int j = 0; j < kPerThread; ++j) {
+        const int idx = min((int)threadIdx.x + j * kThreads, G * D - 1);   // surplus threads repeat the last element
+        as[j][i] = kXcd ? ld_xcd(src + idx) : ld_agent(src + idx);
+      }
+    }
+    float M, L, c[CH];
+    weigh(mine < p.nsplit ? m : -INFINITY, mine < p.nsplit ? l : 0.f, ch_tag, M, L, c);
+#pragma unroll
+    for (int j = 0; j < kPerThread; ++j) {
+      float A = 0.f;
+#pragma unroll
+      for (int i = 0; i < CH; ++i) A = fmaf(as[j][i], c[i], A);
+      const int idx = (int)threadIdx.x + j * kThreads;
+      if (idx < G * D) finish(idx, M, L, A);
+    }
+  };
   constexpr int kTwo = kPerThread >= 2 ? 2 : 1;
-  if (p.nsplit <= 4) combine(std::integral_constant<int, 4>{}, std::integral_constant<int, kTwo>{});
-  else if (p.nsplit <= 8) combine(std::integral_constant<int, 8>{}, std::integral_constant<int, kTwo>{});
-  else combine(std::integral_constant<int, 16>{}, std::integral_constant<int, 1>{});
+  auto combine_all = [&](auto xcd_tag) {
+    if constexpr (kInner) {
+      if (p.nsplit <= 4) return combine_few(std::integral_constant<int, 4>{}, xcd_tag);
+      if (p.nsplit <= 8) return combine_few(std::integral_constant<int, 8>{}, xcd_tag);
+    }
+    if (p.nsplit <= 4) combine(std::integral_constant<int, 4>{}, std::integral_constant<int, kTwo>{}, xcd_tag);
+    else if (p.nsplit <= 8) combine(std::integral_constant<int, 8>{}, std::integral_constant<int, kTwo>{}, xcd_tag);
+    else combine(std::integral_constant<int, 16>{}, std::integral_constant<int, 1>{}, xcd_tag);
+  };
+  bool combined = false;
+  if constexpr (kMayShareXcd) {
+    if (one_xcd) combine_all(std::true_type{});
+    combined = one_xcd;
+  }
+  if (!combined) combine_all(std::false_type{});
   KK_TS(5);
-  if (threadIdx.x == 0) {
-    __hip_atomic_store(&p.ticket[unit], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // ready for the next launch
+  if (threadIdx.x == 0) {                        // the control words are ready for the next launch
+    if (one_xcd) __hip_atomic_store(&p.ticket_xcd[unit], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    else __hip_atomic_store(&p.ticket[unit], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    // (every workgroup of the head looked at this word before it took its ticket)
+    if (kMayShareXcd && p.arrivals != nullptr) __hip_atomic_store(&p.arrivals[unit], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (STEP) p.t_obs[unit] = t_old + 1;             // (every workgroup of the head read it before taking its ticket)
     if (STEP && grow) p.len[unit] = len;
     if (STEP && !grow && p.overflow != nullptr) *p.overflow = 1;
@@ -252,7 +428,7 @@ __global__ __launch_bounds__(kWavesPerBlock* kWave) void decode_attn_kernel(Deco
   __shared__ int s_last;
   __shared__ uint4 s_new[2 * RV];             // step mode: the appended token's K row, then its V row
 
-  const int unit = blockIdx.y, split = blockIdx.x;   // unit = b * Hkv + h
+  const int unit = blockIdx.z, split = blockIdx.y;   // unit = b * Hkv + h
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int grp = lane / LPS, sub = lane % LPS;
   KK_TS(0);
@@ -510,8 +686,8 @@ __global__ __launch_bounds__(kWavesPerBlock* kWave) void decode_attn_kernel(Deco
   __syncthreads();
   KK_TS(2);
 
-  combine_and_finish<T, D, G, kParts, STEP, kWavesPerBlock, false>(p, s_m, s_l, s_acc, G, G * D, &s_last, unit, split,
-                                                                  grow, len, t_old);
+  combine_and_finish<T, D, G, kParts, STEP, kWavesPerBlock, false, false, false>(p, s_m, s_l, s_acc, G, G * D, &s_last, unit, split,
+                                                                  grow, len, t_old, false);
 }
 
 // ---------------------------------------------------------------------------------------------------
@@ -556,34 +732,6 @@ __device__ __forceinline__ uint32_t pack_hi16(float lo_elem, float hi_elem) {   
   return (__builtin_bit_cast(uint32_t, lo_elem) >> 16) | (__builtin_bit_cast(uint32_t, hi_elem) & 0xFFFF0000u);
 }
 
-// a <- {a of the lower half, b of the lower half}, b <- {a of the upper half, b of the upper half} (lanes 0 .. 31 / 32 .. 63)
-__device__ __forceinline__ void swap_halves(float& a, float& b) {
-  const auto r = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(uint32_t, a), __builtin_bit_cast(uint32_t, b), false, false);
-  const uint32_t ra = r[0], rb = r[1];           // (a bit cast of a vector element itself reads element 0)
-  a = __builtin_bit_cast(float, ra);
-  b = __builtin_bit_cast(float, rb);
-}
-// the same for the rows of 16 lanes of each half: a <- {a row 0, b row 0, a row 2, b row 2}, b <- {a row 1, b row 1, a 3, b 3}
-__device__ __forceinline__ void swap_rows(float& a, float& b) {
-  const auto r = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(uint32_t, a), __builtin_bit_cast(uint32_t, b), false, false);
-  const uint32_t ra = r[0], rb = r[1];           // (a bit cast of a vector element itself reads element 0)
-  a = __builtin_bit_cast(float, ra);
-  b = __builtin_bit_cast(float, rb);
-}
-// maximum / sum over the lanes that hold the same head: equal l16 mod G in all four rows of 16 lanes
-template <int G, typename F>
-__device__ __forceinline__ float over_head_lanes(float x, F op) {
-  if constexpr (G <= 1) x = op(x, dpp_f32<0x121>(x));   // row_ror:1
-  if constexpr (G <= 2) x = op(x, dpp_f32<0x122>(x));   // row_ror:2
-  if constexpr (G <= 4) x = op(x, dpp_f32<0x124>(x));   // row_ror:4
-  x = op(x, dpp_f32<0x128>(x));                         // row_ror:8
-  float y = x;
-  swap_rows(x, y);
-  x = y = op(x, y);
-  swap_halves(x, y);
-  return op(x, y);
-}
-
 // The vector ALU's share.  A SIMD has two of these wavefronts and issues one 64-lane instruction in four cycles, so what a
 // tile costs beyond its loads is its instruction count: with every lane working out all 8 slots of its column (16 / G
 // lanes then do the same work) a tile took 430 instructions, 0.8 us alone and 1.6 us beside a second wavefront, most of
@@ -592,17 +740,18 @@ __device__ __forceinline__ float over_head_lanes(float x, F op) {
 // product is head g's sum over lane r's slots and the rows of a head are added once at the end (permlane swaps).
 // Addresses: a tile's base is uniform (scalar registers), a lane adds a 32-bit offset that K and V share.
 // Measured before / after, graph replays, one step (D 128): 64 heads x 852 slots (G 4) 10.6 / 9.8 us, 8 heads 7.9 / 7.0,
-// 128 heads x 828 16.6 / 15.7, 1024 heads x 852 (G 8) 81.9 / 80.8.  Of the 9.8 us the rows need 5 (28.6 MB), the reduction
-// over the wavefronts 0.5, publishing a split's result and taking the ticket 0.9, the combination 1.1, launch and drain 2.
+// 128 heads x 828 16.6 / 15.7, 1024 heads x 852 (G 8) 81.9 / 80.8.  Of the 9.6 us that the first takes now the rows need 5.3 (28.6 MB), the
+// reduction over the wavefronts 0.5, publishing a split's result and taking the ticket 0.8, the combination 0.8, launch and drain 2.
 //
 // MODE (how many tiles a wavefront has at most, kOneTile / kTwoTiles / kTileLoop):
 // - one tile (a split of 128 or 256 slots): no tile loop, no prefetch and no rescaling of the accumulators (the common
 //   steady-state shape);
 // - two tiles: everything is requested before the first wait.  The loop, which requests the second tile's rows when the
 //   first have landed, took 15.7 us for 128 heads x 828 slots and 16.3 us for 64 x 1683; this way 14.8 and 14.5;
-// - more: a loop that requests the next tile's rows while it works on the current one.
-constexpr int kTileLoop = 0, kOneTile = 1, kTwoTiles = 2;
-template <int D, int G, bool STEP, int MODE, int kMfmaWaves>
+// - more: a loop that requests the next tile's rows while it works on the current one; kSoloLoop is the same for heads that
+//   are not split, without the code that combines splits (a third of the kernel: 1024 heads x 852 slots 1 % slower with it).
+constexpr int kTileLoop = 0, kOneTile = 1, kTwoTiles = 2, kSoloLoop = 3;
+template <int D, int G, bool STEP, int kMode, int kMfmaWaves>
 __global__ __launch_bounds__(kMfmaWaves* kWave, 2) void decode_mfma_kernel(DecodeParams p) {
   using T = uint16_t;
   constexpr int ROWB = D * 2, CHUNKS = ROWB / 16, KS = D / 32, NTILE = D / 16;
@@ -610,12 +759,16 @@ __global__ __launch_bounds__(kMfmaWaves* kWave, 2) void decode_mfma_kernel(Decod
   constexpr int LOADS = TILE_BYTES / (kWave * 16);
   constexpr int kParts = kMfmaWaves;
   constexpr int NV = G >= 2 ? G / 2 : 1;         // slots of a tile whose weights one lane works out
+  constexpr bool kSolo = kMode == kSoloLoop;
+  constexpr int MODE = kSolo ? kTileLoop : kMode;
   constexpr bool ONE = MODE == kOneTile, TWO = MODE == kTwoTiles;
+  // (in the tile loop the combination is a smaller share of the step, and reading `arrivals` cost as much as it gave)
+  constexpr bool kMayShareXcd = ONE || TWO;
   extern __shared__ __align__(256) unsigned char smem_tiles[];   // [wave][two tile buffers]; later each wave's deposit
-  __shared__ int s_last;
+  __shared__ int s_last, s_one_xcd;
   __shared__ __align__(16) unsigned char s_new[2 * ROWB];       // step mode: the appended token's K row, V row
 
-  const int unit = blockIdx.y, split = blockIdx.x;
+  const int unit = blockIdx.z * gridDim.x + blockIdx.x, split = blockIdx.y;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int l16 = lane & 15, q = lane >> 4;
   KK_TS(0);
@@ -732,6 +885,10 @@ __global__ __launch_bounds__(kMfmaWaves* kWave, 2) void decode_mfma_kernel(Decod
     }
   }
 
+  // (the last wavefront, whose share is the shortest, behind its requests: they complete in order)
+  if (kMayShareXcd && p.arrivals != nullptr && wave == kMfmaWaves - 1 && lane == 0)
+    __hip_atomic_fetch_add(&p.arrivals[unit], 1ull << (8 * xcd_id()), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+
   // B operand of the score product: column l16 is head l16 mod G, this lane's 8 channels of every k-step
   bf16x8_t qb[KS];
   auto read_q = [&]() {                          // ONE: from this wavefront's LDS copy, once it has landed
@@ -765,8 +922,16 @@ __global__ __launch_bounds__(kMfmaWaves* kWave, 2) void decode_mfma_kernel(Decod
   // v_wait: the V rows have landed when at most that many requests are outstanding; negative: they have landed.
   // k_rows: the K operand (unless ONE).  lp_lane: log2(votes) of slot row_mine.  x_out: the group-mean logit of slot row_mine (of a `writer` lane), and the
   // return value whether this lane stores it.
+  // The first wavefront requests the head's `arrivals` in its last tile, when that tile's rows have landed, to have the
+  // word when the tile is done.
+  uint64_t seen = 0;
+  bool looked = !kMayShareXcd || p.arrivals == nullptr || wave != 0;   // uniform
+  auto look = [&]() {
+    if (!looked) seen = ld_arrivals(p, unit);
+    looked = true;
+  };
   auto compute = [&](int tbase, bool extra, int next, const bf16x8_t (&k_rows)[2][KS], float lp_lane, auto v_wait,
-                     float& x_out) -> bool {
+                     float& x_out, bool last) -> bool {
     constexpr int kVWait = decltype(v_wait)::value;
     const int n_live = extra ? 1 : max(0, min(kMTile, live_end - tbase));
     auto clear_masked_v = [&]() {
@@ -891,6 +1056,7 @@ __global__ __launch_bounds__(kMfmaWaves* kWave, 2) void decode_mfma_kernel(Decod
     if constexpr (kVWait >= 0) {                 // before any store is issued
       // (tied to the softmax sum, so that the wait is not scheduled ahead of the arithmetic it is meant to hide)
       asm volatile("s_waitcnt vmcnt(%1)" : "+v"(l_run) : "n"(kVWait) : "memory");
+      if (last) look();
       clear_masked_v();
     }
     // ---- O += P V with P = hi + lo in bf16.  The places of the slots that other lanes took hold the smallest normal
@@ -1026,9 +1192,9 @@ __global__ __launch_bounds__(kMfmaWaves* kWave, 2) void decode_mfma_kernel(Decod
       request_scalars(second, pv2, ls2);
       issue_rows(vbytes, Tb + TILE_BYTES, second);
       __builtin_amdgcn_sched_barrier(0);
-      const bool mine = compute(base, false, -1, kn, fast_log2((float)pv_next), kAwaitFirst, x);
+      const bool mine = compute(base, false, -1, kn, fast_log2((float)pv_next), kAwaitFirst, x, false);
       Vb = Tb + TILE_BYTES;
-      const bool mine2 = compute(second, false, -1, kreg, fast_log2((float)pv2), kAwaitAll, x2);
+      const bool mine2 = compute(second, false, -1, kreg, fast_log2((float)pv2), kAwaitAll, x2, true);
       publish(base, mine, x, ls_next);
       publish(second, mine2, x2, ls2);
     } else if (has_tile) {
@@ -1036,7 +1202,7 @@ __global__ __launch_bounds__(kMfmaWaves* kWave, 2) void decode_mfma_kernel(Decod
       issue_k(base, kn);
       request_scalars(base, pv_next, ls_next);
       issue_rows(vbytes, Tb, base);
-      const bool mine = compute(base, false, -1, kn, fast_log2((float)pv_next), kAwaitAll, x);
+      const bool mine = compute(base, false, -1, kn, fast_log2((float)pv_next), kAwaitAll, x, true);
       publish(base, mine, x, ls_next);
     }
     base = lim;
@@ -1050,7 +1216,7 @@ __global__ __launch_bounds__(kMfmaWaves* kWave, 2) void decode_mfma_kernel(Decod
       const uint32_t sa = (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void*)(s_sc + row_mine * 4);
       asm volatile("ds_read2_b32 %0, %1 offset1:64\n\ts_waitcnt lgkmcnt(0)" : "=v"(sc) : "v"(sa) : "memory");
       const float lp_lane = fast_log2((float)(int32_t)(uint32_t)sc);
-      own_store = compute(base, false, -1, kreg, lp_lane, kAwaitAll, own_x);
+      own_store = compute(base, false, -1, kreg, lp_lane, kAwaitAll, own_x, true);
       if constexpr (STEP) own_ema = ema(__builtin_bit_cast(float, (uint32_t)(sc >> 32)), own_x);
       base = lim;
     } else {
@@ -1073,7 +1239,7 @@ __global__ __launch_bounds__(kMfmaWaves* kWave, 2) void decode_mfma_kernel(Decod
       const float ls_old = ls_next;
       const int next = base + kTileStep;
       float x;
-      const bool mine = compute(base, false, next < wave_lim ? next : -1, kreg, lp_lane, kLanded, x);
+      const bool mine = compute(base, false, next < wave_lim ? next : -1, kreg, lp_lane, kLanded, x, next >= wave_lim);
       // After the second product: the compiler orders the V reads behind every outstanding memory operation,
       // and stores issued before them would be waited for.
       publish(base, mine, x, ls_old);
@@ -1105,7 +1271,7 @@ __global__ __launch_bounds__(kMfmaWaves* kWave, 2) void decode_mfma_kernel(Decod
       }
       __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
       __builtin_amdgcn_wave_barrier();
-      compute(0, true, -1, kreg, 0.f, kLanded, new_x);   // one vote: log2 = 0
+      compute(0, true, -1, kreg, 0.f, kLanded, new_x, false);   // one vote: log2 = 0
     }
   }
 
@@ -1160,6 +1326,10 @@ __global__ __launch_bounds__(kMfmaWaves* kWave, 2) void decode_mfma_kernel(Decod
       s_ml[wave * kPartStride + G + l16] = l_tot;
     }
   }
+  if (threadIdx.x == 0) {
+    look();                                      // (a wavefront without a tile)
+    s_one_xcd = kMayShareXcd && p.arrivals != nullptr && all_on_this_xcd(p, unit, seen);
+  }
   if constexpr (!ONE && STEP) asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the staged EMA state is in LDS
   __syncthreads();
   KK_TS(2);
@@ -1189,8 +1359,9 @@ __global__ __launch_bounds__(kMfmaWaves* kWave, 2) void decode_mfma_kernel(Decod
       p.log_s[ubase + len_old] = ema(-INFINITY, new_x);
     }
   }
-  combine_and_finish<T, D, G, kParts, STEP, kMfmaWaves, true>(p, s_ml, s_ml + G, s_acc, kPartStride, kPartStride, &s_last,
-                                                              unit, split, grow, len, t_old);
+  combine_and_finish<T, D, G, kParts, STEP, kMfmaWaves, true, kSolo, kMayShareXcd>(p, s_ml, s_ml + G, s_acc, kPartStride, kPartStride, &s_last,
+                                                              unit, split, grow, len, t_old,
+                                                              __builtin_amdgcn_readfirstlane(s_one_xcd) != 0);
 }
 
 template <typename T, int D, int G>
@@ -1200,7 +1371,8 @@ keepkv_status launch_decode(const DecodeParams& p, int units, bool step, bool va
   constexpr int RV = D * (int)sizeof(T) / 16;                       // 16-byte vectors per row
   constexpr int LPS = (G >= 8 && RV >= 16) ? RV / (RV >= 32 ? 2 : 1) : (RV >= 32 ? 16 : 8);
   constexpr int U = 4;
-  const dim3 grid(p.nsplit, units), block(kWavesPerBlock * kWave);
+  // (x, then y, is dealt first: with 8 heads along x the splits of a head come to one XCD, see all_on_this_xcd)
+  const dim3 grid = p.arrivals != nullptr ? dim3(8, p.nsplit, units / 8) : dim3(1, p.nsplit, units), block(kWavesPerBlock * kWave);
   if constexpr (sizeof(T) == 2) {
     if (!valu) {
       auto go = [&](auto waves_tag) -> keepkv_status {
@@ -1215,20 +1387,26 @@ keepkv_status launch_decode(const DecodeParams& p, int units, bool step, bool va
                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)tiles) == hipSuccess &&
             hipFuncSetAttribute((const void*)decode_mfma_kernel<D, G, true, kTileLoop, WV>,
                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)tiles) == hipSuccess &&
+            hipFuncSetAttribute((const void*)decode_mfma_kernel<D, G, true, kSoloLoop, WV>,
+                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)tiles) == hipSuccess &&
             hipFuncSetAttribute((const void*)decode_mfma_kernel<D, G, false, kOneTile, WV>,
                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)tiles) == hipSuccess &&
             hipFuncSetAttribute((const void*)decode_mfma_kernel<D, G, false, kTwoTiles, WV>,
                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)tiles) == hipSuccess &&
             hipFuncSetAttribute((const void*)decode_mfma_kernel<D, G, false, kTileLoop, WV>,
+                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)tiles) == hipSuccess &&
+            hipFuncSetAttribute((const void*)decode_mfma_kernel<D, G, false, kSoloLoop, WV>,
                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)tiles) == hipSuccess;
         if (!allowed) return KEEPKV_ERR_DEVICE;
         const dim3 mblock(WV * kWave);
         const int n_tiles = (p.per + WV * kMTile - 1) / (WV * kMTile);      // per wavefront, at most
         if (step && n_tiles == 1) decode_mfma_kernel<D, G, true, kOneTile, WV><<<grid, mblock, tiles, st>>>(p);
         else if (step && n_tiles == 2) decode_mfma_kernel<D, G, true, kTwoTiles, WV><<<grid, mblock, tiles, st>>>(p);
+        else if (step && p.nsplit == 1) decode_mfma_kernel<D, G, true, kSoloLoop, WV><<<grid, mblock, tiles, st>>>(p);
         else if (step) decode_mfma_kernel<D, G, true, kTileLoop, WV><<<grid, mblock, tiles, st>>>(p);
         else if (n_tiles == 1) decode_mfma_kernel<D, G, false, kOneTile, WV><<<grid, mblock, tiles, st>>>(p);
         else if (n_tiles == 2) decode_mfma_kernel<D, G, false, kTwoTiles, WV><<<grid, mblock, tiles, st>>>(p);
+        else if (p.nsplit == 1) decode_mfma_kernel<D, G, false, kSoloLoop, WV><<<grid, mblock, tiles, st>>>(p);
         else decode_mfma_kernel<D, G, false, kTileLoop, WV><<<grid, mblock, tiles, st>>>(p);
         return KEEPKV_OK;
       };
@@ -1280,8 +1458,18 @@ keepkv_status run_decode(const keepkv_layout* layout, const keepkv_cache* cache,
   p.q = q; p.k = cache->k; p.v = cache->v; p.votes = cache->votes; p.log_s = cache->log_s; p.born = cache->born; p.t_obs = cache->t_obs;
   p.len = cache->len; p.k_t = k_t; p.v_t = v_t; p.overflow = overflow;
   p.out = out; p.logits_out = logits_out; p.lse_out = lse_out;
-  p.partial = reinterpret_cast<float*>(reinterpret_cast<char*>(workspace) + pl.partial_off);
-  p.ticket = reinterpret_cast<int32_t*>(workspace);
+  char* const ws = reinterpret_cast<char*>(workspace);
+  p.partial = reinterpret_cast<float*>(ws + pl.partial_off);
+  p.ticket = reinterpret_cast<int32_t*>(ws);
+  p.arrivals = nullptr;
+  p.ticket_xcd = nullptr;
+  p.split_stride = layout->n_q_heads / layout->n_kv_heads * (layout->head_dim + 2);
+  if (pl.xcd_bytes != 0 && workspace_bytes >= pl.xcd_bytes) {   // (a smaller workspace has room for partial results without lines of their own)
+    p.arrivals = reinterpret_cast<uint64_t*>(ws + kArrivalsOff);
+    p.ticket_xcd = reinterpret_cast<int32_t*>(ws + kXcdTicketsOff);
+    p.split_stride = xcd_split_stride(layout);
+    p.partial = reinterpret_cast<float*>(align_up(reinterpret_cast<uintptr_t>(p.partial), kLine));
+  }
   p.n_kv_heads = layout->n_kv_heads; p.capacity = cache->capacity; p.nsplit = pl.nsplit; p.per = pl.per; p.waves = pl.waves; p.scale = layout->scale;
   p.len_hint = cache->len_hint > 0 ? cache->len_hint : 0;
   p.ln_alpha = (step && alpha > 0.f) ? logf(alpha) : -INFINITY;
@@ -1443,6 +1631,17 @@ static size_t decode_bytes(const keepkv_layout* L, long nsplit) {
   return kWorkspaceHead + align_up((size_t)L->batch * L->n_q_heads * nsplit * (L->head_dim + 2) * sizeof(float), 256);
 }
 
+// Partial results with cache lines of their own, for heads that are combined within an XCD.
+static size_t decode_xcd_bytes(const keepkv_layout* L, long nsplit) {
+  return kWorkspaceHead + kLine + align_up((size_t)L->batch * L->n_kv_heads * nsplit * xcd_split_stride(L) * sizeof(float), 256);
+}
+
+// The heads have to divide evenly among the XCDs, or some would idle; with 4 heads, say, half of them.
+static bool heads_fit_xcds(const keepkv_layout* L) {
+  const long units = (long)L->batch * L->n_kv_heads;
+  return units % 8 == 0 && units <= kMaxXcdUnits;
+}
+
 static DecodePlan make_plan(const keepkv_layout* L, int capacity, int force_per, int force_waves) {
   DecodePlan pl;
   const bool valu = L->dtype == KEEPKV_BF16 && force_waves == -1;
@@ -1461,6 +1660,8 @@ static DecodePlan make_plan(const keepkv_layout* L, int capacity, int force_per,
   pl.per = (int)per;
   pl.partial_off = kWorkspaceHead;
   pl.bytes = decode_bytes(L, ns);
+  const bool may_share = mfma && ns > 1 && ns <= kMaxLocalSplits && per <= 2L * waves * kMTile && heads_fit_xcds(L);
+  pl.xcd_bytes = may_share ? decode_xcd_bytes(L, ns) : 0;
   return pl;
 }
 
@@ -1472,6 +1673,7 @@ size_t decode_workspace_bytes(const keepkv_layout* L, int capacity) {
   long ns = (capacity + kMinSplit - 1) / kMinSplit;
   if (ns > most) ns = most;
   if (ns > 1 && decode_bytes(L, ns) > bytes) bytes = decode_bytes(L, ns);
+  if (ns > 1 && L->dtype == KEEPKV_BF16 && heads_fit_xcds(L) && decode_xcd_bytes(L, ns) > bytes) bytes = decode_xcd_bytes(L, ns);
   return bytes;
 }
 

@@ -105,6 +105,7 @@ struct DecodePlan {
   bool valu;          // a bf16 cache on the vector-ALU kernel (only by the caller's override)
   size_t partial_off; // float [B*Hq, nsplit, D + 2]
   size_t bytes;
+  size_t xcd_bytes;   // with room for combining within an XCD (0: not for this shape)
 };
 // force_per / force_waves: the caller's overrides (keepkv_cache.plan_slots_per_split / plan_wavefronts), 0 = none
 DecodePlan plan_decode(const keepkv_layout* L, int capacity, int force_per = 0, int force_waves = 0);
