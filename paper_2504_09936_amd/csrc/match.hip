@@ -379,14 +379,31 @@ __global__ __launch_bounds__(NW* kWave, 2) void match_mfma_kernel(MatchParams p)
   static_assert(VPK == 2 || VPK == 4, "fold_vals handles two or four values per k-step");
   const int n_blk = (n_keep + 31) / 32;
 
-  // values [ks * VPK, (ks + 1) * VPK) of one finished accumulator tile: scale, class maxima, block maximum
-  auto fold_vals = [&](int ks, const f32x16_t& od, int (&c)[16], int& gm) {
+  // values [ks * VPK, (ks + 1) * VPK) of one finished accumulator tile: scale, class maxima, block maximum.  The scaled values of
+  // an even block wait in `held` for those of the odd one behind it, and both enter their classes with one instruction.
+  // (Not in the first event's kernel of D 128, whose 256 registers do not hold them: with 56 bytes of spills it took 193 us
+  // instead of 186 for the batch-8 first event.  The prefill search of 64 heads x 8192 slots gains 6 us of 495, 24 heads x 4500 rows of D 64 0.7 of 16.)
+  constexpr bool kHold = CAUSAL || D == 64;
+  int held[2][16];
+#pragma unroll
+  for (int t = 0; t < 2; ++t)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) held[t][i] = 0;
+  auto fold_vals = [&](int ks, bool hold, const f32x16_t& od, int (&c)[16], int (&h)[16], int& gm) {
 #pragma unroll
     for (int i = ks * VPK; i < (ks + 1) * VPK; i += 2) {
       const int k0 = __builtin_bit_cast(int, od[i] * rn[i / 4][i % 4]);
       const int k1 = __builtin_bit_cast(int, od[i + 1] * rn[(i + 1) / 4][(i + 1) % 4]);
-      c[i] = imax(c[i], k0);
-      c[i + 1] = imax(c[i + 1], k1);
+      if (!kHold) {
+        c[i] = imax(c[i], k0);
+        c[i + 1] = imax(c[i + 1], k1);
+      } else if (hold) {
+        h[i] = k0;
+        h[i + 1] = k1;
+      } else {
+        asm("v_max3_i32 %0, %1, %2, %3" : "=v"(c[i]) : "v"(c[i]), "v"(h[i]), "v"(k0));
+        asm("v_max3_i32 %0, %1, %2, %3" : "=v"(c[i + 1]) : "v"(c[i + 1]), "v"(h[i + 1]), "v"(k1));
+      }
       if (i == 0) gm = imax(k0, k1);
       else asm("v_max3_i32 %0, %1, %2, %3" : "=v"(gm) : "v"(gm), "v"(k0), "v"(k1));   // kept in this order
     }
@@ -410,25 +427,28 @@ __global__ __launch_bounds__(NW* kWave, 2) void match_mfma_kernel(MatchParams p)
     // Explicit interleave: each MFMA is followed by the fold of VPK values of the previous column
     // block, and nothing may be scheduled across the fences, so the matrix pipe and the vector ALU of
     // this wavefront run side by side.
-    auto block = [&](int cbl, f32x16_t& nw0, f32x16_t& nw1, const f32x16_t& od0, const f32x16_t& od1) {
+    auto block = [&](int cbl, bool hold, f32x16_t& nw0, f32x16_t& nw1, const f32x16_t& od0, const f32x16_t& od1) {
       const f32x16_t zero = {0};
       // 1/|k_c| of the 16 columns that this lane's accumulator registers hold in block cbl
       const f32x4_t* rn_src = reinterpret_cast<const f32x4_t*>(s_rn + par * kStageCols + cbl * 32 + 4 * half);
       int gm0 = 0, gm1 = 0;
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks) {
+        // (requested ahead of the operand fragment: the wait for that one then does not wait for a younger request too;
+        // 1024 heads x 7372 x 820 1.2 % faster, as are the other shapes)
+        if (ks > 0 && (ks * VPK) % 4 == 0) rn[(ks * VPK) / 4 - 1] = rn_src[2 * ((ks * VPK) / 4 - 1)];
         const bf16x8_t bnext = (ks + 1 < KS) ? frag(cbl, ks + 1) : frag((cbl + 1) % BPS, 0);
         nw0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bq, e[0][ks], ks == 0 ? zero : nw0, 0, 0, 0);
         __builtin_amdgcn_sched_barrier(0);
-        fold_vals(ks, od0, cls[0], gm0);
+        fold_vals(ks, hold, od0, cls[0], held[0], gm0);
         __builtin_amdgcn_sched_barrier(0);
         nw1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bq, e[1][ks], ks == 0 ? zero : nw1, 0, 0, 0);
         __builtin_amdgcn_sched_barrier(0);
-        fold_vals(ks, od1, cls[1], gm1);
-        if (((ks + 1) * VPK) % 4 == 0) rn[((ks + 1) * VPK) / 4 - 1] = rn_src[2 * (((ks + 1) * VPK) / 4 - 1)];
+        fold_vals(ks, hold, od1, cls[1], held[1], gm1);
         __builtin_amdgcn_sched_barrier(0);
         bq = bnext;
       }
+      rn[3] = rn_src[6];
       fold_group(gm0, cb_prev, b1[0], b2[0], g1[0]);
       fold_group(gm1, cb_prev, b1[1], b2[1], g1[1]);
     };
@@ -436,8 +456,8 @@ __global__ __launch_bounds__(NW* kWave, 2) void match_mfma_kernel(MatchParams p)
     for (int cbl = 0; cbl < BPS; ++cbl) {
       const int cb = s * BPS + cbl;                           // global column block
       if (cb < n_blk) {                                       // uniform over the workgroup
-        if (cbl % 2 == 0) block(cbl, accA0, accA1, accB0, accB1);
-        else block(cbl, accB0, accB1, accA0, accA1);
+        if (cbl % 2 == 0) block(cbl, false, accA0, accA1, accB0, accB1);
+        else block(cbl, true, accB0, accB1, accA0, accA1);
         cb_prev = cb;
       }
     }
@@ -453,11 +473,11 @@ __global__ __launch_bounds__(NW* kWave, 2) void match_mfma_kernel(MatchParams p)
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
       if (even_last) {
-        fold_vals(ks, accA0, cls[0], gm0);
-        fold_vals(ks, accA1, cls[1], gm1);
+        fold_vals(ks, false, accA0, cls[0], held[0], gm0);
+        fold_vals(ks, false, accA1, cls[1], held[1], gm1);
       } else {
-        fold_vals(ks, accB0, cls[0], gm0);
-        fold_vals(ks, accB1, cls[1], gm1);
+        fold_vals(ks, false, accB0, cls[0], held[0], gm0);
+        fold_vals(ks, false, accB1, cls[1], held[1], gm1);
       }
     }
     fold_group(gm0, cb_prev, b1[0], b2[0], g1[0]);
