@@ -1,4 +1,5 @@
-"""ctypes binding of libkeepkv.so: argument marshalling only.
+"""Binding of libkeepkv.so: argument marshalling only (ctypes; the calls made once per layer and token through the
+CPython extension _pycall, built beside the library).
 
 Every function has the name and meaning of the C entry point declared in include/keepkv.h;
 tensors are torch tensors on the GPU (used here purely as device memory), passed down as raw
@@ -104,8 +105,20 @@ try:
     def _stream() -> int:
         return _raw_stream(_device())
 except ImportError:                      # a torch built without them
+    _device = torch.cuda.current_device
+
+    def _raw_stream(device: int) -> int:
+        return torch.cuda.current_stream(device).cuda_stream
+
     def _stream() -> int:
         return torch.cuda.current_stream().cuda_stream
+
+try:
+    from . import _pycall
+except ImportError as e:
+    raise ImportError(f"{e}: build the HIP library first (python -m paper_2504_09936_amd.build)") from e
+_pycall.bind(_raw_stream, _device, *(C.cast(getattr(_lib, "keepkv_" + f), C.c_void_p).value
+                                     for f in ("decode_step", "decode_step_static", "decode_attn", "score")))
 
 
 @dataclass
@@ -196,14 +209,11 @@ def workspace_init(workspace) -> None:
 
 
 def decode_step(layout: Layout, cache: Cache, q, k_t, v_t, out, logits_out, alpha: float, overflow, workspace) -> None:
-    _check(_lib.keepkv_decode_step(C.byref(layout.c()), C.byref(cache.c()), _ptr(q), _ptr(k_t), _ptr(v_t), _ptr(out),
-                                   _ptr(logits_out), alpha, _ptr(overflow), _ptr(workspace), _nbytes(workspace),
-                                   _stream()), "keepkv_decode_step")
+    _check(_pycall.decode_step(layout, cache, q, k_t, v_t, out, logits_out, alpha, overflow, workspace), "keepkv_decode_step")
 
 
 def decode_step_static(layout: Layout, cache: Cache, q, k_t, v_t, out, logits_out, alpha: float, overflow) -> None:
-    _check(_lib.keepkv_decode_step_static(C.byref(layout.c()), C.byref(cache.c()), _ptr(q), _ptr(k_t), _ptr(v_t),
-                                          _ptr(out), _ptr(logits_out), alpha, _ptr(overflow), _stream()),
+    _check(_pycall.decode_step_static(layout, cache, q, k_t, v_t, out, logits_out, alpha, overflow),
            "keepkv_decode_step_static")
 
 
@@ -213,15 +223,11 @@ def append(layout: Layout, cache: Cache, k_t, v_t, overflow=None) -> None:
 
 
 def decode_attn(layout: Layout, cache: Cache, q, out, logits_out, lse_out, workspace) -> None:
-    _check(_lib.keepkv_decode_attn(C.byref(layout.c()), C.byref(cache.c()), _ptr(q), _ptr(out), _ptr(logits_out),
-                                   _ptr(lse_out), _ptr(workspace),
-                                   0 if workspace is None else workspace.numel() * workspace.element_size(),
-                                   _stream()), "keepkv_decode_attn")
+    _check(_pycall.decode_attn(layout, cache, q, out, logits_out, lse_out, workspace), "keepkv_decode_attn")
 
 
 def score(layout: Layout, cache: Cache, logits, alpha: float) -> None:
-    _check(_lib.keepkv_score(C.byref(layout.c()), C.byref(cache.c()), _ptr(logits), alpha, _stream()),
-           "keepkv_score")
+    _check(_pycall.score(layout, cache, logits, alpha), "keepkv_score")
 
 
 def score_window(layout: Layout, cache: Cache, q_win, window: int, alpha: float, first_pos: int = -1) -> None:

@@ -1,15 +1,17 @@
-"""Compile csrc/*.hip for gfx950 into libkeepkv.so (in-tree, next to this file)."""
+"""Compile csrc/*.hip for gfx950 into libkeepkv.so, and csrc/pycall.cpp into _pycall.so (in-tree, next to this file)."""
 from __future__ import annotations
 
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libkeepkv.so")
+PYCALL = os.path.join(HERE, "_pycall.so")
 SOURCES = ["api.hip", "decode_attn.hip", "score_append.hip", "score_window.hip", "select.hip", "match.hip", "merge.hip", "probe.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-ffp-contract=off",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
@@ -36,12 +38,24 @@ def _compile(src: str, obj_dir: str, verbose: bool) -> str:
     return obj
 
 
+def _compile_pycall() -> None:
+    """The host-side CPython extension: no device code."""
+    cmd = [os.environ.get("CXX") or "g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-fvisibility=hidden", "-Wall",
+           "-I", sysconfig.get_paths()["include"], "-I", os.path.join(ROOT, "include"),
+           os.path.join(CSRC, "pycall.cpp"), "-o", PYCALL]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("compiling pycall.cpp failed:\n" + r.stderr)
+
+
 def build(verbose: bool = False, jobs: int = 6) -> str:
     """Always recompiles; returns the path of the shared library."""
     obj_dir = os.path.join(HERE, "_build")
     os.makedirs(obj_dir, exist_ok=True)
     with ThreadPoolExecutor(max_workers=jobs) as ex:
+        pycall = ex.submit(_compile_pycall)
         objs = list(ex.map(lambda s: _compile(s, obj_dir, verbose), SOURCES))
+        pycall.result()
     r = subprocess.run([_hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC", *objs, "-o", LIB],
                        capture_output=True, text=True)
     if r.returncode != 0:
