@@ -830,23 +830,12 @@ __global__ __launch_bounds__(kSmallWaves* kWave, 2) void match_small_kernel(Matc
   KS_TS(5);
 }
 
-// queue every live evicted row (f32 caches)
-__global__ void flag_all_kernel(const int32_t* __restrict__ n_evict, int32_t* flag_count, int32_t* flag_rows,
-                                int max_evict) {
-  const int unit = blockIdx.y;
-  const int n = n_evict[unit];
-  for (int j = blockIdx.x * blockDim.x + threadIdx.x; j < n; j += gridDim.x * blockDim.x) {
-    const int at = atomicAdd(flag_count, 1);
-    flag_rows[at] = unit * max_evict + j;
-  }
-}
-
-
 // ---------------------------------------------------------------------------------------------------
-// f64 evaluation of queued rows: threads stride over the retained keys (each thread evaluates whole keys,
+// f64 evaluation, of all rows (f32 caches, the kernel below) or of the queued ones (bf16 caches, further down).  f32 caches: threads
+// stride over the retained keys (each thread evaluates whole keys,
 // channels in index order, so the sums match an index-order f64 sum).  One workgroup per row; when the
-// queue is so short that the compute units would mostly idle (the steady state: a handful of rows), up to
-// kExactMaxParts workgroups per row, each over a contiguous share of the retained list.  Their results
+// rows are so few that the compute units would mostly idle (the steady state), up to
+// kExactMaxParts workgroups per row, each over a contiguous share of the retained list of 256 keys (one a thread) or more.  Their results
 // meet the way the decode splits do: device-scope stores, a ticket, the last one to arrive combines and
 // clears the ticket (the tickets are control words at the head of the workspace, zero between calls).
 constexpr int kExactMaxParts = 8;
@@ -876,19 +865,27 @@ __global__ __launch_bounds__(256) void match_exact_kernel(MatchParams p) {
   __shared__ double s_best[4];
   __shared__ int s_bestc[4];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int n_flag = *p.flag_count;
-  int rows_finished = 0;                 // (thread 0) queued rows whose result this workgroup has written
   const T* kall = reinterpret_cast<const T*>(p.k);
   constexpr int EPV = 16 / (int)sizeof(T), NV = D / EPV;
+  // (Rows are counted, not queued, which took a launch of its own, and a short list is not shared, which took a ticket: a period of
+  // 32 steps of 4 heads x 52 slots with its event 147.8 us with them, 145.4 without.)
+  const int n_rows = p.n_units * p.max_evict;
   int parts = 1;
   {
-    const int room = imin((int)gridDim.x, kExactResidentGeneric);
-    while (parts < kExactMaxParts && (long)n_flag * (parts * 2) <= (long)room) parts *= 2;
+    const int room = imin((int)gridDim.x, kExactResidentGeneric), cols = p.causal ? p.capacity : p.budget;
+    while (parts < kExactMaxParts && (long)n_rows * (parts * 2) <= (long)room && cols > parts * 256) parts *= 2;
   }
-  for (int w = blockIdx.x; w < n_flag * parts; w += gridDim.x) {
-    const int f = w / parts, part = w % parts;
-    const int o = p.flag_rows[f];
+  for (long w = blockIdx.x; w < (long)n_rows * parts; w += gridDim.x) {
+    const int o = (int)(w / parts), part = (int)(w % parts), f = o;
     const int unit = o / p.max_evict, j = o % p.max_evict;
+    if (j >= (p.causal ? p.len[unit] : p.n_evict[unit])) continue;      // (uniform over the workgroup, the same for all parts)
+    if (p.causal && j == 0) {              // no earlier key
+      if (tid == 0 && part == 0) {
+        p.match[o] = -1;
+        if (p.sim_out != nullptr) p.sim_out[o] = -INFINITY;
+      }
+      continue;
+    }
     const T* kunit = kall + (size_t)unit * p.capacity * D;
     // causal (the prefill pass): the row is slot j itself and its columns are the slots 0 .. j - 1
     const int32_t* keep = p.causal ? nullptr : p.keep_idx + (size_t)unit * p.budget;
@@ -995,11 +992,9 @@ __global__ __launch_bounds__(256) void match_exact_kernel(MatchParams p) {
       if (finish) {
         p.match[o] = (best > (double)p.threshold) ? best_c : -1;
         if (p.sim_out != nullptr) p.sim_out[o] = (float)best;
-        ++rows_finished;
       }
     }
   }
-  exact_exit(p, n_flag, rows_finished);
 }
 
 // ---------------------------------------------------------------------------------------------------
@@ -1038,21 +1033,6 @@ __global__ __launch_bounds__(256) void slot_rnorm_kernel(const T* __restrict__ k
   if (sub == 0) rn[(size_t)unit * capacity + r] = column_rnorm(ss, nonzero);
 }
 
-// queue every live row but the first (f32 caches: the f64 kernel decides all rows)
-__global__ void flag_all_causal_kernel(const int32_t* __restrict__ len, int32_t* flag_count, int32_t* flag_rows,
-                                       int32_t* near, float* sim_out, int capacity) {
-  const int unit = blockIdx.y;
-  const int n = len[unit];
-  for (int j = blockIdx.x * blockDim.x + threadIdx.x; j < n; j += gridDim.x * blockDim.x) {
-    if (j == 0) {
-      near[(size_t)unit * capacity] = -1;
-      if (sim_out != nullptr) sim_out[(size_t)unit * capacity] = -INFINITY;
-      continue;
-    }
-    const int at = atomicAdd(flag_count, 1);
-    flag_rows[at] = unit * capacity + j;
-  }
-}
 
 // The f64 kernels for bf16 caches.  Products of bf16 values are exact in f64 and so are their sums over the head
 // dimension (for any ordinary exponent spread), whatever the order, so a key's channels may be split over lanes:
@@ -1438,9 +1418,7 @@ extern "C" keepkv_status keepkv_prefill_match(const keepkv_layout* layout, const
                                                      : launch_causal<64>(p, cache->k, (unsigned)units, exact_blocks, st);
     if (rc != KEEPKV_OK) return rc;
   } else {
-    int bx = (cap + 255) / 256;
-    if (bx > 64) bx = 64;
-    flag_all_causal_kernel<<<dim3(bx, (unsigned)units), 256, 0, st>>>(cache->len, p.flag_count, p.flag_rows, near, sim_out, cap);
+    p.n_units = (int)units;
     if (layout->head_dim == 128) match_exact_kernel<float, 128><<<exact_blocks, 256, 0, st>>>(p);
     else match_exact_kernel<float, 64><<<exact_blocks, 256, 0, st>>>(p);
   }
@@ -1509,9 +1487,7 @@ extern "C" keepkv_status keepkv_match(const keepkv_layout* layout, const keepkv_
       else match_recheck_kernel<64><<<exact_blocks, 256, 0, st>>>(p);
     }
   } else {
-    int bx = (max_evict + 255) / 256;
-    if (bx > 64) bx = 64;
-    flag_all_kernel<<<dim3(bx, (unsigned)units), 256, 0, st>>>(n_evict, p.flag_count, p.flag_rows, max_evict);
+    p.n_units = (int)units;
     if (layout->head_dim == 128) match_exact_kernel<float, 128><<<exact_blocks, 256, 0, st>>>(p);
     else match_exact_kernel<float, 64><<<exact_blocks, 256, 0, st>>>(p);
   }
