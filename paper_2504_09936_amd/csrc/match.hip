@@ -338,6 +338,9 @@ __global__ __launch_bounds__(NW* kWave, 2) void match_mfma_kernel(MatchParams p)
     }
     ss_row[t] = ss + __shfl_xor(ss, 32);
   }
+  // wavefronts whose rows all lie beyond the last one only copy stages
+  // (they repeated the last row: with 1024 heads of 7372 rows, 14.4 blocks, the first event took 1 % longer)
+  const bool has_rows = rb * kRowsPerBlock + wave * kRowsPerWave < n_ev;
   const int rb_next = rb + p.per_unit;
   const bool more = !CAUSAL && rb_next < n_rb;   // uniform over the workgroup
 
@@ -455,7 +458,7 @@ __global__ __launch_bounds__(NW* kWave, 2) void match_mfma_kernel(MatchParams p)
 #pragma unroll
     for (int cbl = 0; cbl < BPS; ++cbl) {
       const int cb = s * BPS + cbl;                           // global column block
-      if (cb < n_blk) {                                       // uniform over the workgroup
+      if (cb < n_blk && has_rows) {                           // uniform over the wavefront
         if (cbl % 2 == 0) block(cbl, false, accA0, accA1, accB0, accB1);
         else block(cbl, true, accB0, accB1, accA0, accA1);
         cb_prev = cb;
