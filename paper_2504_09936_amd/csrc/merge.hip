@@ -23,7 +23,7 @@ namespace {
 
 constexpr int kGroupThreads = 1024;
 constexpr int kMaxBudget = 4096;
-constexpr int kMaxGroupShares = 8;        // workgroups that share one head's targets in the grouping kernel
+constexpr int kMaxGroupShares = 32;       // workgroups that share one head's targets in the grouping kernel
 typedef __attribute__((ext_vector_type(2))) uint16_t u16x2_t;
 constexpr int kRankMax = 256;             // longest group that is ordered by counting
 constexpr int kMaxEvict = 32768;          // positions in the evict list fit 16 bits
@@ -37,16 +37,19 @@ constexpr double kEllGuard = 1.0e-3;
 // A group longer than kRankMax would make that quadratic: one wavefront scans the head's match list in order
 // for it instead.  With few heads up to kMaxGroupShares workgroups share a head, each taking a range of the
 // targets: every one of them reads the whole match list, so none waits for another.
-// What bounds it: the latency of one workgroup's passes over the match list (three, of a list that stays in the L2).
+// What bounds it: the latency of one workgroup's steps (list, histogram, scan, places, ranks).
 // Measured (MI355X): 8 heads x 29491 entries, clustered keys, all matched: 275 us with a sorting network of one workgroup
-// per head, 103 with counting, 35 with eight workgroups per head; 1024 heads x 7372: 186 -> 90 us; 24 heads x about 3500 (D
-// 64): 40 -> 12 us.
+// per head, 103 with counting, 35 with eight workgroups per head, 20 with 32 (the ranks of lists of up to 230 members are most of the work) and
+// the list read once; 1024 heads x 7372: 186 -> 90 us, 24 heads x about 3500 (D 64): 40 -> 12 -> 10 us.
+// ITEMS: entries per thread that its registers hold from the histogram (the target and the place in the group that the add returned)
+// until the group's range is known: the list is requested once, all of it before the first wait.
+template <int ITEMS>
 __global__ __launch_bounds__(kGroupThreads) void merge_group_kernel(
     const int32_t* __restrict__ match, const int32_t* __restrict__ evict_idx, const int32_t* __restrict__ n_evict,
     const int32_t* __restrict__ votes, int32_t* __restrict__ start, int32_t* __restrict__ members,
     int64_t* __restrict__ dropped_votes, int capacity, int budget, int max_evict, int shares) {
   extern __shared__ __align__(16) uint16_t s_place[];   // [max_evict] positions in the evict list, grouped by target
-  __shared__ int s_cnt[kMaxBudget + 1];            // members per target; after the scan the next free place, then the end
+  __shared__ int s_cnt[kMaxBudget + 1];            // members per target; after the scan the group's first place
   __shared__ int s_wave[kGroupThreads / 64];
   __shared__ int s_long[kMaxEvict / kRankMax];     // targets of the long groups
   __shared__ long long s_drop;
@@ -69,32 +72,39 @@ __global__ __launch_bounds__(kGroupThreads) void merge_group_kernel(
   }
   __syncthreads();
   // histogram of targets, and the number of entries whose targets lie below this workgroup's; unmatched slots (of
-  // every shares-th batch here) give up their votes.  Loads of eight slots are issued together.
+  // every shares-th batch here) give up their votes.
   constexpr int kBatch = 8;
+  static_assert(ITEMS % kBatch == 0 && kMaxBudget <= 1 << 13 && kMaxEvict <= 1 << 16, "entries by batches; a target and a place in one word");
   long long drop = 0;
-  int below = 0, turn = 0;
-  for (int j0 = tid; j0 < n_ev; j0 += kBatch * kGroupThreads) {
-    const bool votes_here = dropped_votes != nullptr && turn == share;   // uniform over the workgroup
-    turn = turn + 1 == shares ? 0 : turn + 1;
-    int t[kBatch], pv[kBatch];
+  int below = 0;
+  int entry[ITEMS];                                // target; then target << 16 | place in the group, or -1
 #pragma unroll
-    for (int u = 0; u < kBatch; ++u) t[u] = mt[min(j0 + u * kGroupThreads, n_ev - 1)];
-    if (votes_here) {
-      int e[kBatch];
+  for (int b = 0; b < ITEMS; b += kBatch)
+    if (b * kGroupThreads < n_ev) {                // uniform over the workgroup
 #pragma unroll
-      for (int u = 0; u < kBatch; ++u) e[u] = ev[min(j0 + u * kGroupThreads, n_ev - 1)];
-#pragma unroll
-      for (int u = 0; u < kBatch; ++u) pv[u] = votes[(size_t)unit * capacity + e[u]];
+      for (int u = b; u < b + kBatch; ++u) entry[u] = mt[min(tid + u * kGroupThreads, n_ev - 1)];
     }
 #pragma unroll
-    for (int u = 0; u < kBatch; ++u) {
-      if (j0 + u * kGroupThreads < n_ev) {
-        if (t[u] >= t_lo && t[u] < t_hi) atomicAdd(&s_cnt[t[u]], 1);
-        else if (t[u] >= 0 && t[u] < t_lo) ++below;
-        else if (t[u] < 0 && votes_here) drop += pv[u];
+  for (int b = 0; b < ITEMS; b += kBatch)
+    if (b * kGroupThreads < n_ev) {
+      const bool votes_here = dropped_votes != nullptr && (b / kBatch) % shares == share;   // uniform over the workgroup
+      int pv[kBatch];
+      if (votes_here) {
+        int e[kBatch];
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u) e[u] = ev[min(tid + (b + u) * kGroupThreads, n_ev - 1)];
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u) pv[u] = votes[(size_t)unit * capacity + e[u]];
+      }
+#pragma unroll
+      for (int u = 0; u < kBatch; ++u) {
+        const int t = tid + (b + u) * kGroupThreads < n_ev ? entry[b + u] : kMaxBudget;
+        entry[b + u] = -1;
+        if (t >= t_lo && t < t_hi) entry[b + u] = t << 16 | atomicAdd(&s_cnt[t], 1);
+        else if (t >= 0 && t < t_lo) ++below;
+        else if (t < 0 && votes_here) drop += pv[u];
       }
     }
-  }
   // one LDS add per wavefront: adds to one word are served a lane at a time
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) {
@@ -139,26 +149,24 @@ __global__ __launch_bounds__(kGroupThreads) void merge_group_kernel(
   for (int r = r0; r < r1; ++r) {
     const int cnt = s_cnt[r];
     st[r] = base + run;
-    s_cnt[r] = run;                                  // from here on: where the group's next member goes
+    s_cnt[r] = run;                                  // from here on: the group's first place
     run += cnt;
   }
   if (tid == 0 && t_hi == budget) st[budget] = base + n_matched;
+  if (tid == 0) s_cnt[t_hi] = n_matched;             // (t_hi <= kMaxBudget)
   if (tid == 0 && s_drop != 0) atomicAdd((unsigned long long*)&dropped_votes[unit], (unsigned long long)s_drop);
   KM_TS(2);
   if (n_matched == 0) return;                       // uniform over the block
-  __syncthreads();                                  // cursors complete
+  __syncthreads();                                  // starts complete
 
-  for (int j0 = tid; j0 < n_ev; j0 += kBatch * kGroupThreads) {
-    int t[kBatch];
 #pragma unroll
-    for (int u = 0; u < kBatch; ++u) t[u] = mt[min(j0 + u * kGroupThreads, n_ev - 1)];
+  for (int b = 0; b < ITEMS; b += kBatch)
+    if (b * kGroupThreads < n_ev) {
 #pragma unroll
-    for (int u = 0; u < kBatch; ++u) {
-      const int j = j0 + u * kGroupThreads;
-      if (j < n_ev && t[u] >= t_lo && t[u] < t_hi) s_place[atomicAdd(&s_cnt[t[u]], 1)] = (uint16_t)j;
+      for (int u = b; u < b + kBatch; ++u)
+        if (entry[u] >= 0) s_place[s_cnt[entry[u] >> 16] + (entry[u] & 0xFFFF)] = (uint16_t)(tid + u * kGroupThreads);
     }
-  }
-  __syncthreads();                                  // s_cnt[r] is now the end of group r
+  __syncthreads();
   KM_TS(3);
 
   for (int i0 = tid; i0 < n_matched; i0 += kBatch * kGroupThreads) {
@@ -172,7 +180,7 @@ __global__ __launch_bounds__(kGroupThreads) void merge_group_kernel(
     }
 #pragma unroll
     for (int u = 0; u < kBatch; ++u) {
-      const int g0 = t[u] > t_lo ? s_cnt[t[u] - 1] : 0, g1 = s_cnt[t[u]];
+      const int g0 = s_cnt[t[u]], g1 = s_cnt[t[u] + 1];
       if (i0 + u * kGroupThreads >= n_matched || g1 - g0 > kRankMax) continue;
       // eight members per LDS read, two per instruction: min(max(j - o, 0), 1) counts the smaller ones.  The first
       // and the last eight may hold neighbours' members, which are replaced by the largest value.
@@ -198,7 +206,7 @@ __global__ __launch_bounds__(kGroupThreads) void merge_group_kernel(
   const int n_long = s_n_long;
   for (int l = wave; l < n_long; l += kGroupThreads / 64) {   // uniform over the wavefront
     const int r = s_long[l];
-    int at = r > t_lo ? s_cnt[r - 1] : 0;
+    int at = s_cnt[r];
     for (int j0 = 0; j0 < n_ev; j0 += kBatch * 64) {
       int t[kBatch];
 #pragma unroll
@@ -1051,16 +1059,22 @@ extern "C" keepkv_status keepkv_merge(const keepkv_layout* layout, const keepkv_
   int32_t* members = reinterpret_cast<int32_t*>(reinterpret_cast<char*>(workspace) + pl.member_off);
 
   const size_t place_bytes = ((size_t)max_evict * sizeof(uint16_t) + 15) / 16 * 16;   // (read 16 bytes at a time)
-  static const hipError_t attr = hipFuncSetAttribute((const void*)merge_group_kernel,
-                                                     hipFuncAttributeMaxDynamicSharedMemorySize, kMaxEvict * (int)sizeof(uint16_t));
-  if (attr != hipSuccess) return KEEPKV_ERR_DEVICE;
+  static const bool allowed = hipFuncSetAttribute((const void*)merge_group_kernel<8>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                                  8 * kGroupThreads * (int)sizeof(uint16_t)) == hipSuccess &&
+                              hipFuncSetAttribute((const void*)merge_group_kernel<32>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                                  kMaxEvict * (int)sizeof(uint16_t)) == hipSuccess;
+  if (!allowed) return KEEPKV_ERR_DEVICE;
   const bool direct = max_evict <= kDirectMaxEvict;   // the steady state: the apply kernel finds its members itself
   if (!direct) {
     int shares = (int)(256 / units);
     shares = shares < 1 ? 1 : (shares > kMaxGroupShares ? kMaxGroupShares : shares);
     if (shares > budget) shares = budget;
-    merge_group_kernel<<<units * shares, kGroupThreads, place_bytes, st>>>(
-        match, evict_idx, n_evict, src->votes, start, members, dropped_votes, src->capacity, budget, max_evict, shares);
+    auto group = [&](auto kernel) {
+      kernel<<<units * shares, kGroupThreads, place_bytes, st>>>(match, evict_idx, n_evict, src->votes, start, members, dropped_votes,
+                                                                 src->capacity, budget, max_evict, shares);
+    };
+    if (max_evict <= 8 * kGroupThreads) group(merge_group_kernel<8>);
+    else group(merge_group_kernel<32>);
   }
   MergeParams p;
   p.sk = src->k; p.sv = src->v; p.svotes = src->votes; p.slog_s = src->log_s; p.sborn = src->born; p.st_obs = src->t_obs; p.slen = src->len;
