@@ -386,8 +386,8 @@ __device__ __forceinline__ void merge_positions(const MergeParams& p, int unit, 
     o.fv = (float)kscale;
     if (mx > -INFINITY) {
       const double L = mx + log_f64(W / P);             // ln(sum p s_hat / sum p)
-      const double ell_bar = WE / W;                // sum w ln s_hat / W
-      if (!(fabs(ell_bar) < kEllGuard)) kscale = (L / ell_bar) / W;
+      // ell = WE / W = sum w ln s_hat / W: (L / ell) / W is L / WE (a division in f64 is some twenty instructions)
+      if (!(fabs(WE) < kEllGuard * W)) kscale = L / WE;
       o.n_r = n_c > 1 ? n_c : 1;
       o.log_s = (float)(L + term.of(o.n_r, p.ln_alpha));
     }
