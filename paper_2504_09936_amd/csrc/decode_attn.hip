@@ -1560,6 +1560,11 @@ static int resident_per_cu(int waves, int head_dim, int group) {
 // heads x 852 7.1 with four against 6.7 with seven.  Over 30 more shapes of one to eight heads and up to 2^20 slots: 0.8 %
 // slower than the best plan (8.6 % at most; 3.6 % and 20 % with one price for combining: one head of 8 query heads x 3405 slots
 // 12.0 us with 27 splits against 9.9 with 16, x 50000 32.3 with 112 against 29.4 with 63).
+// Combining within an XCD came after that fit and is cheaper than it says; a head that would not be split although its wavefronts have more
+// than one and a half tiles each is charged 0.35 us for that, which moves the line between one split and two or three where that measured
+// faster: 96 heads x 520 slots (D 64) 8.7 us whole and 7.9 in two splits, 128 x 700 10.2 and 8.7, 160 x 1300 17.8 and 15.6, 160 x 884 (D 128)
+// 21.9 and 20.1.  (More than that splits 96 x 480 too, 7.7 us whole and 8.2 in two; a lower price for the combination itself
+// also takes four splits for eight, 10 to 20 % slower at 8 heads x 1000.)
 constexpr int kMaxSplitWorkgroups = 512;
 constexpr int kMinSplit = 64;
 static void choose_split(const keepkv_layout* L, int capacity, long& per, int& waves) {
@@ -1592,6 +1597,8 @@ static void choose_split(const keepkv_layout* L, int capacity, long& per, int& w
       double t = full * round_of(res_max) + round_of(rest) + 1.7 * (rounds - 1.0) + (wv == 4 ? 0.46 : 0.0);
       if (n_split > 1.0)
         t += (n_split <= 4.0 ? 1.85 : n_split <= 8.0 ? 2.7 : 4.3 + 1.3 * elements * (double)(long)((n_split - 1.0) / 16.0)) + 0.011 * n_split;
+      else if (2 * tiles > 3 * wv)
+        t += 0.35;                                 // (see above)
       if (t < best) {
         best = t;
         per = cand;
