@@ -34,11 +34,12 @@ N_REPLAY = 5               # timed replays of the K-step graph; the median is re
 MFMA_BF16_PEAK_TFLOPS = 2500.0
 
 
-def decode_kernel_name(head_dim: int, group: int, step: bool, slots_per_split: int, wavefronts: int) -> str:
+def decode_kernel_name(head_dim: int, group: int, step: bool, slots_per_split: int, wavefronts: int, n_split: int = 1) -> str:
     """The matrix-core decode kernel's instance for a launch plan: its fourth template argument is 1 or 2 where a wavefront
-    has at most that many tiles of 32 slots, 0 for the tile loop."""
+    has at most that many tiles of 32 slots; of the tile loops, 0 is that of heads in one split and 3 that of split ones."""
     tiles = -(-slots_per_split // (wavefronts * 32))
-    return f"decode_mfma_kernel<{head_dim},{group},{'true' if step else 'false'},{tiles if tiles <= 2 else 0},{wavefronts}>"
+    mode = tiles if tiles <= 2 else (0 if n_split == 1 else 3)
+    return f"decode_mfma_kernel<{head_dim},{group},{'true' if step else 'false'},{mode},{wavefronts}>"
 
 
 def traffic_from_profile(workload: str, kernel: str):
@@ -632,7 +633,7 @@ def main():
     if bf16 and args.decode_wavefronts == -1:
         kernel_instance = "decode_attn_kernel (vector ALU, bf16)"
     elif bf16:
-        kernel_instance = decode_kernel_name(D, Hq // H, not args.unfused, per_, wv_)
+        kernel_instance = decode_kernel_name(D, Hq // H, not args.unfused, per_, wv_, ns_)
     else:
         kernel_instance = "decode_attn_kernel"
     traffic = traffic_from_profile(w.name, kernel_instance)

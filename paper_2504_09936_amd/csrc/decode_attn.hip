@@ -169,20 +169,29 @@ __device__ __forceinline__ float row_reduce(float x, F op) {
 // marks it (kArriveMark, compare-and-swap on the incomplete word), and a marked word stays marked, so that those who look later
 // use device scope too.
 // Measured through memory / within the XCD (graph replays, a step; the weights below counted in): 64 heads x 852 slots in four
-// splits 9.9 / 9.6 us, 8 heads in seven 6.6 / 6.2, 128 heads x 828 in two 14.7 / 14.6.
+// splits 9.9 / 9.6 us, 8 heads in seven 6.6 / 6.2, 8 heads x 3385 in sixteen 9.25 / 8.5, 128 heads x 828 in two 14.7 / 14.6.  Arriving
+// behind the copies of the query rows (whose address translation it then waits for) made short last splits look in vain: 8 heads x
+// 1180 slots in six 8.0 us, 7.1 so, 7.4 through memory.
 constexpr uint64_t kArriveMark = 1ull << 63;
-constexpr int kMaxLocalSplits = 127;            // a byte of `arrivals`, less the mark
+constexpr int kMaxLocalSplits = 16;             // (at most 127: a byte of `arrivals`, less the mark)
 __device__ __forceinline__ int xcd_id() { return __builtin_amdgcn_s_getreg(20 | (3 << 11)); }   // XCC_ID[3:0]
 __device__ __forceinline__ uint64_t ld_arrivals(const DecodeParams& p, int unit) {
   return __hip_atomic_load(&p.arrivals[unit], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-// v: the word as last read.  One thread per workgroup.
+// v: the word as last read.  One thread per workgroup.  A workgroup with a short split may be done before the others of its head have
+// arrived; it looks a few times more before it gives up.
+constexpr int kLooks = 6;
 __device__ __forceinline__ bool all_on_this_xcd(const DecodeParams& p, int unit, uint64_t v) {
   const uint64_t here = (uint64_t)p.nsplit << (8 * xcd_id());
+  int looks = 0;
   while (v != here && !(v & kArriveMark)) {
     int sum = 0;
     for (int x = 0; x < 64; x += 8) sum += (int)(v >> x) & 255;
     if (sum >= p.nsplit) break;                  // complete, on several XCDs
+    if (looks++ < kLooks) {
+      v = ld_arrivals(p, unit);
+      continue;
+    }
     // still incomplete: mark it (at most nsplit attempts fail, one for each arrival)
     if (__hip_atomic_compare_exchange_strong(&p.arrivals[unit], &v, v | kArriveMark, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
                                              __HIP_MEMORY_SCOPE_AGENT))
@@ -396,6 +405,8 @@ __device__ __forceinline__ void combine_and_finish(const DecodeParams& p, const 
     if constexpr (kInner) {
       if (p.nsplit <= 4) return combine_few(std::integral_constant<int, 4>{}, xcd_tag);
       if (p.nsplit <= 8) return combine_few(std::integral_constant<int, 8>{}, xcd_tag);
+      if constexpr (G <= 4)
+        if (p.nsplit <= 16) return combine_few(std::integral_constant<int, 16>{}, xcd_tag);
     }
     if (p.nsplit <= 4) combine(std::integral_constant<int, 4>{}, std::integral_constant<int, kTwo>{}, xcd_tag);
     else if (p.nsplit <= 8) combine(std::integral_constant<int, 8>{}, std::integral_constant<int, kTwo>{}, xcd_tag);
@@ -761,7 +772,7 @@ __device__ __forceinline__ uint32_t pack_hi16(float lo_elem, float hi_elem) {   
 //   first have landed, took 15.7 us for 128 heads x 828 slots and 16.3 us for 64 x 1683; this way 14.8 and 14.5;
 // - more: a loop that requests the next tile's rows while it works on the current one; kSoloLoop is the same for heads that
 //   are not split, without the code that combines splits (a third of the kernel: 1024 heads x 852 slots 1 % slower with it).
-constexpr int kTileLoop = 0, kOneTile = 1, kTwoTiles = 2, kSoloLoop = 3;
+constexpr int kSoloLoop = 0, kOneTile = 1, kTwoTiles = 2, kTileLoop = 3;
 template <int D, int G, bool STEP, int kMode, int kMfmaWaves>
 __global__ __launch_bounds__(kMfmaWaves* kWave, 2) void decode_mfma_kernel(DecodeParams p) {
   using T = uint16_t;
@@ -783,9 +794,16 @@ __global__ __launch_bounds__(kMfmaWaves* kWave, 2) void decode_mfma_kernel(Decod
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int l16 = lane & 15, q = lane >> 4;
   KK_TS(0);
+  // this workgroup has arrived (the last wavefront, whose share is the shortest; with one tile ahead of everything, so that a workgroup
+  // whose split is short does not look too early)
+  auto arrive = [&]() {
+    if (kMayShareXcd && p.arrivals != nullptr && wave == kMfmaWaves - 1 && lane == 0)
+      __hip_atomic_fetch_add(&p.arrivals[unit], 1ull << (8 * xcd_id()), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  };
   const int len_old = p.len[unit];
   const int t_old = STEP ? p.t_obs[unit] : 0;   // used at the very end only
   const int start = split * p.per;
+  if constexpr (ONE) arrive();
   const bool takes_new = STEP && split == p.nsplit - 1 && wave == kMfmaWaves - 1;
   if (takes_new) {                             // asynchronous copy of (k_t, v_t) into LDS, awaited after the loop
     const size_t at = (size_t)unit * ROWB;
@@ -896,9 +914,8 @@ __global__ __launch_bounds__(kMfmaWaves* kWave, 2) void decode_mfma_kernel(Decod
     }
   }
 
-  // (the last wavefront, whose share is the shortest, behind its requests: they complete in order)
-  if (kMayShareXcd && p.arrivals != nullptr && wave == kMfmaWaves - 1 && lane == 0)
-    __hip_atomic_fetch_add(&p.arrivals[unit], 1ull << (8 * xcd_id()), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  // (with two tiles behind the requests, which it would hold up)
+  if constexpr (TWO) arrive();
 
   // B operand of the score product: column l16 is head l16 mod G, this lane's 8 channels of every k-step
   bf16x8_t qb[KS];

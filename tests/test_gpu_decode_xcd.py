@@ -23,11 +23,12 @@ def _state(kk, lay, cap, n):
     return c
 
 
-# heads a multiple of 8 and at most two tiles a wavefront; (64, 6400, 64): more workgroups than the chip holds, so that the
-# first ones of a head are done before its last ones start
+# heads a multiple of 8 and at most two tiles a wavefront; 256 heads: more workgroups than the chip
+# holds, so that the first ones of a head may be done before its last ones start; 1200 slots: a short last split, which looks early
 @pytest.mark.parametrize("G,D,heads,cap,per,waves", [(4, 128, 64, 884, 0, 0), (4, 128, 8, 884, 128, 8), (8, 64, 16, 300, 64, 4),
                                                      (1, 128, 8, 700, 96, 4), (2, 64, 8, 2000, 512, 8), (8, 128, 64, 600, 256, 4),
-                                                     (4, 128, 16, 1100, 64, 8), (4, 64, 64, 6400, 64, 4)])
+                                                     (4, 128, 16, 1000, 64, 8), (4, 64, 256, 700, 64, 4), (4, 128, 8, 1200, 224, 8),
+                                                     (2, 128, 8, 1000, 64, 8), (8, 128, 8, 1700, 128, 8)])
 def test_same_bits_as_through_memory(G, D, heads, cap, per, waves):
     kk = U.kk()
     lay = kk.Layout(heads // 8, 8 * G, 8, D, kk.BF16, D ** -0.5)
