@@ -34,11 +34,21 @@ N_REPLAY = 5               # timed replays of the K-step graph; the median is re
 MFMA_BF16_PEAK_TFLOPS = 2500.0
 
 
-def decode_kernel_name(head_dim: int, group: int, step: bool, slots_per_split: int, wavefronts: int, n_split: int = 1) -> str:
-    """The matrix-core decode kernel's instance for a launch plan: its fourth template argument is 1 or 2 where a wavefront
-    has at most that many tiles of 32 slots; of the tile loops, 0 is that of heads in one split and 3 that of split ones."""
-    tiles = -(-slots_per_split // (wavefronts * 32))
-    mode = tiles if tiles <= 2 else (0 if n_split == 1 else 3)
+def decode_kernel_name(head_dim: int, group: int, step: bool, slots_per_split: int, wavefronts: int, n_split: int | None = None,
+                       heads: int = 0) -> str:
+    """The matrix-core decode kernel's instance for a launch plan.  Its fourth template argument, for at most one tile of 32 slots a
+    wavefront / two / more: 4 / 5 / 0 for unsplit heads, 6 / 2 / 3 for splits that meet through memory, 1 / 7 / - for those that may meet
+    within an XCD.  Without n_split and heads: what splits of one (1) and two tiles (2) and whole heads of more (0) usually are."""
+    tiles = min(3, -(-slots_per_split // (wavefronts * 32)))
+    if n_split is None:
+        mode = (1, 2, 0)[tiles - 1]
+    elif n_split == 1:
+        mode = (4, 5, 0)[tiles - 1]
+    else:
+        workgroups = heads * n_split
+        pays = tiles == 1 or tiles == 2 and n_split <= 4 and (workgroups >= 192 if head_dim == 64 else n_split > 2 and workgroups >= 256)
+        may = heads % 8 == 0 and heads <= 2048 and n_split <= 16
+        mode = (1, 7)[tiles - 1] if may and pays else (6, 2, 3)[tiles - 1]
     return f"decode_mfma_kernel<{head_dim},{group},{'true' if step else 'false'},{mode},{wavefronts}>"
 
 
@@ -633,7 +643,7 @@ def main():
     if bf16 and args.decode_wavefronts == -1:
         kernel_instance = "decode_attn_kernel (vector ALU, bf16)"
     elif bf16:
-        kernel_instance = decode_kernel_name(D, Hq // H, not args.unfused, per_, wv_, ns_)
+        kernel_instance = decode_kernel_name(D, Hq // H, not args.unfused, per_, wv_, ns_, B * H)
     else:
         kernel_instance = "decode_attn_kernel"
     traffic = traffic_from_profile(w.name, kernel_instance)

@@ -17,6 +17,7 @@
 #include <mutex>
 
 #include <type_traits>
+#include <utility>
 
 #include "kk_common.hpp"
 
@@ -100,7 +101,7 @@ __device__ __forceinline__ float ld_agent(const float* p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// loads of what another workgroup of this XCD wrote (see all_on_this_xcd): they miss L1, L2 serves them
+// loads of what another workgroup of this XCD wrote (see all_on_this_xcd): L1 holds none of these lines, so L2 serves them
 __device__ __forceinline__ float ld_xcd(const float* p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
@@ -168,10 +169,8 @@ __device__ __forceinline__ float row_reduce(float x, F op) {
 // other workgroup of the head sees the same word and does the same, because a workgroup that finds the word incomplete
 // marks it (kArriveMark, compare-and-swap on the incomplete word), and a marked word stays marked, so that those who look later
 // use device scope too.
-// Measured through memory / within the XCD (graph replays, a step; the weights below counted in): 64 heads x 852 slots in four
-// splits 9.9 / 9.6 us, 8 heads in seven 6.6 / 6.2, 8 heads x 3385 in sixteen 9.25 / 8.5, 128 heads x 828 in two 14.7 / 14.6.  Arriving
-// behind the copies of the query rows (whose address translation it then waits for) made short last splits look in vain: 8 heads x
-// 1180 slots in six 8.0 us, 7.1 so, 7.4 through memory.
+// What it gives stands at xcd_pays.  Arriving behind the copies of the query rows (whose address translation it then waits for) made short
+// last splits look in vain: 8 heads x 1180 slots in six 8.0 us, 7.1 so, 7.4 through memory.
 constexpr uint64_t kArriveMark = 1ull << 63;
 constexpr int kMaxLocalSplits = 16;             // (at most 127: a byte of `arrivals`, less the mark)
 __device__ __forceinline__ int xcd_id() { return __builtin_amdgcn_s_getreg(20 | (3 << 11)); }   // XCC_ID[3:0]
@@ -230,37 +229,44 @@ __device__ __forceinline__ void combine_and_finish(const DecodeParams& p, const 
   };
 
   float* const partials = p.partial + (size_t)unit * p.nsplit * p.split_stride;   // this head's splits
-  // kInner: a lane's head is lane mod G for all of its elements, and what the parts weigh in that head is the same for
-  // every channel, so lane i works out the weight of part i / G and the lanes of a head hand them around through a table of the wavefront's
-  // own in LDS: one exponential per lane instead of one per part and element.  weigh(): n parts; m, l: those of part
-  // lane / G (lowest and 0 beyond n); leaves the head's M and L and the n weights.
+  // kInner: a lane's head is lane mod G for all of its elements, and what the splits weigh in that head is the same for
+  // every channel, so lane i works out the weight of split i / G and the lanes of a head hand them around through a table of the wavefront's
+  // own in LDS: one exponential per lane instead of one per split and element.  weigh(): n splits; m, l: those of split
+  // lane / G (-inf and 0 beyond nsplit); leaves the head's M, its L (added up in the order of the splits) and the n weights.
+  // (Not for the parts of a workgroup, whose maxima LDS holds at hand: the maximum over lanes, the exponential and the table
+  // are one chain of latencies there, and an unsplit step of 100 to 300 slots took 0.1 us longer with them.)
   const int lane = threadIdx.x & 63;
-  float* const s_c = const_cast<float*>(s_acc) + (threadIdx.x >> 6) * acc_stride + G * D + 16;   // [G][n], behind this wavefront's deposit
+  float* const s_c = const_cast<float*>(s_acc) + (threadIdx.x >> 6) * acc_stride + G * D + 16;   // 2 x [G][n], behind this wavefront's deposit
   auto weigh = [&](float m, float l, auto n_tag, float& M, float& L, float (&c)[decltype(n_tag)::value]) {
     constexpr int n = decltype(n_tag)::value;
     static_assert(n % 4 == 0 && n * G <= kWave, "one weight per lane");
     M = over_head_lanes<G>(m, [](float a, float b) { return fmaxf(a, b); });
     const float mine = lane < n * G ? fast_exp2(m - M) : 0.f;
-    L = over_head_lanes<G>(l * mine, [](float a, float b) { return a + b; });
-    if (lane < n * G) s_c[(lane % G) * n + lane / G] = mine;
+    if (lane < n * G) {
+      s_c[(lane % G) * n + lane / G] = mine;
+      s_c[n * G + (lane % G) * n + lane / G] = l;
+    }
+    L = 0.f;
 #pragma unroll
     for (int i = 0; i < n; i += 4) {
       const float4 t = *reinterpret_cast<const float4*>(s_c + (lane % G) * n + i);
+      const float4 u = *reinterpret_cast<const float4*>(s_c + n * G + (lane % G) * n + i);
       c[i] = t.x; c[i + 1] = t.y; c[i + 2] = t.z; c[i + 3] = t.w;
+      L = fmaf(u.w, t.w, fmaf(u.z, t.z, fmaf(u.y, t.y, fmaf(u.x, t.x, L))));
     }
   };
-  float M_mine = kLowest, L_mine = 0.f, c_mine[kInner ? kParts : 1];
-  if constexpr (kInner) {
-    const bool held = lane < kParts * G;
-    const int at = (held ? lane / G : 0) * ml_stride + lane % G;
-    weigh(held ? s_m[at] : kLowest, held ? s_l[at] : 0.f, std::integral_constant<int, kParts>{}, M_mine, L_mine, c_mine);
-  }
   for (int idx = threadIdx.x; idx < G * D; idx += kThreads) {
     const int g = head_of(idx);
-    float M = M_mine, L = L_mine, A = 0.f;
+    float M = kLowest, L = 0.f, A = 0.f;
     if constexpr (kInner) {
 #pragma unroll
-      for (int w = 0; w < kParts; ++w) A = fmaf(s_acc[w * acc_stride + idx], c_mine[w], A);
+      for (int w = 0; w < kParts; ++w) M = fmaxf(M, s_m[w * ml_stride + g]);
+#pragma unroll
+      for (int w = 0; w < kParts; ++w) {
+        const float c = fast_exp2(s_m[w * ml_stride + g] - M);
+        L = fmaf(s_l[w * ml_stride + g], c, L);
+        A = fmaf(s_acc[w * acc_stride + idx], c, A);
+      }
     } else {                                     // a wavefront's elements are of one head: lane i of a row weighs part i
       // (sixteen exponentials per element before: 32 steps of 4 heads x 52 .. 84 slots and their event 145.4 us, now 143.3)
       static_assert(kInner || (kParts == 16 && D % kWave == 0), "one weight a lane");
@@ -423,7 +429,7 @@ __device__ __forceinline__ void combine_and_finish(const DecodeParams& p, const 
     if (one_xcd) __hip_atomic_store(&p.ticket_xcd[unit], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     else __hip_atomic_store(&p.ticket[unit], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     // (every workgroup of the head looked at this word before it took its ticket)
-    if (kMayShareXcd && p.arrivals != nullptr) __hip_atomic_store(&p.arrivals[unit], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (kMayShareXcd) __hip_atomic_store(&p.arrivals[unit], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (STEP) p.t_obs[unit] = t_old + 1;             // (every workgroup of the head read it before taking its ticket)
     if (STEP && grow) p.len[unit] = len;
     if (STEP && !grow && p.overflow != nullptr) *p.overflow = 1;
@@ -450,7 +456,7 @@ __global__ __launch_bounds__(kWavesPerBlock* kWave) void decode_attn_kernel(Deco
   __shared__ int s_last;
   __shared__ uint4 s_new[2 * RV];             // step mode: the appended token's K row, then its V row
 
-  const int unit = blockIdx.z, split = blockIdx.y;   // unit = b * Hkv + h
+  const int unit = blockIdx.y, split = blockIdx.x;   // unit = b * Hkv + h
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int grp = lane / LPS, sub = lane % LPS;
   KK_TS(0);
@@ -765,14 +771,16 @@ __device__ __forceinline__ uint32_t pack_hi16(float lo_elem, float hi_elem) {   
 // 128 heads x 828 16.6 / 15.7, 1024 heads x 852 (G 8) 81.9 / 80.8.  Of the 9.6 us that the first takes now the rows need 5.3 (28.6 MB), the
 // reduction over the wavefronts 0.5, publishing a split's result and taking the ticket 0.8, the combination 0.8, launch and drain 2.
 //
-// MODE (how many tiles a wavefront has at most, kOneTile / kTwoTiles / kTileLoop):
+// kMode: how many tiles a wavefront has at most, and where the splits of a head meet.
 // - one tile (a split of 128 or 256 slots): no tile loop, no prefetch and no rescaling of the accumulators (the common
 //   steady-state shape);
 // - two tiles: everything is requested before the first wait.  The loop, which requests the second tile's rows when the
 //   first have landed, took 15.7 us for 128 heads x 828 slots and 16.3 us for 64 x 1683; this way 14.8 and 14.5;
-// - more: a loop that requests the next tile's rows while it works on the current one; kSoloLoop is the same for heads that
-//   are not split, without the code that combines splits (a third of the kernel: 1024 heads x 852 slots 1 % slower with it).
-constexpr int kSoloLoop = 0, kOneTile = 1, kTwoTiles = 2, kTileLoop = 3;
+// - more: a loop that requests the next tile's rows while it works on the current one.
+// A launch fetches code that it does not run, too, so there are instances without what they cannot need: Solo for heads that are not
+// split (without the combination 1024 heads x 852 slots 82.3 us and with it 83.0, 8 heads x 113 slots 4.0 and 4.35), Mem for splits that meet through memory, Xcd for
+// those that may meet within an XCD (36 heads x 334 slots in four splits, which cannot: 6.5 us without its code, 6.95 with it).
+constexpr int kLoopSolo = 0, kOneXcd = 1, kTwoMem = 2, kLoopMem = 3, kOneSolo = 4, kTwoSolo = 5, kOneMem = 6, kTwoXcd = 7, kModes = 8;
 template <int D, int G, bool STEP, int kMode, int kMfmaWaves>
 __global__ __launch_bounds__(kMfmaWaves* kWave, 2) void decode_mfma_kernel(DecodeParams p) {
   using T = uint16_t;
@@ -781,29 +789,27 @@ __global__ __launch_bounds__(kMfmaWaves* kWave, 2) void decode_mfma_kernel(Decod
   constexpr int LOADS = TILE_BYTES / (kWave * 16);
   constexpr int kParts = kMfmaWaves;
   constexpr int NV = G >= 2 ? G / 2 : 1;         // slots of a tile whose weights one lane works out
-  constexpr bool kSolo = kMode == kSoloLoop;
-  constexpr int MODE = kSolo ? kTileLoop : kMode;
-  constexpr bool ONE = MODE == kOneTile, TWO = MODE == kTwoTiles;
-  // (in the tile loop the combination is a smaller share of the step, and reading `arrivals` cost as much as it gave)
-  constexpr bool kMayShareXcd = ONE || TWO;
+  constexpr bool ONE = kMode == kOneXcd || kMode == kOneMem || kMode == kOneSolo;
+  constexpr bool TWO = kMode == kTwoXcd || kMode == kTwoMem || kMode == kTwoSolo;
+  constexpr bool LOOP = !ONE && !TWO;
+  constexpr bool kSolo = kMode == kOneSolo || kMode == kTwoSolo || kMode == kLoopSolo;
+  constexpr bool kMayShareXcd = kMode == kOneXcd || kMode == kTwoXcd;
   extern __shared__ __align__(256) unsigned char smem_tiles[];   // [wave][two tile buffers]; later each wave's deposit
   __shared__ int s_last, s_one_xcd;
   __shared__ __align__(16) unsigned char s_new[2 * ROWB];       // step mode: the appended token's K row, V row
 
-  const int unit = blockIdx.z * gridDim.x + blockIdx.x, split = blockIdx.y;
+  const int unit = kMayShareXcd ? (int)(blockIdx.z * 8 + blockIdx.x) : (int)blockIdx.y;
+  const int split = kMayShareXcd ? blockIdx.y : blockIdx.x;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int l16 = lane & 15, q = lane >> 4;
   KK_TS(0);
-  // this workgroup has arrived (the last wavefront, whose share is the shortest; with one tile ahead of everything, so that a workgroup
-  // whose split is short does not look too early)
-  auto arrive = [&]() {
-    if (kMayShareXcd && p.arrivals != nullptr && wave == kMfmaWaves - 1 && lane == 0)
-      __hip_atomic_fetch_add(&p.arrivals[unit], 1ull << (8 * xcd_id()), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  };
   const int len_old = p.len[unit];
   const int t_old = STEP ? p.t_obs[unit] : 0;   // used at the very end only
   const int start = split * p.per;
-  if constexpr (ONE) arrive();
+  // This workgroup has arrived: ahead of every request, so that a workgroup whose split is short does not look too early (and by the
+  // last wavefront, whose share is the shortest: its rows land behind this).
+  if (kMayShareXcd && wave == kMfmaWaves - 1 && lane == 0)
+    __hip_atomic_fetch_add(&p.arrivals[unit], 1ull << (8 * xcd_id()), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   const bool takes_new = STEP && split == p.nsplit - 1 && wave == kMfmaWaves - 1;
   if (takes_new) {                             // asynchronous copy of (k_t, v_t) into LDS, awaited after the loop
     const size_t at = (size_t)unit * ROWB;
@@ -906,16 +912,13 @@ __global__ __launch_bounds__(kMfmaWaves* kWave, 2) void decode_mfma_kernel(Decod
     pv = (p.votes + ubase + tbase)[at];
     if constexpr (STEP) ls = (p.log_s + ubase + tbase)[at];
   };
-  if constexpr (MODE == kTileLoop) {
+  if constexpr (LOOP) {
     if (has_tile) {
       issue_k(base, kn);
       issue_rows(vbytes, Vb, base);
       request_scalars(base, pv_next, ls_next);
     }
   }
-
-  // (with two tiles behind the requests, which it would hold up)
-  if constexpr (TWO) arrive();
 
   // B operand of the score product: column l16 is head l16 mod G, this lane's 8 channels of every k-step
   bf16x8_t qb[KS];
@@ -953,7 +956,7 @@ __global__ __launch_bounds__(kMfmaWaves* kWave, 2) void decode_mfma_kernel(Decod
   // The first wavefront requests the head's `arrivals` in its last tile, when that tile's rows have landed, to have the
   // word when the tile is done.
   uint64_t seen = 0;
-  bool looked = !kMayShareXcd || p.arrivals == nullptr || wave != 0;   // uniform
+  bool looked = !kMayShareXcd || wave != 0;   // uniform
   auto look = [&]() {
     if (!looked) seen = ld_arrivals(p, unit);
     looked = true;
@@ -971,7 +974,7 @@ __global__ __launch_bounds__(kMfmaWaves* kWave, 2) void decode_mfma_kernel(Decod
       }
     };
     if constexpr (kVWait < 0) clear_masked_v();
-    if (MODE == kTileLoop && next >= 0) {
+    if (LOOP && next >= 0) {
       // the next tile: K rows and scalars into registers, V rows into the other buffer (after the clearing
       // stores above: the compiler orders LDS stores behind outstanding copies into LDS)
       issue_k(next, kn);
@@ -1356,7 +1359,7 @@ __global__ __launch_bounds__(kMfmaWaves* kWave, 2) void decode_mfma_kernel(Decod
   }
   if (threadIdx.x == 0) {
     look();                                      // (a wavefront without a tile)
-    s_one_xcd = kMayShareXcd && p.arrivals != nullptr && all_on_this_xcd(p, unit, seen);
+    s_one_xcd = kMayShareXcd && all_on_this_xcd(p, unit, seen);
   }
   if constexpr (!ONE && STEP) asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the staged EMA state is in LDS
   __syncthreads();
@@ -1392,6 +1395,15 @@ __global__ __launch_bounds__(kMfmaWaves* kWave, 2) void decode_mfma_kernel(Decod
                                                               __builtin_amdgcn_readfirstlane(s_one_xcd) != 0);
 }
 
+template <int D, int G, int WAVES, int... kMode>
+bool allow_lds(int bytes, std::integer_sequence<int, kMode...>) {
+  auto allow = [&](const void* kernel) {
+    return hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes) == hipSuccess;
+  };
+  return ((allow((const void*)decode_mfma_kernel<D, G, true, kMode, WAVES>) &&
+           allow((const void*)decode_mfma_kernel<D, G, false, kMode, WAVES>)) && ...);
+}
+
 template <typename T, int D, int G>
 keepkv_status launch_decode(const DecodeParams& p, int units, bool step, bool valu, hipStream_t st) {
   // 8 lanes per slot (16 channels each at D = 128 bf16) halves the cross-lane reduction work; the
@@ -1400,43 +1412,34 @@ keepkv_status launch_decode(const DecodeParams& p, int units, bool step, bool va
   constexpr int LPS = (G >= 8 && RV >= 16) ? RV / (RV >= 32 ? 2 : 1) : (RV >= 32 ? 16 : 8);
   constexpr int U = 4;
   // (x, then y, is dealt first: with 8 heads along x the splits of a head come to one XCD, see all_on_this_xcd)
-  const dim3 grid = p.arrivals != nullptr ? dim3(8, p.nsplit, units / 8) : dim3(1, p.nsplit, units), block(kWavesPerBlock * kWave);
+  const dim3 grid = p.arrivals != nullptr ? dim3(8, p.nsplit, units / 8) : dim3(p.nsplit, units), block(kWavesPerBlock * kWave);
   if constexpr (sizeof(T) == 2) {
     if (!valu) {
       auto go = [&](auto waves_tag) -> keepkv_status {
         constexpr int WV = decltype(waves_tag)::value;
         constexpr size_t tiles = (size_t)WV * 2 * kMTile * D * 2 + (size_t)WV * mfma_stage_bytes(D, G);
         // 64 or 128 KB of tile buffers at D = 128, the per-wavefront staging of queries and scalars, plus the
-        // kernel's static LDS: allow it explicitly (once per process and instance)
-        static const bool allowed =
-            hipFuncSetAttribute((const void*)decode_mfma_kernel<D, G, true, kOneTile, WV>,
-                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)tiles) == hipSuccess &&
-            hipFuncSetAttribute((const void*)decode_mfma_kernel<D, G, true, kTwoTiles, WV>,
-                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)tiles) == hipSuccess &&
-            hipFuncSetAttribute((const void*)decode_mfma_kernel<D, G, true, kTileLoop, WV>,
-                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)tiles) == hipSuccess &&
-            hipFuncSetAttribute((const void*)decode_mfma_kernel<D, G, true, kSoloLoop, WV>,
-                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)tiles) == hipSuccess &&
-            hipFuncSetAttribute((const void*)decode_mfma_kernel<D, G, false, kOneTile, WV>,
-                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)tiles) == hipSuccess &&
-            hipFuncSetAttribute((const void*)decode_mfma_kernel<D, G, false, kTwoTiles, WV>,
-                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)tiles) == hipSuccess &&
-            hipFuncSetAttribute((const void*)decode_mfma_kernel<D, G, false, kTileLoop, WV>,
-                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)tiles) == hipSuccess &&
-            hipFuncSetAttribute((const void*)decode_mfma_kernel<D, G, false, kSoloLoop, WV>,
-                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)tiles) == hipSuccess;
+        // kernel's static LDS: allow it explicitly (once per process, for all instances)
+        static const bool allowed = allow_lds<D, G, WV>((int)tiles, std::make_integer_sequence<int, kModes>{});
         if (!allowed) return KEEPKV_ERR_DEVICE;
         const dim3 mblock(WV * kWave);
+        auto launch = [&](auto step_tag, auto mode_tag) -> keepkv_status {
+          decode_mfma_kernel<D, G, decltype(step_tag)::value, decltype(mode_tag)::value, WV><<<grid, mblock, tiles, st>>>(p);
+          return KEEPKV_OK;
+        };
         const int n_tiles = (p.per + WV * kMTile - 1) / (WV * kMTile);      // per wavefront, at most
-        if (step && n_tiles == 1) decode_mfma_kernel<D, G, true, kOneTile, WV><<<grid, mblock, tiles, st>>>(p);
-        else if (step && n_tiles == 2) decode_mfma_kernel<D, G, true, kTwoTiles, WV><<<grid, mblock, tiles, st>>>(p);
-        else if (step && p.nsplit == 1) decode_mfma_kernel<D, G, true, kSoloLoop, WV><<<grid, mblock, tiles, st>>>(p);
-        else if (step) decode_mfma_kernel<D, G, true, kTileLoop, WV><<<grid, mblock, tiles, st>>>(p);
-        else if (n_tiles == 1) decode_mfma_kernel<D, G, false, kOneTile, WV><<<grid, mblock, tiles, st>>>(p);
-        else if (n_tiles == 2) decode_mfma_kernel<D, G, false, kTwoTiles, WV><<<grid, mblock, tiles, st>>>(p);
-        else if (p.nsplit == 1) decode_mfma_kernel<D, G, false, kSoloLoop, WV><<<grid, mblock, tiles, st>>>(p);
-        else decode_mfma_kernel<D, G, false, kTileLoop, WV><<<grid, mblock, tiles, st>>>(p);
-        return KEEPKV_OK;
+        auto by_tiles = [&](auto step_tag) -> keepkv_status {
+          const bool solo = p.nsplit == 1, xcd = p.arrivals != nullptr;
+          if (n_tiles == 1 && solo) return launch(step_tag, std::integral_constant<int, kOneSolo>{});
+          if (n_tiles == 1 && xcd) return launch(step_tag, std::integral_constant<int, kOneXcd>{});
+          if (n_tiles == 1) return launch(step_tag, std::integral_constant<int, kOneMem>{});
+          if (n_tiles == 2 && solo) return launch(step_tag, std::integral_constant<int, kTwoSolo>{});
+          if (n_tiles == 2 && xcd) return launch(step_tag, std::integral_constant<int, kTwoXcd>{});
+          if (n_tiles == 2) return launch(step_tag, std::integral_constant<int, kTwoMem>{});
+          if (solo) return launch(step_tag, std::integral_constant<int, kLoopSolo>{});
+          return launch(step_tag, std::integral_constant<int, kLoopMem>{});
+        };
+        return step ? by_tiles(std::true_type{}) : by_tiles(std::false_type{});
       };
       if (p.waves == 8) return go(std::integral_constant<int, 8>{});
       return go(std::integral_constant<int, 4>{});
@@ -1677,6 +1680,19 @@ static bool heads_fit_xcds(const keepkv_layout* L) {
   return units % 8 == 0 && units <= kMaxXcdUnits;
 }
 
+// Where combining within an XCD pays.  Measured through memory / within the XCD, us: with one tile a wavefront always, or it makes no
+// difference (250 shapes, 4 % on average): 8 heads x 852 slots in seven splits 6.5 / 6.2, 64 x 852 in four 10.0 / 9.6, 32 x 1497 in eight 9.9 / 9.4.
+// With two tiles the tail is a smaller share of the step, and how soon a head's workgroups have all arrived matters more.  D 128: 64 x 1487
+// in four splits, which fill the chip, 15.4 / 14.8, but 48 x 1084 in four 10.0 / 10.3, 128 x 476 in two 10.5 / 11.0, 32 x 3284 in eight 15.0 / 15.5.  D 64,
+// half the bytes beside the same tail: 64 x 1384 in four 9.15 / 8.97, 96 x 684 in two 8.5 / 8.3, but 32 x 1084 in four 7.56 / 7.72, 32 x 2584 in eight
+// 9.1 / 9.3.  In the tile loop reading `arrivals` cost as much as it gave.
+static bool xcd_pays(const keepkv_layout* L, long nsplit, long per, int waves) {
+  const long workgroups = (long)L->batch * L->n_kv_heads * nsplit;
+  if (per <= (long)waves * kMTile) return true;
+  if (nsplit > 4) return false;
+  return L->head_dim == 64 ? workgroups >= 192 : nsplit > 2 && workgroups >= 256;
+}
+
 static DecodePlan make_plan(const keepkv_layout* L, int capacity, int force_per, int force_waves) {
   DecodePlan pl;
   const bool valu = L->dtype == KEEPKV_BF16 && force_waves == -1;
@@ -1696,7 +1712,7 @@ static DecodePlan make_plan(const keepkv_layout* L, int capacity, int force_per,
   pl.partial_off = kWorkspaceHead;
   pl.bytes = decode_bytes(L, ns);
   const bool may_share = mfma && ns > 1 && ns <= kMaxLocalSplits && per <= 2L * waves * kMTile && heads_fit_xcds(L);
-  pl.xcd_bytes = may_share ? decode_xcd_bytes(L, ns) : 0;
+  pl.xcd_bytes = may_share && (force_per > 0 || xcd_pays(L, ns, per, waves)) ? decode_xcd_bytes(L, ns) : 0;   // (the caller's splits wherever they can)
   return pl;
 }
 

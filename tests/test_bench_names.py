@@ -19,6 +19,16 @@ def test_decode_kernel_name():
     assert bench.decode_kernel_name(128, 8, True, 896, 4) == "decode_mfma_kernel<128,8,true,0,4>"
 
 
+def test_decode_kernel_name_by_where_the_splits_meet():
+    def mode(*a):
+        return int(bench.decode_kernel_name(*a).split(",")[3])
+    assert [mode(128, 4, True, per, 8, 1, 64) for per in (64, 256, 288, 512, 544)] == [4, 4, 5, 5, 0]              # unsplit
+    assert [mode(128, 4, True, 224, 8, 4, heads) for heads in (64, 8, 36, 2056)] == [1, 1, 6, 6]                    # heads by eights
+    assert [mode(128, 4, True, per, 8, 17, 8) for per in (224, 448, 544)] == [6, 2, 3]                              # more than sixteen splits
+    assert [mode(128, 4, True, 384, 8, ns, heads) for ns, heads in ((4, 64), (4, 56), (2, 128), (8, 32))] == [7, 2, 2, 2]
+    assert [mode(64, 4, True, 384, 8, ns, heads) for ns, heads in ((4, 64), (4, 40), (2, 96), (8, 32))] == [7, 2, 7, 2]
+
+
 @pytest.mark.parametrize("name", ["llama3_8b", "llama3_70b"])
 def test_recorded_traffic_is_that_of_the_planned_instance(name):
     w = W.CONFIGS[name]

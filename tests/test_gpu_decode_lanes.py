@@ -44,6 +44,28 @@ def _attend(w, lay, c, q, waves, per):
     return U.to_host(out)
 
 
+@pytest.mark.parametrize("waves,cap", [(4, 120), (8, 250), (4, 250), (8, 500)])
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("G", [1, 2, 4, 8])
+def test_unsplit(G, D, waves, cap):
+    """Heads that are not split, in one and in two tiles a wavefront: a kernel without combination."""
+    kk = U.kk()
+    w = _workload(G, D).scaled(context=cap)
+    g = np.random.default_rng(G * 100 + D + cap)
+    lens, _ = I._ragged_lens(g, w.batch, w.n_kv_heads, cap, cap, 1)
+    lay, c = I._steady_state(w, cap, 29, lens)
+    c.plan_wavefronts, c.plan_slots_per_split = waves, (cap + 31) // 32 * 32
+    q = W.make_query(w, 29, 7)
+    out = torch.zeros(w.batch, w.n_q_heads, D, dtype=lay.torch_dtype, device="cuda")
+    lse = torch.zeros(w.batch, w.n_q_heads, device="cuda")
+    kk.decode_attn(lay, c, U.to_device(q, w.dtype), out, None, lse, None)
+    o_ref, lse_ref, _ = O.attend(U.download(c), q.astype(np.float64), w.scale)
+    assert U.storage_err_rows(U.to_host(out), o_ref, w.dtype).max() <= I.TOL
+    live = np.repeat(lens > 0, G, axis=1)
+    np.testing.assert_allclose(lse.cpu().numpy()[live], lse_ref[live], rtol=1e-4, atol=2e-3)
+    I._check_steps(w, lay, c, None, list(range(w.batch * w.n_kv_heads)), 2, 29, hint=waves == 8, tag=(G, D, waves, cap))
+
+
 @pytest.mark.parametrize("D", [64, 128])
 @pytest.mark.parametrize("G", [1, 2, 4, 8])
 def test_rising_maximum(G, D):
