@@ -837,13 +837,20 @@ __global__ __launch_bounds__(kSmallWaves* kWave, 2) void match_small_kernel(Matc
 // f64 evaluation, of all rows (f32 caches, the kernel below) or of the queued ones (bf16 caches, further down).  f32 caches: threads
 // stride over the retained keys (each thread evaluates whole keys,
 // channels in index order, so the sums match an index-order f64 sum).  One workgroup per row; when the
-// rows are so few that the compute units would mostly idle (the steady state), up to
-// kExactMaxParts workgroups per row, each over a contiguous share of the retained list of 256 keys (one a thread) or more.  Their results
+// live rows are so few that the compute units would mostly idle (the steady state), up to
+// kExactMaxParts workgroups per row, each over a contiguous share of the retained list, as long as a thread of an undivided list
+// would have a second key to go through (exact_shares).  Their results
 // meet the way the decode splits do: device-scope stores, a ticket, the last one to arrive combines and
 // clears the ticket (the tickets are control words at the head of the workspace, zero between calls).
 constexpr int kExactMaxParts = 8;
 constexpr int kExactResident = 512;     // workgroups of the bf16 f64 kernel that run at once (two per compute unit); size of the partial array
-constexpr int kExactResidentGeneric = 256;   // the generic kernel's registers allow one per compute unit
+constexpr int kExactResidentGeneric = 256;   // f32 rows are shared while every share finds a compute unit of its own
+// most shares that a row of `cols` columns is worth
+__host__ __device__ constexpr int exact_shares(int cols) {
+  int n = 1;
+  while (n < kExactMaxParts && cols > n * 256) n *= 2;
+  return n;
+}
 struct ExactPartial {
   unsigned long long best_bits;
   int best_c, pad;
@@ -870,18 +877,65 @@ __global__ __launch_bounds__(256) void match_exact_kernel(MatchParams p) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const T* kall = reinterpret_cast<const T*>(p.k);
   constexpr int EPV = 16 / (int)sizeof(T), NV = D / EPV;
-  // (Rows are counted, not queued, which took a launch of its own, and a short list is not shared, which took a ticket: a period of
-  // 32 steps of 4 heads x 52 slots with its event 147.8 us with them, 145.4 without.)
-  const int n_rows = p.n_units * p.max_evict;
-  int parts = 1;
-  {
-    const int room = imin((int)gridDim.x, kExactResidentGeneric), cols = p.causal ? p.capacity : p.budget;
-    while (parts < kExactMaxParts && (long)n_rows * (parts * 2) <= (long)room && cols > parts * 256) parts *= 2;
+  // The live rows are counted and not queued, which took a launch of its own.  Where the heads differ, thread t adds up those of `per`
+  // heads, and s_first[t] is how many come before them; the usual case of equally many in every head needs neither that nor a search.
+  // Measured, D 64, queued / stepping over every row that the caches have room for / this way: 4 heads of 32 live rows x 820 keys in caches of
+  // 16384 slots 12.9 / 26.5 / 10.6 us, 4 heads of 32 rows x 52 keys in caches of 84 10.2 / 7.6 / 5.7.
+  __shared__ int s_first[257], s_wave[4];
+  __shared__ int s_unit, s_row;
+  auto live = [&](int u) {
+    return u >= p.n_units ? 0 : imax(p.causal ? imin(p.len[u], p.capacity) : imin(p.n_evict[u], p.max_evict), 0);
+  };
+  const int per = (p.n_units + 255) / 256, n_first = __builtin_amdgcn_readfirstlane(live(0));
+  bool same = true;
+  for (int u = lane; u < p.n_units; u += 64) same = same && live(u) == n_first;
+  same = __all(same);
+  int n_rows = p.n_units * n_first;
+  if (!same) {
+    int n = 0;
+    for (int u = tid * per; u < (tid + 1) * per; ++u) n += live(u);
+    int upto = n;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+      const int o = __shfl_up(upto, off);
+      if (lane >= off) upto += o;
+    }
+    if (lane == 63) s_wave[wave] = upto;
+    __syncthreads();
+    for (int w = 0; w < wave; ++w) upto += s_wave[w];
+    s_first[tid + 1] = upto;
+    if (tid == 0) s_first[0] = 0;
+    __syncthreads();
+    n_rows = __builtin_amdgcn_readfirstlane(s_first[256]);
   }
-  for (long w = blockIdx.x; w < (long)n_rows * parts; w += gridDim.x) {
-    const int o = (int)(w / parts), part = (int)(w % parts), f = o;
-    const int unit = o / p.max_evict, j = o % p.max_evict;
-    if (j >= (p.causal ? p.len[unit] : p.n_evict[unit])) continue;      // (uniform over the workgroup, the same for all parts)
+  int parts = exact_shares(p.causal ? p.capacity : p.budget);
+  while (parts > 1 && (long)n_rows * parts > (long)imin((int)gridDim.x, kExactResidentGeneric)) parts /= 2;
+  const unsigned n_work = (unsigned)n_rows * parts;        // (below 2^31: shared only if at most kExactResidentGeneric)
+  for (unsigned w = blockIdx.x; w < n_work; w += gridDim.x) {
+    const int f = (int)(w / (unsigned)parts), part = (int)(w % (unsigned)parts);
+    __syncthreads();                      // previous row's shared values are no longer read
+    int unit, j;
+    if (same) {
+      unit = f / n_first;
+      j = f % n_first;
+    } else {
+      if (s_first[tid] <= f && f < s_first[tid + 1]) {      // one thread
+        int u = tid * per, at = f - s_first[tid];
+        for (int i = 1; i < per; ++i, ++u) {
+          const int n = live(u);
+          if (at < n) break;
+          at -= n;
+        }
+        s_unit = u;
+        s_row = at;
+      }
+      __syncthreads();
+      unit = s_unit;
+      j = s_row;
+    }
+    unit = __builtin_amdgcn_readfirstlane(unit);
+    j = __builtin_amdgcn_readfirstlane(j);
+    const int o = unit * p.max_evict + j;
     if (p.causal && j == 0) {              // no earlier key
       if (tid == 0 && part == 0) {
         p.match[o] = -1;
@@ -896,7 +950,6 @@ __global__ __launch_bounds__(256) void match_exact_kernel(MatchParams p) {
     const int n_cols = p.causal ? j : p.budget;
     const int share = (n_cols + parts - 1) / parts;
     const int c_lo = part * share, c_hi = imin(n_cols, c_lo + share);
-    __syncthreads();                      // previous row's shared values are no longer read
     for (int d = tid; d < D; d += 256) {
       if constexpr (sizeof(T) == 2) s_e[d] = (double)bf16_to_f32(reinterpret_cast<const uint16_t*>(kunit)[(size_t)e * D + d]);
       else s_e[d] = (double)kunit[(size_t)e * D + d];
@@ -914,6 +967,10 @@ __global__ __launch_bounds__(256) void match_exact_kernel(MatchParams p) {
       uint4 rowv[NV];
 #pragma unroll
       for (int v = 0; v < NV; ++v) rowv[v] = reinterpret_cast<const uint4*>(kc)[v];   // one round trip per key
+      // Left to itself the compiler either loaded a vector when the one before was used up or held the row s_e in registers, two
+      // workgroups per compute unit at D 64 and one at 128; with the loads kept ahead it is four and two (24 heads of 616 rows x 52 keys, D 64,
+      // 80 us, now 52; 8 heads of 512 x 512, D 128, 164, now 142).
+      __builtin_amdgcn_sched_barrier(0);
       double dot = 0.0, ss_c = 0.0;
 #pragma unroll
       for (int v = 0; v < NV; ++v) {
@@ -1355,6 +1412,16 @@ keepkv_status launch_bf16(const MatchParams& p, const void* k, unsigned units, h
   return KEEPKV_OK;
 }
 
+// f32 caches: a workgroup for every row and share that there can be, as many as run at once: four (D 64) or two (D 128) per compute unit.
+// (The workgroups of a sixteenth of the rows, a rule for queues, walked the 128 rows of an event of 4 heads x 84 slots two by two.)
+void launch_exact_f32(MatchParams p, size_t units, int head_dim, int cols, hipStream_t st) {
+  const size_t work = units * (size_t)p.max_evict * (size_t)exact_shares(cols), resident = head_dim == 128 ? 512 : 1024;
+  const int blocks = (int)(work < resident ? work : resident);
+  p.n_units = (int)units;
+  if (head_dim == 128) match_exact_kernel<float, 128><<<blocks, 256, 0, st>>>(p);
+  else match_exact_kernel<float, 64><<<blocks, 256, 0, st>>>(p);
+}
+
 }  // namespace
 
 MatchPlan plan_match(const keepkv_layout* L, int capacity, int budget) {
@@ -1421,9 +1488,7 @@ extern "C" keepkv_status keepkv_prefill_match(const keepkv_layout* layout, const
                                                      : launch_causal<64>(p, cache->k, (unsigned)units, exact_blocks, st);
     if (rc != KEEPKV_OK) return rc;
   } else {
-    p.n_units = (int)units;
-    if (layout->head_dim == 128) match_exact_kernel<float, 128><<<exact_blocks, 256, 0, st>>>(p);
-    else match_exact_kernel<float, 64><<<exact_blocks, 256, 0, st>>>(p);
+    launch_exact_f32(p, units, layout->head_dim, cap, st);
   }
   return launch_status();
 }
@@ -1490,9 +1555,7 @@ extern "C" keepkv_status keepkv_match(const keepkv_layout* layout, const keepkv_
       else match_recheck_kernel<64><<<exact_blocks, 256, 0, st>>>(p);
     }
   } else {
-    p.n_units = (int)units;
-    if (layout->head_dim == 128) match_exact_kernel<float, 128><<<exact_blocks, 256, 0, st>>>(p);
-    else match_exact_kernel<float, 64><<<exact_blocks, 256, 0, st>>>(p);
+    launch_exact_f32(p, units, layout->head_dim, budget, st);
   }
   return launch_status();
 }
