@@ -1,5 +1,5 @@
 """Binding of libkeepkv.so: argument marshalling only (ctypes; the calls made once per layer and token through the
-CPython extension _pycall, built beside the library).
+CPython extension _pycall, built beside the library, if it is there).
 
 Every function has the name and meaning of the C entry point declared in include/keepkv.h;
 tensors are torch tensors on the GPU (used here purely as device memory), passed down as raw
@@ -113,12 +113,20 @@ except ImportError:                      # a torch built without them
     def _stream() -> int:
         return torch.cuda.current_stream().cuda_stream
 
+# decode_step, decode_step_static, decode_attn and score of the extension; None: through ctypes, 4 us of host time a call more.
+_HOT = ("decode_step", "decode_step_static", "decode_attn", "score")
 try:
     from . import _pycall
-except ImportError as e:
-    raise ImportError(f"{e}: build the HIP library first (python -m paper_2504_09936_amd.build)") from e
-_pycall.bind(_raw_stream, _device, *(C.cast(getattr(_lib, "keepkv_" + f), C.c_void_p).value
-                                     for f in ("decode_step", "decode_step_static", "decode_attn", "score")))
+except ImportError:
+    _fast = dict.fromkeys(_HOT)
+else:
+    _fast = dict(zip(_HOT, _pycall.bind(_raw_stream, _device, C.ArgumentError,
+                                        *(C.cast(getattr(_lib, "keepkv_" + f), C.c_void_p).value for f in _HOT))))
+
+
+def _fast_call(name: str, layout, cache):
+    """The extension's function, which reads the attributes of a Layout and a Cache as their c() does; None for other classes."""
+    return _fast[name] if type(layout) is Layout and type(cache) is Cache else None
 
 
 @dataclass
@@ -209,11 +217,18 @@ def workspace_init(workspace) -> None:
 
 
 def decode_step(layout: Layout, cache: Cache, q, k_t, v_t, out, logits_out, alpha: float, overflow, workspace) -> None:
-    _check(_pycall.decode_step(layout, cache, q, k_t, v_t, out, logits_out, alpha, overflow, workspace), "keepkv_decode_step")
+    fast = _fast_call("decode_step", layout, cache)
+    _check(fast(layout, cache, q, k_t, v_t, out, logits_out, alpha, overflow, workspace) if fast else
+           _lib.keepkv_decode_step(C.byref(layout.c()), C.byref(cache.c()), _ptr(q), _ptr(k_t), _ptr(v_t), _ptr(out),
+                                   _ptr(logits_out), alpha, _ptr(overflow), _ptr(workspace), _nbytes(workspace),
+                                   _stream()), "keepkv_decode_step")
 
 
 def decode_step_static(layout: Layout, cache: Cache, q, k_t, v_t, out, logits_out, alpha: float, overflow) -> None:
-    _check(_pycall.decode_step_static(layout, cache, q, k_t, v_t, out, logits_out, alpha, overflow),
+    fast = _fast_call("decode_step_static", layout, cache)
+    _check(fast(layout, cache, q, k_t, v_t, out, logits_out, alpha, overflow) if fast else
+           _lib.keepkv_decode_step_static(C.byref(layout.c()), C.byref(cache.c()), _ptr(q), _ptr(k_t), _ptr(v_t),
+                                          _ptr(out), _ptr(logits_out), alpha, _ptr(overflow), _stream()),
            "keepkv_decode_step_static")
 
 
@@ -223,11 +238,16 @@ def append(layout: Layout, cache: Cache, k_t, v_t, overflow=None) -> None:
 
 
 def decode_attn(layout: Layout, cache: Cache, q, out, logits_out, lse_out, workspace) -> None:
-    _check(_pycall.decode_attn(layout, cache, q, out, logits_out, lse_out, workspace), "keepkv_decode_attn")
+    fast = _fast_call("decode_attn", layout, cache)
+    _check(fast(layout, cache, q, out, logits_out, lse_out, workspace) if fast else
+           _lib.keepkv_decode_attn(C.byref(layout.c()), C.byref(cache.c()), _ptr(q), _ptr(out), _ptr(logits_out),
+                                   _ptr(lse_out), _ptr(workspace), _nbytes(workspace), _stream()), "keepkv_decode_attn")
 
 
 def score(layout: Layout, cache: Cache, logits, alpha: float) -> None:
-    _check(_pycall.score(layout, cache, logits, alpha), "keepkv_score")
+    fast = _fast_call("score", layout, cache)
+    _check(fast(layout, cache, logits, alpha) if fast else
+           _lib.keepkv_score(C.byref(layout.c()), C.byref(cache.c()), _ptr(logits), alpha, _stream()), "keepkv_score")
 
 
 def score_window(layout: Layout, cache: Cache, q_win, window: int, alpha: float, first_pos: int = -1) -> None:
