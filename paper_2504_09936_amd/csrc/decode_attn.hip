@@ -1460,6 +1460,10 @@ keepkv_status launch_decode(const DecodeParams& p, int units, bool step, bool va
   return KEEPKV_OK;
 }
 
+}  // namespace
+static DecodePlan kept_plan(const keepkv_layout* L, int capacity, int force_per, int force_waves, bool charge);
+namespace {
+
 template <typename T, int D>
 keepkv_status dispatch_g(const DecodeParams& p, int units, int G, bool step, bool valu, hipStream_t st) {
   switch (G) {
@@ -1482,8 +1486,11 @@ keepkv_status run_decode(const keepkv_layout* layout, const keepkv_cache* cache,
   if (units > kMaxUnits) return KEEPKV_ERR_UNSUPPORTED;
   const int fw = cache->plan_wavefronts, fp = cache->plan_slots_per_split;
   if (!(fw == 0 || fw == 4 || fw == 8 || fw == -1) || fp < 0 || (fp > 0 && fp < 64)) return KEEPKV_ERR_INVALID_ARG;
-  const DecodePlan pl = plan_decode(layout, cache->capacity, fp, fw);
-  if (pl.nsplit > 1 && (!workspace || workspace_bytes < pl.bytes || !aligned16(workspace))) return KEEPKV_ERR_WORKSPACE;
+  DecodePlan pl = plan_decode(layout, cache->capacity, fp, fw);
+  if (pl.nsplit > 1 && (!workspace || workspace_bytes < pl.bytes || !aligned16(workspace))) {
+    pl = kept_plan(layout, cache->capacity, fp, fw, false);        // heads split for the charge on whole ones alone need no workspace whole
+    if (pl.nsplit > 1) return KEEPKV_ERR_WORKSPACE;
+  }
 
   DecodeParams p;
   p.q = q; p.k = cache->k; p.v = cache->v; p.votes = cache->votes; p.log_s = cache->log_s; p.born = cache->born; p.t_obs = cache->t_obs;
@@ -1580,14 +1587,15 @@ static int resident_per_cu(int waves, int head_dim, int group) {
 // heads x 852 7.1 with four against 6.7 with seven.  Over 30 more shapes of one to eight heads and up to 2^20 slots: 0.8 %
 // slower than the best plan (8.6 % at most; 3.6 % and 20 % with one price for combining: one head of 8 query heads x 3405 slots
 // 12.0 us with 27 splits against 9.9 with 16, x 50000 32.3 with 112 against 29.4 with 63).
-// Combining within an XCD came after that fit and is cheaper than it says; a head that would not be split although its wavefronts have more
-// than one and a half tiles each is charged 0.35 us for that, which moves the line between one split and two or three where that measured
-// faster: 96 heads x 520 slots (D 64) 8.7 us whole and 7.9 in two splits, 128 x 700 10.2 and 8.7, 160 x 1300 17.8 and 15.6, 160 x 884 (D 128)
-// 21.9 and 20.1.  (More than that splits 96 x 480 too, 7.7 us whole and 8.2 in two; a lower price for the combination itself
-// also takes four splits for eight, 10 to 20 % slower at 8 heads x 1000.)
+// Combining came to cost less than that fit says; a head that would not be split although its wavefronts have more
+// than one and a half tiles each is charged 0.35 us for that.  It moves shapes of 76 to 168 heads from one split to two or three, in bands, because
+// splits are whole tiles.  In 362 shapes from all of those bands (every fourth number of heads, 1 and 8 query heads per head) splitting
+// measured 11 % faster than the whole heads, 19 % at best and 0.3 % slower at worst: 96 heads x 460 slots (D 64) 7.4 us whole and 6.8 in two splits,
+// 124 x 796 12.2 and 9.8, 140 x 1006 (D 128) 25.1 and 20.2, 156 x 874 20.3 and 20.4.  (A lower price for the combination itself
+// also takes four splits for eight, 10 to 20 % slower at 8 heads x 1000.)  charge false: without it.
 constexpr int kMaxSplitWorkgroups = 512;
 constexpr int kMinSplit = 64;
-static void choose_split(const keepkv_layout* L, int capacity, long& per, int& waves) {
+static void choose_split(const keepkv_layout* L, int capacity, bool charge, long& per, int& waves) {
   const double units = (double)L->batch * L->n_kv_heads;
   const int group = L->n_q_heads / L->n_kv_heads;
   const double slot_bytes = 4.0 * L->head_dim + 24.0;
@@ -1617,8 +1625,8 @@ static void choose_split(const keepkv_layout* L, int capacity, long& per, int& w
       double t = full * round_of(res_max) + round_of(rest) + 1.7 * (rounds - 1.0) + (wv == 4 ? 0.46 : 0.0);
       if (n_split > 1.0)
         t += (n_split <= 4.0 ? 1.85 : n_split <= 8.0 ? 2.7 : 4.3 + 1.3 * elements * (double)(long)((n_split - 1.0) / 16.0)) + 0.011 * n_split;
-      else if (2 * tiles > 3 * wv)
-        t += 0.35;                                 // (see above)
+      else if (charge && 2 * tiles > 3 * wv)
+        t += 0.35;
       if (t < best) {
         best = t;
         per = cand;
@@ -1693,13 +1701,13 @@ static bool xcd_pays(const keepkv_layout* L, long nsplit, long per, int waves) {
   return L->head_dim == 64 ? workgroups >= 192 : nsplit > 2 && workgroups >= 256;
 }
 
-static DecodePlan make_plan(const keepkv_layout* L, int capacity, int force_per, int force_waves) {
+static DecodePlan make_plan(const keepkv_layout* L, int capacity, int force_per, int force_waves, bool charge) {
   DecodePlan pl;
   const bool valu = L->dtype == KEEPKV_BF16 && force_waves == -1;
   const bool mfma = L->dtype == KEEPKV_BF16 && !valu;
   long per = 128;
   int waves = kWavesPerBlock;
-  if (mfma) choose_split(L, capacity, per, waves);
+  if (mfma) choose_split(L, capacity, charge, per, waves);
   else choose_split_valu(L, capacity, per);
   if (mfma && (force_waves == 4 || force_waves == 8)) waves = force_waves;
   pl.waves = waves;
@@ -1731,21 +1739,24 @@ size_t decode_workspace_bytes(const keepkv_layout* L, int capacity) {
 // The cost model walks up to 1024 candidate plans, microseconds of host time, and a program asks for the same
 // few plans again and again (one per layer shape and step): each thread keeps its last ones.  A plan is a pure function
 // of the fields compared here.
-DecodePlan plan_decode(const keepkv_layout* L, int capacity, int force_per, int force_waves) {
+static DecodePlan kept_plan(const keepkv_layout* L, int capacity, int force_per, int force_waves, bool charge) {
   struct Entry {
-    int32_t key[8];
+    int32_t key[9];
     DecodePlan plan;
   };
   static thread_local Entry kept[8] = {};          // (a zero batch is no valid key)
-  const int32_t key[8] = {L->batch, L->n_q_heads, L->n_kv_heads, L->head_dim, L->dtype, capacity, force_per, force_waves};
+  const int32_t key[9] = {L->batch, L->n_q_heads, L->n_kv_heads, L->head_dim, L->dtype, capacity, force_per, force_waves, charge};
   uint32_t h = 0;
   for (int32_t k : key) h = h * 31u + (uint32_t)k;
   Entry& e = kept[(h ^ (h >> 15)) & 7u];
   if (memcmp(e.key, key, sizeof key) != 0) {
-    e.plan = make_plan(L, capacity, force_per, force_waves);
+    e.plan = make_plan(L, capacity, force_per, force_waves, charge);
     memcpy(e.key, key, sizeof key);
   }
   return e.plan;
+}
+DecodePlan plan_decode(const keepkv_layout* L, int capacity, int force_per, int force_waves) {
+  return kept_plan(L, capacity, force_per, force_waves, true);
 }
 
 }  // namespace kk

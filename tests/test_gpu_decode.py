@@ -222,3 +222,25 @@ def test_decode_extreme_values(name, w):
     assert err.max() <= TOL, (name, err.max())
     np.testing.assert_allclose(logits.cpu().numpy(), lg_ref, rtol=2e-3, atol=2e-3)
     np.testing.assert_allclose(lse.cpu().numpy(), lse_ref, rtol=1e-4, atol=2e-3)
+
+
+def test_heads_split_only_for_speed_need_no_workspace():
+    """Shapes that one split serves nearly as well are accepted without a workspace (and with one too small), as whole heads."""
+    kk = U.kk()
+    w = W.CONFIGS["llama3_8b"].scaled(batch=12, n_q_heads=16, n_kv_heads=8, head_dim=64, context=520)
+    K, V = W.make_cache(w, 5)
+    lay, c = U.new_cache(w, capacity=520, K=K, V=V)
+    assert kk.decode_plan(lay, 520)[0] > 1
+    q = U.to_device(W.make_query(w, 5, 0), "bf16")
+    out, lse = ([torch.zeros(*s, dtype=d, device="cuda") for _ in range(3)] for s, d in (((12, 16, 64), torch.bfloat16), ((12, 16), torch.float32)))
+    for i, ws in enumerate((kk.new_workspace(lay, 520, 52), None, torch.zeros(4096, dtype=torch.uint8, device="cuda"))):
+        kk.decode_attn(lay, c, q, out[i], None, lse[i], ws)
+    assert torch.equal(out[1], out[2]) and torch.equal(lse[1], lse[2])
+    assert U.rel_err_rows(U.to_host(out[1]), U.to_host(out[0])).max() <= TOL
+    np.testing.assert_allclose(lse[1].cpu().numpy(), lse[0].cpu().numpy(), rtol=1e-5, atol=1e-5)
+    few = W.CONFIGS["llama3_8b"].scaled(batch=1, context=884)            # heads that need their splits still ask for it
+    lay, c = U.new_cache(few, capacity=884)
+    with pytest.raises(kk.KeepKVError) as e:
+        kk.decode_attn(lay, c, torch.zeros(1, 32, 128, dtype=torch.bfloat16, device="cuda"),
+                       torch.zeros(1, 32, 128, dtype=torch.bfloat16, device="cuda"), None, None, None)
+    assert e.value.status == kk.ERR_WORKSPACE
