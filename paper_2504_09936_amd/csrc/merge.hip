@@ -341,7 +341,9 @@ __device__ __forceinline__ void merge_positions(const MergeParams& p, int unit, 
                                                 int off, int nm, int dst) {
   constexpr int EPL = 16 / (int)sizeof(T), LPS = D / EPL, GPW = 64 / LPS;
   // entries per lane group and round trip.  With 2 / 3 / 4 (81 / 91 / 101 registers), the whole first event: 1024 heads 3236 / 3200 / 3286
-  // us, 8 heads with lists of up to 230 entries 350.5 / 344.9 / 341.1, 24 heads of D 64 74.3 / 73.7 / 74.5
+  // us, 8 heads with lists of up to 230 entries 350.5 / 344.9 / 341.1, 24 heads of D 64 74.3 / 73.7 / 74.5.  Lists all of one length (1 to 40
+  // entries, 4 to 128 heads), 2 / 3: bf16 1 to 12 % faster with 3 and nowhere more than 2 % slower; f32 up to 14 % faster (8 heads x 100 lists of 40, D 128,
+  // 22.3 / 19.3), 5 % slower at worst (64 heads x 820 lists of 12, D 64, 103 / 108).
   constexpr int kRowBatch = 3;
   constexpr int kOwnRows = LPS == 8 ? 8 : 4;                       // up to this many entries a lane group sums its position by itself
   const size_t sbase = (size_t)unit * p.scap, dbase = (size_t)unit * p.dcap;
@@ -1067,7 +1069,9 @@ extern "C" keepkv_status keepkv_merge(const keepkv_layout* layout, const keepkv_
   const bool direct = max_evict <= kDirectMaxEvict;   // the steady state: the apply kernel finds its members itself
   if (!direct) {
     int shares = (int)(256 / units);
-    shares = shares < 1 ? 1 : (shares > kMaxGroupShares ? kMaxGroupShares : shares);
+    // (more than eight only with 128 entries for each: 8 heads of 300 entries, the whole event, 12.2 us with eight, 12.8 with 32; of 4000 17.1 and 15.6)
+    const int most = max_evict / 128 < 8 ? 8 : (max_evict / 128 > kMaxGroupShares ? kMaxGroupShares : max_evict / 128);
+    shares = shares < 1 ? 1 : (shares > most ? most : shares);
     if (shares > budget) shares = budget;
     auto group = [&](auto kernel) {
       kernel<<<units * shares, kGroupThreads, place_bytes, st>>>(match, evict_idx, n_evict, src->votes, start, members, dropped_votes,

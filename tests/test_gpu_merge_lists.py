@@ -68,3 +68,35 @@ def test_merge_of_given_lists(dtype, head_dim, batch):
         well = ~(np.abs(ref.ell_bar) < 4 * O.ELL_GUARD)
         assert U.storage_err_rows(dv[b, h, :budget], ref.v, dtype).max() <= 2e-3
         assert U.storage_err_rows(dk[b, h, :budget], ref.k, dtype)[well].max() <= 2e-3
+
+
+# eight, sixteen and 32 workgroups a head; 8 entries a thread up to 8192 of them, 32 beyond
+@pytest.mark.parametrize("n_ev", [300, 2100, 4096, 8191, 8192, 8193, 9217])
+def test_merge_of_every_entry(n_ev):
+    """Every entry reaches its target, whatever the number of entries a thread holds and of workgroups that share a head."""
+    kk = U.kk()
+    H, D, budget = 2, 64, 90
+    cap = budget + n_ev
+    w = W.CONFIGS["llama3_8b"].scaled(batch=1, n_q_heads=H, n_kv_heads=H, head_dim=D, context=cap, ratio=(budget - 0.5) / cap)
+    g = np.random.default_rng(n_ev)
+    K, V = (W.round_storage(g.standard_normal((1, H, cap, D)), "bf16") for _ in range(2))
+    votes = g.integers(1, 9, size=(1, H, cap)).astype(np.int32)
+    lay, c = U.new_cache(w, capacity=cap, K=K, V=V, votes=votes)
+    c.log_s[:] = torch.from_numpy((g.standard_normal((1, H, cap)) - 6).astype(np.float32)).cuda()
+    slots = np.stack([g.permutation(cap) for _ in range(H)]).astype(np.int32)
+    keep, evict = np.sort(slots[:, :budget], 1)[None], np.sort(slots[:, budget:], 1)[None]
+    live = np.array([[n_ev, n_ev - 5]], np.int32)
+    match = g.integers(-1, budget, size=(1, H, n_ev)).astype(np.int32)
+    up = lambda a: torch.from_numpy(a).cuda()                                     # noqa: E731
+    dropped = torch.zeros(1, H, dtype=torch.int64, device="cuda")
+    _, d = U.new_cache(w, capacity=budget)
+    kk.merge(lay, c, d, budget, up(keep), up(evict), up(live), up(match), U.f32(0.9), dropped, U.workspace(lay, cap, budget))
+    oc = U.download(c)
+    for h in range(H):
+        n = live[0, h]
+        m, pv = match[0, h, :n], votes[0, h, evict[0, h, :n]].astype(np.int64)
+        want = votes[0, h, keep[0, h]] + np.bincount(m[m >= 0], weights=pv[m >= 0], minlength=budget).astype(np.int64)
+        np.testing.assert_array_equal(d.votes[0, h].cpu().numpy(), want)
+        assert dropped[0, h].item() == pv[m < 0].sum()
+        ref = O.merge(oc.k[0, h], oc.v[0, h], oc.votes[0, h], oc.log_S[0, h], oc.n_obs[0, h], keep[0, h], evict[0, h, :n], m, U.f32(0.9))
+        assert U.storage_err_rows(U.to_host(d.v)[0, h], ref.v, "bf16").max() <= 2e-3
