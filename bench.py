@@ -52,11 +52,29 @@ def decode_kernel_name(head_dim: int, group: int, step: bool, slots_per_split: i
     return f"decode_mfma_kernel<{head_dim},{group},{'true' if step else 'false'},{mode},{wavefronts}>"
 
 
+def decode_source_digest() -> str:
+    """Of the decode kernels' source without comments and white space: tells whether recorded counters are of this code."""
+    import hashlib
+    import re
+    text = open(os.path.join(ROOT, "paper_2504_09936_amd", "csrc", "decode_attn.hip")).read()
+    text = re.sub(r"\s+", "", re.sub(r"//[^\n]*|/\*.*?\*/", "", text, flags=re.S))
+    return hashlib.sha256(text.encode()).hexdigest()[:12]
+
+
+def traffic_is_of_this_source(workload: str) -> bool:
+    """Whether the counters recorded for the workload are of the decode kernels as they are."""
+    try:
+        return f"source={decode_source_digest()} " in open(os.path.join(ROOT, "profiles", f"decode_hbm_traffic_{workload}.md")).read()
+    except OSError:
+        return False
+
+
 def traffic_from_profile(workload: str, kernel: str):
     """HBM bytes per launch of the decode kernel as recorded in profiles/decode_hbm_traffic_<workload>.md
     (rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE in KiB per dispatch, each scaled by what the same counter reads
     for a plain copy of known size).  Counters cannot be read from inside this process; the recorded figure
-    is used only if the summary is for exactly the kernel instance this run launches, else None."""
+    is used only if the summary is for exactly the kernel instance this run launches, else None (and
+    traffic_is_of_this_source says whether that instance has changed since)."""
     import re
     path = os.path.join(ROOT, "profiles", f"decode_hbm_traffic_{workload}.md")
     try:
@@ -64,7 +82,7 @@ def traffic_from_profile(workload: str, kernel: str):
     except OSError:
         return None
     m = re.search(r"<!--\s*bench:\s*kernel=(\S+)\s+fetch_kib=([0-9.]+)\s+write_kib=([0-9.]+)\s+fetch_factor=([0-9.]+)\s+"
-                  r"write_factor=([0-9.]+)\s*-->", text)
+                  r"write_factor=([0-9.]+)(?:\s+source=\w+)?\s*-->", text)
     if not m or m.group(1) != kernel:
         return None
     fetch, write, ff, wf = (float(m.group(i)) for i in range(2, 6))
@@ -649,7 +667,7 @@ def main():
     traffic = traffic_from_profile(w.name, kernel_instance)
     roofline = {"bound": "hbm", "kernel": kernel_instance, "achieved": round(achieved, 1),
                 "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),
-                "traffic": traffic, "bytes_per_launch": int(dec_bytes), "bytes_moved_per_launch": int(dec_bytes_moved),
+                "traffic": traffic, "traffic_of_this_source": traffic is not None and traffic_is_of_this_source(w.name), "bytes_per_launch": int(dec_bytes), "bytes_moved_per_launch": int(dec_bytes_moved),
                 "frac_of_moved_bytes": round(dec_bytes_moved / (dec_us * 1e-6) / 1e9 / HBM_PEAK_GBS, 4),
                 "avg_launch_us": round(dec_us, 2),
                 "frac_of_measured_read": round(achieved / measured["read_decode_working_set_GBps"], 4)}

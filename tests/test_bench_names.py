@@ -38,3 +38,23 @@ def test_recorded_traffic_is_that_of_the_planned_instance(name):
     text = open(os.path.join(PROFILES, f"decode_hbm_traffic_{name}.md")).read()
     assert re.search(r"kernel=(\S+)", text).group(1) == kernel
     assert bench.traffic_from_profile(name, kernel.replace("true", "false")) is None
+
+
+def test_recorded_traffic_says_whether_its_kernel_has_changed(tmp_path, monkeypatch):
+    src, rec = tmp_path / "paper_2504_09936_amd" / "csrc", tmp_path / "profiles"
+    src.mkdir(parents=True)
+    rec.mkdir()
+    monkeypatch.setattr(bench, "ROOT", str(tmp_path))
+    _written(src, "int a;  // one\n")
+    assert not bench.traffic_is_of_this_source("w")                                                   # no record
+    (rec / "decode_hbm_traffic_w.md").write_text(
+        f"<!-- bench: kernel=k<1> fetch_kib=10 write_kib=1 fetch_factor=2.00 write_factor=1.00 source={bench.decode_source_digest()} -->")
+    assert bench.traffic_from_profile("w", "k<1>") == 21 * 1024 and bench.traffic_is_of_this_source("w")
+    _written(src, "int  a;\n/* two\n lines */  // three\n")
+    assert bench.traffic_is_of_this_source("w")                                                       # comments and spaces alone
+    _written(src, "int b;\n")
+    assert bench.traffic_from_profile("w", "k<1>") == 21 * 1024 and not bench.traffic_is_of_this_source("w")
+
+
+def _written(folder, text):
+    (folder / "decode_attn.hip").write_text(text)
