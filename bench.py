@@ -46,7 +46,10 @@ def decode_kernel_name(head_dim: int, group: int, step: bool, slots_per_split: i
         mode = (4, 5, 0)[tiles - 1]
     else:
         workgroups = heads * n_split
-        pays = tiles == 1 or tiles == 2 and n_split <= 4 and (workgroups >= 192 if head_dim == 64 else n_split > 2 and workgroups >= 256)
+        if not step:
+            pays = tiles == 1 or tiles == 2 and n_split <= 8 and (head_dim == 64 or n_split > 2)
+        else:
+            pays = tiles == 1 or tiles == 2 and n_split <= 4 and (workgroups >= 192 if head_dim == 64 else n_split > 2 and workgroups >= 256)
         may = heads % 8 == 0 and heads <= 2048 and n_split <= 16
         mode = (1, 7)[tiles - 1] if may and pays else (6, 2, 3)[tiles - 1]
     return f"decode_mfma_kernel<{head_dim},{group},{'true' if step else 'false'},{mode},{wavefronts}>"

@@ -806,10 +806,14 @@ __global__ __launch_bounds__(kMfmaWaves* kWave, 2) void decode_mfma_kernel(Decod
   const int len_old = p.len[unit];
   const int t_old = STEP ? p.t_obs[unit] : 0;   // used at the very end only
   const int start = split * p.per;
-  // This workgroup has arrived: ahead of every request, so that a workgroup whose split is short does not look too early (and by the
-  // last wavefront, whose share is the shortest: its rows land behind this).
-  if (kMayShareXcd && wave == kMfmaWaves - 1 && lane == 0)
-    __hip_atomic_fetch_add(&p.arrivals[unit], 1ull << (8 * xcd_id()), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  // This workgroup has arrived (the last wavefront, whose share is the shortest; its rows land behind this).  With one tile ahead of
+  // every request, so that a workgroup whose split is short does not look too early; with two a little later, ahead of the rows: 32 heads x 2640
+  // slots of 3300 in eight splits, attention alone, took 15.4 us with the former and 13.7 with the latter.
+  auto arrive = [&]() {
+    if (kMayShareXcd && wave == kMfmaWaves - 1 && lane == 0)
+      __hip_atomic_fetch_add(&p.arrivals[unit], 1ull << (8 * xcd_id()), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  };
+  if constexpr (ONE) arrive();
   const bool takes_new = STEP && split == p.nsplit - 1 && wave == kMfmaWaves - 1;
   if (takes_new) {                             // asynchronous copy of (k_t, v_t) into LDS, awaited after the loop
     const size_t at = (size_t)unit * ROWB;
@@ -919,6 +923,8 @@ __global__ __launch_bounds__(kMfmaWaves* kWave, 2) void decode_mfma_kernel(Decod
       request_scalars(base, pv_next, ls_next);
     }
   }
+
+  if constexpr (TWO) arrive();
 
   // B operand of the score product: column l16 is head l16 mod G, this lane's 8 channels of every k-step
   bf16x8_t qb[KS];
@@ -1502,7 +1508,7 @@ keepkv_status run_decode(const keepkv_layout* layout, const keepkv_cache* cache,
   p.arrivals = nullptr;
   p.ticket_xcd = nullptr;
   p.split_stride = layout->n_q_heads / layout->n_kv_heads * (layout->head_dim + 2);
-  if (pl.xcd_bytes != 0 && workspace_bytes >= pl.xcd_bytes) {   // (a smaller workspace has room for partial results without lines of their own)
+  if (pl.xcd_bytes != 0 && (step ? pl.xcd_step : pl.xcd_attn) && workspace_bytes >= pl.xcd_bytes) {   // (a smaller workspace has room for partial results without lines of their own)
     p.arrivals = reinterpret_cast<uint64_t*>(ws + kArrivalsOff);
     p.ticket_xcd = reinterpret_cast<int32_t*>(ws + kXcdTicketsOff);
     p.split_stride = xcd_split_stride(layout);
@@ -1693,10 +1699,13 @@ static bool heads_fit_xcds(const keepkv_layout* L) {
 // With two tiles the tail is a smaller share of the step, and how soon a head's workgroups have all arrived matters more.  D 128: 64 x 1487
 // in four splits, which fill the chip, 15.4 / 14.8, but 48 x 1084 in four 10.0 / 10.3, 128 x 476 in two 10.5 / 11.0, 32 x 3284 in eight 15.0 / 15.5.  D 64,
 // half the bytes beside the same tail: 64 x 1384 in four 9.15 / 8.97, 96 x 684 in two 8.5 / 8.3, but 32 x 1084 in four 7.56 / 7.72, 32 x 2584 in eight
-// 9.1 / 9.3.  In the tile loop reading `arrivals` cost as much as it gave.
-static bool xcd_pays(const keepkv_layout* L, long nsplit, long per, int waves) {
+// 9.1 / 9.3.  Attention alone has no wavefront that ends later for an appended token, and there it pays up to eight splits: 1 to 3 % (16 heads x
+// 2300 to 5000 slots of D 64 in eight 1.5 %, 64 x 1044 to 1734 in four 2.5 %, partly filled ones of D 128 3 %), but 8 heads in sixteen and 128 x 420 of 600 slots of D 128 in two 3 % slower.  In the tile loop
+// reading `arrivals` cost as much as it gave.
+static bool xcd_pays(const keepkv_layout* L, long nsplit, long per, int waves, bool step) {
   const long workgroups = (long)L->batch * L->n_kv_heads * nsplit;
   if (per <= (long)waves * kMTile) return true;
+  if (!step) return nsplit <= 8 && (L->head_dim == 64 || nsplit > 2);
   if (nsplit > 4) return false;
   return L->head_dim == 64 ? workgroups >= 192 : nsplit > 2 && workgroups >= 256;
 }
@@ -1720,7 +1729,9 @@ static DecodePlan make_plan(const keepkv_layout* L, int capacity, int force_per,
   pl.partial_off = kWorkspaceHead;
   pl.bytes = decode_bytes(L, ns);
   const bool may_share = mfma && ns > 1 && ns <= kMaxLocalSplits && per <= 2L * waves * kMTile && heads_fit_xcds(L);
-  pl.xcd_bytes = may_share && (force_per > 0 || xcd_pays(L, ns, per, waves)) ? decode_xcd_bytes(L, ns) : 0;   // (the caller's splits wherever they can)
+  pl.xcd_bytes = may_share ? decode_xcd_bytes(L, ns) : 0;
+  pl.xcd_step = force_per > 0 || xcd_pays(L, ns, per, waves, true);    // (the caller's splits wherever they can)
+  pl.xcd_attn = force_per > 0 || xcd_pays(L, ns, per, waves, false);
   return pl;
 }
 

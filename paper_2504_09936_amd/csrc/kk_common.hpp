@@ -103,6 +103,7 @@ struct DecodePlan {
   size_t partial_off; // float [B*Hq, nsplit, D + 2]
   size_t bytes;
   size_t xcd_bytes;   // with room for combining within an XCD (0: not for this shape)
+  bool xcd_step, xcd_attn;   // whether that pays in a whole step / for attention alone
 };
 // force_per / force_waves: the caller's overrides (keepkv_cache.plan_slots_per_split / plan_wavefronts), 0 = none
 DecodePlan plan_decode(const keepkv_layout* L, int capacity, int force_per = 0, int force_waves = 0);
