@@ -38,7 +38,8 @@ def decode_kernel_name(head_dim: int, group: int, step: bool, slots_per_split: i
                        heads: int = 0) -> str:
     """The matrix-core decode kernel's instance for a launch plan.  Its fourth template argument, for at most one tile of 32 slots a
     wavefront / two / more: 4 / 5 / 0 for unsplit heads, 6 / 2 / 3 for splits that meet through memory, 1 / 7 / - for those that may meet
-    within an XCD.  Without n_split and heads: what splits of one (1) and two tiles (2) and whole heads of more (0) usually are."""
+    within an XCD (two of D 128 whose second is short by the cache's length hint keep memory's).  Without n_split
+    and heads: what splits of one (1) and two tiles (2) and whole heads of more (0) usually are."""
     tiles = min(3, -(-slots_per_split // (wavefronts * 32)))
     if n_split is None:
         mode = (1, 2, 0)[tiles - 1]
@@ -49,7 +50,7 @@ def decode_kernel_name(head_dim: int, group: int, step: bool, slots_per_split: i
         if not step:
             pays = tiles == 1 or tiles == 2 and n_split <= 8 and (head_dim == 64 or n_split > 2)
         else:
-            pays = tiles == 1 or tiles == 2 and n_split <= 4 and (workgroups >= 192 if head_dim == 64 else n_split > 2 and workgroups >= 256)
+            pays = tiles == 1 or tiles == 2 and n_split <= 4 and workgroups >= (192 if head_dim == 64 else 256)
         may = heads % 8 == 0 and heads <= 2048 and n_split <= 16
         mode = (1, 7)[tiles - 1] if may and pays else (6, 2, 3)[tiles - 1]
     return f"decode_mfma_kernel<{head_dim},{group},{'true' if step else 'false'},{mode},{wavefronts}>"

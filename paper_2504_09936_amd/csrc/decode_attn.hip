@@ -1508,7 +1508,12 @@ keepkv_status run_decode(const keepkv_layout* layout, const keepkv_cache* cache,
   p.arrivals = nullptr;
   p.ticket_xcd = nullptr;
   p.split_stride = layout->n_q_heads / layout->n_kv_heads * (layout->head_dim + 2);
-  if (pl.xcd_bytes != 0 && (step ? pl.xcd_step : pl.xcd_attn) && workspace_bytes >= pl.xcd_bytes) {   // (a smaller workspace has room for partial results without lines of their own)
+  // Of two splits of two tiles (D 128) the second must not be much shorter than the first, or its workgroup looks in vain: 128 heads x 751 of 884
+  // slots 14.2 us through memory, 14.7 within the XCD; x 868 15.08 and 15.09, of eight query heads 15.9 and 15.8.
+  const int bound = cache->len_hint > 0 && cache->len_hint < cache->capacity ? cache->len_hint : cache->capacity;
+  const bool second_short = step && fp == 0 && pl.nsplit == 2 && layout->head_dim == 128 && pl.per > pl.waves * kMTile &&
+                            4 * (bound - pl.per) < 3 * pl.per;
+  if (pl.xcd_bytes != 0 && (step ? pl.xcd_step && !second_short : pl.xcd_attn) && workspace_bytes >= pl.xcd_bytes) {   // (a smaller workspace has room for partial results without lines of their own)
     p.arrivals = reinterpret_cast<uint64_t*>(ws + kArrivalsOff);
     p.ticket_xcd = reinterpret_cast<int32_t*>(ws + kXcdTicketsOff);
     p.split_stride = xcd_split_stride(layout);
@@ -1697,7 +1702,7 @@ static bool heads_fit_xcds(const keepkv_layout* L) {
 // Where combining within an XCD pays.  Measured through memory / within the XCD, us: with one tile a wavefront always, or it makes no
 // difference (250 shapes, 4 % on average): 8 heads x 852 slots in seven splits 6.5 / 6.2, 64 x 852 in four 10.0 / 9.6, 32 x 1497 in eight 9.9 / 9.4.
 // With two tiles the tail is a smaller share of the step, and how soon a head's workgroups have all arrived matters more.  D 128: 64 x 1487
-// in four splits, which fill the chip, 15.4 / 14.8, but 48 x 1084 in four 10.0 / 10.3, 128 x 476 in two 10.5 / 11.0, 32 x 3284 in eight 15.0 / 15.5.  D 64,
+// in four splits, which fill the chip, 15.4 / 14.8, 128 x 828 in two 14.6 / 14.55, but 48 x 1084 in four 10.0 / 10.3, 32 x 3284 in eight 15.0 / 15.5.  D 64,
 // half the bytes beside the same tail: 64 x 1384 in four 9.15 / 8.97, 96 x 684 in two 8.5 / 8.3, but 32 x 1084 in four 7.56 / 7.72, 32 x 2584 in eight
 // 9.1 / 9.3.  Attention alone has no wavefront that ends later for an appended token, and there it pays up to eight splits: 1 to 3 % (16 heads x
 // 2300 to 5000 slots of D 64 in eight 1.5 %, 64 x 1044 to 1734 in four 2.5 %, partly filled ones of D 128 3 %), but 8 heads in sixteen and 128 x 420 of 600 slots of D 128 in two 3 % slower.  In the tile loop
@@ -1707,7 +1712,7 @@ static bool xcd_pays(const keepkv_layout* L, long nsplit, long per, int waves, b
   if (per <= (long)waves * kMTile) return true;
   if (!step) return nsplit <= 8 && (L->head_dim == 64 || nsplit > 2);
   if (nsplit > 4) return false;
-  return L->head_dim == 64 ? workgroups >= 192 : nsplit > 2 && workgroups >= 256;
+  return workgroups >= (L->head_dim == 64 ? 192 : 256);
 }
 
 static DecodePlan make_plan(const keepkv_layout* L, int capacity, int force_per, int force_waves, bool charge) {

@@ -25,7 +25,7 @@ def test_decode_kernel_name_by_where_the_splits_meet():
     assert [mode(128, 4, True, per, 8, 1, 64) for per in (64, 256, 288, 512, 544)] == [4, 4, 5, 5, 0]              # unsplit
     assert [mode(128, 4, True, 224, 8, 4, heads) for heads in (64, 8, 36, 2056)] == [1, 1, 6, 6]                    # heads by eights
     assert [mode(128, 4, True, per, 8, 17, 8) for per in (224, 448, 544)] == [6, 2, 3]                              # more than sixteen splits
-    assert [mode(128, 4, True, 384, 8, ns, heads) for ns, heads in ((4, 64), (4, 56), (2, 128), (8, 32))] == [7, 2, 2, 2]
+    assert [mode(128, 4, True, 384, 8, ns, heads) for ns, heads in ((4, 64), (4, 56), (2, 128), (8, 32))] == [7, 2, 7, 2]
     assert [mode(64, 4, True, 384, 8, ns, heads) for ns, heads in ((4, 64), (4, 40), (2, 96), (8, 32))] == [7, 2, 7, 2]
     assert [mode(128, 4, False, 384, 8, ns, heads) for ns, heads in ((4, 40), (2, 128), (8, 32), (9, 8), (4, 36))] == [7, 2, 7, 2, 2]   # attention alone
 

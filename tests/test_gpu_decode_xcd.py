@@ -29,7 +29,7 @@ def _state(kk, lay, cap, n):
                                                      (1, 128, 8, 700, 96, 4), (2, 64, 8, 2000, 512, 8), (8, 128, 64, 600, 256, 4),
                                                      (4, 128, 16, 1000, 64, 8), (4, 64, 256, 700, 64, 4), (4, 128, 8, 1200, 224, 8),
                                                      (2, 128, 8, 1000, 64, 8), (8, 128, 8, 1700, 128, 8),
-                                                     (4, 128, 64, 1500, 0, 0), (1, 64, 96, 700, 0, 0), (2, 128, 64, 700, 256, 4)])
+                                                     (4, 128, 64, 1500, 0, 0), (1, 64, 96, 700, 0, 0), (2, 128, 64, 700, 256, 4), (4, 128, 128, 836, 0, 0)])
 def test_same_bits_as_through_memory(G, D, heads, cap, per, waves):
     kk = U.kk()
     lay = kk.Layout(heads // 8, 8 * G, 8, D, kk.BF16, D ** -0.5)
@@ -61,7 +61,7 @@ def test_same_bits_as_through_memory(G, D, heads, cap, per, waves):
 
 
 # one tile a wavefront; two, in four and in two splits
-@pytest.mark.parametrize("G,D,heads,cap", [(4, 128, 64, 884), (8, 64, 8, 500), (4, 128, 64, 1500), (1, 64, 96, 700)])
+@pytest.mark.parametrize("G,D,heads,cap", [(4, 128, 64, 884), (8, 64, 8, 500), (4, 128, 64, 1500), (1, 64, 96, 700), (4, 128, 128, 836)])
 def test_the_route_is_taken(G, D, heads, cap):
     """Tickets of the route through memory that can never complete (far below zero; nothing waits for them): a head that meets within
     its XCD leaves its own alone and has its result, any other has added to it.  Workgroups come to the XCDs in turn, so that most
