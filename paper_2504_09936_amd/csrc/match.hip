@@ -869,6 +869,15 @@ __device__ __forceinline__ void exact_exit(const MatchParams& p, int n_flag, int
   }
 }
 
+__device__ __forceinline__ int wave_prefix_sum(int n, int lane) {
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+    const int o = __shfl_up(n, off);
+    if (lane >= off) n += o;
+  }
+  return n;
+}
+
 template <typename T, int D>
 __global__ __launch_bounds__(256) void match_exact_kernel(MatchParams p) {
   __shared__ double s_e[D];
@@ -882,7 +891,7 @@ __global__ __launch_bounds__(256) void match_exact_kernel(MatchParams p) {
   // Measured, D 64, queued / stepping over every row that the caches have room for / this way: 4 heads of 32 live rows x 820 keys in caches of
   // 16384 slots 12.9 / 26.5 / 10.6 us, 4 heads of 32 rows x 52 keys in caches of 84 10.2 / 7.6 / 5.7.
   __shared__ int s_first[257], s_wave[4];
-  __shared__ int s_unit, s_row;
+  __shared__ int s_group;
   auto live = [&](int u) {
     return u >= p.n_units ? 0 : imax(p.causal ? imin(p.len[u], p.capacity) : imin(p.n_evict[u], p.max_evict), 0);
   };
@@ -894,12 +903,7 @@ __global__ __launch_bounds__(256) void match_exact_kernel(MatchParams p) {
   if (!same) {
     int n = 0;
     for (int u = tid * per; u < (tid + 1) * per; ++u) n += live(u);
-    int upto = n;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-      const int o = __shfl_up(upto, off);
-      if (lane >= off) upto += o;
-    }
+    int upto = wave_prefix_sum(n, lane);
     if (lane == 63) s_wave[wave] = upto;
     __syncthreads();
     for (int w = 0; w < wave; ++w) upto += s_wave[w];
@@ -919,19 +923,20 @@ __global__ __launch_bounds__(256) void match_exact_kernel(MatchParams p) {
       unit = f / n_first;
       j = f % n_first;
     } else {
-      if (s_first[tid] <= f && f < s_first[tid + 1]) {      // one thread
-        int u = tid * per, at = f - s_first[tid];
-        for (int i = 1; i < per; ++i, ++u) {
-          const int n = live(u);
-          if (at < n) break;
-          at -= n;
-        }
-        s_unit = u;
-        s_row = at;
-      }
+      if (s_first[tid] <= f && f < s_first[tid + 1]) s_group = tid;      // one thread
       __syncthreads();
-      unit = s_unit;
-      j = s_row;
+      // The row's head among those `per`, a head a lane (16384 heads of 2 to 4 rows x 36 keys, D 64: 521 us when one
+      // thread walked over them, 280).
+      unit = s_group * per;
+      j = f - s_first[s_group];
+      if (per > 1) {
+        static_assert(kMaxUnits <= 256 * 64);
+        const int n = lane < per ? live(unit + lane) : 0;
+        const int end = wave_prefix_sum(n, lane);
+        const int at = __builtin_ctzll(__ballot(j < end) | 1ull << 63);
+        j -= __shfl(end - n, at);
+        unit += at;
+      }
     }
     unit = __builtin_amdgcn_readfirstlane(unit);
     j = __builtin_amdgcn_readfirstlane(j);

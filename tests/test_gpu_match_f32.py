@@ -20,10 +20,11 @@ def _reference(K, keep, evict, n_ev, T):
 
 
 # (heads, most live rows of a head, budget, slots of the cache beyond them).  Workgroups a row: a list is shared by two from 257 keys on, by four
-# from 513, by eight from 1025, if the live rows are at most 128, 64 and 32.  300 heads: two to a thread where the live rows are counted.
+# from 513, by eight from 1025, if the live rows are at most 128, 64 and 32.  300 heads: two to a thread where the live rows are counted, 16384,
+# the most there can be: 64.
 @pytest.mark.parametrize("heads,n_evict,budget,beyond", [(4, 32, 52, 0), (4, 16, 256, 0), (4, 16, 257, 0), (2, 16, 1025, 0), (1, 16, 2049, 0), (8, 64, 600, 0),
                                                          (1, 16, 512, 0), (1, 16, 513, 7), (1, 16, 1024, 0), (1, 16, 1025, 3000), (2, 9, 52, 5000),
-                                                         (300, 4, 40, 0), (300, 4, 40, 90)])
+                                                         (300, 4, 40, 0), (300, 4, 40, 90), (16384, 3, 5, 0)])
 @pytest.mark.parametrize("D", [64, 128])
 @pytest.mark.parametrize("ragged", [True, False])
 def test_match(heads, n_evict, budget, beyond, D, ragged):
